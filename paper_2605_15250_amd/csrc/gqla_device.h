@@ -123,4 +123,39 @@ __device__ __forceinline__ int32_t page_of(const CacheView& c, int32_t b, int32_
   return ((uint32_t)pg < (uint32_t)c.num_pages) ? pg : -1;
 }
 
+// inclusive prefix sum over the 64 lanes: shifts inside the rows of 16 lanes, then the row totals are passed on
+__device__ __forceinline__ int wave_inclusive_sum(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Blocks of BLOCK tokens over ragged sequences, numbered without gaps (sequence 0's blocks first): block `id` is block `blk`
+// of sequence `b`, whose length (at most max_tokens) is `len`; false behind the last one.  A grid over (blocks of the
+// longest sequence, sequences) leaves holes where sequences are shorter, and with workgroups dealt to the eight dies in
+// turn some dies then get a whole extra round of work.  Every wave scans the lengths by itself, 64 at a time.
+template <int BLOCK>
+__device__ __forceinline__ bool find_block(const int32_t* seq_lens, int n_seqs, int max_tokens, int id, int& b, int& blk, int& len) {
+  const int lane = threadIdx.x & 63;
+  for (int base = 0; base < n_seqs; base += 64) {
+    const int l = base + lane < n_seqs ? min(max(seq_lens[base + lane], 0), max_tokens) : 0;
+    const int cnt = (l + BLOCK - 1) / BLOCK;
+    const int incl = wave_inclusive_sum(cnt);
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    if (id < total) {
+      const int s = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl > id));
+      b = base + s;
+      blk = id - __builtin_amdgcn_readlane(incl - cnt, s);
+      len = __builtin_amdgcn_readlane(l, s);
+      return true;
+    }
+    id -= total;
+  }
+  return false;
+}
+
 }  // namespace gqla

@@ -532,148 +532,223 @@ __global__ void __launch_bounds__(256) expand_tail_bf16_kernel(ExpandArgs a, con
 
 // ---- cache compression: latent from the expanded keys (Sec. 3.1: the reverse cache switch) --------------------------
 // c_s = A^+ k^C_s with the caller's left inverse A^+ ([r_kv][g*d_h], k^C ordered group-major, dim-minor); k_R copied.
-// One workgroup of 8 waves per (128 tokens, sequence) computes all r_kv latent dims of its tokens; wave (tw, rw)
-// owns tokens [64 tw, 64 tw + 64) x latent dims [128 rw, 128 rw + 128):
+// One workgroup of 4 waves per 128 tokens of a sequence computes all r_kv latent dims of its tokens; wave w owns latent dims
+// [128 w, 128 w + 128) of all 128 tokens (16 accumulator tiles: half of the SIMD's register file, the wave is alone on it):
 //   C^T[r][tok] = A^+[r][k] * K^T[k][tok]
-// The contraction runs in stages of 32 k.  Per stage the workgroup stages the [512 x 32] slice of A^+ and the
-// [128 tokens x 32] slice of the K_C plane through LDS (registers -> LDS, three buffers, one barrier per stage), as
-// planes of 8-element vectors, so that each MFMA operand is one conflict-free 16-byte LDS read; every element of A^+
-// is fetched once per 128 tokens instead of once per wave.
-constexpr int kCompressKS = 32;                       // contraction elements per stage
+// Stages of 64 k (whole 128-byte lines of A^+).  A wave holds the stage's 16 key fragments in registers and takes its rows of
+// A^+ in four units of 32: a unit is four fragments and 16 MFMAs, so that a fragment read from LDS serves four MFMAs.
+// Both operands travel by LDS-DMA:
+//   A^+   a private ring of seven 4 KB units per wave (it reads what it requested itself: no barrier), up to seven units, or
+//         3.6 k cycles of MFMAs, ahead; rows of 128 bytes, 16-byte chunks XORed with (row >> 1) & 7: conflict-free reads
+//   keys  a ring of three stages shared by the waves, [8 vector planes][128 tokens][16 bytes]: the cache page's own order,
+//         1 KB of consecutive memory per request; one barrier per stage
+// A unit's slot takes the request for the unit seven ahead as soon as its fragments are in registers, one unit before its
+// MFMAs end; the next stage's key fragments replace the current ones one by one behind the MFMAs that use them last.
+// What bounds it is the L2 that serves A^+ (every workgroup reads all of it, 1 MB at g d_h = 1024): 64-byte pieces of lines
+// (stages of 32 k) cost as many L2 requests as whole ones, and workgroups of a die that walk k in step ask one of its 16
+// channels for all their rows (they lie a multiple of 2 KB apart), so each starts at a different stage and wraps.
+// The results leave through LDS as whole rows (c_kv | k_R, 64 of them contiguous in the latent page).
+// Measured, 122 680 tokens in 32 ragged sequences, g d_h = 1024 (129 GFLOP, 409 MB): 246 us with registers -> LDS staging two
+// stages of 32 k ahead; 183 us with LDS-DMA and a ring of four such stages; 171 us with rotated starts; 138 us in this form
+// (whole lines, private rings, dense numbering of the tiles): 0.93 PFLOP/s, 3.0 TB/s.  MFMAs are in flight half of the time
+// a CU is busy; the rest is waiting for A^+ and keys (37 % of the wave cycles) and the start and end of a tile.
+constexpr int kCompressK = 64;                        // contraction elements per stage
 constexpr int kCompressTok = 128;                     // tokens per workgroup
-template <int RKV>
-constexpr int compress_lds_bytes() {
-  return 3 * (kCompressKS / 8) * ((RKV + 4) + kCompressTok) * 16;
-}
+constexpr int kCompressUnits = 7;                     // ring of A^+ units per wave
+constexpr int kCompressKeySlots = 3;                  // ring of key stages
+constexpr int kCompressUnit = 32 * kCompressK * 2;    // bytes of a unit: 32 rows x 128 bytes
+constexpr int kCompressKeys = kCompressTok * kCompressK * 2;
+constexpr int kCompressLds = 4 * kCompressUnits * kCompressUnit + kCompressKeySlots * kCompressKeys;  // all 160 KB
 
 template <int DH, int DV, int RKV, int DR>
-__global__ void __launch_bounds__(512) compress_bf16_kernel(CompressArgs a) {
-  static_assert(RKV == 512 && DH % kCompressKS == 0, "wave tiling below assumes 4 blocks of 128 latent dims");
-  constexpr int NC = kCompressKS / 8;                 // vector planes per stage
-  constexpr int WPL = RKV + 4;                        // plane stride of the A^+ tile, in vectors (padding spreads the writes)
-  constexpr int BUF = NC * (WPL + kCompressTok);      // vectors per buffer
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-  u32x4* smem = (u32x4*)smem_raw;
+__global__ void __launch_bounds__(256) compress_bf16_kernel(CompressArgs a) {
+  static_assert(RKV == 512 && DH % kCompressK == 0 && DH / kCompressK >= 2, "four waves x 128 latent dims, at least two stages");
+  constexpr int W = RKV + DR;
+  constexpr int PITCH = W * 2 + 16;                   // bytes per token of the output tile in LDS
+  static_assert(kCompressTok * PITCH <= kCompressLds, "the output tile reuses the rings");
+  extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, h = lane >> 5;
-  const int tw = wave & 1, rw = wave >> 1;
-  const int b = blockIdx.y;
-  const int L = a.seq_lens[b];
-  const int tok0 = blockIdx.x * kCompressTok;
-  if (tok0 >= L) return;
   const int P = a.expanded.page_size;
-  const int g = a.g;
-  const int K = g * DH;
-  const int64_t in_page_elems = (int64_t)P * (g * (DH + DV) + DR);
+  int b, blk, L;
+  if (!find_block<kCompressTok>(a.seq_lens, a.B, a.expanded.max_pages * P, blockIdx.x, b, blk, L)) return;  // whole workgroup
+  const int tok0 = blk * kCompressTok;
+  const int K = a.g * DH;
+  const int64_t in_page_bytes = (int64_t)P * (a.g * (DH + DV) + DR) * 2;
 
-  // staging role of this thread: one K vector per stage (token kt of the tile, plane kc) and four A^+ vectors
-  const int kt = tid & (kCompressTok - 1), kc = tid >> 7;
-  const __bf16* ksrc = nullptr;
+  // the two 64-token halves of the tile: page and slot (P is a multiple of 64, so a half lies in one page).  A half
+  // without tokens or behind a page id outside the pool reads page 0 instead: a token is one MFMA column, and the
+  // columns of such a half are never stored.
+  // The four table entries (two halves, two caches) come with one load, a lane each.
+  const char* half_src[2];
+  int32_t pg_out[2];
   {
-    const int tk = tok0 + (kt & 64);
-    if (tk < L) {
-      const int32_t pg = page_of(a.expanded, b, tk / P);
-      if (pg >= 0) ksrc = (const __bf16*)a.expanded.pool + pg * in_page_elems + ((int64_t)kc * P + tk % P + (kt & 63)) * 8;
+    const int my_tok = tok0 + 64 * (lane & 1);
+    const CacheView& view = lane & 2 ? a.latent : a.expanded;
+    const int32_t pg = my_tok < L ? page_of(view, b, my_tok / P) : -1;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int tk = tok0 + 64 * e;
+      const int32_t pin = __builtin_amdgcn_readlane(pg, e);
+      pg_out[e] = pin >= 0 ? __builtin_amdgcn_readlane(pg, 2 + e) : -1;
+      half_src[e] = (const char*)a.expanded.pool + (pin >= 0 ? pin : 0) * in_page_bytes + (pin >= 0 ? tk % P : 0) * 16;
     }
   }
-  const __bf16* wsrc = (const __bf16*)a.w_inv + (int64_t)(tid >> 2) * K + (tid & 3) * 8;   // + i * 128 rows, + stage * 32
-  const int wdst = (tid & 3) * WPL + (tid >> 2);                                            // + i * 128
-  const int kdst = NC * WPL + kc * kCompressTok + kt;
-
-  // Global memory is read in pairs of stages (64 contraction elements: whole 128-byte lines of A^+, the two halves
-  // requested back to back) into two register sets.  Rows of A^+ are 2 g d_h bytes apart, a power of two; as a
-  // precaution against all workgroups of an L2 asking for the same address bits at once, every eighth workgroup starts
-  // the contraction at a different stage pair and walks it cyclically (measured: neutral on this chip).
-  u32x4 wreg[2][4], kreg[2];
-  const int stages = K / kCompressKS, pairs = stages / 2;
-  const int rot = (int)((blockIdx.x + gridDim.x * blockIdx.y) >> 3) % pairs;
-  auto fetch = [&](int e, int step) {                 // half e of the step-th stage pair of this workgroup's walk
-    const int pr = step + rot < pairs ? step + rot : step + rot - pairs;
-    const int st = 2 * pr + e;
-    const int j = st / (DH / kCompressKS), v0 = j * (DH / 8) + (st % (DH / kCompressKS)) * NC;
+  // k_R of the tile, kept for the end: vector plane (tid >> 7) + 2 i of token tid % 128
+  u32x4 kr[DR / 16];
+  {
+    const int tk = tid & (kCompressTok - 1);
+    const char* src = (tk & 64 ? half_src[1] : half_src[0]) + (int64_t)a.g * P * (DH + DV) * 2 + (tk & 63) * 16;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) wreg[e][i] = *(const u32x4*)(wsrc + (int64_t)i * 128 * K + st * kCompressKS);
-    kreg[e] = ksrc ? *(const u32x4*)(ksrc + (int64_t)v0 * P * 8) : u32x4{0u, 0u, 0u, 0u};
+    for (int i = 0; i < DR / 16; ++i) kr[i] = *(const u32x4*)(src + (int64_t)((tid >> 7) + 2 * i) * P * 16);
+  }
+
+  // requests.  A^+ unit (u = 4 stage + rt): four of 8 rows; this lane's row and chunk (the swizzle term of rows 8 i .. 8 i + 7
+  // alternates with i).  Key stage: planes 2 wave, 2 wave + 1 of both token halves.
+  const uint32_t a_off0 = (uint32_t)((lane >> 3) * K * 2 + (((lane & 7) ^ (lane >> 4)) << 4));
+  const uint32_t a_off1 = (uint32_t)((lane >> 3) * K * 2 + (((lane & 7) ^ (4 + (lane >> 4))) << 4));
+  const uint32_t k_off = lane * 16;
+  const int stages = K / kCompressK;
+  const int rot = (int)(blockIdx.x >> 3) % stages;    // workgroups go to the eight dies in turn: blockIdx / 8 counts a die's own
+  const char* const a_rows = (const char*)a.w_inv + (int64_t)(128 * wave) * K * 2;
+  const int64_t rows8 = (int64_t)8 * K * 2;           // bytes from one request's rows to the next one's
+  const int64_t plane = (int64_t)P * 16;              // bytes of one vector plane of the page
+  char* const a_ring = smem + wave * (kCompressUnits * kCompressUnit);
+  char* const k_ring = smem + 4 * kCompressUnits * kCompressUnit;
+  const uint32_t a_lds = (uint32_t)(uintptr_t)(lds_ptr_t)a_ring;
+  const uint32_t k_lds = (uint32_t)(uintptr_t)(lds_ptr_t)k_ring + (2 * wave) * (kCompressTok * 16);
+  int a_stage = rot, k_stage = rot;                   // stage (in the rotated walk) of the next A^+ unit / key request
+  int a_fill = 0, k_fill = 0;                         // ring slots they go to
+  auto dma = [&](uint32_t dst, uint32_t off, const char* src) __attribute__((always_inline)) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(__builtin_amdgcn_readfirstlane(dst)), "v"(off), "s"(src) : "memory");
   };
-  auto stash = [&](int e, int buf) {
-    u32x4* dst = smem + buf * BUF;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) dst[wdst + i * 128] = wreg[e][i];
-    dst[kdst] = kreg[e];
+  auto request_a = [&](int rt, int i) __attribute__((always_inline)) {   // request i = 0..3 of the next unit, rows 32 rt ..
+    dma(a_lds + a_fill * kCompressUnit + i * 1024, i & 1 ? a_off1 : a_off0, a_rows + (4 * rt + i) * rows8 + a_stage * (kCompressK * 2));
+    if (i == 3) {
+      a_fill = a_fill + 1 == kCompressUnits ? 0 : a_fill + 1;
+      if (rt == 3) a_stage = a_stage + 1 == stages ? 0 : a_stage + 1;
+    }
   };
-
-  f32x16 acc[2][4];
-#pragma unroll
-  for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-    for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[tt][rt][i] = 0.f;
-
-  auto compute = [&](int buf) {
-    const u32x4* wt = smem + buf * BUF;
-    const u32x4* ktile = wt + NC * WPL;
-#pragma unroll
-    for (int ks = 0; ks < kCompressKS / 16; ++ks) {
-      u32x4 kf[2], wf[4];
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt) kf[tt] = ktile[(2 * ks + h) * kCompressTok + 64 * tw + 32 * tt + n];
-#pragma unroll
-      for (int rt = 0; rt < 4; ++rt) wf[rt] = wt[(2 * ks + h) * WPL + 128 * rw + 32 * rt + n];
-#pragma unroll
-      for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-        for (int rt = 0; rt < 4; ++rt)
-          acc[tt][rt] = mfma32(__builtin_bit_cast(bf16x8, wf[rt]), __builtin_bit_cast(bf16x8, kf[tt]), acc[tt][rt]);
+  auto request_k = [&](int i) __attribute__((always_inline)) {           // i = 0..3: plane 2 wave + i / 2, half i % 2
+    dma(k_lds + k_fill * kCompressKeys + (i >> 1) * (kCompressTok * 16) + (i & 1) * 1024, k_off,
+        half_src[i & 1] + (int64_t)(8 * k_stage + 2 * wave + (i >> 1)) * plane);
+    if (i == 3) {
+      k_fill = k_fill + 1 == kCompressKeySlots ? 0 : k_fill + 1;
+      k_stage = k_stage + 1 == stages ? 0 : k_stage + 1;
     }
   };
 
-  // Step s (in the rotated order) is computed from buffer s % 3 while step s + 1 goes from registers into buffer
-  // (s + 1) % 3 -- last read in iteration s - 2, which every wave has left through the barrier of iteration s - 1.
-  // Each register set is refilled from global memory right after it has been written to LDS, two steps before it is
-  // needed again.
-  fetch(0, 0);
-  fetch(1, 0);
-  stash(0, 0);
-  if (pairs > 1) fetch(0, 1);
-  __syncthreads();
-  int buf = 0;                                        // buffer of the even step of the pair
-  for (int pr = 0; pr < pairs; ++pr) {
-    const int b1 = buf == 2 ? 0 : buf + 1, b2 = b1 == 2 ? 0 : b1 + 1;
-    stash(1, b1);                                     // odd step of this pair
-    if (pr + 1 < pairs) fetch(1, pr + 1);
-    compute(buf);
-    __syncthreads();
-    if (pr + 1 < pairs) stash(0, b2);                 // even step of the next pair
-    if (pr + 2 < pairs) fetch(0, pr + 2);
-    compute(b1);
-    __syncthreads();
-    buf = b2;
-  }
-
-  const int tokh = tok0 + 64 * tw;                    // this wave's 64 tokens lie in one page
-  if (tokh >= L) return;
-  const int32_t pg_in = page_of(a.expanded, b, tokh / P), pg_out = page_of(a.latent, b, tokh / P);
-  if (pg_in < 0 || pg_out < 0) return;
-  const __bf16* in_page = (const __bf16*)a.expanded.pool + pg_in * in_page_elems;
-  __bf16* out_page = (__bf16*)a.latent.pool + (int64_t)pg_out * P * (RKV + DR);
+  f32x16 acc[4][4];                                   // [latent tile][token tile]
 #pragma unroll
-  for (int tt = 0; tt < 2; ++tt) {
-    const int slot = tokh % P + 32 * tt + n;
-    if (tokh + 32 * tt + n >= L) continue;
-    __bf16* row = out_page + (int64_t)slot * (RKV + DR);
+  for (int rt = 0; rt < 4; ++rt)
+#pragma unroll
+    for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[rt][tt][i] = 0.f;
+
+  bf16x8 af[2][4], kf[4][4];                          // A^+ fragments [unit parity][k-step], key fragments [k-step][token tile]
+  uint32_t a_read[4], k_read = h * (kCompressTok * 16) + n * 16;
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) a_read[ks] = n * 128 + (((2 * ks + h) ^ ((n >> 1) & 7)) << 4);
+  int a_slot = 0, k_slot = 0;                         // ring slots of the next unit / key stage to be read
+  auto load_a = [&](int par, int ks) __attribute__((always_inline)) { af[par][ks] = *(const bf16x8*)(a_ring + a_slot * kCompressUnit + a_read[ks]); };
+  auto load_k = [&](int ks, int tt) __attribute__((always_inline)) {
+    kf[ks][tt] = *(const bf16x8*)(k_ring + k_slot * kCompressKeys + k_read + 2 * ks * (kCompressTok * 16) + 32 * tt * 16);
+  };
+
+  // Order of the requests: key stage s + 3 goes out right before A^+ unit 4 s + 10.  Requests complete in order, so a
+  // unit that has landed vouches for the key stage requested before it.
+  auto request_unit = [&](int rt) __attribute__((always_inline)) {
+    static_for<4>([&](auto I) __attribute__((always_inline)) { request_a(rt, decltype(I)::value); });
+  };
+  auto request_keys = [&]() __attribute__((always_inline)) {
+    static_for<4>([&](auto I) __attribute__((always_inline)) { request_k(decltype(I)::value); });
+  };
+  request_keys();
+  request_unit(0);
+  request_unit(1);
+  request_keys();
+  request_unit(2);
+  request_unit(3);
+  request_unit(0);
+  request_unit(1);
+  if (stages > 2) request_keys();
+  request_unit(2);
+  asm volatile("s_waitcnt vmcnt(28)" ::: "memory");   // at most units 1 .. 6 and the second key stage outstanding
+  __syncthreads();                                    // key stage 0 has landed for every wave
+  static_for<4>([&](auto KS) __attribute__((always_inline)) {
+    load_a(0, decltype(KS)::value);
+    static_for<4>([&](auto TT) __attribute__((always_inline)) { load_k(decltype(KS)::value, decltype(TT)::value); });
+  });
+  a_slot = 1;
+  k_slot = 1;
+
+  // One unit: its 16 MFMAs, and behind them the fragments of the next unit, the request for the unit seven ahead and, in
+  // the stage's last unit, the next stage's key fragments.  KIND: 0 steady, 3 the third last
+  // (no key stage left to request), 1 the stage before the last, 2 the last (nothing left to request): compile-time, so
+  // that nothing branches between the MFMAs.
+  auto stage_step = [&](auto KIND_T) __attribute__((always_inline)) {
+    constexpr int KIND = decltype(KIND_T)::value;
+    static_for<4>([&](auto RT_T) __attribute__((always_inline)) {
+      constexpr int rt = decltype(RT_T)::value;
+      constexpr bool next_unit = KIND != 2 || rt < 3;             // a unit follows
+      constexpr bool req = KIND == 0 || KIND == 3 || (KIND == 1 && rt == 0);   // the unit seven ahead exists
+      constexpr bool next_keys = KIND != 2 && rt == 3;
+      // requests made after those of the next unit (see the order above): what may still be outstanding
+      constexpr int behind = KIND == 0 || KIND == 3 ? (rt == 0 ? 28 : 24) : (KIND == 1 ? (rt == 0 ? 24 : (rt == 1 ? 20 : (rt == 2 ? 16 : 12)))
+                                                                          : (rt == 0 ? 8 : (rt == 1 ? 4 : 0)));
+      if constexpr (next_unit) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(behind) : "memory");
+      if constexpr (next_keys) __syncthreads();       // the next key stage has landed for every wave; all hold this one in registers
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<16>([&](auto X) __attribute__((always_inline)) {
+        constexpr int x = decltype(X)::value, ks = x >> 2, tt = x & 3;
+        acc[rt][tt] = mfma32(af[rt & 1][ks], kf[ks][tt], acc[rt][tt]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (next_unit && x < 4) load_a((rt + 1) & 1, x);
+        if constexpr (next_keys) load_k(ks, tt);      // (the fragment's last use was the MFMA above)
+        if constexpr (KIND == 0 && rt == 3 && x >= 4 && x < 8) request_k(x - 4);
+        // (the unit's last fragments were operands of MFMA 12: its ring slot is free)
+        if constexpr (req && x >= 12) request_a((rt + 3) & 3, x - 12);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      a_slot = a_slot + 1 == kCompressUnits ? 0 : a_slot + 1;
+      if constexpr (next_keys) k_slot = k_slot + 1 == kCompressKeySlots ? 0 : k_slot + 1;
+    });
+  };
+  int st = 0;
+#pragma unroll 1
+  for (; st + 3 < stages; ++st) stage_step(std::integral_constant<int, 0>{});
+#pragma unroll 1
+  for (; st + 2 < stages; ++st) stage_step(std::integral_constant<int, 3>{});
+  stage_step(std::integral_constant<int, 1>{});
+  stage_step(std::integral_constant<int, 2>{});
+
+  __syncthreads();                                    // (every fragment has been read: the last barrier was before that)
+#pragma unroll
+  for (int tt = 0; tt < 4; ++tt)
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const u32x2 v = {pack_bf16(acc[tt][rt][4 * q], acc[tt][rt][4 * q + 1]), pack_bf16(acc[tt][rt][4 * q + 2], acc[tt][rt][4 * q + 3])};
-        *(u32x2*)(row + 128 * rw + 32 * rt + 8 * q + 4 * h) = v;
+        const u32x2 v = {pack_bf16(acc[rt][tt][4 * q], acc[rt][tt][4 * q + 1]), pack_bf16(acc[rt][tt][4 * q + 2], acc[rt][tt][4 * q + 3])};
+        *(u32x2*)(smem + (32 * tt + n) * PITCH + (128 * wave + 32 * rt + 8 * q + 4 * h) * 2) = v;
       }
-    if (rw == 0) {  // k_R: dims 8c .. 8c + 7 for c = h, h + 2, ...
-      const __bf16* rp = in_page + (int64_t)g * P * (DH + DV);
 #pragma unroll
-      for (int c = h; c < DR / 8; c += 2) *(u32x4*)(row + RKV + c * 8) = *(const u32x4*)(rp + ((int64_t)c * P + slot) * 8);
+  for (int i = 0; i < DR / 16; ++i)
+    *(u32x4*)(smem + (tid & (kCompressTok - 1)) * PITCH + RKV * 2 + ((tid >> 7) + 2 * i) * 16) = kr[i];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    if (pg_out[e] < 0) continue;
+    const int tk = tok0 + 64 * e;
+    constexpr int VPR = W / 8;                        // 16-byte vectors per row
+    const int total = min(64, L - tk) * VPR;
+    u32x4* dst = (u32x4*)((char*)a.latent.pool + ((int64_t)pg_out[e] * P + tk % P) * (W * 2));
+    for (int v = tid; v < total; v += 256) {
+      const int r = v / VPR, c = v % VPR;
+      __builtin_nontemporal_store(*(const u32x4*)(smem + (64 * e + r) * PITCH + c * 16), dst + v);
     }
   }
 }
@@ -682,12 +757,13 @@ __global__ void __launch_bounds__(512) compress_bf16_kernel(CompressArgs a) {
 
 template <int DH, int DV>
 static hipError_t launch_compress_dims(const CompressArgs& a, hipStream_t s) {
-  constexpr int lds = compress_lds_bytes<512>();
   static const hipError_t attr =
-      hipFuncSetAttribute((const void*)compress_bf16_kernel<DH, DV, 512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      hipFuncSetAttribute((const void*)compress_bf16_kernel<DH, DV, 512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kCompressLds);
   if (attr != hipSuccess) return attr;
   const int64_t max_tokens = (int64_t)a.expanded.max_pages * a.expanded.page_size;
-  compress_bf16_kernel<DH, DV, 512, 64><<<dim3((unsigned)((max_tokens + kCompressTok - 1) / kCompressTok), a.B), 512, lds, s>>>(a);
+  const int64_t blocks = (max_tokens + kCompressTok - 1) / kCompressTok * a.B;
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  compress_bf16_kernel<DH, DV, 512, 64><<<(unsigned)blocks, 256, kCompressLds, s>>>(a);
   return hipGetLastError();
 }
 

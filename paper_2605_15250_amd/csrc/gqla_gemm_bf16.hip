@@ -162,7 +162,7 @@ __global__ void __launch_bounds__(256) pack_weights_bf16_kernel(ExpandArgs a, __
   }
 }
 
-// Step 2: one workgroup of 4 waves per (256-token block, sequence); wave w owns 64 tokens (two 32-token tiles) and,
+// Step 2: one workgroup of 4 waves per 256-token block of a sequence; wave w owns 64 tokens (two 32-token tiles) and,
 // alone on its SIMD, the whole 512-entry register file.  Each wave keeps its tokens' latent rows as 2 x 32 register
 // fragments (lane = token, 8 consecutive latent dims per k-step) and reuses them for every group and for both K and V,
 // so the latent is read from HBM once.  The packed weights stream through LDS one 64 KB stage at a time (LDS-DMA,
@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(256) pack_weights_bf16_kernel(ExpandArgs a, __
 // With an odd number of stages per group (DH = 192, DV = 256: seven) the two result sets would meet at the group
 // boundary, so there the group's last stage stores its results at once instead of in the next stage's shadow.
 template <int DH, int DV, int RKV, int DR, bool FP8>
-__global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __bf16* packed) {
+__global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __bf16* packed, int parts) {
   constexpr int W = RKV + DR;
   constexpr int KS = RKV / 16;
   constexpr int STAGE_BYTES = KS * 2 * 1024;  // 64 KB
@@ -189,12 +189,14 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
-  const int b = blockIdx.y;
-  const int L = a.seq_lens[b];
-  const int tok0 = blockIdx.x * 256;
-  if (tok0 >= L) return;  // whole workgroup
   const int P = a.latent.page_size;
   const int gc = a.group_count;
+  // workgroup -> (256-token block, share of the groups)
+  int b, blk, L;
+  const int part = blockIdx.x % parts;
+  if (!find_block<256>(a.seq_lens, a.B, a.latent.max_pages * P, blockIdx.x / parts, b, blk, L)) return;  // whole workgroup
+  const int tok0 = blk * 256;
+  const int jj_begin = gc * part / parts, jj_end = gc * (part + 1) / parts;
   const int tokw = tok0 + wave * 64;  // first token of this wave (a wave never straddles a page: P % 64 == 0)
   int32_t pg_in = -1, pg_out = -1;
   if (tokw < L) {
@@ -220,7 +222,7 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
     for (int ks = 0; ks < KS; ++ks)
       asm volatile("global_load_dwordx4 %0, %1, off" : "=a"(xf[nt][ks]) : "v"(in_row + ks * 16 + h * 8));
     // k_R plane: a straight copy, 8 dims (16 bytes) per lane and step
-    if (tok_ok) {
+    if (tok_ok && part == 0) {
 #pragma unroll
       for (int cb = h; cb < DR / 8; cb += 2) {
         const u32x4 v = *(const u32x4*)(in_row + RKV + cb * 8);
@@ -333,22 +335,23 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
     emit_prev(pack_prev(par, nt, e, qp), kind, mtp, jj, nt, e, qp);
   };
 
-  const int n_stages = gc * NSUB;
-  stage_in(0, smem);
+  const int stage0 = jj_begin * NSUB, n_stages = jj_end * NSUB;  // this workgroup's stages
+  stage_in(stage0, smem);
   wait_all_memory();
   __syncthreads();
-  for (int jj = 0; jj < gc; ++jj) {
+  for (int jj = jj_begin; jj < jj_end; ++jj) {
     static_for<NSUB>([&](auto SUB) __attribute__((always_inline)) {  // compile time: fixes the kind (MFMA operand order) and the result set
       constexpr int sub = decltype(SUB)::value;
       const int stage = jj * NSUB + sub;
-      const char* buf = smem + (stage & 1) * STAGE_BYTES + lane * 16;
+      const int odd = (stage - stage0) & 1;            // LDS buffer of this stage
+      const char* buf = smem + odd * STAGE_BYTES + lane * 16;
       f32x16 (&acc)[2][2] = accs[sub & 1];
       // the stage before this one, whose results leave in this stage's shadow (none at the start of a group when the
       // group's last stage has stored its own)
       constexpr int kPrevNone = -1;
       constexpr int psub = sub > 0 ? sub - 1 : (ODD ? kPrevNone : NSUB - 1);
       constexpr int pkind = psub >= NSK, pmtp = pkind ? psub - NSK : psub, ppar = psub & 1;
-      const int pjj = psub == kPrevNone ? -1 : (sub == 0 ? jj - 1 : jj);
+      const int pjj = psub == kPrevNone ? -1 : (sub == 0 ? (jj > jj_begin ? jj - 1 : -1) : jj);
       if (wave_ok) {
         bf16x8 w[DEPTH + 1][2];
 #pragma unroll
@@ -384,7 +387,7 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
           __builtin_amdgcn_sched_barrier(0);
           mm(ks, 1, 0);
           // (after the last stage this stages that stage once more, into the buffer nobody reads any more: no branch)
-          if (ks < 16) stage_in_step(min(stage + 1, n_stages - 1), smem + ((stage + 1) & 1) * STAGE_BYTES, ks);
+          if (ks < 16) stage_in_step(min(stage + 1, n_stages - 1), smem + (odd ^ 1) * STAGE_BYTES, ks);
           __builtin_amdgcn_sched_barrier(0);
           mm(ks, 1, 1);
           // the previous stage's results leave in the shadow of this stage's MFMAs
@@ -408,7 +411,7 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
           }
         }
       } else {
-        stage_in(min(stage + 1, n_stages - 1), smem + ((stage + 1) & 1) * STAGE_BYTES);  // a wave without tokens still stages its share
+        stage_in(min(stage + 1, n_stages - 1), smem + (odd ^ 1) * STAGE_BYTES);  // a wave without tokens still stages its share
       }
       wait_all_memory();
       __syncthreads();  // next stage has landed; everyone is done with this stage's buffer
@@ -416,10 +419,10 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
   }
   if constexpr (FP8) {
 #pragma unroll
-    for (int piece = 0; piece < 4; ++piece) store_prev8((NSUB - 1) & 1, 1, NSUB - 1 - NSK, gc - 1, piece >> 1, piece & 1);
+    for (int piece = 0; piece < 4; ++piece) store_prev8((NSUB - 1) & 1, 1, NSUB - 1 - NSK, jj_end - 1, piece >> 1, piece & 1);
   } else if constexpr (!ODD) {
 #pragma unroll
-    for (int piece = 0; piece < 8; ++piece) store_prev((NSUB - 1) & 1, 1, NSUB - 1 - NSK, gc - 1, piece >> 2, (piece >> 1) & 1, piece & 1);
+    for (int piece = 0; piece < 8; ++piece) store_prev((NSUB - 1) & 1, 1, NSUB - 1 - NSK, jj_end - 1, piece >> 2, (piece >> 1) & 1, piece & 1);
   }
 }
 
@@ -814,11 +817,17 @@ static hipError_t launch_expand_one_shot(const ExpandArgs& a, void* ws, hipStrea
       hipFuncSetAttribute((const void*)expand_bf16_kernel<DH, DV, 512, 64, FP8>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
   const int64_t max_tokens = (int64_t)a.latent.max_pages * a.latent.page_size;
-  dim3 grid((unsigned)((max_tokens + 255) / 256), a.B);
+  const int64_t blocks = (max_tokens + 255) / 256 * a.B;
+  // Few blocks (a short prefill, a single sequence): the groups are shared out as well, as far as one round of workgroups
+  // takes it; the latent rows are then read once per share.  (One sequence of 8192 tokens, 8 groups: 81 us in 32 workgroups,
+  // 28 us in 256.  Half a chip's worth of blocks or more is left alone: 122 680 ragged tokens, 480 blocks, take 242 us --
+  // 285 us before find_block, when the holes of the grid left some dies a third round of blocks.)
+  const int parts = (int)(blocks * 2 <= 256 ? (256 / blocks < a.group_count ? 256 / blocks : a.group_count) : 1);
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   pack_weights_bf16_kernel<DH, DV, 512><<<dim3(a.group_count * NSUB, 512 / 64), 256, 0, s>>>(a, (__bf16*)ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  expand_bf16_kernel<DH, DV, 512, 64, FP8><<<grid, 256, kLds, s>>>(a, (const __bf16*)ws);
+  expand_bf16_kernel<DH, DV, 512, 64, FP8><<<(unsigned)(blocks * parts), 256, kLds, s>>>(a, (const __bf16*)ws, parts);
   return hipGetLastError();
 }
 hipError_t launch_expand_bf16(const ExpandArgs& a, void* ws, hipStream_t s) {

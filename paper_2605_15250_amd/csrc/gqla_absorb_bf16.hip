@@ -1279,134 +1279,179 @@ __global__ void __launch_bounds__(256) decode_absorb_fp8_kernel(DecodeArgs a, in
 }
 
 // ---- combine + latent-output projection: out = W_UV[j]^T (sum_k w_k o_hat_k)   (MQA-absorb equation, line 6) ----
-// One workgroup of 4 waves per (group j, 32 query rows of that group; 8 rows when the batch is small).  W_UV[j] ([r_kv][d_h], 128 KB) is staged in LDS
-// and read transposed; wave w contracts over latent dims [w*RKV/4, (w+1)*RKV/4):
-//   O^T[d][row] += W^T[d][r] * Ohat^T[r][row]     A = transposed LDS fragments, B = the combined chunk partials
-// and the four partial O^T are summed through LDS.
-// DV: value dims per head (columns of W_UV[j], elements of an output row); a workgroup projects onto DH = 128 of them,
-// blockIdx.z selects which (the staged slice of W_UV is then 128 KB whatever DV is; the merge is repeated per slice).
-template <int RKV, int DH, int DV>
-__global__ void __launch_bounds__(256) combine_project_bf16_kernel(CombineArgs a, int rows_per_group, int rows_per_wg) {
-  constexpr int KSW = RKV / 16 / 4;  // k-steps per wave
-  constexpr int MT = DH / 32;
-  static_assert(MT == 4, "one output tile per wave in the final reduction");
+// A workgroup of 8 waves takes blocks of query rows of one group j.  W_UV[j] ([r_kv][128 of the value dims], 128 KB) is
+// staged in LDS once and stays there for all of them.  Per block:
+//   merge     wave w merges the chunk partials of latent dims [64 w, 64 w + 64) by their log-sum-exps (online, kNB chunks in
+//             flight) and writes the merged latent as four MFMA operand fragments (bf16) into a 32 KB exchange
+//   project   O^T[d][row] = W^T[d][r] * Ohat^T[r][row]: wave w < 4 owns value dims [32 w, 32 w + 32) over all r; the first
+//             partials of everyone's next block are already requested
+// A block has 32 columns: 32 rows, or rows_per_block = 8 or 4 rows times 4 or 8 slices of the chunks (column = row +
+// rows_per_block * slice), so that a single sequence's long chain of partials (20 to 130 chunks) is merged by all lanes at
+// once.  The projection is linear: the slices' columns, each scaled by its share of the softmax weight, are projected as
+// they are and summed afterwards, when a row has 16 values per lane left instead of 64.
+// What it costs is the chain first_slot -> partials -> exchange -> MFMAs and the bytes of partials and W_UV a CU pulls in; the
+// staging of W_UV goes out behind the first partials, because loads complete in order and the partials are needed first.
+// Measured (kernel): one sequence, 22 chunks, 128 rows: 18.2 -> 7.9 us; 64 sequences, 4 chunks each: 13.1 -> 12.0 us; 128
+// ragged sequences of 256 rows, 201 MB of partials: 50.7 -> 35.5 us.  (Before: a block per workgroup, W_UV staged by each and
+// ahead of the partials, the K range split over the waves and 64 KB of fp32 results summed through LDS.)
+// DV: value dims per head (columns of W_UV[j], elements of an output row); a workgroup projects onto 128 of them, blockIdx.z
+// selects which (the merge is repeated per slice of 128).
+template <int RKV, int DV>
+__global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a, int rows_per_group, int log2_rows, int n_blocks) {
+  constexpr int DH = 128;
+  constexpr int KSW = RKV / 16 / 8;  // k-steps of the contraction that one wave merges
+  constexpr int kNB = 4;             // chunks in flight
+  static_assert(KSW == 4, "eight waves x 4 k-steps");
   extern __shared__ __attribute__((aligned(16))) char smem[];
+  char* const exch = smem + RKV * DH * 2;  // [k-step][lane][16 bytes]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
   const int j = blockIdx.y;
   const int col0 = blockIdx.z * DH;  // first value dim of this workgroup
-  stage_panels_full<RKV, DH / 64, 4, DV * 2>(smem, (const char*)a.w_uv + ((int64_t)j * RKV * DV + col0) * 2, wave, lane);
+  const int rows = 1 << log2_rows, slice = n >> log2_rows, slices = 32 >> log2_rows;
+  const int64_t chunk_stride = (int64_t)((a.M + 31) / 32) * 32 * RKV;  // elements from one chunk's partials to the next
 
-  // row of this lane among the rows of group j: x = (b * s_q + t) * G + head-in-group
-  // rows_per_wg < 32 (small batches): more workgroups, each with only its first lanes holding a row, so that the merge of
-  // many chunk partials is spread over the chip; lanes without a row compute on row 0 and store nothing.
-  const int x = blockIdx.x * rows_per_wg + n;
-  const bool row_ok = n < rows_per_wg && x < rows_per_group;
-  const int xc = row_ok ? x : 0;
-  const int b = xc / (a.s_q * a.G);
-  const int t = (xc / a.G) % a.s_q;
-  const int rho = t * a.h_q + j * a.G + xc % a.G;
-  const int s0 = a.first_slot[b], s1 = a.first_slot[b + 1];
-  // Log-sum-exp merge of the row's chunk partials in ONE pass, kNB chunks at a time so that their loads (log-sum-exps
-  // and latent vectors) are in flight together; the running maximum moves as in an online softmax.  (Three passes
-  // with one dependent load per chunk each cost three memory latencies per chunk.)
-  constexpr int kNB = 4;
-  float m = GQLA_NEG_INF, den = 0.f;
-  // combined latent output of this lane's row, dims 16*(KSW*wave + ksl) + 8*h + 0..7, fp32
-  float acc[KSW][8];
+  // this lane's row (index rho within its sequence b) and its chunks: s0 + slice, s0 + slice + slices, ... below s1
+  struct Row {
+    int b, rho, s0, s1, ok;
+  };
+  auto row_of = [&](int blk) __attribute__((always_inline)) {
+    Row r;
+    const int x = blk * rows + (n & (rows - 1));  // row of group j: (b * s_q + t) * G + head-in-group
+    r.ok = x < rows_per_group;
+    const int xc = r.ok ? x : 0;                  // a lane without a row computes on row 0 and stores nothing
+    r.b = xc / (a.s_q * a.G);
+    r.rho = (xc / a.G) % a.s_q * a.h_q + j * a.G + xc % a.G;
+    r.s0 = a.first_slot[r.b];
+    r.s1 = a.first_slot[r.b + 1];
+    return r;
+  };
+  float l[kNB];
+  u32x4 v[kNB][KSW];
+  auto fetch = [&](const Row& r, int k, int chunk) __attribute__((always_inline)) {
+    const int sc = min(chunk, r.s1 - 1);          // a chunk beyond the range is loaded again and given weight 0
+    l[k] = a.part_lse[(int64_t)sc * a.M + r.rho];
+    const __bf16* po = (const __bf16*)a.part_o + part_vec_index(0, r.rho, a.M, RKV / 8, 2 * KSW * wave + h) * 8 + sc * chunk_stride;
 #pragma unroll
-  for (int ksl = 0; ksl < KSW; ++ksl)
+    for (int ks = 0; ks < KSW; ++ks) v[k][ks] = *(const u32x4*)(po + ks * (2 * 32 * 8));
+  };
+
+  Row row = row_of(blockIdx.x);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[ksl][e] = 0.f;
-  // vector 2 (KSW wave + ksl) + h of the lane's row, chunk 0 (see part_vec_index: consecutive rows are 16 bytes apart)
-  const __bf16* po = (const __bf16*)a.part_o + part_vec_index(0, rho, a.M, RKV / 8, 2 * KSW * wave + h) * 8;
-  const int64_t chunk_stride = (int64_t)((a.M + 31) / 32) * 32 * RKV;   // elements from one chunk's partials to the next
-  for (int sb = s0; sb < s1; sb += kNB) {
-    float l[kNB];
-    u32x4 v[kNB][KSW];
+  for (int k = 0; k < kNB; ++k) fetch(row, k, row.s0 + slice + k * slices);
+  {
+    // (the builtin, not the assembly of gqla_lds.h: the compiler then counts these requests and waits for the partials
+    // without them)
+    __builtin_amdgcn_sched_barrier(0);
+    const uint32_t off = stage_lane_offset<RKV, DH / 64, 8, DV * 2>(wave, lane);
+    const char* w = (const char*)a.w_uv + ((int64_t)j * RKV * DV + col0) * 2;
 #pragma unroll
-    for (int k = 0; k < kNB; ++k) {
-      const int sc = min(sb + k, s1 - 1);  // clamped: a chunk beyond the range is loaded again and given weight 0
-      l[k] = a.part_lse[(int64_t)sc * a.M + rho];
-#pragma unroll
-      for (int ksl = 0; ksl < KSW; ++ksl) v[k][ksl] = *(const u32x4*)(po + sc * chunk_stride + ksl * (2 * 32 * 8));
-    }
-    float m_new = m;
-#pragma unroll
-    for (int k = 0; k < kNB; ++k) {
-      if (sb + k >= s1) l[k] = GQLA_NEG_INF;
-      m_new = fmaxf(m_new, l[k]);
-    }
-    const float m_use = (m_new == GQLA_NEG_INF) ? 0.f : m_new;
-    const float rescale = __expf(m - m_use);  // 0 on the first batch (m = -inf), where den and acc are 0 anyway
-    den *= rescale;
-#pragma unroll
-    for (int ksl = 0; ksl < KSW; ++ksl)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) acc[ksl][e] *= rescale;
-    m = m_new;
-#pragma unroll
-    for (int k = 0; k < kNB; ++k) {
-      const float w = __expf(l[k] - m_use);
-      den += w;
-#pragma unroll
-      for (int ksl = 0; ksl < KSW; ++ksl)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc[ksl][2 * e] += w * bf16_bits_to_float(v[k][ksl][e] & 0xffffu);
-          acc[ksl][2 * e + 1] += w * bf16_bits_to_float(v[k][ksl][e] >> 16);
-        }
-    }
+    for (int u = 0; u < 16; ++u)  // panel u / 8, rows 64 (u % 8) + 8 wave + 0..7
+      __builtin_amdgcn_global_load_lds((gbl_ptr_t)(w + off + (64 * (u & 7)) * (DV * 2) + (u >> 3) * 128),
+                                       (lds_ptr_t)(smem + (u >> 3) * (RKV * 128) + (wave + 8 * (u & 7)) * 1024), 16, 0, 0);
   }
-  const float inv_den = (row_ok && den > 0.f) ? 1.f / den : 0.f;
-#pragma unroll
-  for (int ksl = 0; ksl < KSW; ++ksl)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[ksl][e] *= inv_den;
-
-  wait_all_memory();
-  __syncthreads();  // W_UV[j] staged
-
+  // transposed fragments of W_UV (tr_natural_frag of gqla_lds.h for tile `wave`: its parity picks the lane offsets)
   const TrNatural tr = make_tr_natural(lane);
-  f32x16 o[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) o[mt][i] = 0.f;
-  const char* wbase = smem + (KSW * wave) * 2048;  // this wave's rows of the staged matrix
-#pragma unroll
-  for (int ksl = 0; ksl < KSW; ++ksl) {
-    u32x4 pw = {pack_bf16(acc[ksl][0], acc[ksl][1]), pack_bf16(acc[ksl][2], acc[ksl][3]),
-                pack_bf16(acc[ksl][4], acc[ksl][5]), pack_bf16(acc[ksl][6], acc[ksl][7])};
-    const bf16x8 bfrag = __builtin_bit_cast(bf16x8, pw);
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) o[mt] = mfma32(tr_natural_frag<RKV>(wbase, tr, ksl, mt), bfrag, o[mt]);
-  }
+  const char* const tr0 = smem + (wave >> 1) * (RKV * 128) + (wave & 1 ? tr.base[0][1] : tr.base[0][0]);
+  const char* const tr1 = smem + (wave >> 1) * (RKV * 128) + (wave & 1 ? tr.base[1][1] : tr.base[1][0]);
+  auto w_frag = [&](int ks) __attribute__((always_inline)) -> bf16x8 {
+    const i16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tr0 + ks * 2048));
+    const i16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tr1 + ks * 2048));
+    const i16x8 r = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+    return __builtin_bit_cast(bf16x8, r);
+  };
+  bool staged = false;
 
-  // sum the four waves' partial O^T through LDS: slot [wave][mt][i][lane]
-  __syncthreads();  // everyone is done reading the staged weights
-  float* red = (float*)smem;
+  for (int blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {
+    Row next = row;
+    if (blk + (int)gridDim.x < n_blocks) next = row_of(blk + gridDim.x);  // (its chunk range arrives behind the merge)
+    float m = GQLA_NEG_INF, den = 0.f;
+    float acc[KSW][8];  // merged latent of this lane's column, dims 16 * (KSW * wave + ks) + 8 * h + 0..7
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+    for (int ks = 0; ks < KSW; ++ks)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) red[((wave * MT + mt) * 16 + i) * 64 + lane] = o[mt][i];
-  __syncthreads();
-  float r[16];
+      for (int e = 0; e < 8; ++e) acc[ks][e] = 0.f;
+    auto add_batch = [&](int sb) __attribute__((always_inline)) {  // chunks sb, sb + slices, ... in the registers
+      float w[kNB], m_new = m;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    r[i] = 0.f;
+      for (int k = 0; k < kNB; ++k) {
+        w[k] = sb + k * slices < row.s1 ? l[k] : GQLA_NEG_INF;
+        m_new = fmaxf(m_new, w[k]);
+      }
+      const float m_use = (m_new == GQLA_NEG_INF) ? 0.f : m_new;
+      const float rescale = __expf(m - m_use);  // 0 on the first batch (m = -inf), where den and acc are 0 anyway
+      den *= rescale;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) r[i] += red[((w * MT + wave) * 16 + i) * 64 + lane];
+      for (int ks = 0; ks < KSW; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[ks][e] *= rescale;
+      m = m_new;
+#pragma unroll
+      for (int k = 0; k < kNB; ++k) {
+        const float wk = __expf(w[k] - m_use);
+        den += wk;
+#pragma unroll
+        for (int ks = 0; ks < KSW; ++ks)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            acc[ks][2 * e] += wk * bf16_bits_to_float(v[k][ks][e] & 0xffffu);
+            acc[ks][2 * e + 1] += wk * bf16_bits_to_float(v[k][ks][e] >> 16);
+          }
+      }
+    };
+    int sb = row.s0 + slice;
+    add_batch(sb);
+    sb += kNB * slices;
+    // (every lane walks as many batches as the longest of its wave needs)
+    for (; __builtin_amdgcn_ballot_w64(sb < row.s1) != 0; sb += kNB * slices) {
+#pragma unroll
+      for (int k = 0; k < kNB; ++k) fetch(row, k, sb + k * slices);
+      add_batch(sb);
+    }
+    // the slices of a row: common reference and denominator
+    float m_row = m;
+    for (int o = rows; o < 32; o <<= 1) m_row = fmaxf(m_row, __shfl_xor(m_row, o));
+    const float scale_own = __expf(m - ((m_row == GQLA_NEG_INF) ? 0.f : m_row));
+    float den_row = den * scale_own;
+    for (int o = rows; o < 32; o <<= 1) den_row += __shfl_xor(den_row, o);
+    const float norm = (row.ok && den_row > 0.f) ? scale_own / den_row : 0.f;
+    if (blk != (int)blockIdx.x) __syncthreads();  // every wave has read the previous block's exchange
+#pragma unroll
+    for (int ks = 0; ks < KSW; ++ks)
+      *(u32x4*)(exch + (KSW * wave + ks) * 1024 + lane * 16) =
+          u32x4{pack_bf16(acc[ks][0] * norm, acc[ks][1] * norm), pack_bf16(acc[ks][2] * norm, acc[ks][3] * norm),
+                pack_bf16(acc[ks][4] * norm, acc[ks][5] * norm), pack_bf16(acc[ks][6] * norm, acc[ks][7] * norm)};
+    if (!staged) {
+      wait_all_memory();                           // W_UV[j]: this wave's share
+      staged = true;
+    }
+    if (blk + (int)gridDim.x < n_blocks) {
+#pragma unroll
+      for (int k = 0; k < kNB; ++k) fetch(next, k, next.s0 + slice + k * slices);
+    }
+    __builtin_amdgcn_s_waitcnt(0xc07f);            // lgkmcnt(0)
+    __syncthreads();                               // the exchange (and, the first time, W_UV[j]) is complete
+    if (wave < 4) {
+      f32x16 o;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) o[i] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < RKV / 16; ++ks)
+        o = mfma32(w_frag(ks), *(const bf16x8*)(exch + ks * 1024 + lane * 16), o);
+      for (int sh = rows; sh < 32; sh <<= 1)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) o[i] += __shfl_xor(o[i], sh);
+      if (row.ok && slice == 0) {
+        __bf16* out = (__bf16*)a.out + ((int64_t)row.b * a.M + row.rho) * DV + col0 + wave * 32;  // this wave's dims
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *(u32x2*)(out + 8 * q + 4 * h) = u32x2{pack_bf16(o[4 * q], o[4 * q + 1]), pack_bf16(o[4 * q + 2], o[4 * q + 3])};
+        if (a.lse && h == 0 && wave == 0 && col0 == 0) a.lse[(int64_t)row.b * a.M + row.rho] = m_row + __logf(den_row);
+      }
+    }
+    row = next;
   }
-  if (!row_ok) return;
-  __bf16* out = (__bf16*)a.out + ((int64_t)b * a.M + rho) * DV + col0 + wave * 32;  // this wave writes dims col0 + 32*wave .. +31
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    u32x2 v = {pack_bf16(r[4 * q], r[4 * q + 1]), pack_bf16(r[4 * q + 2], r[4 * q + 3])};
-    *(u32x2*)(out + 8 * q + 4 * h) = v;
-  }
-  if (a.lse && h == 0 && wave == 0 && col0 == 0) a.lse[(int64_t)b * a.M + rho] = m + __logf(den);
 }
 
 }  // namespace
@@ -1469,16 +1514,18 @@ hipError_t launch_decode_absorb_fp8(const DecodeArgs& a, float c_scale, hipStrea
 
 template <int DV>
 static hipError_t launch_combine_project_dv(const CombineArgs& a, hipStream_t s) {
-  constexpr int kLds = 512 * 128 * 2;
+  constexpr int kLds = 512 * 128 * 2 + 32 * 1024;  // W_UV[j] and the exchange: all 160 KB
   // once per process (function-local statics are initialised under a lock); an error is reported by every call
   static const hipError_t attr =
-      hipFuncSetAttribute((const void*)combine_project_bf16_kernel<512, 128, DV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+      hipFuncSetAttribute((const void*)combine_project_bf16_kernel<512, DV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
   const int rows_per_group = a.B * a.s_q * a.G;
-  // 32 rows per workgroup fill the MFMA tile; with fewer than half a chip's worth of such workgroups, 8 or 4 rows each
-  const int rows_per_wg = ((rows_per_group + 31) / 32) * a.g >= 128 ? 32 : (((rows_per_group + 7) / 8) * a.g >= 128 ? 8 : 4);
-  combine_project_bf16_kernel<512, 128, DV><<<dim3((rows_per_group + rows_per_wg - 1) / rows_per_wg, a.g, DV / 128), 256, kLds, s>>>(
-      a, rows_per_group, rows_per_wg);
+  // 32 rows per block fill the MFMA tile; with fewer than half a chip's worth of such blocks, 8 or 4 rows each
+  const int log2_rows = ((rows_per_group + 31) / 32) * a.g >= 128 ? 5 : (((rows_per_group + 7) / 8) * a.g >= 128 ? 3 : 2);
+  const int n_blocks = (rows_per_group + (1 << log2_rows) - 1) >> log2_rows;
+  const int per_group = 256 / (a.g * (DV / 128));  // workgroups per group: one per compute unit, each with its share of the blocks
+  combine_project_bf16_kernel<512, DV><<<dim3(n_blocks < per_group || per_group < 1 ? n_blocks : per_group, a.g, DV / 128), 512, kLds, s>>>(
+      a, rows_per_group, log2_rows, n_blocks);
   return hipGetLastError();
 }
 

@@ -224,6 +224,7 @@ CombineArgs combine_args(const gqla_shape* s, const gqla_plan* plan, void* ws, c
   c.r_kv = s->r_kv;
   c.s_q = s->s_q;
   c.M = s->s_q * s->h_q;
+  c.n_chunks = (int32_t)plan->chunks.size();
   return c;
 }
 

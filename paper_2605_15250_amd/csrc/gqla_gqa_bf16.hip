@@ -427,50 +427,60 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
 
 
 // ---- log-sum-exp merge of the chunk partials (not in the paper: the split over the context is this library's) ----------
-// One workgroup per (sequence, block of 32 rows); thread (row n = tid % 32, vector slot tid / 32) merges vectors
-// slot, slot + 8, ... of its row (4 floats each), so that the loads of a wave are 32 consecutive 16-byte vectors.
-// Chunks are merged kNB at a time (their loads in flight together) with a running maximum, as in an online softmax.  The
-// merged block goes through LDS (32 rows, padded) and leaves as whole rows: 16 lanes x 16 bytes per row of 128 value dims.
-template <int DV>
+// A workgroup takes a block of 32 rows of one sequence and VPT * 8 / CS of the DV / 4 vectors (4 floats each) of every row;
+// thread (row n = tid % 32, slot = tid / 32) merges vectors slot / CS + (8 / CS) v of its row over every CS-th chunk, so that
+// the loads of a wave are 32 consecutive 16-byte vectors.  Chunks are merged kNB at a time (their loads in flight together)
+// with a running maximum, as in an online softmax; CS > 1: the CS slices of a row then meet in LDS.  The merged block
+// goes through LDS (32 rows, padded) and leaves as runs of whole vectors.
+// The three uses (see the launcher): many rows (VPT = DV / 32, CS = 1: a workgroup per block of rows); few rows (VPT = 1,
+// CS = 1: the dims are shared out as well); few rows with long chains of chunks (VPT = 2, CS = 8: the merge is bound by
+// the latency of its batches, one after the other -- 4 sequences x 40 rows x 256 dims with 24 to 117 chunks each: 32.4 us
+// in 8 workgroups with batches of four, 4.0 us this way).
+template <int DV, int VPT, int CS>
 __global__ void __launch_bounds__(256) combine_gqa_bf16_kernel(CombineArgs a) {
-  constexpr int kNB = 4;
+  constexpr int kNB = CS > 1 ? 8 : 4;
   constexpr int NV = DV / 4;                 // 4-float vectors per row
-  constexpr int PITCH = DV * 2 + 16;         // bytes per row of the block in LDS
+  constexpr int VS = 8 / CS;                 // vector slots of the workgroup
+  constexpr int VW = VPT * VS;               // vectors per row that the workgroup merges
+  constexpr int PITCH = VW * 8 + 16;         // bytes per row of the block in LDS
+  static_assert(NV % VW == 0 && VW % 2 == 0, "whole slices, whole 16-byte pieces on the way out");
   __shared__ __attribute__((aligned(16))) char tile[32 * PITCH];
   const int blocks_per_seq = (a.M + 31) / 32;
   const int b = blockIdx.x / blocks_per_seq, rb = blockIdx.x % blocks_per_seq;
   const int n = threadIdx.x & 31, slot = threadIdx.x >> 5;
+  const int cs = slot % CS, vs = slot / CS;
+  const int vec0 = blockIdx.y * VW;
   const int rho = rb * 32 + n;
   const bool row_ok = rho < a.M;
   const int rc = row_ok ? rho : 0;
   const int s0 = a.first_slot[b], s1 = a.first_slot[b + 1];
-  const f32x4* po = (const f32x4*)a.part_o + part_vec_index(0, rc, a.M, NV, slot);
+  const f32x4* po = (const f32x4*)a.part_o + part_vec_index(0, rc, a.M, NV, vec0 + vs);
   const int64_t chunk_stride = (int64_t)blocks_per_seq * NV * 32;   // vectors from one chunk's partials to the next
   float m = GQLA_NEG_INF, den = 0.f;
-  f32x4 acc[NV / 8];
+  f32x4 acc[VPT];
 #pragma unroll
-  for (int v = 0; v < NV / 8; ++v) acc[v] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int sb = s0; sb < s1; sb += kNB) {
+  for (int v = 0; v < VPT; ++v) acc[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int sb = s0 + cs; sb < s1; sb += kNB * CS) {
     float l[kNB];
-    f32x4 x[kNB][NV / 8];
+    f32x4 x[kNB][VPT];
 #pragma unroll
     for (int k = 0; k < kNB; ++k) {
-      const int sc = min(sb + k, s1 - 1);  // clamped: a chunk beyond the range is loaded again and given weight 0
+      const int sc = min(sb + k * CS, s1 - 1);  // clamped: a chunk beyond the range is loaded again and given weight 0
       l[k] = a.part_lse[(int64_t)sc * a.M + rc];
 #pragma unroll
-      for (int v = 0; v < NV / 8; ++v) x[k][v] = po[sc * chunk_stride + v * (8 * 32)];
+      for (int v = 0; v < VPT; ++v) x[k][v] = po[sc * chunk_stride + v * (VS * 32)];
     }
     float m_new = m;
 #pragma unroll
     for (int k = 0; k < kNB; ++k) {
-      if (sb + k >= s1) l[k] = GQLA_NEG_INF;
+      if (sb + k * CS >= s1) l[k] = GQLA_NEG_INF;
       m_new = fmaxf(m_new, l[k]);
     }
     const float m_use = (m_new == GQLA_NEG_INF) ? 0.f : m_new;
     const float rescale = __expf(m - m_use);  // 0 on the first batch (m = -inf), where den and acc are 0 anyway
     den *= rescale;
 #pragma unroll
-    for (int v = 0; v < NV / 8; ++v) acc[v] *= rescale;
+    for (int v = 0; v < VPT; ++v) acc[v] *= rescale;
     m = m_new;
 #pragma unroll
     for (int k = 0; k < kNB; ++k) {
@@ -478,21 +488,48 @@ __global__ void __launch_bounds__(256) combine_gqa_bf16_kernel(CombineArgs a) {
       den += w;
       if (w > 0.f) {  // a chunk without visible tokens may hold anything
 #pragma unroll
-        for (int v = 0; v < NV / 8; ++v) acc[v] += w * x[k][v];
+        for (int v = 0; v < VPT; ++v) acc[v] += w * x[k][v];
       }
     }
   }
-  const float inv = den > 0.f ? 1.f / den : 0.f;
+  if constexpr (CS > 1) {
+    static_assert(CS == 8, "one vector slot: thread (row, slot) sums vector `slot` of the slices");
+    __shared__ float ml[2][CS][32];
+    __shared__ f32x4 part[CS][VPT][32];
+    ml[0][cs][n] = m;
+    ml[1][cs][n] = den;
 #pragma unroll
-  for (int v = 0; v < NV / 8; ++v)
-    *(u32x2*)(tile + n * PITCH + (slot + 8 * v) * 8) = u32x2{pack_bf16(acc[v][0] * inv, acc[v][1] * inv), pack_bf16(acc[v][2] * inv, acc[v][3] * inv)};
-  if (a.lse && row_ok && slot == 0) a.lse[(int64_t)b * a.M + rho] = m + __logf(den);
+    for (int v = 0; v < VPT; ++v) part[cs][v][n] = acc[v];
+    __syncthreads();
+    if (slot < VPT) {
+      m = GQLA_NEG_INF;
+#pragma unroll
+      for (int c = 0; c < CS; ++c) m = fmaxf(m, ml[0][c][n]);
+      const float m_use = (m == GQLA_NEG_INF) ? 0.f : m;
+      den = 0.f;
+      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < CS; ++c) {
+        const float w = __expf(ml[0][c][n] - m_use);  // 0 for a slice without chunks
+        den += w * ml[1][c][n];
+        sum += w * part[c][slot][n];
+      }
+      const float inv = den > 0.f ? 1.f / den : 0.f;
+      *(u32x2*)(tile + n * PITCH + slot * 8) = u32x2{pack_bf16(sum[0] * inv, sum[1] * inv), pack_bf16(sum[2] * inv, sum[3] * inv)};
+    }
+  } else {
+    const float inv = den > 0.f ? 1.f / den : 0.f;
+#pragma unroll
+    for (int v = 0; v < VPT; ++v)
+      *(u32x2*)(tile + n * PITCH + (vs + VS * v) * 8) = u32x2{pack_bf16(acc[v][0] * inv, acc[v][1] * inv), pack_bf16(acc[v][2] * inv, acc[v][3] * inv)};
+  }
+  if (a.lse && row_ok && slot == 0 && blockIdx.y == 0) a.lse[(int64_t)b * a.M + rho] = m + __logf(den);
   __syncthreads();
-  constexpr int LPR = DV / 8;                // lanes per row on the way out (16 bytes each)
+  constexpr int LPR = VW / 2;                // lanes per row on the way out (16 bytes each)
   for (int idx = threadIdx.x; idx < 32 * LPR; idx += 256) {
     const int r = idx / LPR, c = idx % LPR;
     if (rb * 32 + r < a.M)
-      *(u32x4*)((__bf16*)a.out + ((int64_t)b * a.M + rb * 32 + r) * DV + c * 8) = *(const u32x4*)(tile + r * PITCH + c * 16);
+      *(u32x4*)((__bf16*)a.out + ((int64_t)b * a.M + rb * 32 + r) * DV + vec0 * 4 + c * 8) = *(const u32x4*)(tile + r * PITCH + c * 16);
   }
 }
 
@@ -555,11 +592,17 @@ hipError_t launch_decode_gqa_fp8(const DecodeArgs& a, float k_scale, float v_sca
   return launch_decode_gqa_128<true>(a, k_scale, v_scale, s);
 }
 
-hipError_t launch_combine_gqa_bf16(const CombineArgs& a, hipStream_t s) {
+template <int DV>
+static hipError_t launch_combine_gqa_dv(const CombineArgs& a, hipStream_t s) {
   const unsigned blocks = (unsigned)(a.B * ((a.M + 31) / 32));
-  if (a.d_h == 256) combine_gqa_bf16_kernel<256><<<blocks, 256, 0, s>>>(a);   // a.d_h: value dims here
-  else combine_gqa_bf16_kernel<128><<<blocks, 256, 0, s>>>(a);
+  if (blocks >= 256) combine_gqa_bf16_kernel<DV, DV / 32, 1><<<blocks, 256, 0, s>>>(a);
+  else if (a.n_chunks <= 8 * a.B) combine_gqa_bf16_kernel<DV, 1, 1><<<dim3(blocks, DV / 32), 256, 0, s>>>(a);
+  else combine_gqa_bf16_kernel<DV, 2, 8><<<dim3(blocks, DV / 8), 256, 0, s>>>(a);
   return hipGetLastError();
+}
+
+hipError_t launch_combine_gqa_bf16(const CombineArgs& a, hipStream_t s) {
+  return a.d_h == 256 ? launch_combine_gqa_dv<256>(a, s) : launch_combine_gqa_dv<128>(a, s);  // a.d_h: value dims here
 }
 
 }  // namespace gqla

@@ -47,6 +47,7 @@ struct CombineArgs {
   void* out;                  // [B][s_q][h_q][d_h]
   float* lse;                 // optional [B][s_q][h_q]
   int32_t B, h_q, g, G, d_h, r_kv, s_q, M;
+  int32_t n_chunks;           // of the whole batch (launch-shape choices only)
 };
 
 struct ExpandArgs {

@@ -1,14 +1,13 @@
 // fp32 kernels of the GQLA library (vector ALU only, any dims that are multiples of 8).
 // They serve the small fp32 configuration; the bf16 MFMA kernels live in their own files.
-// One wave (64 lanes) per query row and chunk: lanes run over cached tokens for the logits and over
-// output dims for the weighted sum.
+// The calls are small (a few thousand tokens at most), so what bounds them is the chain of dependent memory accesses of
+// one workgroup, not bandwidth or arithmetic: every kernel shares its sums out over 256 threads and joins them through
+// lane exchanges or LDS, and reads 16-byte vectors.
 #include "gqla_device.h"
 
 namespace gqla {
 
 namespace {
-
-constexpr int kMaxDimsPerLane = 8;  // output dims per lane: d_h <= 512 (GQA), r_kv <= 512 (absorb)
 
 __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
@@ -18,100 +17,189 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   return v;
 }
+__device__ __forceinline__ float dot4(f32x4 x, f32x4 y, float acc) {
+  for (int k = 0; k < 4; ++k) acc = fmaf(x[k], y[k], acc);
+  return acc;
+}
+
+constexpr int kThreads = 256;
+constexpr int kTile = 64;          // cached tokens per pass of the decode
+constexpr int kRed = 4 * kThreads; // floats through which 256 threads join up to four sums each
 
 // q_hat[row, i, r] = sum_d W_UK[j(i)][r][d] * q_c[row, i, d]      (MQA-absorb equation, line 1)
-__global__ void absorb_query_f32_kernel(AbsorbQueryArgs a) {
+// Four neighbouring lanes share a row of W_UK, so that they ask for 64 consecutive bytes of it.
+__global__ void __launch_bounds__(kThreads) absorb_query_f32_kernel(AbsorbQueryArgs a) {
   const int head = blockIdx.x, row = blockIdx.y;
-  const int j = head / a.G;
-  const float* q = (const float*)a.q_c + ((int64_t)row * a.h_q + head) * a.d_h;
-  const float* w = (const float*)a.w_uk + (int64_t)j * a.r_kv * a.d_h;
+  const int j = head / a.G, quarter = threadIdx.x & 3, nv = a.d_h / 4;
+  const f32x4* q = (const f32x4*)((const float*)a.q_c + ((int64_t)row * a.h_q + head) * a.d_h);
+  const f32x4* w = (const f32x4*)((const float*)a.w_uk + (int64_t)j * a.r_kv * a.d_h);
   float* out = (float*)a.q_hat + ((int64_t)row * a.h_q + head) * a.r_kv;
-  for (int r = threadIdx.x; r < a.r_kv; r += blockDim.x) {
+  for (int r = threadIdx.x >> 2; r < a.r_kv; r += kThreads / 4) {
     float acc = 0.f;
-    for (int d = 0; d < a.d_h; ++d) acc += w[(int64_t)r * a.d_h + d] * q[d];
-    out[r] = acc;
+    for (int v = quarter; v < nv; v += 4) acc = dot4(w[(int64_t)r * nv + v], q[v], acc);
+    acc += __shfl_xor(acc, 1);
+    acc += __shfl_xor(acc, 2);
+    if (quarter == 0) out[r] = acc;
   }
 }
 
-// Shared body of the two fp32 decode kernels.  kAbsorb: keys = [c | k_R] rows of the latent page, values = c.
-// Otherwise: keys = [K_C[j] | k_R], values = V[j] of the expanded page.
-template <bool kAbsorb>
-__global__ void __launch_bounds__(64) decode_f32_kernel(DecodeArgs a) {
+// o = W_UV[j]^T o_hat (MQA-absorb equation, line 6) by a whole workgroup: four columns and a share of the latent dims per
+// thread, joined through `red`.  `o_hat` and `red` are LDS; the caller has put a barrier behind the writes of o_hat.
+__device__ __forceinline__ void project_latent_f32(const float* o_hat, const float* w_uv, int r_kv, int d_v, float* red, float* out) {
+  const int nv = d_v / 4, shares = kThreads / nv;
+  const int share = threadIdx.x / nv, v = threadIdx.x % nv;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (share < shares) {
+    const f32x4* w = (const f32x4*)w_uv + v;
+#pragma unroll 4
+    for (int r = share; r < r_kv; r += shares) {
+      const f32x4 x = w[(int64_t)r * nv];
+      for (int k = 0; k < 4; ++k) acc[k] = fmaf(x[k], o_hat[r], acc[k]);
+    }
+    *(f32x4*)(red + (share * nv + v) * 4) = acc;
+  }
+  __syncthreads();
+  for (int d = threadIdx.x; d < d_v; d += kThreads) {
+    float sum = 0.f;
+    for (int s = 0; s < shares; ++s) sum += red[s * d_v + d];
+    out[d] = sum;
+  }
+}
+
+// Shared body of the two fp32 decode kernels, one workgroup per (chunk, query row).  kAbsorb: keys = [c | k_R] rows of the
+// latent page, values = c.  Otherwise: keys = [K_C[j] | k_R], values = V[j] of the expanded page.  Logits: four lanes per
+// token; weighted sum: as many shares of the tile's tokens as 256 threads allow, joined through LDS behind the last tile.
+// (One wave per row, whose lanes fetched one token's row each and then walked the 64 tokens in turn, took 13.4 us over 64
+// tokens at r_kv = 32 where this takes 5.0; both paths over 4 x 1000 tokens, 64 rows, r_kv = 128: 741 -> 92 us.)
+// kFinal: every sequence is one chunk, so that there is nothing to combine and the rows of the output (projected, on the
+// absorb path) are written here, with the values that a combine of one partial gives.
+template <bool kAbsorb, bool kFinal>
+__global__ void __launch_bounds__(kThreads) decode_f32_kernel(DecodeArgs a, CombineArgs c) {
+  __shared__ float z_s[2][kTile], p_s[kThreads / 64][kTile], red[kRed], o_hat[kFinal && kAbsorb ? 512 : 1];
+  __shared__ int64_t page_s[2][kTile];  // first element of the token's page, -1: the token is not seen
   const int chunk = blockIdx.x, rho = blockIdx.y;  // rho = t * h_q + i
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const ChunkEntry ce = a.chunks[chunk];
   const int t = rho / a.h_q, i = rho % a.h_q, j = i / a.G;
   const int P = a.cache.page_size;
   const int dk = kAbsorb ? a.r_kv : a.d_h;  // content part of the key
   const int dv = kAbsorb ? a.r_kv : a.d_v;  // value dims
-  const float* qa = (const float*)a.q_a + ((int64_t)(ce.b * a.s_q + t) * a.h_q + i) * dk;
-  const float* qr = (const float*)a.q_r + ((int64_t)(ce.b * a.s_q + t) * a.h_q + i) * a.d_r;
+  const f32x4* qa = (const f32x4*)((const float*)a.q_a + ((int64_t)(ce.b * a.s_q + t) * a.h_q + i) * dk);
+  const f32x4* qr = (const f32x4*)((const float*)a.q_r + ((int64_t)(ce.b * a.s_q + t) * a.h_q + i) * a.d_r);
   const float* pool = (const float*)a.cache.pool;
-  const int gc = a.cache.groups;
-  const int64_t page_elems = kAbsorb ? (int64_t)P * (a.r_kv + a.d_r) : (int64_t)P * (gc * (a.d_h + a.d_v) + a.d_r);
+  const int gc = a.cache.groups, W = a.r_kv + a.d_r;
+  const int64_t page_elems = kAbsorb ? (int64_t)P * W : (int64_t)P * (gc * (a.d_h + a.d_v) + a.d_r);
   const int vis_end = min(ce.tok_end, ce.L - a.s_q + t + 1);
 
-  float m_run = GQLA_NEG_INF, l_run = 0.f;
-  float o[kMaxDimsPerLane];
-  for (int u = 0; u < kMaxDimsPerLane; ++u) o[u] = 0.f;
+  // units of the weighted sum: four dims of a token (absorb), four tokens of a dim (GQA)
+  const int units = kAbsorb ? dv / 4 : 2 * dv;
+  const int shares = max(1, kThreads / units), share = units <= kThreads ? threadIdx.x / units : 0;
+  const int unit = units <= kThreads ? threadIdx.x % units : threadIdx.x;
 
-  for (int tok0 = ce.tok_begin; tok0 < ce.tok_end; tok0 += 64) {
-    const int tok = tok0 + lane;
+  float m_run = GQLA_NEG_INF, l_run = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};  // absorb: the unit's four dims;  GQA: units unit, unit + 256, ...
+
+  for (int tok0 = ce.tok_begin, buf = 0; tok0 < ce.tok_end; tok0 += kTile, buf ^= 1) {
+    const int x = threadIdx.x >> 2, quarter = threadIdx.x & 3, tok = tok0 + x;
+    int64_t page = -1;
     float z = GQLA_NEG_INF;
-    int32_t pg = -1;
-    int slot = 0;
     if (tok < vis_end) {
-      pg = page_of(a.cache, ce.b, tok / P);
-      slot = tok % P;
+      const int32_t pg = page_of(a.cache, ce.b, tok / P);
+      if (pg >= 0) page = pg * page_elems;
     }
-    if (pg >= 0) {
-      const float* base = pool + pg * page_elems;
+    if (page >= 0) {
+      const int slot = tok % P;
       float acc = 0.f;
       if (kAbsorb) {
-        const float* row = base + (int64_t)slot * (a.r_kv + a.d_r);
-        for (int d = 0; d < a.r_kv; ++d) acc += qa[d] * row[d];
-        for (int d = 0; d < a.d_r; ++d) acc += qr[d] * row[a.r_kv + d];
+        const f32x4* row = (const f32x4*)(pool + page + (int64_t)slot * W);
+#pragma unroll 4
+        for (int v = quarter; v < dk / 4; v += 4) acc = dot4(qa[v], row[v], acc);
+        for (int v = quarter; v < a.d_r / 4; v += 4) acc = dot4(qr[v], row[dk / 4 + v], acc);
       } else {
-        for (int d = 0; d < a.d_h; ++d)
-          acc += qa[d] * base[((int64_t)(j * (a.d_h / 8) + d / 8) * P + slot) * 8 + d % 8];
-        const float* rb = base + (int64_t)gc * P * (a.d_h + a.d_v);
-        for (int d = 0; d < a.d_r; ++d) acc += qr[d] * rb[((int64_t)(d / 8) * P + slot) * 8 + d % 8];
+        const f32x4* kc = (const f32x4*)(pool + page + ((int64_t)j * (dk / 8) * P + slot) * 8);
+        const f32x4* kr = (const f32x4*)(pool + page + ((int64_t)gc * P * (a.d_h + a.d_v) + slot * 8));
+#pragma unroll 4
+        for (int v = quarter; v < dk / 4; v += 4) acc = dot4(qa[v], kc[(int64_t)(v >> 1) * P * 2 + (v & 1)], acc);
+        for (int v = quarter; v < a.d_r / 4; v += 4) acc = dot4(qr[v], kr[(int64_t)(v >> 1) * P * 2 + (v & 1)], acc);
       }
-      z = acc * a.scale_log2e;
+      z = acc;
     }
-    const float tmax = wave_max(z);
-    const float m_new = fmaxf(m_run, tmax);
+    // every lane of the quad takes part, seen or not: the four have the same token
+    z += __shfl_xor(z, 1);
+    z += __shfl_xor(z, 2);
+    if (quarter == 0) {
+      z_s[buf][x] = page >= 0 ? z * a.scale_log2e : GQLA_NEG_INF;
+      page_s[buf][x] = page;
+    }
+    __syncthreads();  // the other buffer is free again: everyone has left the pass before
+    const float zt = z_s[buf][lane];
+    const float m_new = fmaxf(m_run, wave_max(zt));
     const float m_use = (m_new == GQLA_NEG_INF) ? 0.f : m_new;
     const float alpha = fast_exp2(m_run - m_use);
-    const float p = (z == GQLA_NEG_INF) ? 0.f : fast_exp2(z - m_use);
+    const float p = (zt == GQLA_NEG_INF) ? 0.f : fast_exp2(zt - m_use);
     l_run = l_run * alpha + wave_sum(p);
     m_run = m_new;
-    for (int u = 0; u < kMaxDimsPerLane; ++u) o[u] *= alpha;
-    // weighted sum of values: lane owns dims lane, lane + 64, ...
-    for (int src = 0; src < 64; ++src) {
-      const float ps = __shfl(p, src);
-      const int32_t pgs = __shfl(pg, src);
-      const int slots = __shfl(slot, src);
-      if (ps == 0.f || pgs < 0) continue;  // wave-uniform
-      const float* base = pool + pgs * page_elems;
-      for (int u = 0; u < kMaxDimsPerLane; ++u) {
-        const int d = lane + 64 * u;
-        if (d < dv) {
-          float v;
-          if (kAbsorb) v = base[(int64_t)slots * (a.r_kv + a.d_r) + d];
-          else v = base[(int64_t)gc * P * a.d_h + ((int64_t)(j * (P / 8) + slots / 8) * a.d_v + d) * 8 + slots % 8];
-          o[u] += ps * v;
+    o *= alpha;
+    p_s[wave][lane] = p;  // read by this wave only
+    __builtin_amdgcn_wave_barrier();
+    if (share < shares) {
+      if (kAbsorb) {
+#pragma unroll 4
+        for (int src = share; src < kTile; src += shares) {
+          const float ps = p_s[wave][src];
+          const int64_t pgs = page_s[buf][src];
+          if (ps != 0.f && pgs >= 0) {
+            const f32x4 v = *(const f32x4*)(pool + pgs + (int64_t)((tok0 + src) % P) * W + unit * 4);
+            for (int k = 0; k < 4; ++k) o[k] = fmaf(ps, v[k], o[k]);
+          }
+        }
+      } else {
+        for (int u = 0; u < 4; ++u) {
+          const int un = unit + u * kThreads;
+          if (un >= units) break;
+          for (int oct = share; oct < kTile / 8; oct += shares) {
+            const int64_t pgs = page_s[buf][oct * 8];  // an octet lies in one page, and its first token is seen if any is
+            if (pgs < 0) continue;
+            const f32x4 v = *(const f32x4*)(pool + pgs + (int64_t)gc * P * a.d_h +
+                                            ((int64_t)(j * (P / 8) + (tok0 + oct * 8) % P / 8) * dv) * 8 + un * 4);
+            for (int k = 0; k < 4; ++k) {
+              const float ps = p_s[wave][oct * 8 + (un & 1) * 4 + k];
+              o[u] = ps != 0.f ? fmaf(ps, v[k], o[u]) : o[u];  // a slot that is not seen may hold anything
+            }
+          }
         }
       }
     }
   }
-  const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
-  float* po = (float*)a.part_o + ((int64_t)chunk * a.M + rho) * dv;
-  for (int u = 0; u < kMaxDimsPerLane; ++u) {
-    const int d = lane + 64 * u;
-    if (d < dv) po[d] = o[u] * inv;
+  // a row without a visible token: 0 and -inf as a partial; with nothing to combine, what a combine makes of that
+  const bool any = l_run > 0.f;
+  const float inv = any ? 1.f / l_run : (kFinal ? __builtin_nanf("") : 0.f);
+  if (share < shares) {
+    if (kAbsorb) *(f32x4*)(red + (share * units + unit) * 4) = o * inv;
+    else
+      for (int u = 0; u < 4; ++u) {
+        const int un = unit + u * kThreads;
+        if (un < units) red[(share * 2 + (un & 1)) * dv + (un >> 1)] = o[u] * inv;
+      }
   }
-  if (lane == 0) a.part_lse[(int64_t)chunk * a.M + rho] = l_run > 0.f ? (m_run + fast_log2(l_run)) * kLn2 : GQLA_NEG_INF;
+  __syncthreads();
+  const int parts = kAbsorb ? shares : 2 * shares;
+  const int64_t row = kFinal ? (int64_t)ce.b * a.M + rho : (int64_t)chunk * a.M + rho;
+  float* dst = kFinal ? (kAbsorb ? o_hat : (float*)c.out + row * dv) : (float*)a.part_o + row * dv;
+  for (int d = threadIdx.x; d < dv; d += kThreads) {
+    float sum = 0.f;
+    for (int s = 0; s < parts; ++s) sum += red[s * dv + d];
+    dst[d] = sum;
+  }
+  if (threadIdx.x == 0) {
+    const float lse = any ? (m_run + fast_log2(l_run)) * kLn2 : (kFinal && kAbsorb ? __builtin_nanf("") : GQLA_NEG_INF);
+    if (!kFinal) a.part_lse[row] = lse;
+    else if (c.lse) c.lse[row] = lse;
+  }
+  if (kFinal && kAbsorb) {
+    __syncthreads();
+    project_latent_f32(o_hat, (const float*)c.w_uv + (int64_t)j * a.r_kv * c.d_h, a.r_kv, c.d_h, red, (float*)c.out + row * c.d_h);
+  }
 }
 
 // Log-sum-exp combine of chunk partials that are already in d_h space.  32 lanes per (b, row), 4 dims per lane and
@@ -164,97 +252,115 @@ __global__ void __launch_bounds__(256) combine_kernel(CombineArgs a) {
 }
 
 // fp32 absorb path: combine latent-space partials, then o = W_UV[j]^T o_hat  (MQA-absorb equation, line 6).
-__global__ void combine_project_f32_kernel(CombineArgs a) {
-  extern __shared__ float o_hat[];  // r_kv floats
-  const int rho = blockIdx.x, b = blockIdx.y;
+// One workgroup per (row, sequence); the chunks are shared out over the threads, four dims each.
+__global__ void __launch_bounds__(kThreads) combine_project_f32_kernel(CombineArgs a) {
+  __shared__ float o_hat[512], red[kRed];
+  const int rho = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63;
   const int i = rho % a.h_q, j = i / a.G;
   const int s0 = a.first_slot[b], s1 = a.first_slot[b + 1];
-  float m = GQLA_NEG_INF;
-  for (int s = s0; s < s1; ++s) m = fmaxf(m, a.part_lse[(int64_t)s * a.M + rho]);
-  float den = 0.f;
-  for (int s = s0; s < s1; ++s) den += __expf(a.part_lse[(int64_t)s * a.M + rho] - m);
-  const float* po = (const float*)a.part_o;
-  for (int r = threadIdx.x; r < a.r_kv; r += blockDim.x) {
-    float acc = 0.f;
-    for (int s = s0; s < s1; ++s) {
+  // every wave by itself: largest lse, then the sum of the weights
+  float m = GQLA_NEG_INF, den = 0.f;
+  for (int s = s0 + lane; s < s1; s += 64) m = fmaxf(m, a.part_lse[(int64_t)s * a.M + rho]);
+  m = wave_max(m);
+  for (int s = s0 + lane; s < s1; s += 64) den += __expf(a.part_lse[(int64_t)s * a.M + rho] - m);
+  den = wave_sum(den);
+  const int nv = a.r_kv / 4, shares = kThreads / nv;
+  const int share = threadIdx.x / nv, v = threadIdx.x % nv;
+  if (share < shares) {
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int s = s0 + share; s < s1; s += shares) {
       const float w = __expf(a.part_lse[(int64_t)s * a.M + rho] - m);
-      if (w > 0.f) acc += w * po[((int64_t)s * a.M + rho) * a.r_kv + r];
+      const f32x4 x = *(const f32x4*)((const float*)a.part_o + ((int64_t)s * a.M + rho) * a.r_kv + v * 4);
+      if (w > 0.f) acc += w * x;
     }
-    o_hat[r] = acc / den;
+    *(f32x4*)(red + (share * nv + v) * 4) = acc;
   }
   __syncthreads();
-  const float* w = (const float*)a.w_uv + (int64_t)j * a.r_kv * a.d_h;
-  for (int d = threadIdx.x; d < a.d_h; d += blockDim.x) {
-    float acc = 0.f;
-    for (int r = 0; r < a.r_kv; ++r) acc += w[(int64_t)r * a.d_h + d] * o_hat[r];
-    ((float*)a.out)[((int64_t)b * a.M + rho) * a.d_h + d] = acc;
+  for (int r = threadIdx.x; r < a.r_kv; r += kThreads) {
+    float sum = 0.f;
+    for (int s = 0; s < shares; ++s) sum += red[s * a.r_kv + r];
+    o_hat[r] = sum / den;
   }
+  __syncthreads();
+  project_latent_f32(o_hat, (const float*)a.w_uv + (int64_t)j * a.r_kv * a.d_h, a.r_kv, a.d_h, red,
+                     (float*)a.out + ((int64_t)b * a.M + rho) * a.d_h);
   if (a.lse && threadIdx.x == 0) a.lse[(int64_t)b * a.M + rho] = m + __logf(den);
 }
 
-// Cache switch, fp32: one workgroup per (logical page, sequence).
-__global__ void expand_f32_kernel(ExpandArgs a) {
-  const int p = blockIdx.x, b = blockIdx.y;
-  const int L = a.seq_lens[b];
-  const int P = a.latent.page_size;
-  if ((int64_t)p * P >= L) return;
-  const int32_t pg_in = page_of(a.latent, b, p);
-  const int32_t pg_out = page_of(a.expanded, b, p);
+// Cache switch, fp32: one workgroup per (8 tokens of a page, sequence, 256 of the weights' columns).  A thread has four
+// columns (a 16-byte vector of a weight row) times the eight tokens, so every weight that is read serves eight tokens, and
+// the four waves share out r_kv and join their sums through LDS, whence results leave as 16-byte vectors.
+// kTail: only the last a.tail positions of every sequence, from the same sums (the two calls give the same bits).
+// (Each element by itself, two loads a product and one workgroup a page: 14 us where this takes 4.9, over 64 tokens, r_kv = 32.)
+template <bool kTail>
+__global__ void __launch_bounds__(kThreads) expand_f32_kernel(ExpandArgs a) {
+  constexpr int kTok = 8, kRow = 72;  // kRow: 64 column vectors; padded so that the writes below spread over the banks
+  __shared__ f32x4 c_s[512 * kTok / 4];             // [r][token]
+  __shared__ float red[kThreads / 64][4 * kTok][kRow];
+  const int P = a.latent.page_size, b = blockIdx.y;
+  const int L = a.seq_lens[b], from = kTail ? max(L - a.tail, 0) : 0;
+  const int tok0 = from / kTok * kTok + blockIdx.x * kTok;
+  if (tok0 >= L) return;
+  const int32_t pg_in = page_of(a.latent, b, tok0 / P);
+  const int32_t pg_out = page_of(a.expanded, b, tok0 / P);
   if (pg_in < 0 || pg_out < 0) return;
-  const int valid = min(P, L - p * P);
-  const int W = a.r_kv + a.d_r;
-  const int gc = a.group_count;
-  const float* in = (const float*)a.latent.pool + (int64_t)pg_in * P * W;
+  const int slot0 = tok0 % P, first = max(from - tok0, 0), valid = min(kTok, L - tok0);  // tokens first .. valid - 1 are written
+  const int W = a.r_kv + a.d_r, gc = a.group_count;
+  const float* in = (const float*)a.latent.pool + ((int64_t)pg_in * P + slot0) * W;
   float* out = (float*)a.expanded.pool + (int64_t)pg_out * P * (gc * (a.d_h + a.d_v) + a.d_r);
-  const int nk = gc * a.d_h, per_tok = gc * (a.d_h + a.d_v) + a.d_r;  // K elements, all elements of a token
-  for (int idx = threadIdx.x; idx < valid * per_tok; idx += blockDim.x) {
-    const int slot = idx / per_tok, e = idx % per_tok;
-    const float* c = in + (int64_t)slot * W;
-    if (e < per_tok - a.d_r) {
-      const int kind = e >= nk;                       // 0: a K_C element, 1: a V element
-      const int dim = kind ? a.d_v : a.d_h;           // columns of this kind's weight
-      const int x = kind ? e - nk : e, jj = x / dim, d = x % dim;
-      const float* w = (const float*)(kind ? a.w_uv : a.w_uk) + (int64_t)(a.group_begin + jj) * a.r_kv * dim;
-      float acc = 0.f;
-      for (int r = 0; r < a.r_kv; ++r) acc += w[(int64_t)r * dim + d] * c[r];
-      if (kind == 0) out[((int64_t)(jj * (a.d_h / 8) + d / 8) * P + slot) * 8 + d % 8] = acc;
-      else out[(int64_t)gc * P * a.d_h + ((int64_t)(jj * (P / 8) + slot / 8) * a.d_v + d) * 8 + slot % 8] = acc;
-    } else {
-      const int d = e - (per_tok - a.d_r);
-      out[(int64_t)gc * P * (a.d_h + a.d_v) + ((int64_t)(d / 8) * P + slot) * 8 + d % 8] = c[a.r_kv + d];
-    }
+  for (int idx = threadIdx.x; idx < kTok * a.r_kv; idx += kThreads) {
+    const int tok = idx / a.r_kv, r = idx % a.r_kv;
+    ((float*)c_s)[r * kTok + tok] = tok < valid ? in[(int64_t)tok * W + r] : 0.f;
   }
-}
-
-// Cache switch for the last a.tail positions of every sequence, fp32: one workgroup per (tail token, sequence).
-__global__ void expand_tail_f32_kernel(ExpandArgs a) {
-  const int t = blockIdx.x, b = blockIdx.y;
-  const int L = a.seq_lens[b];
-  const int pos = L - a.tail + t;
-  if (pos < 0) return;
-  const int P = a.latent.page_size;
-  const int32_t pg_in = page_of(a.latent, b, pos / P);
-  const int32_t pg_out = page_of(a.expanded, b, pos / P);
-  if (pg_in < 0 || pg_out < 0) return;
-  const int W = a.r_kv + a.d_r;
-  const int gc = a.group_count;
-  const int slot = pos % P;
-  const float* c = (const float*)a.latent.pool + ((int64_t)pg_in * P + slot) * W;
-  float* out = (float*)a.expanded.pool + (int64_t)pg_out * P * (gc * (a.d_h + a.d_v) + a.d_r);
-  const int nk = gc * a.d_h, per_tok = gc * (a.d_h + a.d_v) + a.d_r;  // K elements, all elements of a token
-  for (int e = threadIdx.x; e < per_tok; e += blockDim.x) {
-    if (e < per_tok - a.d_r) {
-      const int kind = e >= nk;                       // 0: a K_C element, 1: a V element
-      const int dim = kind ? a.d_v : a.d_h;           // columns of this kind's weight
-      const int x = kind ? e - nk : e, jj = x / dim, d = x % dim;
-      const float* w = (const float*)(kind ? a.w_uv : a.w_uk) + (int64_t)(a.group_begin + jj) * a.r_kv * dim;
-      float acc = 0.f;
-      for (int r = 0; r < a.r_kv; ++r) acc += w[(int64_t)r * dim + d] * c[r];
-      if (kind == 0) out[((int64_t)(jj * (a.d_h / 8) + d / 8) * P + slot) * 8 + d % 8] = acc;
-      else out[(int64_t)gc * P * a.d_h + ((int64_t)(jj * (P / 8) + slot / 8) * a.d_v + d) * 8 + slot % 8] = acc;
-    } else {
-      const int d = e - (per_tok - a.d_r);
-      out[(int64_t)gc * P * (a.d_h + a.d_v) + ((int64_t)(d / 8) * P + slot) * 8 + d % 8] = c[a.r_kv + d];
+  if (blockIdx.z == 0)
+    for (int idx = first * a.d_r + threadIdx.x; idx < valid * a.d_r; idx += kThreads) {
+      const int tok = idx / a.d_r, d = idx % a.d_r;
+      out[(int64_t)gc * P * (a.d_h + a.d_v) + ((int64_t)(d / 8) * P + slot0 + tok) * 8 + d % 8] = in[(int64_t)tok * W + a.r_kv + d];
+    }
+  __syncthreads();
+  const int nk = gc * a.d_h / 4, n_all = nk + gc * a.d_v / 4;  // column vectors: keys, all
+  const int cv0 = blockIdx.z * 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int cv = cv0 + lane;
+  if (cv < n_all) {
+    const bool is_v = cv >= nk;
+    const int per = (is_v ? a.d_v : a.d_h) / 4, x = is_v ? cv - nk : cv;
+    const f32x4* w = (const f32x4*)(is_v ? a.w_uv : a.w_uk) + (int64_t)(a.group_begin + x / per) * a.r_kv * per + x % per;
+    f32x4 lo[4] = {}, hi[4] = {};  // [column]: tokens 0..3, 4..7
+#pragma unroll 4
+    for (int r = wave; r < a.r_kv; r += kThreads / 64) {
+      const f32x4 wv = w[(int64_t)r * per], c0 = c_s[r * 2], c1 = c_s[r * 2 + 1];
+      for (int k = 0; k < 4; ++k)
+        for (int y = 0; y < 4; ++y) {
+          lo[k][y] = fmaf(wv[k], c0[y], lo[k][y]);
+          hi[k][y] = fmaf(wv[k], c1[y], hi[k][y]);
+        }
+    }
+    for (int k = 0; k < 4; ++k)
+      for (int y = 0; y < 4; ++y) {
+        red[wave][y * 4 + k][lane] = lo[k][y];
+        red[wave][(y + 4) * 4 + k][lane] = hi[k][y];
+      }
+  }
+  __syncthreads();
+  // 512 vectors: of a key, four columns of one token; of a value, four tokens of one column
+  for (int u = threadIdx.x; u < 8 * 64; u += kThreads) {
+    const int l = u >> 3, vec = cv0 + l;
+    if (vec >= n_all) break;
+    const bool is_v = vec >= nk;
+    const int dim = is_v ? a.d_v : a.d_h, e = (is_v ? vec - nk : vec) * 4, jj = e / dim, d = e % dim;
+    const int tok = is_v ? (u & 1) * 4 : u & 7, col = is_v ? (u >> 1) & 3 : 0;
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < kThreads / 64; ++s)
+      for (int k = 0; k < 4; ++k) sum[k] += is_v ? red[s][(tok + k) * 4 + col][l] : red[s][tok * 4 + k][l];
+    if (is_v) {
+      float* dst = out + (int64_t)gc * P * a.d_h + ((int64_t)(jj * (P / 8) + slot0 / 8) * a.d_v + d + col) * 8 + tok;
+      if (tok >= first && tok + 4 <= valid) *(f32x4*)dst = sum;
+      else
+        for (int k = 0; k < 4; ++k)
+          if (tok + k >= first && tok + k < valid) dst[k] = sum[k];  // slots that no token owns are not written
+    } else if (tok >= first && tok < valid) {
+      *(f32x4*)(out + ((int64_t)(jj * (a.d_h / 8) + d / 8) * P + slot0 + tok) * 8 + d % 8) = sum;
     }
   }
 }
@@ -311,7 +417,8 @@ hipError_t launch_compress_f32(const CompressArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_expand_tail_f32(const ExpandArgs& a, hipStream_t s) {
-  expand_tail_f32_kernel<<<dim3(a.tail, a.B), 256, 0, s>>>(a);
+  const int col_blocks = (a.group_count * (a.d_h + a.d_v) + 255) / 256;
+  expand_f32_kernel<true><<<dim3((a.tail + 6) / 8 + 1, a.B, col_blocks), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 hipError_t launch_append_latent(const AppendArgs& a, hipStream_t s) {
@@ -319,28 +426,35 @@ hipError_t launch_append_latent(const AppendArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_absorb_query_f32(const AbsorbQueryArgs& a, hipStream_t s) {
-  absorb_query_f32_kernel<<<dim3(a.h_q, a.rows), 64, 0, s>>>(a);
+  absorb_query_f32_kernel<<<dim3(a.h_q, a.rows), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
-hipError_t launch_decode_gqa_f32(const DecodeArgs& a, hipStream_t s) {
-  decode_f32_kernel<false><<<dim3(a.n_chunks, a.M), 64, 0, s>>>(a);
+// One chunk per sequence: the decode writes the output itself, the combine of one partial (2 to 5 us) falls away.
+bool f32_decode_is_final(const DecodeArgs& a) { return a.n_chunks == a.B; }
+hipError_t launch_decode_gqa_f32(const DecodeArgs& a, const CombineArgs& c, hipStream_t s) {
+  if (f32_decode_is_final(a)) decode_f32_kernel<false, true><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
+  else decode_f32_kernel<false, false><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
   return hipGetLastError();
 }
-hipError_t launch_decode_absorb_f32(const DecodeArgs& a, hipStream_t s) {
-  decode_f32_kernel<true><<<dim3(a.n_chunks, a.M), 64, 0, s>>>(a);
+hipError_t launch_decode_absorb_f32(const DecodeArgs& a, const CombineArgs& c, hipStream_t s) {
+  if (f32_decode_is_final(a)) decode_f32_kernel<true, true><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
+  else decode_f32_kernel<true, false><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
   return hipGetLastError();
 }
 hipError_t launch_combine_f32(const CombineArgs& a, hipStream_t s) {
+  if (a.n_chunks == a.B) return hipSuccess;  // the decode has written the output
   const unsigned blocks = (unsigned)(((int64_t)a.B * a.M + 7) / 8);
   combine_kernel<<<blocks, 256, 0, s>>>(a);
   return hipGetLastError();
 }
 hipError_t launch_combine_project_f32(const CombineArgs& a, hipStream_t s) {
-  combine_project_f32_kernel<<<dim3(a.M, a.B), 128, a.r_kv * sizeof(float), s>>>(a);
+  if (a.n_chunks == a.B) return hipSuccess;  // the decode has written the output
+  combine_project_f32_kernel<<<dim3(a.M, a.B), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 hipError_t launch_expand_f32(const ExpandArgs& a, hipStream_t s) {
-  expand_f32_kernel<<<dim3(a.latent.max_pages, a.B), 256, 0, s>>>(a);
+  const int col_blocks = (a.group_count * (a.d_h + a.d_v) + 255) / 256;
+  expand_f32_kernel<false><<<dim3(a.latent.max_pages * (a.latent.page_size / 8), a.B, col_blocks), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 

@@ -58,7 +58,7 @@ NAMED_AGPR_SOURCES = {"gqla_absorb_bf16.hip": ["decode_absorb_bf16_kernel", "dec
 # later: a compiler-made copy of that register ahead of the wait would read it while the load is pending (the compiler
 # cannot see the load, so nothing protects such a read).  The build scans the generated assembly for any read of the
 # register between the load and the next wait for scalar memory and refuses the kernel.
-HAND_SCALAR_LOAD_KERNELS = {"gqla_absorb_bf16.hip": ["decode_absorb_bf16_kernel", "decode_absorb_shared_bf16_kernel"],
+HAND_SCALAR_LOAD_KERNELS = {"gqla_absorb_bf16.hip": ["decode_absorb_bf16_kernel", "decode_absorb_shared_bf16_kernel", "decode_absorb_rows32_bf16_kernel"],
                             "gqla_gqa_bf16.hip": ["decode_gqa_bf16_kernel"]}
 
 
@@ -66,7 +66,7 @@ HAND_SCALAR_LOAD_KERNELS = {"gqla_absorb_bf16.hip": ["decode_absorb_bf16_kernel"
 # for the loads the source issues): a register spill would add scratch loads and stores of the compiler's own to that
 # count and silently break the waits.  The build reads the compiler's resource report and refuses any vector-register
 # spill or scratch use in them.
-COUNTED_WAIT_KERNELS = {"gqla_absorb_bf16.hip": ["decode_absorb_bf16_kernel", "decode_absorb_shared_bf16_kernel"],
+COUNTED_WAIT_KERNELS = {"gqla_absorb_bf16.hip": ["decode_absorb_bf16_kernel", "decode_absorb_shared_bf16_kernel", "decode_absorb_rows32_bf16_kernel"],
                         "gqla_gemm_bf16.hip": ["expand_bf16_kernel", "compress_bf16_kernel"],
                         "gqla_gqa_bf16.hip": ["decode_gqa_bf16_kernel"],
                         "gqla_step_ops.hip": ["out_proj_bf16_kernel"]}

@@ -120,14 +120,8 @@ __device__ __forceinline__ void acc_read(int dt, bool wait, float (&x)[16]) {
   }
 }
 
-// SPLIT = 1: the layout above.  SPLIT = 4 (at most 32 query rows per sequence, e.g. one rank's heads under tensor
-// parallelism; or so few chunks that one workgroup per 32 rows still fits the chip in one round): the four waves
-// share a block of 32 rows instead of owning 32 rows each.  A wave of
-// the team contracts a quarter of the key dimension (k-step `part` of each 4-step panel), the team sums its partial
-// S^T through LDS (every wave adds them in the same order, so all hold the same bits), each wave runs the same
-// softmax and then updates its own RKV/4 slice of O^T.  With so few rows the kernel is bound by the rate at which
-// tiles stream into LDS (measured: 64 rows gain nothing from two-wave teams, so those keep SPLIT = 1).
-template <int RKV, int DR, int SPLIT>
+// The layout above; any row count (whole blocks of 128 rows and at most 32 rows per workgroup have kernels of their own below).
+template <int RKV, int DR>
 __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, int row_blocks) {
   constexpr int W = RKV + DR;        // elements per latent row
   constexpr int ROWB = W * 2;        // bytes per latent row
@@ -136,10 +130,6 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
   constexpr int KS = W / 16;         // k-steps of the key contraction
   constexpr int DT = RKV / 32;       // 32-wide tiles of the latent output
   constexpr int TILE_BYTES = kTile * ROWB;
-  constexpr int RPB = kRowsPerBlock / SPLIT;  // query rows per workgroup
-  constexpr int KB = 4 / SPLIT;               // k-steps of every 4-step panel that one wave contracts
-  constexpr int DTW = DT / SPLIT;             // output tiles per wave
-  static_assert(SPLIT == 1 || SPLIT == 4, "one wave or the whole workgroup per 32 rows");
   static_assert(W % 64 == 0 && RKV % 64 == 0, "latent row must be a whole number of 128-byte panels");
   static_assert((16 + 8 + 4) * 128 + 128 + PANEL * (RKV / 64 - 1) < 65536, "value-fragment offsets must fit the 16-bit LDS immediate");
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -159,15 +149,12 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
   const int n = lane & 31, h = lane >> 5;
   const ChunkEntry ce = a.chunks[chunk];
 
-  const int part = wave & (SPLIT - 1), team = wave / SPLIT;  // this wave's share of its 32 rows' work; which 32 rows
-  const int rho = rbk * RPB + team * 32 + n;                 // row = t * h_q + i
+  const int rho = rbk * kRowsPerBlock + wave * 32 + n;  // row = t * h_q + i
   const bool row_ok = rho < a.M;
   const int t = row_ok ? rho / a.h_q : 0;
   const int vis_end = row_ok ? min(ce.tok_end, ce.L - a.s_q + t + 1) : 0;
   const int unmasked_end = min(ce.tok_end, ce.L - a.s_q + 1);
-  // With SPLIT > 1 a workgroup is one team, and the launcher only makes row blocks that have rows (all waves meet
-  // at the team's exchange barrier, so none may skip a tile).
-  const bool wave_active = SPLIT > 1 || rbk * RPB + team * 32 < a.M;
+  const bool wave_active = rbk * kRowsPerBlock + wave * 32 < a.M;
 
   const int P = a.cache.page_size;
   const char* pool = (const char*)a.cache.pool;
@@ -186,13 +173,12 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
   //                    4 columns at 32*dt + 16*g1 + 4*q: panel dt/2, in-panel chunk 4*(dt & 1) + cl, cl = 2*g1 + q/2.
   //                    With R0 a multiple of 16, swz = 2*h + e/2 for the first read and 4 + that for the second, so the
   //                    chunk lands at 4*(dt & 1) + (cl ^ swz) resp. 4*(1 - (dt & 1)) + (cl ^ swz): one base per lane.
-  uint32_t kbase[KB], vbase;
+  uint32_t kbase[4], vbase;
   {
 #pragma unroll
-    for (int b = 0; b < KB; ++b) kbase[b] = n * 128 + (((2 * (part * KB + b) + h) ^ lds_swz(n)) << 4);
+    for (int b = 0; b < 4; ++b) kbase[b] = n * 128 + (((2 * b + h) ^ lds_swz(n)) << 4);
     const int i16 = lane & 15, e = i16 >> 2, q = i16 & 3, g1 = (lane >> 4) & 1;
     vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8;
-    vbase += part * (DTW / 2) * PANEL;  // this wave's output tiles are part*DTW .. part*DTW + DTW-1
   }
 
   static_assert(DT == 16, "O^T fills the 256 accumulation registers exactly");
@@ -241,18 +227,17 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
   if (n_tiles > 1) stage_panels_full<kTile, NP, 4, ROWB, true>(smem + TILE_BYTES, tile_src(pg1, kTile % P), wave, lane);
   if (n_tiles > 2) stage_panels_full<kTile, NP, 4, ROWB, true>(smem + 2 * TILE_BYTES, tile_src(pg2, (2 * kTile) % P), wave, lane);
 
-  // queries of this lane's row, as B fragments: [q_hat (RKV) | q_R (DR)], 8 consecutive dims per k-step; this wave's
-  // k-steps are 4*a4 + part*KB + b
-  bf16x8 qf[KS / SPLIT];
+  // queries of this lane's row, as B fragments: [q_hat (RKV) | q_R (DR)], 8 consecutive dims per k-step
+  bf16x8 qf[KS];
   {
     const int64_t qrow = (int64_t)ce.b * a.M + min(rho, a.M - 1);
-    const __bf16* ph = (const __bf16*)a.q_a + qrow * RKV + h * 8 + part * KB * 16;
-    const __bf16* pr = (const __bf16*)a.q_r + qrow * DR + h * 8 + part * KB * 16;
+    const __bf16* ph = (const __bf16*)a.q_a + qrow * RKV + h * 8;
+    const __bf16* pr = (const __bf16*)a.q_r + qrow * DR + h * 8;
 #pragma unroll
     for (int a4 = 0; a4 < KS / 4; ++a4)
 #pragma unroll
-      for (int b = 0; b < KB; ++b)
-        qf[a4 * KB + b] = *(const bf16x8*)((a4 < RKV / 64 ? ph + a4 * 64 : pr + (a4 - RKV / 64) * 64) + b * 16);
+      for (int b = 0; b < 4; ++b)
+        qf[a4 * 4 + b] = *(const bf16x8*)((a4 < RKV / 64 ? ph + a4 * 64 : pr + (a4 - RKV / 64) * 64) + b * 16);
   }
 
   // The query loads go out behind the first tile requests (one memory latency for both) and are made to complete
@@ -261,10 +246,10 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
   // cover the tile requests in flight and drain the ring on every tile.  (The wait that the compiler places here
   // covers the three tiles requested above as well; the loop's own counted waits then pass at once for them.)
 #pragma unroll
-  for (int k = 0; k < KS / SPLIT; k += 9)
+  for (int k = 0; k < KS; k += 9)
     asm volatile("" : "+v"(qf[k]), "+v"(qf[k + 1]), "+v"(qf[k + 2]), "+v"(qf[k + 3]), "+v"(qf[k + 4]), "+v"(qf[k + 5]),
                       "+v"(qf[k + 6]), "+v"(qf[k + 7]), "+v"(qf[k + 8]));
-  static_assert((KS / SPLIT) % 9 == 0, "query fragments are touched nine at a time");
+  static_assert(KS % 9 == 0, "query fragments are touched nine at a time");
 
 #pragma unroll 1
   for (int it = 0; it < n_tiles; ++it) {
@@ -324,12 +309,7 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
       // These MFMAs accumulate in ordinary VGPRs (written as inline assembly) because all 256 accumulation
       // registers hold O^T; the compiler's own MFMA selection would put S^T there as well and spill.
       f32x16 s;
-      // With few query rows the kernel is bound by how many bytes it keeps in flight, not by its MFMAs: the request
-      // for tile it + kAhead goes out first (no LDS read is outstanding here either).
-      if constexpr (SPLIT > 1) {
-        if (stage_next) stage_panels_full<kTile, NP, 4, ROWB, true>(next_buf, next_g, wave, lane);
-      }
-      if constexpr (SPLIT == 1) {
+      {
         bf16x8 f[3][4];  // ring of fragment batches: loads run two batches (8 MFMAs) ahead of their use
 #pragma unroll
         for (int b = 0; b < 4; ++b) f[0][b] = *(const bf16x8*)(buf + kbase[b]);
@@ -349,28 +329,11 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
           }
           __builtin_amdgcn_sched_barrier(0);
         }
-      } else {
-        bf16x8 f[KS / 4][KB];  // this wave's share is short: every fragment is requested up front
-#pragma unroll
-        for (int a4 = 0; a4 < KS / 4; ++a4)
-#pragma unroll
-          for (int b = 0; b < KB; ++b) f[a4][b] = *(const bf16x8*)(buf + kbase[b] + a4 * PANEL);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int a4 = 0; a4 < KS / 4; ++a4)
-#pragma unroll
-          for (int b = 0; b < KB; ++b) {
-            if (a4 == 0 && b == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(f[0][0]), "v"(qf[0]));  // result registers must not overlap the operands
-            else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(f[a4][b]), "v"(qf[a4 * KB + b]));
-          }
-        __builtin_amdgcn_sched_barrier(0);
       }
       // Tile it + kAhead is requested here, in one burst: at this point no LDS read of this wave is outstanding.
       // (An LDS-DMA instruction issued while reads are in flight holds the wave, and with it the MFMA stream, until
       // they have returned.)
-      if constexpr (SPLIT == 1) {
-        if (stage_next) stage_panels_full<kTile, NP, 4, ROWB, true>(next_buf, next_g, wave, lane);
-      }
+      if (stage_next) stage_panels_full<kTile, NP, 4, ROWB, true>(next_buf, next_g, wave, lane);
       // first batches of value fragments: issued now, consumed after the softmax
       i16x4 r[3][4][2];
       auto load_v = [&](int slot, int u, int p4) {  // output tiles dt = 4*p4 .. 4*p4 + 3 of k-step u
@@ -382,28 +345,11 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
           r[slot][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 8 * 128 + 64 * (1 - (dt & 1)))));
         }
       };
-      constexpr int NBT = 2 * (DTW / 4);  // batches of four value fragments: k-step bt / (DTW/4), tiles 4*(bt % (DTW/4)) ..
+      constexpr int NBT = 2 * (DT / 4);  // batches of four value fragments: k-step bt / (DT/4), tiles 4*(bt % (DT/4)) ..
       load_v(0, 0, 0);
-      load_v(1, 1 / (DTW / 4), 1 % (DTW / 4));
+      load_v(1, 1 / (DT / 4), 1 % (DT / 4));
       // the matrix pipeline's result is not interlocked against vector-ALU reads: wait out its 8 passes
       asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s));
-      if constexpr (SPLIT > 1) {
-        // team sum of the partial S^T: [wave][quarter][lane] 16-byte slots behind the tile ring
-        char* ex = smem + kSlots * TILE_BYTES;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *(f32x4*)(ex + wave * 4096 + q * 1024 + lane * 16) = f32x4{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-        __syncthreads();  // the next write to these slots comes after the next tile's barrier, which follows these reads
-#pragma unroll
-        for (int w = 0; w < SPLIT; ++w)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const f32x4 x = *(const f32x4*)(ex + (team * SPLIT + w) * 4096 + q * 1024 + lane * 16);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s[4 * q + e] = (w == 0) ? x[e] : s[4 * q + e] + x[e];
-          }
-      }
 
       // ---- online softmax (base 2); register i is token tok + 8*(i/4) + 4*h + i%4 ----
       // The maximum is taken on the raw logits (the scale is positive) and the scale rides in the exponent's FMA.
@@ -430,16 +376,6 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
       bf16x8 pf[2];
       float p1[8];
       u32x4 w1;
-      if constexpr (SPLIT > 1) {  // too few MFMAs per k-step to hide exponentials behind: both halves now
-        float psum = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          p1[e] = fast_exp2(__builtin_fmaf(s[8 + e], a.scale_log2e, -m_use));
-          psum += p1[e];
-        }
-        w1 = u32x4{pack_bf16(p1[0], p1[1]), pack_bf16(p1[2], p1[3]), pack_bf16(p1[4], p1[5]), pack_bf16(p1[6], p1[7])};
-        l_run += psum;
-      }
       {
         float p[8], psum = 0.f;
 #pragma unroll
@@ -454,23 +390,22 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
       // An MFMA may read a register as an operand no sooner than two wait states after a vector-ALU instruction wrote
       // it.  The compiler keeps that distance for its own MFMAs but does not look inside inline assembly, so the
       // distance between the last pack of the probabilities and the first O^T update is made here.
-      if constexpr (SPLIT > 1) asm volatile("s_nop 1" : "+v"(pf[0]), "+v"(w1));
-      else asm volatile("s_nop 1" : "+v"(pf[0]));
+      asm volatile("s_nop 1" : "+v"(pf[0]));
       __builtin_amdgcn_sched_barrier(0);
 
       // ---- O^T[r][row] += C^T * P^T, value fragments one batch of four tiles ahead ----
 #pragma unroll
       for (int bt = 0; bt < NBT; ++bt) {
-        const int u = bt / (DTW / 4), p4 = bt % (DTW / 4);
-        if (bt + 2 < NBT) load_v((bt + 2) % 3, (bt + 2) / (DTW / 4), (bt + 2) % (DTW / 4));
-        if (bt == DTW / 4) pf[1] = __builtin_bit_cast(bf16x8, w1);
+        const int u = bt / (DT / 4), p4 = bt % (DT / 4);
+        if (bt + 2 < NBT) load_v((bt + 2) % 3, (bt + 2) / (DT / 4), (bt + 2) % (DT / 4));
+        if (bt == DT / 4) pf[1] = __builtin_bit_cast(bf16x8, w1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
           const i16x4 lo = r[bt % 3][d][0], hi = r[bt % 3][d][1];
           const i16x8 fr = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
           acc_mfma(4 * p4 + d, __builtin_bit_cast(bf16x8, fr), pf[u]);
-          if (SPLIT == 1 && u == 0) {  // second k-step's probabilities, one piece per MFMA
+          if (u == 0) {  // second k-step's probabilities, one piece per MFMA
             const int idx = 4 * bt + d;
             if (idx < 8) {
               p1[idx] = fast_exp2(__builtin_fmaf(s[8 + idx], a.scale_log2e, -m_use));
@@ -491,20 +426,325 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
   if (!row_ok) return;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   const int64_t prow = (int64_t)chunk * a.M + rho;
-  // this lane holds dims 4 h .. 4 h + 3 of vector 4 (part DTW + dt) + q of its row: with consecutive rows in consecutive
+  // this lane holds dims 4 h .. 4 h + 3 of vector 4 dt + q of its row: with consecutive rows in consecutive
   // lanes a store instruction writes 512 contiguous bytes
   __bf16* po = (__bf16*)a.part_o + part_vec_index(chunk, rho, a.M, RKV / 8, 0) * 8 + 4 * h;
 #pragma unroll
-  for (int dt = 0; dt < DTW; ++dt) {
+  for (int dt = 0; dt < DT; ++dt) {
     float x[16];
     acc_read(dt, dt == 0, x);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       u32x2 v = {pack_bf16(x[4 * q] * inv, x[4 * q + 1] * inv), pack_bf16(x[4 * q + 2] * inv, x[4 * q + 3] * inv)};
-      *(u32x2*)(po + ((part * DTW + dt) * 4 + q) * (32 * 8)) = v;
+      *(u32x2*)(po + (dt * 4 + q) * (32 * 8)) = v;
     }
   }
-  if (h == 0 && part == 0) a.part_lse[prow] = l_tot > 0.f ? (m_ref + fast_log2(l_tot)) * kLn2 : GQLA_NEG_INF;
+  if (h == 0) a.part_lse[prow] = l_tot > 0.f ? (m_ref + fast_log2(l_tot)) * kLn2 : GQLA_NEG_INF;
+}
+
+// At most 32 query rows per workgroup (at most 32 rows per sequence, or so few chunks that one workgroup per 32 rows still
+// fits the chip in one round).  With so few rows a tile is little work and what costs is the chain of a tile -- S^T, softmax,
+// probabilities to everyone, O^T -- on which one wave per SIMD issues at best an instruction every four cycles.  So eight
+// waves, two per SIMD, take pairs of tiles (64 tokens) with one barrier per pair:
+//   S^T: wave w owns 16 tokens (16 (w & 3) ..) against 16 rows (16 (w >> 2) ..) over the whole key dimension: 18 MFMAs of
+//        16 x 16 x 32, no partial sums to trade, four logits per lane.
+//   P^T: published in LDS, already in operand order.
+//   O^T: wave w owns latent dims 64 w .. 64 w + 63 of all 32 rows, one pair late: iteration j is
+//        barrier (pair j has landed, probabilities of j - 1 published) | requests for pair j + 1, into the buffers of j - 1,
+//        whose value fragments are in registers | S^T(j) and O^T(j - 1) | value fragments of j requested, softmax, P^T(j) out
+// The queries come through the ring (same layout and fragment addresses as keys) with the first tiles.
+// The reference maximum of a row is common to the eight waves and moves rarely (threshold 2^8): a wave that wants to move it
+// says so in the sign bit of a probability, which every wave reads with its operands; all then trade their maxima, rescale,
+// and publish the probabilities of that pair again.
+// Measured: one sequence of 8192 tokens x 128 rows (88 workgroups of 6 pairs) 23.0 -> 15.5 us, against four waves that split
+// the key dimension and traded fp32 partial sums (2.9 k cycles a tile; the same four waves with O^T one tile late: 22.0 us);
+// one of 32768 tokens x 16 rows 81 -> 46 us for the whole step; 32 ragged sequences of 4096 tokens x 32 rows (151 MB, all
+// compute units) 34.9 -> 29.5 us, 5.1 TB/s: there the loop runs at the memory's rate and the rest is its start.
+template <int RKV, int DR>
+__global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeArgs a, int row_blocks) {
+  constexpr int W = RKV + DR;
+  constexpr int ROWB = W * 2;
+  constexpr int NP = W / 64;
+  constexpr int PANEL = kTile * 128;
+  constexpr int KS = W / 32;                  // k-steps of 32
+  constexpr int TILE_BYTES = kTile * ROWB;
+  constexpr int kQPanels = (NP + 1) / 2;      // panels of the queries that waves 0..3 request; the others take the rest
+  static_assert(RKV == 512 && DR == 64 && kSlots == 4, "eight waves of 64 latent dims; two pairs of tiles");
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  // Probabilities, [parity of the pair][16 tokens][lane] 16 bytes: with one barrier per pair a wave may publish those of pair
+  // j while another still reads those of j - 1.
+  char* const pex = smem + kSlots * TILE_BYTES;
+  float* const mex = (float*)(pex + 2 * 4096);   // row maxima, and at the end the denominators: [16 tokens][row]
+
+  int chunk, rbk;
+  {
+    const int id = blockIdx.x;
+    const int grp = id / (8 * row_blocks), rem = id % (8 * row_blocks);
+    rbk = rem / 8;
+    chunk = grp * 8 + rem % 8;
+  }
+  if (chunk >= a.n_chunks) return;  // whole workgroup leaves together
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 31, h = lane >> 5;        // O^T: row n
+  const int n16 = lane & 15, g4 = lane >> 4;     // S^T: row 16 rh + n16, tokens 16 tb + 4 g4 + 0..3
+  const int tb = wave & 3, rh = wave >> 2;       // (staging: wave tb of the four that request tile rh of a pair)
+  const ChunkEntry ce = a.chunks[chunk];
+  const int rho0 = rbk * 32;
+  const int rho = rho0 + 16 * rh + n16;
+  const bool row_ok = rho < a.M;
+  const int vis_end = row_ok ? min(ce.tok_end, ce.L - a.s_q + rho / a.h_q + 1) : 0;
+  const int unmasked_end = rho0 + 16 * rh + 16 <= a.M ? min(ce.tok_end, ce.L - a.s_q + 1) : 0;  // wave-uniform
+  const int P = a.cache.page_size;
+  const char* pool = (const char*)a.cache.pool;
+  const int32_t* table_row = a.cache.page_table ? a.cache.page_table + (int64_t)ce.b * a.cache.max_pages : nullptr;
+  auto checked = [&](int32_t pg) -> int32_t { return ((uint32_t)pg < (uint32_t)a.cache.num_pages) ? pg : -1; };
+  // tiles are always staged whole: rows past the chunk end come from the page, an out-of-pool page id falls back to page 0;
+  // such rows are zeroed in LDS before use
+  auto tile_src = [&](int32_t pg, int slot) -> const char* { return pool + ((int64_t)(pg >= 0 ? pg : 0) * P + slot) * ROWB; };
+
+  {  // queries into buffer 3; rows beyond the last read that one instead (their results are not stored)
+    const int srow = 8 * tb + (lane >> 3), c = (lane & 7) ^ ((4 * tb + (lane >> 4)) & 7);
+    const int64_t qrow = (int64_t)ce.b * a.M + min(rho0 + srow, a.M - 1);
+    const char* gh = (const char*)a.q_a + qrow * (RKV * 2) + c * 16;
+    const char* gr = (const char*)a.q_r + qrow * (DR * 2) + c * 16;
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+      if ((u < kQPanels) != (rh == 0)) continue;
+      const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr_t)(smem + 3 * TILE_BYTES + u * PANEL + tb * 1024);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(u < RKV / 64 ? gh + u * 128 : gr + (u - RKV / 64) * 128) : "memory");
+    }
+  }
+  const int n_tiles = (ce.tok_end - ce.tok_begin + kTile - 1) / kTile;
+  const int n_pairs = (n_tiles + 1) / 2;
+  // A pair of tiles lies in one page (pages hold a multiple of 64 tokens, chunks start on one).  Pages of pairs j (cur) and
+  // j + 1 (nxt, first token in slot nxt_slot); the table entry of pair j + 2 is looked up during iteration j through the
+  // scalar cache.  (lk_p, lk_slot): page index and slot of the next pair to look up.
+  constexpr int kPair = 2 * kTile;
+  int lk_p = ce.tok_begin / P, lk_slot = 0;
+  auto advance = [&]() {
+    lk_slot += kPair;
+    if (lk_slot == P) {
+      lk_slot = 0;
+      ++lk_p;
+    }
+  };
+  int32_t cur, nxt, raw = 0;
+  int nxt_slot;
+  {
+    const int p0 = __builtin_amdgcn_readfirstlane(lk_p);
+    advance();
+    const int p1 = __builtin_amdgcn_readfirstlane(n_pairs > 1 ? lk_p : p0);
+    nxt_slot = lk_slot;
+    advance();
+    int32_t r0, r1;
+    if (table_row) {  // both scalar loads in flight together, one wait
+      asm volatile("s_load_dword %0, %1, 0x0" : "=s"(r0) : "s"(table_row + p0) : "memory");
+      asm volatile("s_load_dword %0, %1, 0x0" : "=s"(r1) : "s"(table_row + p1) : "memory");
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r0), "+s"(r1) : : "memory");
+    } else {
+      r0 = ce.b * a.cache.max_pages + p0;
+      r1 = ce.b * a.cache.max_pages + p1;
+    }
+    cur = checked(r0);
+    nxt = checked(r1);
+  }
+  auto stage_tile = [&](int buffer, int32_t pg, int slot) { stage_panels_full<kTile, NP, 4, ROWB, true>(smem + buffer * TILE_BYTES, tile_src(pg, slot), tb, lane); };
+  // tiles 0 and 1, and 2 behind them; tile 3 waits until the queries have left its buffer
+  if (rh == 0) {
+    stage_tile(0, cur, 0);
+    if (n_tiles > 2) stage_tile(2, nxt, nxt_slot);
+  } else if (n_tiles > 1) {
+    stage_tile(1, cur, kTile);
+  }
+
+  // per-lane LDS offsets.  Operand fragments of S^T, k-step ks: panel ks / 2, in-panel chunk 4 (ks & 1) + g4.
+  uint32_t kbase[2], qbase[2], vbase;
+  {
+    const int krow = 16 * (tb & 1) + n16, qrow = 16 * rh + n16;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      kbase[b] = (tb >> 1) * TILE_BYTES + krow * 128 + (((4 * b + g4) ^ lds_swz(krow)) << 4);
+      qbase[b] = 3 * TILE_BYTES + qrow * 128 + (((4 * b + g4) ^ lds_swz(qrow)) << 4);
+    }
+    // value fragments (transposed reads): as in the kernel above, panel `wave`
+    const int i16 = lane & 15, e = i16 >> 2, q = i16 & 3, g1 = (lane >> 4) & 1;
+    vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8 + wave * PANEL;
+  }
+  f32x16 o[2];
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[d][i] = 0.f;
+  float m_s = GQLA_NEG_INF, m_o = GQLA_NEG_INF, l_run = 0.f;  // reference of this lane's row in S^T, in O^T
+
+  // queries and tiles 0, 1 (tile 2, if there, is what waves 0..3 have requested last)
+  if (rh == 0 && n_tiles > 2) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  bf16x8 qf[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(smem + qbase[ks & 1] + (ks >> 1) * PANEL);
+
+  float z[4], z_max = GQLA_NEG_INF, psum_last = 0.f;  // of the last pair: raw logits, scaled maximum, sum of probabilities
+  i16x4 r[4][2][2] = {};                              // value fragments of the last pair
+  char* const p_dst = pex + tb * 1024 + ((g4 & 1) * 32 + 16 * rh + n16) * 16 + (g4 >> 1) * 8;
+  auto publish = [&](int pair, float m_use, bool flag) {
+    float p[4], sum = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      p[i] = fast_exp2(__builtin_fmaf(z[i], a.scale_log2e, -m_use));
+      sum += p[i];
+    }
+    *(u32x2*)(p_dst + (pair & 1) * 4096) = u32x2{pack_bf16(p[0], p[1]) | (flag ? 0x8000u : 0u), pack_bf16(p[2], p[3])};
+    return sum;
+  };
+
+#pragma unroll 1
+  for (int j = 0;; ++j) {
+    const int tok = ce.tok_begin + j * kPair;
+    char* const buf = smem + (j & 1) * 2 * TILE_BYTES;
+    const bool more = j < n_pairs;
+    const bool lookup = j + 2 < n_pairs;
+    const int look_slot = lk_slot;
+    if (lookup) {
+      const int p = __builtin_amdgcn_readfirstlane(lk_p);
+      if (table_row) asm volatile("s_load_dword %0, %1, 0x0" : "=s"(raw) : "s"(table_row + p) : "memory");  // consumed at the end of the iteration (the wait is written out there)
+      else raw = ce.b * a.cache.max_pages + p;
+      advance();
+    }
+    if (j > 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (2 * j + 2 + rh < n_tiles && !(j == 0 && rh == 0)) stage_tile((2 * (j + 1) & 2) + rh, nxt, nxt_slot + rh * kTile);
+    const bool whole = cur >= 0 && tok + kPair <= ce.tok_end;
+    if (more && !whole) {
+      // rows past the chunk end hold whatever the page holds (NaN bits included): zero them so that 0 * v stays 0
+      const int valid = cur >= 0 ? max(ce.tok_end - tok, 0) : 0;
+      for (int idx = threadIdx.x; idx < (kPair - valid) * (W / 8); idx += 512) {
+        const int rr = valid + idx / (W / 8), c = idx % (W / 8);
+        *(u32x4*)(buf + rr / kTile * TILE_BYTES + (c >> 3) * PANEL + rr % kTile * 128 + (c & 7) * 16) = u32x4{0u, 0u, 0u, 0u};
+      }
+      __syncthreads();
+    }
+    // operands of the iteration: probabilities of the last pair (0 ahead of the first: O^T is updated without a branch), key
+    // fragments of this one (behind the last, whatever is there: not used)
+    u32x4 pw[4];
+    auto read_p = [&]() {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) pw[u] = *(const u32x4*)(pex + ((j - 1) & 1) * 4096 + u * 1024 + lane * 16);
+    };
+    if (j > 0) {
+      read_p();
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) pw[u] = u32x4{0u, 0u, 0u, 0u};
+    }
+    auto key_frag = [&](int ks) { return *(const bf16x8*)(buf + kbase[ks & 1] + (ks >> 1) * PANEL); };
+    bf16x8 f[NP];
+    static_for<NP>([&](auto k) { f[decltype(k)::value] = key_frag(decltype(k)::value); });
+    if (j > 0) {
+      const uint32_t flags = pw[0][0] | pw[0][2] | pw[1][0] | pw[1][2] | pw[2][0] | pw[2][2] | pw[3][0] | pw[3][2];
+      if (__builtin_amdgcn_ballot_w64((flags & 0x8000u) != 0) != 0) {  // the same bits in every wave: all come here or none
+        if (g4 == 0) mex[tb * 32 + 16 * rh + n16] = z_max;
+        __syncthreads();  // (also: every wave has read the probabilities that are about to be replaced)
+        auto moved = [&](float m, int row) {
+#pragma unroll
+          for (int k = 0; k < 4; ++k) m = fmaxf(m, mex[k * 32 + row]);
+          return m;
+        };
+        auto factor = [&](float m_old, float m_new) { return fast_exp2(m_old - ((m_new == GQLA_NEG_INF) ? 0.f : m_new)); };
+        const float ms_new = moved(m_s, 16 * rh + n16), mo_new = moved(m_o, n);
+        l_run *= factor(m_s, ms_new);
+        if (j > 1) {
+          const float alpha = factor(m_o, mo_new);
+#pragma unroll
+          for (int d = 0; d < 2; ++d) o[d] *= alpha;
+        }
+        m_s = ms_new;
+        m_o = mo_new;
+        psum_last = publish(j - 1, (m_s == GQLA_NEG_INF) ? 0.f : m_s, false);
+        __syncthreads();
+        read_p();
+      }
+      l_run += psum_last;
+    }
+    auto output_step = [&](auto uc) {  // O^T of the last pair, 16 tokens
+      constexpr int u = decltype(uc)::value;
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        const i16x4 lo = r[u][d][0], hi = r[u][d][1];
+        const i16x8 fr = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        o[d] = mfma32(__builtin_bit_cast(bf16x8, fr), __builtin_bit_cast(bf16x8, pw[u]), o[d]);
+      }
+    };
+    f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    static_for<KS>([&](auto kc) {
+      constexpr int ks = decltype(kc)::value;
+      s[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[ks % NP], qf[ks], s[ks & 1], 0, 0, 0);
+      if constexpr (ks + NP < KS) f[ks] = key_frag(ks + NP);
+      if constexpr (ks % 4 == 3) output_step(std::integral_constant<int, ks / 4>{});
+    });
+    if (!more) break;
+    // value fragments of this pair, consumed in the next iteration
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        const int off = (u >> 1) * TILE_BYTES + 16 * (u & 1) * 128;
+        r[u][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 64 * d)));
+        r[u][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 8 * 128 + 64 * (1 - d))));
+      }
+    // ---- softmax of this wave's 16 tokens x 16 rows ----
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z[i] = s[0][i] + s[1][i];
+    if (!whole || tok + kPair > unmasked_end) {
+      const int lim = cur >= 0 ? vis_end : 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (tok + 16 * tb + 4 * g4 + i >= lim) z[i] = GQLA_NEG_INF;
+    }
+    z_max = pair_max(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])));
+    {
+      const uint32_t u = __builtin_bit_cast(uint32_t, z_max);
+      const auto x = __builtin_amdgcn_permlane16_swap(u, u, false, false);  // the other row of 16 lanes
+      z_max = fmaxf(__builtin_bit_cast(float, (uint32_t)x[0]), __builtin_bit_cast(float, (uint32_t)x[1])) * a.scale_log2e;
+    }
+    const bool move = __builtin_amdgcn_ballot_w64(z_max > m_s + kRescaleThreshold) != 0;
+    psum_last = publish(j, (m_s == GQLA_NEG_INF) ? 0.f : m_s, move);
+
+    cur = nxt;
+    nxt = -1;
+    nxt_slot = look_slot;
+    if (lookup) {
+      if (table_row) asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(raw) : : "memory");
+      nxt = checked(raw);
+    }
+  }
+
+  // denominators: the four lanes of a row, then its four waves, in the same order for all
+  l_run = pair_sum(l_run);
+  {
+    const uint32_t u = __builtin_bit_cast(uint32_t, l_run);
+    const auto x = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    l_run = __builtin_bit_cast(float, (uint32_t)x[0]) + __builtin_bit_cast(float, (uint32_t)x[1]);
+  }
+  __syncthreads();  // (the maxima of a move in the last iteration have been read)
+  if (g4 == 0) mex[tb * 32 + 16 * rh + n16] = l_run;
+  __syncthreads();
+  const float l_tot = mex[n] + mex[32 + n] + mex[64 + n] + mex[96 + n];
+  const int row = rho0 + n;
+  if (row >= a.M) return;
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  // dims 4 h .. 4 h + 3 of vector 4 (2 wave + d) + q of the row: consecutive rows in consecutive lanes
+  __bf16* po = (__bf16*)a.part_o + part_vec_index(chunk, row, a.M, RKV / 8, 0) * 8 + 4 * h;
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *(u32x2*)(po + ((wave * 2 + d) * 4 + q) * (32 * 8)) =
+          u32x2{pack_bf16(o[d][4 * q] * inv, o[d][4 * q + 1] * inv), pack_bf16(o[d][4 * q + 2] * inv, o[d][4 * q + 3] * inv)};
+  if (h == 0 && wave == 0)
+    a.part_lse[(int64_t)chunk * a.M + row] = l_tot > 0.f ? (m_o + fast_log2(l_tot)) * kLn2 : GQLA_NEG_INF;
 }
 
 // every accumulator of row block rb (tiles 4*dtl + rb, dtl = 0..3) of this lane times alpha
@@ -1456,17 +1696,26 @@ __global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a
 
 }  // namespace
 
-template <int SPLIT>
-static hipError_t launch_decode_absorb_split(const DecodeArgs& a, hipStream_t s) {
-  // tile ring, plus the team exchange (4 KB per wave) when waves share rows
-  constexpr int kLds = kSlots * kTile * (512 + 64) * 2 + (SPLIT > 1 ? 4 * 4096 : 0);
+static hipError_t launch_decode_absorb_general(const DecodeArgs& a, hipStream_t s) {
+  constexpr int kLds = kSlots * kTile * (512 + 64) * 2;  // tile ring
   // once per process (function-local statics are initialised under a lock); an error is reported by every call
   static const hipError_t attr =
-      hipFuncSetAttribute((const void*)decode_absorb_bf16_kernel<512, 64, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+      hipFuncSetAttribute((const void*)decode_absorb_bf16_kernel<512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
-  const int row_blocks = (a.M + kRowsPerBlock / SPLIT - 1) / (kRowsPerBlock / SPLIT);
+  const int row_blocks = (a.M + kRowsPerBlock - 1) / kRowsPerBlock;
   const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
-  decode_absorb_bf16_kernel<512, 64, SPLIT><<<chunks_padded * row_blocks, 256, kLds, s>>>(a, row_blocks);
+  decode_absorb_bf16_kernel<512, 64><<<chunks_padded * row_blocks, 256, kLds, s>>>(a, row_blocks);
+  return hipGetLastError();
+}
+
+static hipError_t launch_decode_absorb_rows32(const DecodeArgs& a, hipStream_t s) {
+  constexpr int kLds = kSlots * kTile * (512 + 64) * 2 + 2 * 4096 + 512;  // tile ring, probabilities, row maxima
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void*)decode_absorb_rows32_bf16_kernel<512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  if (attr != hipSuccess) return attr;
+  const int row_blocks = (a.M + 31) / 32;
+  const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
+  decode_absorb_rows32_bf16_kernel<512, 64><<<chunks_padded * row_blocks, 512, kLds, s>>>(a, row_blocks);
   return hipGetLastError();
 }
 
@@ -1482,15 +1731,15 @@ static hipError_t launch_decode_absorb_shared(const DecodeArgs& a, hipStream_t s
 }
 
 hipError_t launch_decode_absorb_bf16(const DecodeArgs& a, hipStream_t s) {
-  // At most 32 query rows: the four waves share them, so that none is left without work.  More rows but few chunks
-  // (small batches): one workgroup per (chunk, 32 rows) with the four waves sharing its rows, as long as all of them
-  // still run at once -- four times the workgroups, each with a shorter tile (the tiles' re-reads hit the L2, and
-  // with so few chunks the chip is nowhere near its memory rate).
+  // At most 32 query rows, or more but few chunks (small batches): one workgroup per (chunk, 32 rows) as long as all of them
+  // still run at once -- more workgroups, each with a shorter chain per tile (the tiles' re-reads hit the L2, and with so few
+  // chunks the chip is nowhere near its memory rate).  Beyond one round the re-reads cost more than they give: 64 sequences
+  // x 4096 tokens x 64 rows take 104 us a step that way and 92 us with the general kernel, 96 rows 139 and 97 us.
   const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
-  if (a.M <= 32 || chunks_padded * ((a.M + 31) / 32) <= a.num_cus) return launch_decode_absorb_split<4>(a, s);
+  if (a.M <= 32 || chunks_padded * ((a.M + 31) / 32) <= a.num_cus) return launch_decode_absorb_rows32(a, s);
   // whole blocks of 128 rows (h_q s_q a multiple of 128): the pipelined kernel with shared probabilities; other row
   // counts above 32: one wave per 32 rows, each with its own probabilities
-  return a.M % kRowsPerBlock == 0 ? launch_decode_absorb_shared(a, s) : launch_decode_absorb_split<1>(a, s);
+  return a.M % kRowsPerBlock == 0 ? launch_decode_absorb_shared(a, s) : launch_decode_absorb_general(a, s);
 }
 
 template <int SPLIT>

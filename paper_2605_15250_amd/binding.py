@@ -193,10 +193,37 @@ def _ptr(t):
     return t.data_ptr()
 
 
+# The current stream's handle through torch's own C entry: what torch.cuda.current_stream().cuda_stream returns, without the
+# Stream object and the device checks around it: 2.7 us -> 0.2 us of the 6.5 us a call costs the host (steps of a few users
+# are bound by that: rope, append, absorption, decode and merge 36 -> 25 us).
+# Resolved by the first call that finds CUDA initialised; a forked child starts over, so that torch refuses it as before.
+_raw_stream = None
+
+
+def _forget_raw_stream():
+    global _raw_stream
+    _raw_stream = None
+
+
+os.register_at_fork(after_in_child=_forget_raw_stream)
+
+
+def _current_stream():
+    global _raw_stream
+    if _raw_stream is not None:
+        get_stream, get_device = _raw_stream
+        return get_stream(get_device())
+    import torch
+    handle = torch.cuda.current_stream().cuda_stream   # initialises CUDA; raises without a device
+    get_stream, get_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if get_stream is not None and get_device is not None:
+        _raw_stream = (get_stream, get_device)
+    return handle
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

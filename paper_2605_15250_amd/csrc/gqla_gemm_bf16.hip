@@ -50,58 +50,70 @@ __global__ void __launch_bounds__(256) absorb_query_bf16_kernel(AbsorbQueryArgs 
 }
 
 // The same product for d_h = 128 with both sides of the kernel coalesced (the call is a short kernel in front of every
-// absorb decode, and what it costs is how many memory lines its instructions touch): one workgroup per (group j, 32 query
-// rows of the group), wave w taking latent dims 128 w .. 128 w + 127.  W_UK[j] (512 rows of 256 bytes, contiguous) is
-// staged in LDS with LDS-DMA, 1 KB of consecutive memory per instruction, and read back as conflict-free A fragments; the
-// results go back through LDS (a wave's 32 x 128 tile, rows padded to 272 bytes) so that a store instruction writes four
-// rows of 256 contiguous bytes instead of 8-byte pieces of 32 rows.  Same MFMAs in the same order as the kernel above.
-template <int RKV>
+// absorb decode, and what it costs is how many memory lines its instructions touch): one workgroup per group j and share of
+// RKV / SHARES latent dims, for one or more blocks of 32 query rows of the group; a wave takes a quarter of the share.  The
+// share's rows of W_UK[j] (256 bytes each, contiguous) are staged in LDS once, with LDS-DMA, 1 KB of consecutive memory per
+// instruction, and read back as conflict-free A fragments; the results go back through LDS so that a store instruction writes
+// whole lines of rows instead of 8-byte pieces of 32 rows.  Same MFMAs in the same order as the kernel above.
+// SHARES: with few row blocks the staging of 128 KB by one compute unit is most of the call, so it is shared out; with more
+// than a round of workgroups they keep their weights and walk over the row blocks, the next block's queries in flight.
+// Measured: one sequence, 128 heads in 8 groups 5.2 -> 3.5 us (8 -> 32 workgroups); 128 sequences x 2 tokens, 1024 blocks
+// 24.3 -> 17.9 us (256 workgroups of four blocks; q_c read and q_hat written once are 42 MB, 6 us).
+template <int RKV, int SHARES>
 __global__ void __launch_bounds__(256) absorb_query_staged_bf16_kernel(AbsorbQueryArgs a, int rows_per_group) {
   constexpr int DH = 128, KS = DH / 16;
-  constexpr int PITCH = 272;                      // bytes per row of the output tile in LDS
-  static_assert(RKV == 512, "four waves x 128 latent dims");
+  constexpr int ROWS = RKV / SHARES;              // latent dims of the workgroup
+  constexpr int MT = ROWS / 128;                  // 32-dim tiles of a wave
+  constexpr int MP = MT < 2 ? MT : 2;             // ... that leave through LDS together
+  constexpr int PITCH = MP * 64 + 16;             // bytes per row of the output tile in LDS
+  constexpr int LPR = MP * 4;                     // lanes per row of a store
+  static_assert(RKV == 512 && (SHARES == 1 || SHARES == 2 || SHARES == 4), "four waves x 32 to 128 latent dims");
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ int64_t qrow_of[32];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
-  const int j = blockIdx.z;
-  stage_panels_full<RKV, DH / 64, 4, DH * 2>(smem, (const char*)a.w_uk + (int64_t)j * RKV * DH * 2, wave, lane);
-  const int x = blockIdx.x * 32 + n;       // x = row * G + head-in-group, row = b * s_q + t
-  const bool row_ok = x < rows_per_group;
-  const int64_t qrow = row_ok ? (int64_t)(x / a.G) * a.h_q + j * a.G + x % a.G : -1;
-  if (wave == 0 && h == 0) qrow_of[n] = qrow;
+  const int j = blockIdx.z, dim0 = blockIdx.y * ROWS;
+  stage_panels_full<ROWS, DH / 64, 4, DH * 2>(smem, (const char*)a.w_uk + ((int64_t)j * RKV + dim0) * DH * 2, wave, lane);
+  char* tile = smem + ROWS * DH * 2 + wave * (32 * PITCH);  // read by this wave only
+  auto query_row = [&](int x) -> int64_t { return (int64_t)(x / a.G) * a.h_q + j * a.G + x % a.G; };  // x = row * G + head-in-group
   bf16x8 qf[KS];
-  const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+  auto load_queries = [&](int blk) {              // rows beyond the last: that one (not stored)
+    const __bf16* q = (const __bf16*)a.q_c + query_row(min(blk * 32 + n, rows_per_group - 1)) * DH + h * 8;
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks)
-    qf[ks] = row_ok ? *(const bf16x8*)((const __bf16*)a.q_c + qrow * DH + ks * 16 + h * 8) : zero;
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(q + ks * 16);
+  };
+  const int n_blocks = (rows_per_group + 31) / 32;
+  load_queries(blockIdx.x);
   wait_all_memory();
-  __syncthreads();  // W_UK[j] staged
-  f32x16 acc[4];
+  __syncthreads();  // the weights are staged
+  for (int blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {
+    f32x16 acc[MT];
 #pragma unroll
-  for (int mt = 0; mt < 4; ++mt) {
+    for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[mt][i] = 0.f;
+      for (int i = 0; i < 16; ++i) acc[mt][i] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) acc[mt] = mfma32(row_frag<RKV>(smem, 128 * wave + 32 * mt + n, 2 * ks + h), qf[ks], acc[mt]);
-  }
-  __syncthreads();  // every wave is done reading the staged weights: the space becomes the output tiles
-  char* tile = smem + wave * (32 * PITCH);
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const u32x2 v = {pack_bf16(acc[mt][4 * q], acc[mt][4 * q + 1]), pack_bf16(acc[mt][4 * q + 2], acc[mt][4 * q + 3])};
-      *(u32x2*)(tile + n * PITCH + (mt * 32 + 8 * q + 4 * h) * 2) = v;
+      for (int ks = 0; ks < KS; ++ks) acc[mt] = mfma32(row_frag<ROWS>(smem, (MT * wave + mt) * 32 + n, 2 * ks + h), qf[ks], acc[mt]);
     }
-  // (only this wave reads its tile: the compiler's wait for the LDS writes is all the ordering needed)
+    if (blk + (int)gridDim.x < n_blocks) load_queries(blk + gridDim.x);
 #pragma unroll
-  for (int p = 0; p < 8; ++p) {
-    const int r = 4 * p + (lane >> 4), c = lane & 15;
-    const int64_t orow = qrow_of[r];
-    const u32x4 v = *(const u32x4*)(tile + r * PITCH + c * 16);
-    if (orow >= 0) *(u32x4*)((__bf16*)a.q_hat + orow * RKV + wave * 128 + c * 8) = v;
+    for (int m0 = 0; m0 < MT; m0 += MP) {
+#pragma unroll
+      for (int mt = 0; mt < MP; ++mt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x16 x = acc[m0 + mt];
+          *(u32x2*)(tile + n * PITCH + (mt * 32 + 8 * q + 4 * h) * 2) = u32x2{pack_bf16(x[4 * q], x[4 * q + 1]), pack_bf16(x[4 * q + 2], x[4 * q + 3])};
+        }
+      // (the compiler's wait for the LDS writes is all the ordering needed)
+#pragma unroll
+      for (int p = 0; p < 32 * LPR / 64; ++p) {
+        const int r = (64 / LPR) * p + lane / LPR, c = lane % LPR;
+        const u32x4 v = *(const u32x4*)(tile + r * PITCH + c * 16);
+        if (blk * 32 + r < rows_per_group)
+          *(u32x4*)((__bf16*)a.q_hat + query_row(blk * 32 + r) * RKV + dim0 + (MT * wave + m0) * 32 + c * 8) = v;
+      }
+    }
   }
 }
 
@@ -427,9 +439,10 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
 }
 
 // ---- cache expansion of the last a.tail positions of every sequence (the step's new tokens) ------------------------
-// The B * tail tokens form one list (index = b * tail + t) cut into 32-token tiles; a workgroup is one packed weight
-// stage (64 output columns of one group's W_UK or W_UV, see pack_weights_bf16_kernel) times 64 tokens, wave w taking
-// the 32-column half w & 1 and the token tile w >> 1:
+// The B * tail tokens form one list (index = b * tail + t) cut into 32-token tiles; a workgroup is one wave: half of a packed
+// weight stage (32 output columns of one group's W_UK or W_UV, see pack_weights_bf16_kernel) times a tile.  (The call is
+// latency and what one compute unit can fetch: 64 KB a wave, so the waves are spread over as many units as there are.
+// 128 tokens, 8 groups, 256 waves: 11.9 us as 64 workgroups of four, 5.9 us this way; one group 9.5 -> 4.9 us):
 //   K^T[d][tok] = W_UK^T[d][r] * C^T[r][tok]   and   V^T[d][tok] = W_UV^T[d][r] * C^T[r][tok]
 //   A = packed weight fragment straight from global memory (1 KB, contiguous), B = the tokens' latent rows, gathered
 //   (lane = token, 8 consecutive latent dims per k-step).
@@ -440,18 +453,18 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
 // the value the 16-bit cache would hold, and then quantised, so that the codes equal those of expanding into a 16-bit
 // cache and converting it.
 template <int DH, int DV, int RKV, int DR, bool FP8>
-__global__ void __launch_bounds__(256) expand_tail_bf16_kernel(ExpandArgs a, const __bf16* packed) {
+__global__ void __launch_bounds__(64) expand_tail_bf16_kernel(ExpandArgs a, const __bf16* packed) {
   constexpr int W = RKV + DR;
   constexpr int KS = RKV / 16;
   constexpr int NSK = DH / 64, NSUB = (DH + DV) / 64;
   static_assert(!FP8 || (DH == 128 && DV == 128), "the 8-bit page format is written for equal dims of 128");
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x;
   const int n = lane & 31, h = lane >> 5;
-  const int stage = blockIdx.x;  // jj * NSUB + sub
+  const int stage = blockIdx.x >> 1;  // jj * NSUB + sub
   const int jj = stage / NSUB, sub = stage % NSUB;
   const int kind = sub >= NSK, mtp = kind ? sub - NSK : sub;
-  const int e = wave & 1;
-  const int idx = blockIdx.y * 64 + (wave >> 1) * 32 + n;  // this lane's token in the list
+  const int e = blockIdx.x & 1;
+  const int idx = blockIdx.y * 32 + n;  // this lane's token in the list
   const int P = a.latent.page_size;
   const int gc = a.group_count;
   bool ok = idx < a.B * a.tail;
@@ -774,6 +787,16 @@ hipError_t launch_compress_bf16(const CompressArgs& a, hipStream_t s) {
   return a.d_h == 192 ? launch_compress_dims<192, 256>(a, s) : launch_compress_dims<128, 128>(a, s);
 }
 
+template <int SHARES>
+static hipError_t launch_absorb_query_staged(const AbsorbQueryArgs& a, int rows_per_group, int grid_x, hipStream_t s) {
+  constexpr int kRows = 512 / SHARES, kLds = kRows * 128 * 2 + 4 * 32 * ((kRows >= 256 ? 128 : 64) + 16);  // the share of W_UK[j], output tiles
+  static const hipError_t attr = hipFuncSetAttribute((const void*)absorb_query_staged_bf16_kernel<512, SHARES>,
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  if (attr != hipSuccess) return attr;
+  absorb_query_staged_bf16_kernel<512, SHARES><<<dim3(grid_x, SHARES, a.g), 256, kLds, s>>>(a, rows_per_group);
+  return hipGetLastError();
+}
+
 hipError_t launch_absorb_query_bf16(const AbsorbQueryArgs& a, hipStream_t s) {
   const int rows_per_group = a.rows * a.G;
   dim3 grid((rows_per_group + 31) / 32, (512 / 128 + 3) / 4, a.g);
@@ -781,12 +804,13 @@ hipError_t launch_absorb_query_bf16(const AbsorbQueryArgs& a, hipStream_t s) {
     absorb_query_bf16_kernel<192, 512><<<grid, 256, 0, s>>>(a, rows_per_group);
     return hipGetLastError();
   }
-  constexpr int kLds = 512 * 128 * 2;   // W_UK[j]
-  static const hipError_t attr =
-      hipFuncSetAttribute((const void*)absorb_query_staged_bf16_kernel<512>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-  if (attr != hipSuccess) return attr;
-  absorb_query_staged_bf16_kernel<512><<<dim3(grid.x, 1, a.g), 256, kLds, s>>>(a, rows_per_group);
-  return hipGetLastError();
+  // one workgroup per compute unit: the latent dims in 4 or 2 shares while that leaves units idle, several row blocks each
+  // where there are more
+  const int blocks = (int)grid.x * a.g;
+  if (blocks * 4 <= 256) return launch_absorb_query_staged<4>(a, rows_per_group, grid.x, s);
+  if (blocks * 2 <= 256) return launch_absorb_query_staged<2>(a, rows_per_group, grid.x, s);
+  const int per_group = a.g < 256 ? 256 / a.g : 1;
+  return launch_absorb_query_staged<1>(a, rows_per_group, (int)grid.x < per_group ? (int)grid.x : per_group, s);
 }
 
 template <int DH, int DV, bool FP8>
@@ -798,7 +822,7 @@ static hipError_t launch_expand_tail_dims(const ExpandArgs& a, void* ws, hipStre
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.weights == 1) return e;
   }
-  expand_tail_bf16_kernel<DH, DV, 512, 64, FP8><<<dim3(a.group_count * NSUB, (tokens + 63) / 64), 256, 0, s>>>(a, (const __bf16*)ws);
+  expand_tail_bf16_kernel<DH, DV, 512, 64, FP8><<<dim3(a.group_count * NSUB * 2, (tokens + 31) / 32), 64, 0, s>>>(a, (const __bf16*)ws);
   return hipGetLastError();
 }
 

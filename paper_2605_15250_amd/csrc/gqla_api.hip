@@ -191,6 +191,7 @@ DecodeArgs decode_args(const gqla_shape* s, const gqla_plan* plan, const void* q
   a.cache = view_of(c);
   a.chunks = reinterpret_cast<const ChunkEntry*>(static_cast<char*>(ws) + plan->ws.table_off);
   a.n_chunks = (int32_t)plan->chunks.size();
+  a.chunk_tiles = (int32_t)std::min<int64_t>(ceil_div((int64_t)plan->chunk_pages * plan->page_size, 32), 1 << 20);
   a.part_o = static_cast<char*>(ws) + plan->ws.part_o_off;
   a.part_lse = reinterpret_cast<float*>(static_cast<char*>(ws) + plan->ws.part_lse_off);
   a.B = s->batch;

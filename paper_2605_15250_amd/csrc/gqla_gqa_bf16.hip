@@ -40,22 +40,23 @@ __device__ __forceinline__ bf16x8 widen_e4m3(uint32_t w0, uint32_t w1) {
 // O^T, so that the vector crosses the vector-memory path once (two waves with 32 rows each would both load it; such a
 // wave also needs a SIMD's whole register file: MAXT = 256).  Its query fragments (96 registers' worth, the same for
 // every tile) live in LDS instead, 24 KB per wave, and are read back one 16-byte vector per MFMA.
-// tt (kernel argument): token team.  1: a wave works through its chunk alone.  8 (one group with at most 32 query rows,
-// RB = 1): the eight waves of a workgroup share one chunk, wave w taking tiles w, w + 8, ...; their eight partial
-// states (m, l, O^T) are merged through LDS, so that one partial per chunk reaches memory instead of eight.
-template <int DH, int DV, int DR, bool FP8, int MAXT, int RB>
+// TEAM: token teams.  false: a wave works through its chunk alone.  true (RB = 1): tt (kernel argument) = 2, 4 or 8 waves of a
+// workgroup share one item, wave w of the team taking tiles w, w + tt, ...; their partial states (m, l, O^T) are merged
+// through LDS, so that one partial per item reaches memory.
+template <int DH, int DV, int DR, bool FP8, int MAXT, int RB, bool TEAM>
 __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int n_items, int row_blocks, int share_kr_arg,
                                                                int tt_arg, float k_scale, float v_scale) {
   constexpr int KS_C = DH / 16;  // k-steps over the content dims
   constexpr int KS_R = DR / 16;  // k-steps over the RoPE dims
   constexpr int MT = DV / 32;    // 32-dim tiles of the output
   static_assert(!FP8 || DH == DV, "the 8-bit page format is written for equal dims");
-  constexpr bool CAN_TEAM = RB == 1 && MT == 4;  // the merge below is written (and its LDS sized) for 64 accumulators per lane
-  const int tt = CAN_TEAM ? tt_arg : 1;
+  static_assert(!TEAM || RB == 1, "the merge below is written for one row block");
+  const int tt = TEAM ? tt_arg : 1;
   const int lane = threadIdx.x & 63;
   const int wpb = __builtin_amdgcn_readfirstlane(blockDim.x >> 6);  // waves per workgroup: 8, or the number of groups when that is 2 or 4
   const int wave_in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int item = __builtin_amdgcn_readfirstlane(blockIdx.x * (wpb / tt) + wave_in_wg / tt);  // wave-uniform: keep it scalar
+  int item = __builtin_amdgcn_readfirstlane(blockIdx.x * (wpb / tt) + wave_in_wg / tt);  // wave-uniform: keep it scalar
+  if (TEAM) item = min(item, n_items - 1);  // (spare teams of the last workgroup repeat its last item: all meet at the merge's barrier)
   const int tw = wave_in_wg % tt;   // position in the token team
   const int tstep = 32 * tt;        // tokens from one tile of this wave to its next
   if (item >= n_items) return;      // (a whole token team leaves together)
@@ -123,7 +124,7 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
   // fragments from there, instead of every wave pulling the same lines through the vector memory path (a fifth of
   // all its load instructions).
   __shared__ __attribute__((aligned(16))) char kr_lds[2][KS_R * 1024];
-  const bool share_kr = share_kr_arg != 0;                                  // kernel-uniform
+  const bool share_kr = !TEAM && share_kr_arg != 0;                         // kernel-uniform
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);        // position in the workgroup (scalar)
   auto stage_kr = [&](int tok, int32_t pg, int buf) {
     for (int ks = wave; ks < KS_R; ks += wpb) {  // k-step ks: dims 16*ks .. 16*ks + 15
@@ -346,60 +347,61 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
     }
   }
 
-  if constexpr (CAN_TEAM) {
-    if (tt > 1) {
-      // ---- merge of the team's partial states (tt = 8 waves; row = lane % 32) ----
-      // dyn_lds: O^T of every wave as [wave][quad q = 4 mt + i/4][lane][4] fp32 (16 KB per wave, MT = 4), then m and l
-      // per (wave, row).  Wave w sums quads 2w, 2w + 1 of all eight waves in a fixed order and writes them.
-      constexpr int kQuads = MT * 4;
-      float* const o_lds = (float*)dyn_lds;
-      float* const ml_lds = o_lds + 8 * kQuads * 64 * 4;
-      const float l_mine = pair_sum(l_run[0]);
+  if constexpr (TEAM) {
+    // ---- merge of the team's partial states (row = lane % 32) ----
+    // dyn_lds: O^T of every wave as [wave][quad q = 4 mt + i/4][lane][4] fp32 (MT * 4 KB per wave), then m and l per (wave,
+    // row).  Wave w of a team sums quads kQuads / tt * w, ... of all its waves in a fixed order and writes them.
+    constexpr int kQuads = MT * 4, kMaxTeam = MAXT / 64;
+    float* const ml_lds = (float*)dyn_lds + wpb * kQuads * 64 * 4 + (wave_in_wg - tw) * 32;   // l: 32 wpb floats further
+    float* const o_lds = (float*)dyn_lds + (wave_in_wg - tw) * kQuads * 64 * 4;
+    const float l_mine = pair_sum(l_run[0]);
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *(f32x4*)(o_lds + ((tw * kQuads + 4 * mt + q) * 64 + lane) * 4) =
-              f32x4{o[0][mt][4 * q], o[0][mt][4 * q + 1], o[0][mt][4 * q + 2], o[0][mt][4 * q + 3]};
-      if (h == 0) {
-        ml_lds[tw * 32 + n] = m_run[0];
-        ml_lds[256 + tw * 32 + n] = l_mine;
-      }
-      __syncthreads();
-      float m_all = GQLA_NEG_INF;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) m_all = fmaxf(m_all, ml_lds[w * 32 + n]);
-      const float m_use = (m_all == GQLA_NEG_INF) ? 0.f : m_all;
-      float c[8], l_all = 0.f;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) {
-        c[w] = fast_exp2(ml_lds[w * 32 + n] - m_use);  // 0 for a wave that saw no visible token
-        l_all += c[w] * ml_lds[256 + w * 32 + n];
-      }
-      const bool ok = row_ok[0];
-      const float inv = (l_all > 0.f ? 1.f / l_all : 0.f) * (FP8 ? v_scale : 1.f);
-      const int rho = t_of[0] * a.h_q + head_of[0];
-      const int64_t prow = (int64_t)chunk * a.M + rho;
-      // chunk partial in fp32, 4-dim vectors ordered [chunk][32-row block][d_v / 4][row] (part_vec_index): this lane
-      // holds vector 2 quad + h of its row
-      float* po = (float*)a.part_o + part_vec_index(chunk, rho, a.M, DV / 4, h) * 4;
-      constexpr int kQuadsPerWave = kQuads / 8;
-      static_assert(kQuads % 8 == 0, "every wave of the team sums the same number of quads");
-#pragma unroll
-      for (int qq = 0; qq < kQuadsPerWave; ++qq) {
-        const int quad = tw * kQuadsPerWave + qq;  // = 4 mt + q
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int w = 0; w < 8; ++w) {
-          const f32x4 v = *(const f32x4*)(o_lds + ((w * kQuads + quad) * 64 + lane) * 4);
-          if (c[w] > 0.f) acc += c[w] * v;  // (a wave without tiles holds zeros; one whose rows were all masked may hold anything times 0)
-        }
-        acc *= inv;
-        if (ok) *(f32x4*)(po + 2 * quad * (32 * 4)) = acc;
-      }
-      if (ok && tw == 0 && h == 0) a.part_lse[prow] = l_all > 0.f ? (m_all + fast_log2(l_all)) * kLn2 : GQLA_NEG_INF;
-      return;
+      for (int q = 0; q < 4; ++q)
+        *(f32x4*)(o_lds + ((tw * kQuads + 4 * mt + q) * 64 + lane) * 4) =
+            f32x4{o[0][mt][4 * q], o[0][mt][4 * q + 1], o[0][mt][4 * q + 2], o[0][mt][4 * q + 3]};
+    if (h == 0) {
+      ml_lds[tw * 32 + n] = m_run[0];
+      ml_lds[(wpb + tw) * 32 + n] = l_mine;
     }
+    __syncthreads();
+    float m_all = GQLA_NEG_INF;
+    for (int w = 0; w < tt; ++w) m_all = fmaxf(m_all, ml_lds[w * 32 + n]);
+    const float m_use = (m_all == GQLA_NEG_INF) ? 0.f : m_all;
+    float c[kMaxTeam], l_all = 0.f;
+#pragma unroll
+    for (int w = 0; w < kMaxTeam; ++w) {
+      c[w] = 0.f;
+      if (w < tt) {
+        c[w] = fast_exp2(ml_lds[w * 32 + n] - m_use);  // 0 for a wave that saw no visible token
+        l_all += c[w] * ml_lds[(wpb + w) * 32 + n];
+      }
+    }
+    const bool ok = row_ok[0];
+    const float inv = (l_all > 0.f ? 1.f / l_all : 0.f) * (FP8 ? v_scale : 1.f);
+    const int rho = t_of[0] * a.h_q + head_of[0];
+    const int64_t prow = (int64_t)chunk * a.M + rho;
+    // chunk partial in fp32, 4-dim vectors ordered [chunk][32-row block][d_v / 4][row] (part_vec_index): this lane
+    // holds vector 2 quad + h of its row
+    float* po = (float*)a.part_o + part_vec_index(chunk, rho, a.M, DV / 4, h) * 4;
+    static_assert(kQuads % kMaxTeam == 0, "every wave of the team sums the same number of quads");
+    const int quads_per_wave = kQuads / tt;
+#pragma unroll 2
+    for (int qq = 0; qq < quads_per_wave; ++qq) {
+      const int quad = tw * quads_per_wave + qq;  // = 4 mt + q
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int w = 0; w < kMaxTeam; ++w) {
+        if (w >= tt) break;
+        const f32x4 v = *(const f32x4*)(o_lds + ((w * kQuads + quad) * 64 + lane) * 4);
+        if (c[w] > 0.f) acc += c[w] * v;  // (a wave without tiles holds zeros; one whose rows were all masked may hold anything times 0)
+      }
+      acc *= inv;
+      if (ok) *(f32x4*)(po + 2 * quad * (32 * 4)) = acc;
+    }
+    if (ok && tw == 0 && h == 0) a.part_lse[prow] = l_all > 0.f ? (m_all + fast_log2(l_all)) * kLn2 : GQLA_NEG_INF;
+    return;
   }
 
 #pragma unroll
@@ -550,6 +552,19 @@ static void gqa_launch_shape(const DecodeArgs& a, int max_wpb, int rows_per_wave
   blocks = (n_items + wpb - 1) / wpb;
 }
 
+// Few items (small batches, few groups): up to a workgroup's waves share each, as long as all of them run at once and a chunk
+// has a tile for each.  A chunk is a chain of tiles, two memory latencies each at its start; with the chip this empty nothing
+// else hides them.
+// Measured (kernel): one sequence of 8192 tokens, 8 groups 24.7 -> 13.8 us, 2 x 8192 tokens, 4 groups 18.2 -> 14.4 us, 4 ragged
+// sequences at (192, 256) 21.1 -> 16.4 us, 2 x 3000 tokens of 8-bit codes 13.3 -> 9.2 us; 500 tokens 10.7 -> 10.2 us.
+static int gqa_token_team_size(const DecodeArgs& a, int n_items, int waves) {
+  int tt = 1;
+  while (2 * tt <= waves && (int64_t)n_items * (2 * tt) <= (int64_t)a.num_cus * waves && 2 * tt <= a.chunk_tiles) tt *= 2;
+  return tt;
+}
+template <int DV>
+constexpr int gqa_merge_bytes(int waves) { return waves * (DV / 32 * 4 * 64 * 16 + 2 * 32 * 4); }  // O^T, then m and l per (wave, row)
+
 template <bool FP8>
 static hipError_t launch_decode_gqa_128(const DecodeArgs& a, float k_scale, float v_scale, hipStream_t s) {
   int row_blocks, n_items, wpb, blocks;
@@ -557,23 +572,25 @@ static hipError_t launch_decode_gqa_128(const DecodeArgs& a, float k_scale, floa
   if (a.G * a.s_q > 32) {  // more than one row block per group: two per wave, four waves per workgroup
     gqa_launch_shape(a, 4, 64, row_blocks, n_items, team, wpb, blocks);
     constexpr int kQBytesPerWave = 2 * (128 / 16 + 64 / 16) * 1024;  // both row blocks' query fragments
-    static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 256, 2>,
+    static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 256, 2, false>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 4 * kQBytesPerWave);
     if (attr != hipSuccess) return attr;
-    decode_gqa_bf16_kernel<128, 128, 64, FP8, 256, 2><<<blocks, 64 * wpb, wpb * kQBytesPerWave, s>>>(a, n_items, row_blocks, team ? 1 : 0,
+    decode_gqa_bf16_kernel<128, 128, 64, FP8, 256, 2, false><<<blocks, 64 * wpb, wpb * kQBytesPerWave, s>>>(a, n_items, row_blocks, team ? 1 : 0,
                                                                                                     1, k_scale, v_scale);
     return hipGetLastError();
   }
-  if (a.g == 1) {  // one group with at most 32 query rows: a token team of eight waves per chunk (the plan cuts chunks for that)
-    constexpr int kMergeBytes = 8 * (128 / 32) * 4 * 64 * 16 + 2 * 8 * 32 * 4;  // eight O^T of 16 KB, then m and l per (wave, row)
-    static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kMergeBytes);
+  gqa_launch_shape(a, 8, 32, row_blocks, n_items, team, wpb, blocks);
+  // one group: the plan cuts chunks for teams of eight
+  const int tt = a.g == 1 ? 8 : gqa_token_team_size(a, n_items, 8);
+  if (tt > 1) {
+    static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, gqa_merge_bytes<128>(8));
     if (attr != hipSuccess) return attr;
-    decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1><<<a.n_chunks, 512, kMergeBytes, s>>>(a, a.n_chunks, 1, 0, 8, k_scale, v_scale);
+    decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true><<<(n_items * tt + 7) / 8, 512, gqa_merge_bytes<128>(8), s>>>(a, n_items, row_blocks, 0, tt,
+                                                                                                                  k_scale, v_scale);
     return hipGetLastError();
   }
-  gqa_launch_shape(a, 8, 32, row_blocks, n_items, team, wpb, blocks);
-  decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, k_scale, v_scale);
+  decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, false><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, k_scale, v_scale);
   return hipGetLastError();
 }
 
@@ -582,7 +599,15 @@ hipError_t launch_decode_gqa_bf16(const DecodeArgs& a, hipStream_t s) {
     int row_blocks, n_items, wpb, blocks;
     bool team;
     gqa_launch_shape(a, 4, 32, row_blocks, n_items, team, wpb, blocks);
-    decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, 1.f, 1.f);
+    const int tt = gqa_token_team_size(a, n_items, 4);
+    if (tt > 1) {
+      static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, true>,
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, gqa_merge_bytes<256>(4));
+      if (attr != hipSuccess) return attr;
+      decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, true><<<(n_items * tt + 3) / 4, 256, gqa_merge_bytes<256>(4), s>>>(a, n_items, row_blocks, 0, tt, 1.f, 1.f);
+      return hipGetLastError();
+    }
+    decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, false><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, 1.f, 1.f);
     return hipGetLastError();
   }
   return launch_decode_gqa_128<false>(a, 1.f, 1.f, s);

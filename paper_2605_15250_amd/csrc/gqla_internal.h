@@ -30,7 +30,7 @@ struct DecodeArgs {
   const void* q_r;
   CacheView cache;
   const ChunkEntry* chunks;
-  int32_t n_chunks;
+  int32_t n_chunks, chunk_tiles;                 // chunk_tiles: 32-token tiles of the longest possible chunk (launch-shape choices only)
   void* part_o;      // GQA fp32: fp32 [chunks][M][d_v];  GQA bf16 / 8-bit: fp32 vectors [chunks][M / 32][d_v / 4][32][4] (part_vec_index);  absorb bf16: bf16 vectors [chunks][M / 32][r_kv / 8][32][8] (part_vec_index);  absorb f32: fp32 [chunks][M][r_kv]
   float* part_lse;   // fp32 [chunks][M], natural log
   int32_t B, h_q, g, G, d_h, d_v, r_kv, d_r, s_q, M;  // M = s_q * h_q rows per sequence, row = t*h_q + i; d_v: value dim (GQA path)

@@ -1194,9 +1194,9 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
 // ---- MQA-absorb decode over an 8-bit latent cache (c_kv as E4M3 codes with one scale, k_R in 16 bits) ----
 // The paper names quantised caches as complementary and fixes no format (Sec. 2; Sec. 5.1, item (i)); the page format is
 // this library's (gqla.h): code rows [P][r_kv] back to back, then k_R [P][d_r] in 16 bits -- r_kv + 2 d_r bytes per token.
-// The decode is the MQA-absorb equation on c' = value(code) * scale.  Same mapping of rows to waves as
-// decode_absorb_bf16_kernel above (one wave per 32 rows, or four waves sharing 32 rows), same MFMAs: the codes are
-// widened to bf16 ONCE per tile on their way into LDS, by the wave that fetched them, so that every row block reads
+// The decode is the MQA-absorb equation on c' = value(code) * scale.  One wave per 32 rows as in
+// decode_absorb_bf16_kernel above, or (SPLIT = 4) four waves sharing 32 rows: each contracts a quarter of the key dimension,
+// they sum their S^T through LDS and own a quarter of O^T each.  Same MFMAs: the codes are widened to bf16 ONCE per tile on their way into LDS, by the wave that fetched them, so that every row block reads
 // ready-made bf16 fragments:
 //   tile it+2:  four 16-byte loads of codes per lane (whole 128-byte lines: 8 rows x 128 code bytes per wave
 //               instruction) and one of k_R, in flight in 20 registers for one whole iteration

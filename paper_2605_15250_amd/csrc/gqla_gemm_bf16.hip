@@ -187,8 +187,15 @@ __global__ void __launch_bounds__(256) pack_weights_bf16_kernel(ExpandArgs a, __
 // that the end-of-stage wait (which also covers stores on this hardware) finds them long gone.
 // With an odd number of stages per group (DH = 192, DV = 256: seven) the two result sets would meet at the group
 // boundary, so there the group's last stage stores its results at once instead of in the next stage's shadow.
+__host__ __device__ inline int expand_parts(int rest, int groups) {  // shares of the groups for `rest` blocks of a round
+  int p = 256 / rest;
+  if (p > groups) p = groups;
+  const int per = (groups + p - 1) / p;
+  return (groups + per - 1) / per;   // no more shares than that size of share needs
+}
+
 template <int DH, int DV, int RKV, int DR, bool FP8>
-__global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __bf16* packed, int parts) {
+__global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __bf16* packed) {
   constexpr int W = RKV + DR;
   constexpr int KS = RKV / 16;
   constexpr int STAGE_BYTES = KS * 2 * 1024;  // 64 KB
@@ -203,12 +210,25 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
   const int n = lane & 31, h = lane >> 5;
   const int P = a.latent.page_size;
   const int gc = a.group_count;
-  // workgroup -> (256-token block, share of the groups)
-  int b, blk, L;
-  const int part = blockIdx.x % parts;
-  if (!find_block<256>(a.seq_lens, a.B, a.latent.max_pages * P, blockIdx.x / parts, b, blk, L)) return;  // whole workgroup
+  // Workgroup -> (256-token block, share of the groups).  A compute unit holds one workgroup: blocks run in rounds of 256.
+  // Blocks of whole rounds keep all groups; if the last round has at most 128, its blocks share their groups out over `parts`
+  // workgroups, as far as one round takes it (each reads the latent rows again).
+  int b, blk, L, part = 0, parts = 1;
+  BlockScan<256> blocks;
+  const int total = blocks.count(a.seq_lens, a.B, a.latent.max_pages * P);
+  const int whole = total & ~255, rest = total & 255;
+  int id = blockIdx.x;
+  if (id >= whole) {
+    if (rest == 0) return;           // whole workgroup, as below
+    parts = expand_parts(rest, gc);
+    id -= whole;
+    if (id >= rest * parts) return;
+    part = id % parts;
+    id = whole + id / parts;
+  }
+  if (!blocks.find(id, b, blk, L)) return;
   const int tok0 = blk * 256;
-  const int jj_begin = gc * part / parts, jj_end = gc * (part + 1) / parts;
+  const int jj_begin = parts == 1 ? 0 : gc * part / parts, jj_end = parts == 1 ? gc : gc * (part + 1) / parts;
   const int tokw = tok0 + wave * 64;  // first token of this wave (a wave never straddles a page: P % 64 == 0)
   int32_t pg_in = -1, pg_out = -1;
   if (tokw < L) {
@@ -842,16 +862,22 @@ static hipError_t launch_expand_one_shot(const ExpandArgs& a, void* ws, hipStrea
   if (attr != hipSuccess) return attr;
   const int64_t max_tokens = (int64_t)a.latent.max_pages * a.latent.page_size;
   const int64_t blocks = (max_tokens + 255) / 256 * a.B;
-  // Few blocks (a short prefill, a single sequence): the groups are shared out as well, as far as one round of workgroups
-  // takes it; the latent rows are then read once per share.  (One sequence of 8192 tokens, 8 groups: 81 us in 32 workgroups,
-  // 28 us in 256.  Half a chip's worth of blocks or more is left alone: 122 680 ragged tokens, 480 blocks, take 242 us --
-  // 285 us before find_block, when the holes of the grid left some dies a third round of blocks.)
-  const int parts = (int)(blocks * 2 <= 256 ? (256 / blocks < a.group_count ? 256 / blocks : a.group_count) : 1);
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  // The lengths live on the device, so the kernel decides how the last round is shared out; `blocks` bounds them, and the grid
+  // has room for what the kernel may choose for any number of blocks up to that.  Measured: one sequence of 8192 tokens, 8
+  // groups 81 us in 32 workgroups, 28 us in 256; 20 ragged sequences of 3000 to 6000 tokens into the 8-bit cache (355 blocks)
+  // 207 -> 183 us; 122 680 ragged tokens in 32 sequences 285 -> 240 us (holes in a grid over sequences gave some dies a third
+  // round of blocks).
+  const int64_t whole = blocks & ~(int64_t)255, rest = blocks & 255;
+  int64_t grid = whole;
+  for (int r = 1; r <= (whole ? rest : blocks); ++r) {
+    const int64_t n = whole + (int64_t)r * expand_parts(r, a.group_count);
+    if (n > grid) grid = n;
+  }
+  if (grid > 0x7fffffff) return hipErrorInvalidValue;
   pack_weights_bf16_kernel<DH, DV, 512><<<dim3(a.group_count * NSUB, 512 / 64), 256, 0, s>>>(a, (__bf16*)ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  expand_bf16_kernel<DH, DV, 512, 64, FP8><<<(unsigned)(blocks * parts), 256, kLds, s>>>(a, (const __bf16*)ws, parts);
+  expand_bf16_kernel<DH, DV, 512, 64, FP8><<<(unsigned)grid, 256, kLds, s>>>(a, (const __bf16*)ws);
   return hipGetLastError();
 }
 hipError_t launch_expand_bf16(const ExpandArgs& a, void* ws, hipStream_t s) {

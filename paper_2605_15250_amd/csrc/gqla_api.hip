@@ -172,6 +172,9 @@ struct KernelTimer {  // takes the pending pair; record_begin / record_end are n
   hipError_t end() const { return e1 ? hipEventRecord(e1, s) : hipSuccess; }
 };
 
+// Tokens that a row of the page table holds, as far as 32-bit positions go (whole blocks of the kernels).
+int32_t row_tokens(const gqla_cache* c) { return (int32_t)std::min<int64_t>((int64_t)c->max_pages * c->page_size, INT32_MAX & ~1023); }
+
 CacheView view_of(const gqla_cache* c) {
   CacheView v;
   v.pool = c->pool;
@@ -423,6 +426,7 @@ gqla_status expand_impl(const gqla_shape* shape, const gqla_cache* latent, const
   a.group_begin = group_begin;
   a.group_count = group_count;
   a.tail = tail;
+  a.max_tokens = row_tokens(latent);
   a.weights = weights_packed ? 2 : 0;
   a.k_inv_scale = 1.0f / k_scale;
   a.v_inv_scale = 1.0f / v_scale;
@@ -730,6 +734,7 @@ gqla_status gqla_compress_cache(const gqla_shape* shape, const gqla_cache* expan
   a.latent = view_of(latent);
   a.seq_lens = expanded->seq_lens;
   a.w_inv = w_inv;
+  a.max_tokens = row_tokens(expanded);
   a.B = shape->batch;
   a.g = shape->g;
   a.d_h = shape->d_h;

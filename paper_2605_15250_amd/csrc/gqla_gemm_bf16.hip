@@ -215,7 +215,7 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
   // workgroups, as far as one round takes it (each reads the latent rows again).
   int b, blk, L, part = 0, parts = 1;
   BlockScan<256> blocks;
-  const int total = blocks.count(a.seq_lens, a.B, a.latent.max_pages * P);
+  const int total = blocks.count(a.seq_lens, a.B, a.max_tokens);
   const int whole = total & ~255, rest = total & 255;
   int id = blockIdx.x;
   if (id >= whole) {
@@ -609,7 +609,7 @@ __global__ void __launch_bounds__(256) compress_bf16_kernel(CompressArgs a) {
   const int n = lane & 31, h = lane >> 5;
   const int P = a.expanded.page_size;
   int b, blk, L;
-  if (!find_block<kCompressTok>(a.seq_lens, a.B, a.expanded.max_pages * P, blockIdx.x, b, blk, L)) return;  // whole workgroup
+  if (!find_block<kCompressTok>(a.seq_lens, a.B, a.max_tokens, blockIdx.x, b, blk, L)) return;  // whole workgroup
   const int tok0 = blk * kCompressTok;
   const int K = a.g * DH;
   const int64_t in_page_bytes = (int64_t)P * (a.g * (DH + DV) + DR) * 2;
@@ -796,8 +796,7 @@ static hipError_t launch_compress_dims(const CompressArgs& a, hipStream_t s) {
   static const hipError_t attr =
       hipFuncSetAttribute((const void*)compress_bf16_kernel<DH, DV, 512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kCompressLds);
   if (attr != hipSuccess) return attr;
-  const int64_t max_tokens = (int64_t)a.expanded.max_pages * a.expanded.page_size;
-  const int64_t blocks = (max_tokens + kCompressTok - 1) / kCompressTok * a.B;
+  const int64_t blocks = ((int64_t)a.max_tokens + kCompressTok - 1) / kCompressTok * a.B;
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   compress_bf16_kernel<DH, DV, 512, 64><<<(unsigned)blocks, 256, kCompressLds, s>>>(a);
   return hipGetLastError();
@@ -860,8 +859,7 @@ static hipError_t launch_expand_one_shot(const ExpandArgs& a, void* ws, hipStrea
   static const hipError_t attr =
       hipFuncSetAttribute((const void*)expand_bf16_kernel<DH, DV, 512, 64, FP8>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
-  const int64_t max_tokens = (int64_t)a.latent.max_pages * a.latent.page_size;
-  const int64_t blocks = (max_tokens + 255) / 256 * a.B;
+  const int64_t blocks = ((int64_t)a.max_tokens + 255) / 256 * a.B;
   // The lengths live on the device, so the kernel decides how the last round is shared out; `blocks` bounds them, and the grid
   // has room for what the kernel may choose for any number of blocks up to that.  Measured: one sequence of 8192 tokens, 8
   // groups 81 us in 32 workgroups, 28 us in 256; 20 ragged sequences of 3000 to 6000 tokens into the 8-bit cache (355 blocks)

@@ -1,6 +1,8 @@
 // The two dense contractions around the decode kernels, bf16 MFMA with fp32 accumulation:
 //   query absorption  q_hat = W_UK[j] q_C              (paper Sec. 3.1, MQA-absorb equation, line 1)
 //   cache expansion   K_C = W_UK^T c,  V = W_UV^T c    (Sec. 3.1, "Two equivalent decoding paths": one-shot expand)
+#include <algorithm>
+
 #include "gqla_device.h"
 #include "gqla_lds.h"
 
@@ -194,8 +196,9 @@ __host__ __device__ inline int expand_parts(int rest, int groups) {  // shares o
   return (groups + per - 1) / per;   // no more shares than that size of share needs
 }
 
+// One block of 256 tokens (block `blk` of sequence b, which has L) and groups jj_begin .. jj_end - 1 of the slice.
 template <int DH, int DV, int RKV, int DR, bool FP8>
-__global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __bf16* packed) {
+__device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* packed, char* smem, int b, int blk, int L, int jj_begin, int jj_end) {
   constexpr int W = RKV + DR;
   constexpr int KS = RKV / 16;
   constexpr int STAGE_BYTES = KS * 2 * 1024;  // 64 KB
@@ -204,31 +207,12 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
   constexpr bool ODD = (NSUB & 1) != 0;
   static_assert(DH % 64 == 0 && DV % 64 == 0, "64-column stages");
   static_assert(!FP8 || (DH == 128 && DV == 128), "the 8-bit page format is written for equal dims of 128");
-  extern __shared__ __attribute__((aligned(16))) char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
   const int P = a.latent.page_size;
   const int gc = a.group_count;
-  // Workgroup -> (256-token block, share of the groups).  A compute unit holds one workgroup: blocks run in rounds of 256.
-  // Blocks of whole rounds keep all groups; if the last round has at most 128, its blocks share their groups out over `parts`
-  // workgroups, as far as one round takes it (each reads the latent rows again).
-  int b, blk, L, part = 0, parts = 1;
-  BlockScan<256> blocks;
-  const int total = blocks.count(a.seq_lens, a.B, a.max_tokens);
-  const int whole = total & ~255, rest = total & 255;
-  int id = blockIdx.x;
-  if (id >= whole) {
-    if (rest == 0) return;           // whole workgroup, as below
-    parts = expand_parts(rest, gc);
-    id -= whole;
-    if (id >= rest * parts) return;
-    part = id % parts;
-    id = whole + id / parts;
-  }
-  if (!blocks.find(id, b, blk, L)) return;
   const int tok0 = blk * 256;
-  const int jj_begin = parts == 1 ? 0 : gc * part / parts, jj_end = parts == 1 ? gc : gc * (part + 1) / parts;
   const int tokw = tok0 + wave * 64;  // first token of this wave (a wave never straddles a page: P % 64 == 0)
   int32_t pg_in = -1, pg_out = -1;
   if (tokw < L) {
@@ -254,7 +238,7 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
     for (int ks = 0; ks < KS; ++ks)
       asm volatile("global_load_dwordx4 %0, %1, off" : "=a"(xf[nt][ks]) : "v"(in_row + ks * 16 + h * 8));
     // k_R plane: a straight copy, 8 dims (16 bytes) per lane and step
-    if (tok_ok && part == 0) {
+    if (tok_ok && jj_begin == 0) {
 #pragma unroll
       for (int cb = h; cb < DR / 8; cb += 2) {
         const u32x4 v = *(const u32x4*)(in_row + RKV + cb * 8);
@@ -458,6 +442,34 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
   }
 }
 
+// Workgroup -> (256-token block, share of the groups).  A compute unit holds one workgroup: blocks run in rounds of 256.
+// Blocks of whole rounds keep all groups; if the last round has at most 128, its blocks share their groups out over `parts`
+// workgroups, as far as one round takes it (each reads the latent rows again).
+// The lengths live on the device and the host knows only what a page-table row could hold, so the grid is bounded and a
+// workgroup takes block blockIdx.x, then the one a grid further, and so on.
+template <int DH, int DV, int RKV, int DR, bool FP8>
+__global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __bf16* packed) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int gc = a.group_count;
+  BlockScan<256> blocks;
+  const int total = blocks.count(a.seq_lens, a.B, a.max_tokens);
+  const int whole = total & ~255, rest = total & 255;
+  const int parts = rest ? expand_parts(rest, gc) : 1;
+  for (int wg = blockIdx.x; wg < whole + rest * parts; wg += gridDim.x) {
+    int id = wg, jj_begin = 0, jj_end = gc;
+    if (wg >= whole && parts > 1) {
+      const int part = (wg - whole) % parts;
+      id = whole + (wg - whole) / parts;
+      jj_begin = gc * part / parts;
+      jj_end = gc * (part + 1) / parts;
+    }
+    int b, blk, L;
+    if (!blocks.find(id, b, blk, L)) return;  // whole workgroup
+    // (the last stage's barrier has freed both LDS buffers for the next block)
+    expand_block<DH, DV, RKV, DR, FP8>(a, packed, smem, b, blk, L, jj_begin, jj_end);
+  }
+}
+
 // ---- cache expansion of the last a.tail positions of every sequence (the step's new tokens) ------------------------
 // The B * tail tokens form one list (index = b * tail + t) cut into 32-token tiles; a workgroup is one wave: half of a packed
 // weight stage (32 output columns of one group's W_UK or W_UV, see pack_weights_bf16_kernel) times a tile.  (The call is
@@ -596,20 +608,18 @@ constexpr int kCompressUnit = 32 * kCompressK * 2;    // bytes of a unit: 32 row
 constexpr int kCompressKeys = kCompressTok * kCompressK * 2;
 constexpr int kCompressLds = 4 * kCompressUnits * kCompressUnit + kCompressKeySlots * kCompressKeys;  // all 160 KB
 
+// Tile `id` of the numbering: 128-token tile `blk` of sequence b, which has L tokens.
 template <int DH, int DV, int RKV, int DR>
-__global__ void __launch_bounds__(256) compress_bf16_kernel(CompressArgs a) {
+__device__ __forceinline__ void compress_tile(const CompressArgs& a, char* smem, int id, int b, int blk, int L) {
   static_assert(RKV == 512 && DH % kCompressK == 0 && DH / kCompressK >= 2, "four waves x 128 latent dims, at least two stages");
   constexpr int W = RKV + DR;
   constexpr int PITCH = W * 2 + 16;                   // bytes per token of the output tile in LDS
   static_assert(kCompressTok * PITCH <= kCompressLds, "the output tile reuses the rings");
-  extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, h = lane >> 5;
   const int P = a.expanded.page_size;
-  int b, blk, L;
-  if (!find_block<kCompressTok>(a.seq_lens, a.B, a.max_tokens, blockIdx.x, b, blk, L)) return;  // whole workgroup
   const int tok0 = blk * kCompressTok;
   const int K = a.g * DH;
   const int64_t in_page_bytes = (int64_t)P * (a.g * (DH + DV) + DR) * 2;
@@ -647,7 +657,7 @@ __global__ void __launch_bounds__(256) compress_bf16_kernel(CompressArgs a) {
   const uint32_t a_off1 = (uint32_t)((lane >> 3) * K * 2 + (((lane & 7) ^ (4 + (lane >> 4))) << 4));
   const uint32_t k_off = lane * 16;
   const int stages = K / kCompressK;
-  const int rot = (int)(blockIdx.x >> 3) % stages;    // workgroups go to the eight dies in turn: blockIdx / 8 counts a die's own
+  const int rot = (id >> 3) % stages;                 // workgroups go to the eight dies in turn: id / 8 counts a die's own
   const char* const a_rows = (const char*)a.w_inv + (int64_t)(128 * wave) * K * 2;
   const int64_t rows8 = (int64_t)8 * K * 2;           // bytes from one request's rows to the next one's
   const int64_t plane = (int64_t)P * 16;              // bytes of one vector plane of the page
@@ -789,6 +799,25 @@ __global__ void __launch_bounds__(256) compress_bf16_kernel(CompressArgs a) {
   }
 }
 
+// Grid as in the expansion: bounded, a workgroup takes tile blockIdx.x, then the one a grid further, and so on.
+template <int DH, int DV, int RKV, int DR>
+__global__ void __launch_bounds__(256) compress_bf16_kernel(CompressArgs a) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  for (int id = blockIdx.x;; id += gridDim.x) {
+    int b, blk, L;
+    if (!find_block<kCompressTok>(a.seq_lens, a.B, a.max_tokens, id, b, blk, L)) return;  // whole workgroup
+    compress_tile<DH, DV, RKV, DR>(a, smem, id, b, blk, L);
+    __syncthreads();  // the next tile's requests go where this one's rows leave from
+  }
+}
+
+// Workgroups of a launch over blocks of ragged sequences: eight rounds of 256.  Up to that number (half a million tokens of
+// the expansion) the blocks are dealt out as workgroups come free; beyond it the workgroups loop.  A workgroup without a
+// block only scans the lengths, but holds a compute unit's LDS meanwhile, 1.4 to 2.1 ns each over the chip.  Measured with rows of
+// 2^20 tokens, one workgroup per block that the rows could hold -> this: expansion of 32 ragged sequences 448 -> 251 us, of
+// 128 short ones 1358 -> 101 us; compression 442 -> 157 and 2076 -> 57 us (all as with rows of the sequences' own size).
+constexpr int kMaxWorkgroups = 8 * 256;
+
 }  // namespace
 
 template <int DH, int DV>
@@ -797,8 +826,7 @@ static hipError_t launch_compress_dims(const CompressArgs& a, hipStream_t s) {
       hipFuncSetAttribute((const void*)compress_bf16_kernel<DH, DV, 512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kCompressLds);
   if (attr != hipSuccess) return attr;
   const int64_t blocks = ((int64_t)a.max_tokens + kCompressTok - 1) / kCompressTok * a.B;
-  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-  compress_bf16_kernel<DH, DV, 512, 64><<<(unsigned)blocks, 256, kCompressLds, s>>>(a);
+  compress_bf16_kernel<DH, DV, 512, 64><<<(unsigned)std::min<int64_t>(blocks, kMaxWorkgroups), 256, kCompressLds, s>>>(a);
   return hipGetLastError();
 }
 
@@ -859,23 +887,16 @@ static hipError_t launch_expand_one_shot(const ExpandArgs& a, void* ws, hipStrea
   static const hipError_t attr =
       hipFuncSetAttribute((const void*)expand_bf16_kernel<DH, DV, 512, 64, FP8>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
+  // The lengths live on the device, so the kernel decides how the last round is shared out; whole rounds of 256, so that
+  // those shares find workgroups as well.  Measured: one sequence of 8192 tokens, 8 groups 81 us in 32 workgroups, 28 us in
+  // 256; 20 ragged sequences of 3000 to 6000 tokens into the 8-bit cache (355 blocks) 207 -> 183 us; 122 680 ragged tokens in
+  // 32 sequences 285 -> 240 us (holes in a grid over sequences gave some dies a third round of blocks).
   const int64_t blocks = ((int64_t)a.max_tokens + 255) / 256 * a.B;
-  // The lengths live on the device, so the kernel decides how the last round is shared out; `blocks` bounds them, and the grid
-  // has room for what the kernel may choose for any number of blocks up to that.  Measured: one sequence of 8192 tokens, 8
-  // groups 81 us in 32 workgroups, 28 us in 256; 20 ragged sequences of 3000 to 6000 tokens into the 8-bit cache (355 blocks)
-  // 207 -> 183 us; 122 680 ragged tokens in 32 sequences 285 -> 240 us (holes in a grid over sequences gave some dies a third
-  // round of blocks).
-  const int64_t whole = blocks & ~(int64_t)255, rest = blocks & 255;
-  int64_t grid = whole;
-  for (int r = 1; r <= (whole ? rest : blocks); ++r) {
-    const int64_t n = whole + (int64_t)r * expand_parts(r, a.group_count);
-    if (n > grid) grid = n;
-  }
-  if (grid > 0x7fffffff) return hipErrorInvalidValue;
+  const unsigned grid = (unsigned)std::min<int64_t>((blocks + 255) & ~(int64_t)255, kMaxWorkgroups);
   pack_weights_bf16_kernel<DH, DV, 512><<<dim3(a.group_count * NSUB, 512 / 64), 256, 0, s>>>(a, (__bf16*)ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  expand_bf16_kernel<DH, DV, 512, 64, FP8><<<(unsigned)grid, 256, kLds, s>>>(a, (const __bf16*)ws);
+  expand_bf16_kernel<DH, DV, 512, 64, FP8><<<grid, 256, kLds, s>>>(a, (const __bf16*)ws);
   return hipGetLastError();
 }
 hipError_t launch_expand_bf16(const ExpandArgs& a, void* ws, hipStream_t s) {

@@ -43,8 +43,48 @@ def _switch(op, nb, max_pages):
     return out
 
 
-@pytest.mark.parametrize("op,nb", [("expand", 1), ("expand_fp8", 1)])
+# (a grid over what two such rows hold, or one of the compression, would not fit a launch)
+@pytest.mark.parametrize("op,nb", [("expand", 1), ("expand_fp8", 1), ("expand", 2), ("expand_fp8", 2), ("compress", 1), ("compress", 2)])
 def test_row_of_two_to_the_31_tokens(op, nb):
     narrow = _switch(op, nb, 2)
     assert int((narrow != 0).sum()) > 0
     assert torch.equal(_switch(op, nb, 1 << 21), narrow)
+
+
+@pytest.mark.parametrize("op,d_h,d_v", [("expand", 128, 128), ("expand", 192, 256), ("compress", 128, 128), ("compress", 192, 256)])
+def test_more_blocks_than_workgroups(op, d_h, d_v):
+    """Beyond 2048 workgroups one takes several blocks in turn: sequences whose pages are a few shared ones, so that every
+    sequence's result has to be that of the first with its length (the same bits for the expansion; the compression starts its
+    sums at another place from tile to tile, which moves them by the order of fp32 sums)."""
+    from paper_2605_15250_amd import binding as B
+    g, page = 4, 64
+    block = 256 if op == "expand" else 128
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    lens = [3 * block, 2 * block + 70, 1, 0, block] * (2100 // 8)      # eight blocks in five sequences: 2096 and a few more
+    lens += [3 * block] * 2 + [5]
+    nb, per = len(lens), 3 * block // page
+    n_out = nb * per
+    wide_in = torch.randn(per, page * ((R_KV + D_R) if op == "expand" else g * (d_h + d_v) + D_R), generator=gen, device="cuda").bfloat16()
+    t_in = torch.arange(per, dtype=torch.int32).repeat(nb, 1).cuda()
+    d_lens = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    shape = B.make_shape(nb, g, g, d_h, R_KV, D_R, 1, B.GQLA_BF16, 0.0, d_v)
+    out = torch.zeros(n_out, page * ((R_KV + D_R) if op != "expand" else g * (d_h + d_v) + D_R), dtype=torch.bfloat16, device="cuda")
+    src = B.make_cache(wide_in, d_lens, t_in, page, per, per, 0 if op == "expand" else g)
+    dst = B.make_cache(out, d_lens, None, page, per, n_out, g if op == "expand" else 0)
+    print(op, d_h, nb, flush=True)
+    if op == "expand":
+        w_uk = (torch.randn(g, R_KV, d_h, generator=gen, device="cuda") * R_KV ** -0.5).bfloat16()
+        w_uv = (torch.randn(g, R_KV, d_v, generator=gen, device="cuda") * R_KV ** -0.5).bfloat16()
+        ws = torch.empty(B.gqla_expand_workspace_bytes(shape, g), dtype=torch.uint8, device="cuda")
+        B.gqla_expand_cache(shape, src, w_uk, w_uv, 0, g, dst, ws)
+    else:
+        w_inv = (torch.randn(R_KV, g * d_h, generator=gen, device="cuda") * (g * d_h) ** -0.5).bfloat16()
+        B.gqla_compress_cache(shape, src, w_inv, dst)
+    torch.cuda.synchronize()
+    seqs = out.reshape(nb, per, -1)
+    for n in sorted(set(lens)):
+        same = seqs[[b for b in range(nb) if lens[b] == n]].float()
+        assert bool(torch.isfinite(same).all()) and (n == 0) == (int((same != 0).sum()) == 0)
+        # fp32 sums of up to 768 products in another order, then one rounding to bf16: a step of 2^-8 of the value at most
+        bound = 0.0 if op == "expand" else same[:1].abs() * 2.0 ** -7 + 1e-4
+        assert bool(((same - same[:1]).abs() <= bound).all()), n

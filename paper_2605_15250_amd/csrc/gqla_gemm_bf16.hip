@@ -189,16 +189,16 @@ __global__ void __launch_bounds__(256) pack_weights_bf16_kernel(ExpandArgs a, __
 // that the end-of-stage wait (which also covers stores on this hardware) finds them long gone.
 // With an odd number of stages per group (DH = 192, DV = 256: seven) the two result sets would meet at the group
 // boundary, so there the group's last stage stores its results at once instead of in the next stage's shadow.
-__host__ __device__ inline int expand_parts(int rest, int groups) {  // shares of the groups for `rest` blocks of a round
+__device__ __forceinline__ int expand_parts(int rest, int groups) {  // shares of the groups for `rest` blocks of a round
   int p = 256 / rest;
   if (p > groups) p = groups;
   const int per = (groups + p - 1) / p;
   return (groups + per - 1) / per;   // no more shares than that size of share needs
 }
 
-// One block of 256 tokens (block `blk` of sequence b, which has L) and groups jj_begin .. jj_end - 1 of the slice.
+// One block of 256 tokens (block `blk` of sequence b, which has L) and groups jj_begin .. jj_begin + jj_count - 1 of the slice.
 template <int DH, int DV, int RKV, int DR, bool FP8>
-__device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* packed, char* smem, int b, int blk, int L, int jj_begin, int jj_end) {
+__device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* packed, char* smem, int b, int blk, int L, int jj_begin, int jj_count) {
   constexpr int W = RKV + DR;
   constexpr int KS = RKV / 16;
   constexpr int STAGE_BYTES = KS * 2 * 1024;  // 64 KB
@@ -216,8 +216,8 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
   const int tokw = tok0 + wave * 64;  // first token of this wave (a wave never straddles a page: P % 64 == 0)
   int32_t pg_in = -1, pg_out = -1;
   if (tokw < L) {
-    pg_in = page_of(a.latent, b, tokw / P);
-    pg_out = page_of(a.expanded, b, tokw / P);
+    pg_in = page_of_uniform(a.latent, b, tokw / P);
+    pg_out = page_of_uniform(a.expanded, b, tokw / P);
   }
   const bool wave_ok = pg_in >= 0 && pg_out >= 0;  // wave-uniform
   const int slot0 = tokw % P;
@@ -237,14 +237,6 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
       asm volatile("global_load_dwordx4 %0, %1, off" : "=a"(xf[nt][ks]) : "v"(in_row + ks * 16 + h * 8));
-    // k_R plane: a straight copy, 8 dims (16 bytes) per lane and step
-    if (tok_ok && jj_begin == 0) {
-#pragma unroll
-      for (int cb = h; cb < DR / 8; cb += 2) {
-        const u32x4 v = *(const u32x4*)(in_row + RKV + cb * 8);
-        __builtin_nontemporal_store(v, (u32x4*)(page_bytes + (int64_t)gc * (DH + DV) * P * EB + ((int64_t)cb * P + slot0 + 32 * nt + n) * 16));
-      }
-    }
   }
 
   // LDS-DMA of one stage: 64 instructions of 1 KB, 16 per wave, linear (the packed layout is already fragment order)
@@ -265,8 +257,10 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
     for (int k = 0; k < 16; ++k) accs[i >> 2][(i >> 1) & 1][i & 1][k] = 0.f;
   // stores address the page through one uniform base and 32-bit offsets (a page is at most a few MB)
   const uint32_t plane_k = (uint32_t)DH * P, plane_v = (uint32_t)DV * P;          // elements of one group's K and V plane
-  const uint32_t k_lane = (uint32_t)(slot0 + n) * 8 + (uint32_t)h * P * 8;        // K plane: token slot0 + n, 8-dim block + h
-  const uint32_t v_lane = (uint32_t)((slot0 >> 3) + h) * DV * 8 + n * 8;          // V plane: dim n, 8-token block slot0/8 + h
+  // from here on groups are counted from the share's first: its offset is in these and in `packed`
+  packed += (int64_t)jj_begin * NSUB * (STAGE_BYTES / 2);
+  const uint32_t k_lane = (uint32_t)jj_begin * plane_k + (uint32_t)(slot0 + n) * 8 + (uint32_t)h * P * 8;   // K plane: token slot0 + n, 8-dim block + h
+  const uint32_t v_lane = (uint32_t)jj_begin * plane_v + (uint32_t)((slot0 >> 3) + h) * DV * 8 + n * 8;     // V plane: dim n, 8-token block slot0/8 + h
   const bool wave_full = tokw + 64 <= L;                                          // no token of this wave lies beyond L_b
   // One 16-byte store per lane: piece (nt, e, qp) of the previous stage's results; kind, mtp and the piece are compile-time.
   // A lane holds rows 4h..4h+3 of each 8-row block of its column; the two half-waves trade so that lane (n, h) ends up
@@ -293,12 +287,12 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
     if (kind == 0) {
       // lane = token; vector h of pair kp = 2 mtp + e of the K8 plane
       if (wave_full || tokw + 32 * nt + n < L) {
-        const uint32_t off = ((uint32_t)(jj * (DH / 16) + 2 * (2 * mtp + e) + h) * P + slot0 + 32 * nt + n) * 16;
+        const uint32_t off = ((uint32_t)(jj * (DH / 16) + 2 * (2 * mtp + e) + h) * P + slot0 + 32 * nt + n) * 16 + jj_begin * plane_k;
         __builtin_nontemporal_store(v, (u32x4*)(page_bytes + off));
       }
     } else {
       // lane = dim 64 mtp + 32 e + n; vector h of 32-token tile (slot0 + 32 nt) / 32 of the V8 plane: tokens 8h + 0..7, 16 + 8h + 0..7
-      const uint32_t off = (uint32_t)gc * P * DH +
+      const uint32_t off = (uint32_t)(gc + jj_begin) * plane_k +
                            (((uint32_t)(jj * (P / 32) + (slot0 >> 5) + nt) * DH + 64 * mtp + 32 * e + n) * 2 + h) * 16;
       char* dst = page_bytes + off;
       const int tk = tokw + 32 * nt + 8 * h;  // first token of the vector's first half; the second half starts 16 later
@@ -351,15 +345,15 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
     emit_prev(pack_prev(par, nt, e, qp), kind, mtp, jj, nt, e, qp);
   };
 
-  const int stage0 = jj_begin * NSUB, n_stages = jj_end * NSUB;  // this workgroup's stages
-  stage_in(stage0, smem);
+  const int n_stages = jj_count * NSUB;
+  stage_in(0, smem);
   wait_all_memory();
   __syncthreads();
-  for (int jj = jj_begin; jj < jj_end; ++jj) {
+  for (int jj = 0; jj < jj_count; ++jj) {
     static_for<NSUB>([&](auto SUB) __attribute__((always_inline)) {  // compile time: fixes the kind (MFMA operand order) and the result set
       constexpr int sub = decltype(SUB)::value;
       const int stage = jj * NSUB + sub;
-      const int odd = (stage - stage0) & 1;            // LDS buffer of this stage
+      const int odd = stage & 1;                       // LDS buffer of this stage
       const char* buf = smem + odd * STAGE_BYTES + lane * 16;
       f32x16 (&acc)[2][2] = accs[sub & 1];
       // the stage before this one, whose results leave in this stage's shadow (none at the start of a group when the
@@ -367,7 +361,7 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
       constexpr int kPrevNone = -1;
       constexpr int psub = sub > 0 ? sub - 1 : (ODD ? kPrevNone : NSUB - 1);
       constexpr int pkind = psub >= NSK, pmtp = pkind ? psub - NSK : psub, ppar = psub & 1;
-      const int pjj = psub == kPrevNone ? -1 : (sub == 0 ? (jj > jj_begin ? jj - 1 : -1) : jj);
+      const int pjj = psub == kPrevNone ? -1 : (sub == 0 ? jj - 1 : jj);
       if (wave_ok) {
         bf16x8 w[DEPTH + 1][2];
 #pragma unroll
@@ -433,12 +427,31 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
       __syncthreads();  // next stage has landed; everyone is done with this stage's buffer
     });
   }
+  // k_R plane: a straight copy, 8 dims (16 bytes) per lane and vector, fetched behind the last stage's results: there its
+  // latency is covered by their stores, and the start of the block has one wait for all of its loads
+  u32x4 kr[2][DR / 16];
+  auto rope_row = [&](int nt) { return in_page + (int64_t)(slot0 + (wave_ok && tokw + 32 * nt + n < L ? 32 * nt + n : 0)) * W + RKV + h * 8; };
+  if (jj_begin == 0) {
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int i = 0; i < DR / 16; ++i) kr[nt][i] = *(const u32x4*)(rope_row(nt) + 16 * i);
+  }
   if constexpr (FP8) {
 #pragma unroll
-    for (int piece = 0; piece < 4; ++piece) store_prev8((NSUB - 1) & 1, 1, NSUB - 1 - NSK, jj_end - 1, piece >> 1, piece & 1);
+    for (int piece = 0; piece < 4; ++piece) store_prev8((NSUB - 1) & 1, 1, NSUB - 1 - NSK, jj_count - 1, piece >> 1, piece & 1);
   } else if constexpr (!ODD) {
 #pragma unroll
-    for (int piece = 0; piece < 8; ++piece) store_prev((NSUB - 1) & 1, 1, NSUB - 1 - NSK, jj_end - 1, piece >> 2, (piece >> 1) & 1, piece & 1);
+    for (int piece = 0; piece < 8; ++piece) store_prev((NSUB - 1) & 1, 1, NSUB - 1 - NSK, jj_count - 1, piece >> 2, (piece >> 1) & 1, piece & 1);
+  }
+  if (jj_begin == 0) {
+    char* const rp = page_bytes + (int64_t)gc * (DH + DV) * P * EB + ((int64_t)h * P + slot0 + n) * 16;
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+      if (wave_ok && tokw + 32 * nt + n < L) {
+#pragma unroll
+        for (int i = 0; i < DR / 16; ++i) __builtin_nontemporal_store(kr[nt][i], (u32x4*)(rp + ((int64_t)2 * i * P + 32 * nt) * 16));
+      }
   }
 }
 
@@ -454,7 +467,7 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
   BlockScan<256> blocks;
   const int total = blocks.count(a.seq_lens, a.B, a.max_tokens);
   const int whole = total & ~255, rest = total & 255;
-  const int parts = rest ? expand_parts(rest, gc) : 1;
+  const int parts = rest > 0 && rest <= 128 && gc > 1 ? expand_parts(rest, gc) : 1;
   for (int wg = blockIdx.x; wg < whole + rest * parts; wg += gridDim.x) {
     int id = wg, jj_begin = 0, jj_end = gc;
     if (wg >= whole && parts > 1) {
@@ -466,7 +479,7 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
     int b, blk, L;
     if (!blocks.find(id, b, blk, L)) return;  // whole workgroup
     // (the last stage's barrier has freed both LDS buffers for the next block)
-    expand_block<DH, DV, RKV, DR, FP8>(a, packed, smem, b, blk, L, jj_begin, jj_end);
+    expand_block<DH, DV, RKV, DR, FP8>(a, packed, smem, b, blk, L, jj_begin, jj_end - jj_begin);
   }
 }
 
@@ -803,9 +816,11 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, char* smem,
 template <int DH, int DV, int RKV, int DR>
 __global__ void __launch_bounds__(256) compress_bf16_kernel(CompressArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  for (int id = blockIdx.x;; id += gridDim.x) {
+  BlockScan<kCompressTok> blocks;
+  const int total = blocks.count(a.seq_lens, a.B, a.max_tokens);
+  for (int id = blockIdx.x; id < total; id += gridDim.x) {
     int b, blk, L;
-    if (!find_block<kCompressTok>(a.seq_lens, a.B, a.max_tokens, id, b, blk, L)) return;  // whole workgroup
+    if (!blocks.find(id, b, blk, L)) return;  // whole workgroup
     compress_tile<DH, DV, RKV, DR>(a, smem, id, b, blk, L);
     __syncthreads();  // the next tile's requests go where this one's rows leave from
   }

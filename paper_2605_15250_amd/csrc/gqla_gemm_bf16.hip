@@ -484,10 +484,9 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
 }
 
 // ---- cache expansion of the last a.tail positions of every sequence (the step's new tokens) ------------------------
-// The B * tail tokens form one list (index = b * tail + t) cut into 32-token tiles; a workgroup is one wave: half of a packed
-// weight stage (32 output columns of one group's W_UK or W_UV, see pack_weights_bf16_kernel) times a tile.  (The call is
-// latency and what one compute unit can fetch: 64 KB a wave, so the waves are spread over as many units as there are.
-// 128 tokens, 8 groups, 256 waves: 11.9 us as 64 workgroups of four, 5.9 us this way; one group 9.5 -> 4.9 us):
+// The B * tail tokens form one list (index = b * tail + t) cut into 32-token tiles; a wave takes half of a packed weight
+// stage (32 output columns of one group's W_UK or W_UV, see pack_weights_bf16_kernel) times a tile.  A workgroup is one wave
+// or the two halves of a stage on one tile (see the launcher):
 //   K^T[d][tok] = W_UK^T[d][r] * C^T[r][tok]   and   V^T[d][tok] = W_UV^T[d][r] * C^T[r][tok]
 //   A = packed weight fragment straight from global memory (1 KB, contiguous), B = the tokens' latent rows, gathered
 //   (lane = token, 8 consecutive latent dims per k-step).
@@ -497,18 +496,20 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
 // FP8 = true: `expanded` is an 8-bit cache (E4M3 code planes, see the header); every result is first rounded to bf16,
 // the value the 16-bit cache would hold, and then quantised, so that the codes equal those of expanding into a 16-bit
 // cache and converting it.
-template <int DH, int DV, int RKV, int DR, bool FP8>
-__global__ void __launch_bounds__(64) expand_tail_bf16_kernel(ExpandArgs a, const __bf16* packed) {
+template <int DH, int DV, int RKV, int DR, bool FP8, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES) expand_tail_bf16_kernel(ExpandArgs a, const __bf16* packed) {
   constexpr int W = RKV + DR;
   constexpr int KS = RKV / 16;
   constexpr int NSK = DH / 64, NSUB = (DH + DV) / 64;
   static_assert(!FP8 || (DH == 128 && DV == 128), "the 8-bit page format is written for equal dims of 128");
-  const int lane = threadIdx.x;
+  static_assert(WAVES == 1 || WAVES == 2, "one half of a stage, or both halves");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
-  const int stage = blockIdx.x >> 1;  // jj * NSUB + sub
+  const int stage = WAVES == 1 ? blockIdx.x >> 1 : blockIdx.x;  // jj * NSUB + sub
   const int jj = stage / NSUB, sub = stage % NSUB;
   const int kind = sub >= NSK, mtp = kind ? sub - NSK : sub;
-  const int e = blockIdx.x & 1;
+  const int e = WAVES == 1 ? blockIdx.x & 1 : wave & 1;
   const int idx = blockIdx.y * 32 + n;  // this lane's token in the list
   const int P = a.latent.page_size;
   const int gc = a.group_count;
@@ -884,7 +885,17 @@ static hipError_t launch_expand_tail_dims(const ExpandArgs& a, void* ws, hipStre
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.weights == 1) return e;
   }
-  expand_tail_bf16_kernel<DH, DV, 512, 64, FP8><<<dim3(a.group_count * NSUB * 2, (tokens + 31) / 32), 64, 0, s>>>(a, (const __bf16*)ws);
+  // The call is latency and what one compute unit can fetch, 64 KB a wave, so the waves are spread over as many units as there
+  // are: 128 tokens, 8 groups, 256 waves: 9.2 us as 64 workgroups of four waves, 5.1 us as 256 of one; one group 8.8 -> 4.9 us.
+  // Workgroups go to the eight dies in turn: with at most four stages no die has two halves, every die reads all the latent
+  // rows by itself, and from a few hundred waves on that costs more than the spread gives.  Two waves on the same rows then:
+  // one group, 1024 waves 9.6 -> 8.8 us, 4096 waves 33.8 -> 29.5 us; 512 waves 5.9 us either way, 256 waves 4.9 against 5.5.
+  // (8 groups, 8192 tokens: 104 us in pairs, 92 us as single waves; 4 groups the same to 3 %.)
+  const int stages = a.group_count * NSUB, tiles = (tokens + 31) / 32;
+  if (stages <= 4 && (int64_t)tiles * stages * 2 >= 512)
+    expand_tail_bf16_kernel<DH, DV, 512, 64, FP8, 2><<<dim3(stages, tiles), 128, 0, s>>>(a, (const __bf16*)ws);
+  else
+    expand_tail_bf16_kernel<DH, DV, 512, 64, FP8, 1><<<dim3(stages * 2, tiles), 64, 0, s>>>(a, (const __bf16*)ws);
   return hipGetLastError();
 }
 

@@ -299,68 +299,69 @@ __global__ void __launch_bounds__(kThreads) expand_f32_kernel(ExpandArgs a) {
   __shared__ f32x4 c_s[512 * kTok / 4];             // [r][token]
   __shared__ float red[kThreads / 64][4 * kTok][kRow];
   const int P = a.latent.page_size, b = blockIdx.y;
-  const int L = a.seq_lens[b], from = kTail ? max(L - a.tail, 0) : 0;
-  const int tok0 = from / kTok * kTok + blockIdx.x * kTok;
-  if (tok0 >= L) return;
-  const int32_t pg_in = page_of(a.latent, b, tok0 / P);
-  const int32_t pg_out = page_of(a.expanded, b, tok0 / P);
-  if (pg_in < 0 || pg_out < 0) return;
-  const int slot0 = tok0 % P, first = max(from - tok0, 0), valid = min(kTok, L - tok0);  // tokens first .. valid - 1 are written
-  const int W = a.r_kv + a.d_r, gc = a.group_count;
-  const float* in = (const float*)a.latent.pool + ((int64_t)pg_in * P + slot0) * W;
-  float* out = (float*)a.expanded.pool + (int64_t)pg_out * P * (gc * (a.d_h + a.d_v) + a.d_r);
-  for (int idx = threadIdx.x; idx < kTok * a.r_kv; idx += kThreads) {
-    const int tok = idx / a.r_kv, r = idx % a.r_kv;
-    ((float*)c_s)[r * kTok + tok] = tok < valid ? in[(int64_t)tok * W + r] : 0.f;
-  }
-  if (blockIdx.z == 0)
-    for (int idx = first * a.d_r + threadIdx.x; idx < valid * a.d_r; idx += kThreads) {
-      const int tok = idx / a.d_r, d = idx % a.d_r;
-      out[(int64_t)gc * P * (a.d_h + a.d_v) + ((int64_t)(d / 8) * P + slot0 + tok) * 8 + d % 8] = in[(int64_t)tok * W + a.r_kv + d];
+  const int L = a.seq_lens[b], from = kTail ? max(L - a.tail, 0) : 0, end = kTail ? L : min(L, a.max_tokens);
+  for (int64_t at = from / kTok * kTok + (int64_t)blockIdx.x * kTok; at < end; at += (int64_t)gridDim.x * kTok) {
+    const int tok0 = (int)at;
+    const int32_t pg_in = page_of(a.latent, b, tok0 / P);
+    const int32_t pg_out = page_of(a.expanded, b, tok0 / P);
+    if (pg_in < 0 || pg_out < 0) continue;  // whole workgroup
+    const int slot0 = tok0 % P, first = max(from - tok0, 0), valid = min(kTok, L - tok0);  // tokens first .. valid - 1 are written
+    const int W = a.r_kv + a.d_r, gc = a.group_count;
+    const float* in = (const float*)a.latent.pool + ((int64_t)pg_in * P + slot0) * W;
+    float* out = (float*)a.expanded.pool + (int64_t)pg_out * P * (gc * (a.d_h + a.d_v) + a.d_r);
+    for (int idx = threadIdx.x; idx < kTok * a.r_kv; idx += kThreads) {
+      const int tok = idx / a.r_kv, r = idx % a.r_kv;
+      ((float*)c_s)[r * kTok + tok] = tok < valid ? in[(int64_t)tok * W + r] : 0.f;
     }
-  __syncthreads();
-  const int nk = gc * a.d_h / 4, n_all = nk + gc * a.d_v / 4;  // column vectors: keys, all
-  const int cv0 = blockIdx.z * 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int cv = cv0 + lane;
-  if (cv < n_all) {
-    const bool is_v = cv >= nk;
-    const int per = (is_v ? a.d_v : a.d_h) / 4, x = is_v ? cv - nk : cv;
-    const f32x4* w = (const f32x4*)(is_v ? a.w_uv : a.w_uk) + (int64_t)(a.group_begin + x / per) * a.r_kv * per + x % per;
-    f32x4 lo[4] = {}, hi[4] = {};  // [column]: tokens 0..3, 4..7
-#pragma unroll 4
-    for (int r = wave; r < a.r_kv; r += kThreads / 64) {
-      const f32x4 wv = w[(int64_t)r * per], c0 = c_s[r * 2], c1 = c_s[r * 2 + 1];
+    if (blockIdx.z == 0)
+      for (int idx = first * a.d_r + threadIdx.x; idx < valid * a.d_r; idx += kThreads) {
+        const int tok = idx / a.d_r, d = idx % a.d_r;
+        out[(int64_t)gc * P * (a.d_h + a.d_v) + ((int64_t)(d / 8) * P + slot0 + tok) * 8 + d % 8] = in[(int64_t)tok * W + a.r_kv + d];
+      }
+    __syncthreads();
+    const int nk = gc * a.d_h / 4, n_all = nk + gc * a.d_v / 4;  // column vectors: keys, all
+    const int cv0 = blockIdx.z * 64, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int cv = cv0 + lane;
+    if (cv < n_all) {
+      const bool is_v = cv >= nk;
+      const int per = (is_v ? a.d_v : a.d_h) / 4, x = is_v ? cv - nk : cv;
+      const f32x4* w = (const f32x4*)(is_v ? a.w_uv : a.w_uk) + (int64_t)(a.group_begin + x / per) * a.r_kv * per + x % per;
+      f32x4 lo[4] = {}, hi[4] = {};  // [column]: tokens 0..3, 4..7
+  #pragma unroll 4
+      for (int r = wave; r < a.r_kv; r += kThreads / 64) {
+        const f32x4 wv = w[(int64_t)r * per], c0 = c_s[r * 2], c1 = c_s[r * 2 + 1];
+        for (int k = 0; k < 4; ++k)
+          for (int y = 0; y < 4; ++y) {
+            lo[k][y] = fmaf(wv[k], c0[y], lo[k][y]);
+            hi[k][y] = fmaf(wv[k], c1[y], hi[k][y]);
+          }
+      }
       for (int k = 0; k < 4; ++k)
         for (int y = 0; y < 4; ++y) {
-          lo[k][y] = fmaf(wv[k], c0[y], lo[k][y]);
-          hi[k][y] = fmaf(wv[k], c1[y], hi[k][y]);
+          red[wave][y * 4 + k][lane] = lo[k][y];
+          red[wave][(y + 4) * 4 + k][lane] = hi[k][y];
         }
     }
-    for (int k = 0; k < 4; ++k)
-      for (int y = 0; y < 4; ++y) {
-        red[wave][y * 4 + k][lane] = lo[k][y];
-        red[wave][(y + 4) * 4 + k][lane] = hi[k][y];
+    __syncthreads();
+    // 512 vectors: of a key, four columns of one token; of a value, four tokens of one column
+    for (int u = threadIdx.x; u < 8 * 64; u += kThreads) {
+      const int l = u >> 3, vec = cv0 + l;
+      if (vec >= n_all) break;
+      const bool is_v = vec >= nk;
+      const int dim = is_v ? a.d_v : a.d_h, e = (is_v ? vec - nk : vec) * 4, jj = e / dim, d = e % dim;
+      const int tok = is_v ? (u & 1) * 4 : u & 7, col = is_v ? (u >> 1) & 3 : 0;
+      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+      for (int s = 0; s < kThreads / 64; ++s)
+        for (int k = 0; k < 4; ++k) sum[k] += is_v ? red[s][(tok + k) * 4 + col][l] : red[s][tok * 4 + k][l];
+      if (is_v) {
+        float* dst = out + (int64_t)gc * P * a.d_h + ((int64_t)(jj * (P / 8) + slot0 / 8) * a.d_v + d + col) * 8 + tok;
+        if (tok >= first && tok + 4 <= valid) *(f32x4*)dst = sum;
+        else
+          for (int k = 0; k < 4; ++k)
+            if (tok + k >= first && tok + k < valid) dst[k] = sum[k];  // slots that no token owns are not written
+      } else if (tok >= first && tok < valid) {
+        *(f32x4*)(out + ((int64_t)(jj * (a.d_h / 8) + d / 8) * P + slot0 + tok) * 8 + d % 8) = sum;
       }
-  }
-  __syncthreads();
-  // 512 vectors: of a key, four columns of one token; of a value, four tokens of one column
-  for (int u = threadIdx.x; u < 8 * 64; u += kThreads) {
-    const int l = u >> 3, vec = cv0 + l;
-    if (vec >= n_all) break;
-    const bool is_v = vec >= nk;
-    const int dim = is_v ? a.d_v : a.d_h, e = (is_v ? vec - nk : vec) * 4, jj = e / dim, d = e % dim;
-    const int tok = is_v ? (u & 1) * 4 : u & 7, col = is_v ? (u >> 1) & 3 : 0;
-    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < kThreads / 64; ++s)
-      for (int k = 0; k < 4; ++k) sum[k] += is_v ? red[s][(tok + k) * 4 + col][l] : red[s][tok * 4 + k][l];
-    if (is_v) {
-      float* dst = out + (int64_t)gc * P * a.d_h + ((int64_t)(jj * (P / 8) + slot0 / 8) * a.d_v + d + col) * 8 + tok;
-      if (tok >= first && tok + 4 <= valid) *(f32x4*)dst = sum;
-      else
-        for (int k = 0; k < 4; ++k)
-          if (tok + k >= first && tok + k < valid) dst[k] = sum[k];  // slots that no token owns are not written
-    } else if (tok >= first && tok < valid) {
-      *(f32x4*)(out + ((int64_t)(jj * (a.d_h / 8) + d / 8) * P + slot0 + tok) * 8 + d % 8) = sum;
     }
   }
 }
@@ -454,7 +455,10 @@ hipError_t launch_combine_project_f32(const CombineArgs& a, hipStream_t s) {
 }
 hipError_t launch_expand_f32(const ExpandArgs& a, hipStream_t s) {
   const int col_blocks = (a.group_count * (a.d_h + a.d_v) + 255) / 256;
-  expand_f32_kernel<false><<<dim3(a.latent.max_pages * (a.latent.page_size / 8), a.B, col_blocks), kThreads, 0, s>>>(a);
+  // What a row of the page table could hold bounds the tokens; beyond 8192 of them a workgroup takes every 1024th eight.  (With a
+  // workgroup for each, rows of 131 072 tokens made 16 sequences x 4000 tokens, four column blocks take 231 us instead of 190.)
+  const int eights = a.max_tokens / 8;
+  expand_f32_kernel<false><<<dim3(eights < 1024 ? eights : 1024, a.B, col_blocks), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 

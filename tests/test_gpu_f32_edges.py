@@ -2,6 +2,8 @@
 several passes of 64 tokens, one chunk per sequence (the decode writes the output itself) and several (partials and a
 merge), column blocks that end inside a wave, pages of 8.  Bars as for every fp32 shape: 1e-4 absolute, 1e-5 relative."""
 import pytest
+import torch
+
 import synth_inputs as S
 from test_gpu_parity import Case, run_absorb_path, run_gqa_path
 
@@ -27,3 +29,33 @@ def test_fp32_edges(h_q, g, s_q, d_h, d_v, r_kv, d_r, page, lens, cp):
         run_gqa_path(case)
     finally:
         case.close()
+
+
+@pytest.mark.parametrize("lens", [[8192, 8193, 20011], [7]])
+def test_f32_expansion_of_more_eights_than_workgroups(lens):
+    """Beyond 8192 tokens of a row a workgroup takes several groups of eight tokens in turn.  Against the fp64 product."""
+    from paper_2605_15250_amd import binding as B
+    g, d, r_kv, d_r, P = 2, 8, 16, 8, 16
+    nb, max_pages = len(lens), 20016 // P
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    pool = torch.randn(nb * max_pages, P, r_kv + d_r, generator=gen, device="cuda")
+    w_uk, w_uv = (torch.randn(g, r_kv, d, generator=gen, device="cuda") for _ in range(2))
+    d_lens = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    out = torch.full((nb * max_pages, P * (2 * g * d + d_r)), float("nan"), device="cuda")
+    shape = B.make_shape(nb, g, g, d, r_kv, d_r, 1, B.GQLA_F32)
+    print("expand f32", lens, flush=True)
+    B.gqla_expand_cache(shape, B.make_cache(pool, d_lens, None, P, max_pages, nb * max_pages), w_uk, w_uv, 0, g,
+                        B.make_cache(out, d_lens, None, P, max_pages, nb * max_pages, g))
+    torch.cuda.synchronize()
+    n = g * P * d
+    keys = out[:, :n].reshape(-1, g, P, 8).transpose(1, 2).reshape(nb, max_pages * P, g * d)
+    vals = out[:, n:2 * n].reshape(-1, g, P // 8, d, 8).permute(0, 2, 4, 1, 3).reshape(nb, max_pages * P, g * d)
+    rope = out[:, 2 * n:].reshape(nb, max_pages * P, d_r)
+    rows = pool.reshape(nb, max_pages * P, r_kv + d_r)
+    for b, L in enumerate(lens):
+        c = rows[b, :L, :r_kv].double()
+        for got, w in ((keys, w_uk), (vals, w_uv)):
+            ref = c @ w.double().permute(1, 0, 2).reshape(r_kv, g * d)
+            assert float((got[b, :L].double() - ref).norm() / ref.norm()) < 1e-6      # fp32 sums of 16 products
+            assert bool(got[b, L:].isnan().all())
+        assert torch.equal(rope[b, :L], rows[b, :L, r_kv:]) and bool(rope[b, L:].isnan().all())

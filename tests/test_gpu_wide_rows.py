@@ -19,18 +19,19 @@ def _switch(op, nb, max_pages):
         table[b, :n] = torch.arange(at, at + n, dtype=torch.int32)
         at += n
     d_table, d_lens = table.cuda(), torch.tensor(lens, dtype=torch.int32, device="cuda")
-    shape = B.make_shape(nb, G, G, D, R_KV, D_R, 1, B.GQLA_BF16)
+    f32 = op == "expand_f32"
+    shape = B.make_shape(nb, G, G, D, R_KV, D_R, 1, B.GQLA_F32 if f32 else B.GQLA_BF16)
 
     def values(*size):
-        return torch.randn(*size, generator=gen, device="cuda").bfloat16()
+        return torch.randn(*size, generator=gen, device="cuda").to(torch.float32 if f32 else torch.bfloat16)
 
     def cache(pool, groups=0):
         return B.make_cache(pool, d_lens, d_table, P, max_pages, num_pages, groups)
     latent, keys = values(num_pages, P * (R_KV + D_R)), values(num_pages, P * (2 * G * D + D_R))
     w_uk, w_uv, w_inv = values(G, R_KV, D), values(G, R_KV, D), values(R_KV, G * D)
-    ws = torch.empty(B.gqla_expand_workspace_bytes(shape, G), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(max(16, B.gqla_expand_workspace_bytes(shape, G)), dtype=torch.uint8, device="cuda")
     print(op, nb, max_pages, flush=True)
-    if op == "expand":
+    if op in ("expand", "expand_f32"):
         out = torch.zeros_like(keys)
         B.gqla_expand_cache(shape, cache(latent), w_uk, w_uv, 0, G, cache(out, G), ws)
     elif op == "expand_fp8":
@@ -44,7 +45,7 @@ def _switch(op, nb, max_pages):
 
 
 # (a grid over what two such rows hold, or one of the compression, would not fit a launch)
-@pytest.mark.parametrize("op,nb", [("expand", 1), ("expand_fp8", 1), ("expand", 2), ("expand_fp8", 2), ("compress", 1), ("compress", 2)])
+@pytest.mark.parametrize("op,nb", [("expand", 1), ("expand_fp8", 1), ("expand", 2), ("expand_fp8", 2), ("compress", 1), ("compress", 2), ("expand_f32", 1)])
 def test_row_of_two_to_the_31_tokens(op, nb):
     narrow = _switch(op, nb, 2)
     assert int((narrow != 0).sum()) > 0

@@ -430,26 +430,33 @@ hipError_t launch_absorb_query_f32(const AbsorbQueryArgs& a, hipStream_t s) {
   absorb_query_f32_kernel<<<dim3(a.h_q, a.rows), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
-// One chunk per sequence: the decode writes the output itself, the combine of one partial (2 to 5 us) falls away.
-bool f32_decode_is_final(const DecodeArgs& a) { return a.n_chunks == a.B; }
+// One chunk per sequence: the decode writes the output itself, the combine of one partial (2 to 5 us) falls away.  Not where
+// the caller has laid the output over the queries: other workgroups still read those then.
+static bool f32_decode_is_final(const DecodeArgs& a, const CombineArgs& c, int dk) {
+  auto apart = [](const void* x, size_t nx, const void* y, size_t ny) { return (const char*)x + nx <= (const char*)y || (const char*)y + ny <= (const char*)x; };
+  const size_t rows = (size_t)a.B * a.M, out = rows * c.d_h * sizeof(float), lse = rows * sizeof(float);
+  const size_t q_a = rows * dk * sizeof(float), q_r = rows * a.d_r * sizeof(float);
+  return a.n_chunks == a.B && apart(c.out, out, a.q_a, q_a) && apart(c.out, out, a.q_r, q_r) &&
+         (!c.lse || (apart(c.lse, lse, a.q_a, q_a) && apart(c.lse, lse, a.q_r, q_r)));
+}
 hipError_t launch_decode_gqa_f32(const DecodeArgs& a, const CombineArgs& c, hipStream_t s) {
-  if (f32_decode_is_final(a)) decode_f32_kernel<false, true><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
+  if (f32_decode_is_final(a, c, a.d_h)) decode_f32_kernel<false, true><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
   else decode_f32_kernel<false, false><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
   return hipGetLastError();
 }
 hipError_t launch_decode_absorb_f32(const DecodeArgs& a, const CombineArgs& c, hipStream_t s) {
-  if (f32_decode_is_final(a)) decode_f32_kernel<true, true><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
+  if (f32_decode_is_final(a, c, a.r_kv)) decode_f32_kernel<true, true><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
   else decode_f32_kernel<true, false><<<dim3(a.n_chunks, a.M), kThreads, 0, s>>>(a, c);
   return hipGetLastError();
 }
-hipError_t launch_combine_f32(const CombineArgs& a, hipStream_t s) {
-  if (a.n_chunks == a.B) return hipSuccess;  // the decode has written the output
+hipError_t launch_combine_f32(const DecodeArgs& d, const CombineArgs& a, hipStream_t s) {
+  if (f32_decode_is_final(d, a, d.d_h)) return hipSuccess;  // the decode has written the output
   const unsigned blocks = (unsigned)(((int64_t)a.B * a.M + 7) / 8);
   combine_kernel<<<blocks, 256, 0, s>>>(a);
   return hipGetLastError();
 }
-hipError_t launch_combine_project_f32(const CombineArgs& a, hipStream_t s) {
-  if (a.n_chunks == a.B) return hipSuccess;  // the decode has written the output
+hipError_t launch_combine_project_f32(const DecodeArgs& d, const CombineArgs& a, hipStream_t s) {
+  if (f32_decode_is_final(d, a, d.r_kv)) return hipSuccess;  // the decode has written the output
   combine_project_f32_kernel<<<dim3(a.M, a.B), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }

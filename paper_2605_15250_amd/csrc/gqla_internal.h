@@ -119,13 +119,13 @@ struct WsLayout {
 // Kernel launchers (each returns the hipError_t of its launch).
 hipError_t launch_absorb_query_f32(const AbsorbQueryArgs&, hipStream_t);
 hipError_t launch_absorb_query_bf16(const AbsorbQueryArgs&, hipStream_t);
-hipError_t launch_decode_gqa_f32(const DecodeArgs&, const CombineArgs&, hipStream_t);     // with one chunk per sequence it writes the output, and
+hipError_t launch_decode_gqa_f32(const DecodeArgs&, const CombineArgs&, hipStream_t);     // with one chunk per sequence (and output and queries apart) it
 hipError_t launch_decode_gqa_bf16(const DecodeArgs&, hipStream_t);
-hipError_t launch_decode_absorb_f32(const DecodeArgs&, const CombineArgs&, hipStream_t);  // the fp32 combine launchers enqueue nothing
+hipError_t launch_decode_absorb_f32(const DecodeArgs&, const CombineArgs&, hipStream_t);  // writes the output, and the fp32 combine launchers enqueue nothing
 hipError_t launch_decode_absorb_bf16(const DecodeArgs&, hipStream_t);
-hipError_t launch_combine_f32(const CombineArgs&, hipStream_t);                          // fp32 partials in d_h space, [chunks][M][d_v]
+hipError_t launch_combine_f32(const DecodeArgs&, const CombineArgs&, hipStream_t);       // fp32 partials in d_h space, [chunks][M][d_v]
 hipError_t launch_combine_gqa_bf16(const CombineArgs&, hipStream_t);                     // fp32 partials in d_h space, vector order (part_vec_index), bf16 out
-hipError_t launch_combine_project_f32(const CombineArgs&, hipStream_t);                  // fp32 latent partials, fp32 out
+hipError_t launch_combine_project_f32(const DecodeArgs&, const CombineArgs&, hipStream_t);  // fp32 latent partials, fp32 out
 hipError_t launch_combine_project_bf16(const CombineArgs&, hipStream_t);                 // bf16 latent partials, bf16 out
 hipError_t launch_expand_f32(const ExpandArgs&, hipStream_t);
 hipError_t launch_expand_bf16(const ExpandArgs&, void* ws /* packed weights, 2*group_count*r_kv*d_h bf16 */, hipStream_t);

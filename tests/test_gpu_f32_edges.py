@@ -59,3 +59,43 @@ def test_f32_expansion_of_more_eights_than_workgroups(lens):
             assert float((got[b, :L].double() - ref).norm() / ref.norm()) < 1e-6      # fp32 sums of 16 products
             assert bool(got[b, L:].isnan().all())
         assert torch.equal(rope[b, :L], rows[b, :L, r_kv:]) and bool(rope[b, L:].isnan().all())
+
+
+@pytest.mark.parametrize("path", ["absorb", "gqa"])
+@pytest.mark.parametrize("cp", [0, 1])
+def test_f32_output_laid_over_the_queries(path, cp):
+    """The output may lie where the queries were (value dims other than the queries' make rows meet those of other heads and
+    sequences), with one chunk per sequence and with several: the values of a call with an output of its own."""
+    from paper_2605_15250_amd import binding as B
+    g, h_q, d_h, d_v, r_kv, d_r, P, lens = 2, 32, 64, 16, 64, 8, 16, [100, 40, 77] * 20
+    nb, max_pages = len(lens), 7
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    absorb = path == "absorb"
+    width = r_kv + d_r if absorb else g * (d_h + d_v) + d_r
+    pool = torch.randn(nb * max_pages, P * width, generator=gen, device="cuda")
+    q = torch.randn(nb, h_q, r_kv if absorb else d_h, generator=gen, device="cuda")
+    q_r = torch.randn(nb, h_q, d_r, generator=gen, device="cuda")
+    w_uv = torch.randn(g, r_kv, d_v, generator=gen, device="cuda")
+    d_lens = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    shape = B.make_shape(nb, h_q, g, d_h, r_kv, d_r, 1, B.GQLA_F32, 0.0, d_v)
+    cache = B.make_cache(pool, d_lens, None, P, max_pages, nb * max_pages, 0 if absorb else g)
+    plan = B.gqla_plan_create(shape, lens, P, 256, B.GQLA_PATH_ABSORB if absorb else B.GQLA_PATH_GQA, cp or max_pages)
+    assert (B.gqla_plan_num_chunks(plan) == nb) == (cp == 0)
+    ws = torch.empty(B.gqla_plan_workspace_bytes(plan), dtype=torch.uint8, device="cuda")
+    B.gqla_plan_upload(plan, ws)
+
+    def decode(out, lse):
+        print(path, cp, flush=True)
+        if absorb:
+            B.gqla_decode_absorb(shape, plan, q, q_r, cache, w_uv, out, lse, ws)
+        else:
+            B.gqla_decode_gqa(shape, plan, q, q_r, cache, out, lse, ws)
+        torch.cuda.synchronize()
+        return out.clone(), lse.clone()
+    n = nb * h_q
+    apart = decode(torch.empty(nb, h_q, d_v, device="cuda"), torch.empty(nb, h_q, device="cuda"))
+    over = decode(q.view(-1)[:n * d_v].view(nb, h_q, d_v), q_r.view(-1)[:n].view(nb, h_q))
+    B.gqla_plan_destroy(plan)
+    # (a merge of one partial rounds its weight of 1 through an exponential and a logarithm: 2^-22)
+    assert float((apart[0] - over[0]).abs().max()) <= 1e-6 * float(apart[0].abs().max())
+    assert float((apart[1] - over[1]).abs().max()) <= 1e-5

@@ -370,17 +370,19 @@ gqla_status gqla_estimate_paths(const gqla_shape* shape, int64_t cached_tokens, 
                                 double mfma_flops_per_s, gqla_path_estimate* out);
 
 /* The same choice for THIS library's kernels on the MI355X (GQLA_BF16 only; GQLA_ERR_DTYPE otherwise): the paper's
- * two-roof form with the rates the kernels sustain instead of the chip's peaks and a fixed cost per call, and, for
- * the absorb path, the critical path of one workgroup when the batch is too small to fill the chip.  All constants are
- * measurements of this build (the operating-point, batch-sweep and all-config tables under profiles/):
- *   absorb (query absorption + decode):  24 us + max(bytes / 5.5 TB/s, flops / 1.09 PFLOP/s, rounds * (per + 4) * page)
- *          where the split-plan rule of gqla_plan_create, applied to `batch` sequences of cached_tokens / batch tokens
- *          on 64-token pages and 256 compute units, gives every workgroup `rounds` chunks of `per` pages, and a page
- *          costs a workgroup 3.8 us (1.6 us when h_q s_q <= 32; 2.6 us when 8 * ceil(chunks / 8) * ceil(h_q s_q / 32) <= 256,
- *          where the launch gives every 32 rows their own workgroup; else 3.0 us when h_q s_q <= 64)
- *   gqa    (decode on the expanded cache): 26 us + min(f bytes, 200 MB) / 10 TB/s + max(0, f bytes - 200 MB) / 7.0 TB/s,
- *          f = 1 + 0.05 * (ceil(G s_q / 32) - 1): a cache of up to 200 MB is still in the chip's last-level cache from
- *          the step before; a group with 64 query rows costs a few percent more per byte (a wave takes both row blocks)
+ * two-roof form with the rates the kernels sustain instead of the chip's peaks, a fixed cost per call, the critical path
+ * of one workgroup when the batch is too small to fill the chip, and the chunk partials, written and read once.  The
+ * split-plan rule of gqla_plan_create, applied to `batch` sequences of cached_tokens / batch tokens on 64-token pages and
+ * 256 compute units, gives the chunks, the pages of one and the rounds they run in.  All constants are measurements of
+ * this build (the operating-point, batch-sweep and all-config tables under profiles/, and path_sweep there, over B = 1 to 128,
+ * 512 to 32768 tokens and five head layouts, of whose points the absorb time is within 12 % and the GQA time within 18 %):
+ *   absorb (query absorption + decode):  15.3 us + max(bytes / 6.2 TB/s, flops / 1.08 PFLOP/s, rounds * pages * page)
+ *          + 2 * partials / 4.7 TB/s, page = 1.9 us when h_q s_q <= 32; 2.05 us when 8 * ceil(chunks / 8) * ceil(h_q s_q / 32) <= 256,
+ *          where the launch gives every 32 rows their own workgroup; else 3.8 us when h_q s_q <= 64, 3.55 us beyond;
+ *          partials = chunks * 32 ceil(h_q s_q / 32) * r_kv * 2 bytes
+ *   gqa    (decode on the expanded cache): 8.5 us + max(bytes / 6.9 TB/s, rounds * pages * page) + 2 * partials / 3.9 TB/s,
+ *          page = 5.5 us when G s_q > 32 (a wave then takes two row blocks); else 0.65 us when g = 1 (eight waves share a
+ *          chunk), 2.15 us otherwise;  partials = chunks * 32 ceil(h_q s_q / 32) * d_v * 4 bytes
  * with bytes and flops as in gqla_estimate_paths.  faster_path is the path with the smaller time (absorb on a tie). */
 typedef struct {
   double absorb_seconds, gqa_seconds;

@@ -103,6 +103,9 @@ int32_t plan_slots(const gqla_shape& s, int32_t num_cus, int32_t path) {
 // On the absorb path a page costs 53 instead of 80 when the launch gives every 32 query rows a workgroup of their own
 // (at most 32 rows per sequence, or so few chunks that all those workgroups run at once).  On the GQA path with a token
 // team a page costs the workgroup an eighth (10), and the fixed cost counts eight times as many pages (16).
+// (The weights were fitted before the eight-wave absorb kernel, the token teams of several groups and the sliced merges; for
+// those a chunk's fixed cost and the merge are cheaper than they say: one sequence of 8192 tokens x 128 rows is cut into 22
+// chunks where 64 workgroups' worth would run at once.)
 int32_t choose_chunk_pages(const std::vector<int32_t>& npages, const gqla_shape& s, int32_t num_cus, int32_t path) {
   int32_t max_np = 1;
   for (int32_t v : npages) max_np = std::max(max_np, v);
@@ -125,6 +128,21 @@ int32_t choose_chunk_pages(const std::vector<int32_t>& npages, const gqla_shape&
     }
   }
   return cp;
+}
+
+// What the split rule makes of `batch` equal sequences on 64-token pages and 256 compute units (batch, cached_tokens > 0).
+struct SplitEstimate {
+  int64_t chunks = 0, pages = 0, rounds = 0;  // chunks, pages of one, rounds of chunks on the device
+};
+SplitEstimate estimate_split(const gqla_shape& s, int64_t cached_tokens, int32_t path) {
+  const int64_t np = ceil_div(ceil_div(cached_tokens, s.batch), 64);
+  const int64_t cp = choose_chunk_pages(std::vector<int32_t>((size_t)s.batch, (int32_t)np), s, 256, path);
+  SplitEstimate r;
+  const int64_t per_seq = ceil_div(np, cp);
+  r.pages = ceil_div(np, per_seq);
+  r.chunks = s.batch * per_seq;
+  r.rounds = ceil_div(r.chunks, plan_slots(s, 256, path));
+  return r;
 }
 
 WsLayout make_layout(const gqla_plan& p) {
@@ -913,29 +931,18 @@ gqla_status gqla_select_path(const gqla_shape* shape, int64_t cached_tokens, gql
   gqla_path_estimate e;
   st = gqla_estimate_paths(shape, cached_tokens, 1.0, 1.0, &e);  // only its byte and FLOP counts are used
   if (st != GQLA_OK) return st;
-  const double row_blocks = (double)(((shape->h_q / shape->g) * shape->s_q + 31) / 32);
-  // absorb, throughput form: the rates the kernel sustains when every compute unit has a long chunk
-  double ta = 24e-6 + std::max(e.absorb_bytes / 5.5e12, e.absorb_flops / 1.09e15);
-  // absorb, critical path of one workgroup: the split plan of `batch` equal sequences on 64-token pages and 256 compute
-  // units gives every workgroup `rounds` chunks of `per` pages; a page costs a workgroup 3.8 us (128 rows, one wave
-  // per 32 rows), 3.0 us with 64 rows (two of the four waves have rows), 2.6 us when the chunks are so few that the
-  // launch gives every 32 rows a workgroup of their own, and 1.6 us when a sequence has at most 32 rows; a chunk's
-  // fixed cost is that of 4 pages.
-  if (shape->batch > 0 && cached_tokens > 0) {
-    const int64_t np = ceil_div(ceil_div(cached_tokens, shape->batch), 64);
-    const int64_t slots = plan_slots(*shape, 256, GQLA_PATH_ABSORB);
-    const int64_t cp = choose_chunk_pages(std::vector<int32_t>((size_t)shape->batch, (int32_t)np), *shape, 256, GQLA_PATH_ABSORB);
-    const int64_t per_seq = ceil_div(np, cp), per = ceil_div(np, per_seq), chunks = shape->batch * per_seq;
-    const int64_t M = (int64_t)shape->h_q * shape->s_q;
-    const double page_s = M <= 32 ? 1.6e-6 : (ceil_div(chunks, 8) * 8 * ceil_div(M, 32) <= 256 ? 2.6e-6 : (M <= 64 ? 3.0e-6 : 3.8e-6));
-    ta = std::max(ta, 24e-6 + (double)(ceil_div(chunks, slots) * (per + 4)) * page_s);
-  }
-  out->absorb_seconds = ta;
-  // GQA: a fixed cost plus the cache bytes at the rate the kernel streams them -- 7.0 TB/s from HBM; a cache of up to
-  // 200 MB is still in the chip's last-level cache from the previous step and streams at about 10 TB/s.  (A group with
-  // 64 query rows costs a few percent more per byte than one with 32: a wave then takes both row blocks.)
-  const double gqa_bytes = (1.0 + 0.05 * (row_blocks - 1.0)) * e.gqa_bytes;
-  out->gqa_seconds = 26e-6 + std::min(gqa_bytes, 200e6) / 10e12 + std::max(0.0, gqa_bytes - 200e6) / 7.0e12;
+  // Fitted to 150 points (B = 1 to 128 sequences of 512 to 32768 tokens; 128 heads in 8 or 4 groups, 64 and 32 heads in 8, one
+  // rank's 16 heads in 1; one and two step tokens), measured twice: absorb within 12 % of every one, GQA within 18 %.
+  const int64_t M = (int64_t)shape->h_q * shape->s_q, rows = ceil_div(M, 32) * 32;
+  const bool any = shape->batch > 0 && cached_tokens > 0;
+  const SplitEstimate a = any ? estimate_split(*shape, cached_tokens, GQLA_PATH_ABSORB) : SplitEstimate{};
+  const SplitEstimate g = any ? estimate_split(*shape, cached_tokens, GQLA_PATH_GQA) : SplitEstimate{};
+  const double page_a = M <= 32 ? 1.9e-6 : (ceil_div(a.chunks, 8) * 8 * ceil_div(M, 32) <= 256 ? 2.05e-6 : (M <= 64 ? 3.8e-6 : 3.55e-6));
+  out->absorb_seconds = 15.3e-6 + std::max(std::max(e.absorb_bytes / 6.2e12, e.absorb_flops / 1.08e15), (double)(a.rounds * a.pages) * page_a) +
+                        2.0 * (double)(a.chunks * rows * shape->r_kv * 2) / 4.7e12;
+  const double page_g = (int64_t)(shape->h_q / shape->g) * shape->s_q > 32 ? 5.5e-6 : (shape->g == 1 ? 0.65e-6 : 2.15e-6);
+  out->gqa_seconds = 8.5e-6 + std::max(e.gqa_bytes / 6.9e12, (double)(g.rounds * g.pages) * page_g) +
+                     2.0 * (double)(g.chunks * rows * value_dim(shape) * 4) / 3.9e12;
   out->faster_path = out->gqa_seconds < out->absorb_seconds ? GQLA_PATH_GQA : GQLA_PATH_ABSORB;
   return GQLA_OK;
 }

@@ -272,21 +272,28 @@ def test_path_estimate_matches_the_papers_model():
 
 def test_calibrated_path_choice_matches_the_measured_operating_points():
     """gqla_select_path against the committed measurements (profiles/operating_points_bench.txt,
-    profiles/batch_sweep_bench.txt and profiles/all_configs_bench.txt: microseconds of absorb_query + decode_absorb and
+    profiles/batch_sweep_bench.txt, profiles/all_configs_bench.txt, profiles/path_sweep.txt: us of absorb_query + decode_absorb and
     of decode_gqa on one MI355X): predicted times within 25 % of every measured row, and the measured faster path
     wherever the two paths are more than 12 % apart (the model is good to about that per path)."""
     measured = [  # B, h_q, g, s_q, cached tokens, absorb us, gqa us
-        (1, 128, 8, 1, 8192, 46.0, 33.7), (1, 128, 8, 2, 8192, 51.4, 37.7), (1, 128, 4, 1, 8192, 46.6, 25.7),
-        (1, 128, 4, 2, 8192, 50.1, 35.8), (64, 128, 8, 1, 524288, 165.1, 327.2), (64, 128, 8, 2, 524288, 292.4, 337.0),
-        (64, 128, 4, 1, 524288, 168.4, 189.0), (64, 128, 4, 2, 524288, 290.2, 190.7),
-        (64, 64, 8, 1, 524288, 134.2, 324.6), (64, 64, 8, 2, 524288, 165.1, 326.5),   # 64 heads
-        (32, 32, 8, 1, 131072, 46.1 + 7.5, 89.7),          # configs[1]; its absorb figure there is the decode call alone
-        (128, 128, 8, 2, 2234929, 1208.2 + 12.0, 1536.2),  # configs[4], same remark
+        (1, 128, 8, 1, 8192, 27.0, 15.5), (1, 128, 8, 2, 8192, 31.2, 17.3), (1, 128, 4, 1, 8192, 27.2, 15.1),
+        (1, 128, 4, 2, 8192, 30.5, 26.6), (64, 128, 8, 1, 524288, 158.9, 327.8), (64, 128, 8, 2, 524288, 278.8, 332.1),
+        (64, 128, 4, 1, 524288, 159.3, 190.1), (64, 128, 4, 2, 524288, 279.5, 186.7),
+        (64, 64, 8, 1, 524288, 130.5, 323.3), (64, 64, 8, 2, 524288, 159.0, 327.0),   # 64 heads
+        (32, 32, 8, 1, 131072, 38.8 + 4.0, 89.3),          # 32 sequences of 4096; the absorb figure there is the decode call alone
+        (128, 128, 8, 2, 2234929, 1161.0 + 17.9, 1539.3),  # 128 ragged sequences, same remark
         # batch sweep, canonical shape, 8192 tokens per sequence
-        (2, 128, 8, 1, 16384, 51.7, 36.7), (4, 128, 8, 1, 32768, 55.1, 42.2), (8, 128, 8, 1, 65536, 57.3, 58.3),
-        (16, 128, 8, 1, 131072, 68.4, 94.8), (32, 128, 8, 1, 262144, 96.1, 171.7), (128, 128, 8, 1, 1048576, 310.0, 643.7),
-        (2, 128, 8, 2, 16384, 52.8, 41.6), (4, 128, 8, 2, 32768, 56.4, 46.0), (8, 128, 8, 2, 65536, 64.9, 62.8),
-        (16, 128, 8, 2, 131072, 91.5, 102.2), (32, 128, 8, 2, 262144, 153.1, 178.2), (128, 128, 8, 2, 1048576, 567.4, 644.7),
+        (2, 128, 8, 1, 16384, 31.0, 22.3), (4, 128, 8, 1, 32768, 36.5, 34.9), (8, 128, 8, 1, 65536, 42.1, 54.6),
+        (16, 128, 8, 1, 131072, 57.0, 93.5), (32, 128, 8, 1, 262144, 92.3, 173.0), (128, 128, 8, 1, 1048576, 299.7, 640.4),
+        (2, 128, 8, 2, 16384, 34.1, 26.0), (4, 128, 8, 2, 32768, 42.8, 39.6), (8, 128, 8, 2, 65536, 55.6, 61.7),
+        (16, 128, 8, 2, 131072, 85.8, 100.3), (32, 128, 8, 2, 262144, 145.1, 178.3), (128, 128, 8, 2, 1048576, 537.0, 647.5),
+        # other lengths, 32 heads, and one rank's 16 heads of one group
+        (1, 128, 8, 1, 512, 18.7, 12.2), (1, 128, 8, 1, 32768, 43.1, 36.2), (8, 128, 8, 1, 8192, 24.7, 18.7),
+        (32, 128, 8, 1, 32768, 40.1, 34.7), (128, 128, 8, 1, 131072, 70.7, 95.7), (1, 128, 4, 2, 512, 19.4, 15.6),
+        (8, 128, 4, 2, 8192, 28.7, 26.4), (128, 128, 4, 2, 131072, 106.2, 64.1), (4, 128, 4, 2, 32768, 44.9, 37.5),
+        (1, 32, 8, 1, 8192, 25.3, 13.9), (8, 32, 8, 1, 8192, 20.0, 13.2), (64, 32, 8, 1, 524288, 112.0, 329.4),
+        (1, 16, 1, 2, 8192, 25.4, 13.9), (8, 16, 1, 1, 65536, 31.3, 15.5), (64, 16, 1, 2, 524288, 116.5, 59.3),
+        (128, 16, 1, 1, 131072, 40.3, 19.5), (1, 16, 1, 1, 512, 17.5, 9.0),
     ]
     for Bn, h_q, g, s_q, tokens, t_a, t_g in measured:
         ch = B.gqla_select_path(B.make_shape(Bn, h_q, g, 128, 512, 64, s_q, B.GQLA_BF16), tokens)

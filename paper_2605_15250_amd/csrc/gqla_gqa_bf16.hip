@@ -555,12 +555,28 @@ static void gqa_launch_shape(const DecodeArgs& a, int max_wpb, int rows_per_wave
 // Few items (small batches, few groups): up to a workgroup's waves share each, as long as all of them run at once and a chunk
 // has a tile for each.  A chunk is a chain of tiles, two memory latencies each at its start; with the chip this empty nothing
 // else hides them.
-// Measured (kernel): one sequence of 8192 tokens, 8 groups 24.7 -> 13.8 us, 2 x 8192 tokens, 4 groups 18.2 -> 14.4 us, 4 ragged
-// sequences at (192, 256) 21.1 -> 16.4 us, 2 x 3000 tokens of 8-bit codes 13.3 -> 9.2 us; 500 tokens 10.7 -> 10.2 us.
+// Measured (call, before -> with teams): one sequence of 1000 tokens, 8 groups 17.3 -> 11.7 us; 4 x 1000 at (192, 256) 22.5 ->
+// 13.4 us; 500 tokens, 8 groups 13.9 -> 11.4 us.
+// Two or four groups of 128 dims are workgroups of two or four waves without teams, which share k_R and spread over the
+// chip by themselves; a team has to win more than that.  So with two groups chunks of one page stay with one wave (8 x 300 tokens
+// 11.4 us without, 11.9 with), and both use teams in half of the chip only (32 x 2048 tokens, 2 groups: 27.2 us without, 29.6 with
+// teams of two that fill it; 16 x 2048, 4 groups: 29.3 and 29.9; 4 x 250, 4 groups, a quarter: 11.5 and 8.8).
 static int gqa_token_team_size(const DecodeArgs& a, int n_items, int waves) {
+  const bool by_itself = waves == 8 && (a.g == 2 || a.g == 4);
+  if (by_itself && a.chunk_tiles < 8 / a.g) return 1;
+  const int64_t slots = (int64_t)a.num_cus * waves / (by_itself ? 2 : 1);
   int tt = 1;
-  while (2 * tt <= waves && (int64_t)n_items * (2 * tt) <= (int64_t)a.num_cus * waves && 2 * tt <= a.chunk_tiles) tt *= 2;
+  while (2 * tt <= waves && (int64_t)n_items * (2 * tt) <= slots && 2 * tt <= a.chunk_tiles) tt *= 2;
   return tt;
+}
+// Waves of a workgroup of teams: one team while that is no more workgroups than compute units.  A workgroup of eight waves holds
+// 133 KB for the merge and puts all its loads on one unit: one sequence of 250 tokens, 4 groups 11.8 us in two of them, 8.7 us
+// in 8 of two waves; 4 x 1000 tokens, 4 groups 13.9 -> 10.3 us.  With more workgroups than units the larger ones are better
+// (344 items in teams of four: 15 % faster as 172 of eight waves than as 344 of four).
+static int gqa_team_waves(const DecodeArgs& a, int n_items, int tt, int waves) {
+  int w = tt;
+  while (w < waves && ((int64_t)n_items * tt + w - 1) / w > a.num_cus) w *= 2;
+  return w;
 }
 template <int DV>
 constexpr int gqa_merge_bytes(int waves) { return waves * (DV / 32 * 4 * 64 * 16 + 2 * 32 * 4); }  // O^T, then m and l per (wave, row)
@@ -586,8 +602,9 @@ static hipError_t launch_decode_gqa_128(const DecodeArgs& a, float k_scale, floa
     static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, gqa_merge_bytes<128>(8));
     if (attr != hipSuccess) return attr;
-    decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true><<<(n_items * tt + 7) / 8, 512, gqa_merge_bytes<128>(8), s>>>(a, n_items, row_blocks, 0, tt,
-                                                                                                                  k_scale, v_scale);
+    const int w = gqa_team_waves(a, n_items, tt, 8);
+    decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true><<<(n_items * tt + w - 1) / w, 64 * w, gqa_merge_bytes<128>(w), s>>>(a, n_items, row_blocks, 0, tt,
+                                                                                                                         k_scale, v_scale);
     return hipGetLastError();
   }
   decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, false><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, k_scale, v_scale);
@@ -604,7 +621,8 @@ hipError_t launch_decode_gqa_bf16(const DecodeArgs& a, hipStream_t s) {
       static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, true>,
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, gqa_merge_bytes<256>(4));
       if (attr != hipSuccess) return attr;
-      decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, true><<<(n_items * tt + 3) / 4, 256, gqa_merge_bytes<256>(4), s>>>(a, n_items, row_blocks, 0, tt, 1.f, 1.f);
+      const int w = gqa_team_waves(a, n_items, tt, 4);
+      decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, true><<<(n_items * tt + w - 1) / w, 64 * w, gqa_merge_bytes<256>(w), s>>>(a, n_items, row_blocks, 0, tt, 1.f, 1.f);
       return hipGetLastError();
     }
     decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, false><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, 1.f, 1.f);

@@ -434,7 +434,7 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
 // the loads of a wave are 32 consecutive 16-byte vectors.  Chunks are merged kNB at a time (their loads in flight together)
 // with a running maximum, as in an online softmax; CS > 1: the CS slices of a row then meet in LDS.  The merged block
 // goes through LDS (32 rows, padded) and leaves as runs of whole vectors.
-// The three uses (see the launcher): many rows (VPT = DV / 32, CS = 1: a workgroup per block of rows); few rows (VPT = 1,
+// The three uses (see the launcher): many rows (VPT = DV / 32, CS = 1: a workgroup per block of rows); fewer (VPT = 1,
 // CS = 1: the dims are shared out as well); few rows with long chains of chunks (VPT = 2, CS = 8: the merge is bound by
 // the latency of its batches, one after the other -- 4 sequences x 40 rows x 256 dims with 24 to 117 chunks each: 32.4 us
 // in 8 workgroups with batches of four, 4.0 us this way).
@@ -638,8 +638,11 @@ hipError_t launch_decode_gqa_fp8(const DecodeArgs& a, float k_scale, float v_sca
 template <int DV>
 static hipError_t launch_combine_gqa_dv(const CombineArgs& a, hipStream_t s) {
   const unsigned blocks = (unsigned)(a.B * ((a.M + 31) / 32));
+  // Sliced chains only where nothing else fills the chip: with 128 blocks of rows, 16 chunks each and 256 dims the merge is bound
+  // by its 67 MB of partials; the whole call takes 58.5 us with slices (4096 workgroups), 51.3 us without (1024), 55.7 us with
+  // a workgroup per block.
   if (blocks >= 256) combine_gqa_bf16_kernel<DV, DV / 32, 1><<<blocks, 256, 0, s>>>(a);
-  else if (a.n_chunks <= 8 * a.B) combine_gqa_bf16_kernel<DV, 1, 1><<<dim3(blocks, DV / 32), 256, 0, s>>>(a);
+  else if (a.n_chunks <= 8 * a.B || blocks * (DV / 32) >= 256) combine_gqa_bf16_kernel<DV, 1, 1><<<dim3(blocks, DV / 32), 256, 0, s>>>(a);
   else combine_gqa_bf16_kernel<DV, 2, 8><<<dim3(blocks, DV / 8), 256, 0, s>>>(a);
   return hipGetLastError();
 }

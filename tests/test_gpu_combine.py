@@ -20,6 +20,8 @@ P = 64
     (64, 8, 1, [P * k + 3 for k in range(1, 30)]),      # mixed batches inside a block of rows
     (128, 8, 2, [70 + 40 * (k % 9) for k in range(40)]),  # 320 blocks of 32 rows: two per workgroup
     (128, 8, 1, [P * 4 + k for k in range(4)] * 16),    # 256 row blocks on the GQA path, four to five chunks each
+    (128, 8, 1, [P * 12 + k for k in range(4)] * 4),    # 64 row blocks, 12 to 13 chunks: long chains, but workgroups enough without slices
+    (128, 8, 1, [P * 12 + k for k in range(15)]),       # 60: slices
 ])
 def test_merge_of_one_page_chunks(h_q, g, s_q, lens):
     cfg = S.CONFIGS["C3"].with_(B=len(lens), h_q=h_q, g=g, s_q=s_q, L=0, paged=True, seed=91)

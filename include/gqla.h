@@ -375,14 +375,14 @@ gqla_status gqla_estimate_paths(const gqla_shape* shape, int64_t cached_tokens, 
  * split-plan rule of gqla_plan_create, applied to `batch` sequences of cached_tokens / batch tokens on 64-token pages and
  * 256 compute units, gives the chunks, the pages of one and the rounds they run in.  All constants are measurements of
  * this build (the operating-point, batch-sweep and all-config tables under profiles/, and path_sweep there, over B = 1 to 128,
- * 512 to 32768 tokens and five head layouts, of whose points the absorb time is within 12 % and the GQA time within 18 %):
+ * 512 to 32768 tokens and five head layouts, of whose points the absorb time is within 12 % and the GQA time within 16 %):
  *   absorb (query absorption + decode):  15.3 us + max(bytes / 6.2 TB/s, flops / 1.08 PFLOP/s, rounds * pages * page)
  *          + 2 * partials / 4.7 TB/s, page = 1.9 us when h_q s_q <= 32; 2.05 us when 8 * ceil(chunks / 8) * ceil(h_q s_q / 32) <= 256,
  *          where the launch gives every 32 rows their own workgroup; else 3.8 us when h_q s_q <= 64, 3.55 us beyond;
  *          partials = chunks * 32 ceil(h_q s_q / 32) * r_kv * 2 bytes
- *   gqa    (decode on the expanded cache): 8.5 us + max(bytes / 6.9 TB/s, rounds * pages * page) + 2 * partials / 3.9 TB/s,
- *          page = 5.5 us when G s_q > 32 (a wave then takes two row blocks); else 0.65 us when g = 1 (eight waves share a
- *          chunk), 2.15 us otherwise;  partials = chunks * 32 ceil(h_q s_q / 32) * d_v * 4 bytes
+ *   gqa    (decode on the expanded cache): 8.4 us + max(bytes / 6.75 TB/s, rounds * pages * page) + 2 * partials / 3.9 TB/s,
+ *          page = 5.9 us when G s_q > 32 (a wave then takes two row blocks); else 0.65 us when g = 1 (eight waves share a
+ *          chunk), 0.8 us otherwise;  partials = chunks * 32 ceil(h_q s_q / 32) * d_v * 4 bytes
  * with bytes and flops as in gqla_estimate_paths.  faster_path is the path with the smaller time (absorb on a tie). */
 typedef struct {
   double absorb_seconds, gqa_seconds;

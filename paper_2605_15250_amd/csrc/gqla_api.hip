@@ -932,7 +932,7 @@ gqla_status gqla_select_path(const gqla_shape* shape, int64_t cached_tokens, gql
   st = gqla_estimate_paths(shape, cached_tokens, 1.0, 1.0, &e);  // only its byte and FLOP counts are used
   if (st != GQLA_OK) return st;
   // Fitted to 150 points (B = 1 to 128 sequences of 512 to 32768 tokens; 128 heads in 8 or 4 groups, 64 and 32 heads in 8, one
-  // rank's 16 heads in 1; one and two step tokens), measured twice: absorb within 12 % of every one, GQA within 18 %.
+  // rank's 16 heads in 1; one and two step tokens), measured on two machines: absorb within 12 % of every one, GQA within 16 %.
   const int64_t M = (int64_t)shape->h_q * shape->s_q, rows = ceil_div(M, 32) * 32;
   const bool any = shape->batch > 0 && cached_tokens > 0;
   const SplitEstimate a = any ? estimate_split(*shape, cached_tokens, GQLA_PATH_ABSORB) : SplitEstimate{};
@@ -940,8 +940,8 @@ gqla_status gqla_select_path(const gqla_shape* shape, int64_t cached_tokens, gql
   const double page_a = M <= 32 ? 1.9e-6 : (ceil_div(a.chunks, 8) * 8 * ceil_div(M, 32) <= 256 ? 2.05e-6 : (M <= 64 ? 3.8e-6 : 3.55e-6));
   out->absorb_seconds = 15.3e-6 + std::max(std::max(e.absorb_bytes / 6.2e12, e.absorb_flops / 1.08e15), (double)(a.rounds * a.pages) * page_a) +
                         2.0 * (double)(a.chunks * rows * shape->r_kv * 2) / 4.7e12;
-  const double page_g = (int64_t)(shape->h_q / shape->g) * shape->s_q > 32 ? 5.5e-6 : (shape->g == 1 ? 0.65e-6 : 2.15e-6);
-  out->gqa_seconds = 8.5e-6 + std::max(e.gqa_bytes / 6.9e12, (double)(g.rounds * g.pages) * page_g) +
+  const double page_g = (int64_t)(shape->h_q / shape->g) * shape->s_q > 32 ? 5.9e-6 : (shape->g == 1 ? 0.65e-6 : 0.8e-6);
+  out->gqa_seconds = 8.4e-6 + std::max(e.gqa_bytes / 6.75e12, (double)(g.rounds * g.pages) * page_g) +
                      2.0 * (double)(g.chunks * rows * value_dim(shape) * 4) / 3.9e12;
   out->faster_path = out->gqa_seconds < out->absorb_seconds ? GQLA_PATH_GQA : GQLA_PATH_ABSORB;
   return GQLA_OK;

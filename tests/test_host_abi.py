@@ -276,24 +276,24 @@ def test_calibrated_path_choice_matches_the_measured_operating_points():
     of decode_gqa on one MI355X): predicted times within 25 % of every measured row, and the measured faster path
     wherever the two paths are more than 12 % apart (the model is good to about that per path)."""
     measured = [  # B, h_q, g, s_q, cached tokens, absorb us, gqa us
-        (1, 128, 8, 1, 8192, 27.0, 15.5), (1, 128, 8, 2, 8192, 31.2, 17.3), (1, 128, 4, 1, 8192, 27.2, 15.1),
-        (1, 128, 4, 2, 8192, 30.5, 26.6), (64, 128, 8, 1, 524288, 158.9, 327.8), (64, 128, 8, 2, 524288, 278.8, 332.1),
-        (64, 128, 4, 1, 524288, 159.3, 190.1), (64, 128, 4, 2, 524288, 279.5, 186.7),
-        (64, 64, 8, 1, 524288, 130.5, 323.3), (64, 64, 8, 2, 524288, 159.0, 327.0),   # 64 heads
-        (32, 32, 8, 1, 131072, 38.8 + 4.0, 89.3),          # 32 sequences of 4096; the absorb figure there is the decode call alone
-        (128, 128, 8, 2, 2234929, 1161.0 + 17.9, 1539.3),  # 128 ragged sequences, same remark
+        (1, 128, 8, 1, 8192, 27.0, 15.2), (1, 128, 8, 2, 8192, 31.1, 17.2), (1, 128, 4, 1, 8192, 26.9, 12.2),
+        (1, 128, 4, 2, 8192, 30.3, 26.8), (64, 128, 8, 1, 524288, 159.5, 330.7), (64, 128, 8, 2, 524288, 267.5, 333.3),
+        (64, 128, 4, 1, 524288, 163.8, 189.7), (64, 128, 4, 2, 524288, 270.7, 184.1),
+        (64, 64, 8, 1, 524288, 135.0, 323.4), (64, 64, 8, 2, 524288, 155.4, 326.7),   # 64 heads
+        (32, 32, 8, 1, 131072, 38.9 + 4.0, 87.8),          # 32 sequences of 4096; the absorb figure there is the decode call alone
+        (128, 128, 8, 2, 2234929, 1142.9 + 17.9, 1551.1),  # 128 ragged sequences, same remark
         # batch sweep, canonical shape, 8192 tokens per sequence
-        (2, 128, 8, 1, 16384, 31.0, 22.3), (4, 128, 8, 1, 32768, 36.5, 34.9), (8, 128, 8, 1, 65536, 42.1, 54.6),
-        (16, 128, 8, 1, 131072, 57.0, 93.5), (32, 128, 8, 1, 262144, 92.3, 173.0), (128, 128, 8, 1, 1048576, 299.7, 640.4),
-        (2, 128, 8, 2, 16384, 34.1, 26.0), (4, 128, 8, 2, 32768, 42.8, 39.6), (8, 128, 8, 2, 65536, 55.6, 61.7),
-        (16, 128, 8, 2, 131072, 85.8, 100.3), (32, 128, 8, 2, 262144, 145.1, 178.3), (128, 128, 8, 2, 1048576, 537.0, 647.5),
+        (2, 128, 8, 1, 16384, 30.8, 22.3), (4, 128, 8, 1, 32768, 35.4, 35.1), (8, 128, 8, 1, 65536, 43.4, 54.2),
+        (16, 128, 8, 1, 131072, 59.6, 93.3), (32, 128, 8, 1, 262144, 90.8, 171.0), (128, 128, 8, 1, 1048576, 303.7, 641.4),
+        (2, 128, 8, 2, 16384, 34.0, 25.7), (4, 128, 8, 2, 32768, 43.6, 39.5), (8, 128, 8, 2, 65536, 56.0, 62.3),
+        (16, 128, 8, 2, 131072, 85.3, 99.1), (32, 128, 8, 2, 262144, 150.9, 178.9), (128, 128, 8, 2, 1048576, 520.5, 648.6),
         # other lengths, 32 heads, and one rank's 16 heads of one group
-        (1, 128, 8, 1, 512, 18.7, 12.2), (1, 128, 8, 1, 32768, 43.1, 36.2), (8, 128, 8, 1, 8192, 24.7, 18.7),
-        (32, 128, 8, 1, 32768, 40.1, 34.7), (128, 128, 8, 1, 131072, 70.7, 95.7), (1, 128, 4, 2, 512, 19.4, 15.6),
-        (8, 128, 4, 2, 8192, 28.7, 26.4), (128, 128, 4, 2, 131072, 106.2, 64.1), (4, 128, 4, 2, 32768, 44.9, 37.5),
-        (1, 32, 8, 1, 8192, 25.3, 13.9), (8, 32, 8, 1, 8192, 20.0, 13.2), (64, 32, 8, 1, 524288, 112.0, 329.4),
-        (1, 16, 1, 2, 8192, 25.4, 13.9), (8, 16, 1, 1, 65536, 31.3, 15.5), (64, 16, 1, 2, 524288, 116.5, 59.3),
-        (128, 16, 1, 1, 131072, 40.3, 19.5), (1, 16, 1, 1, 512, 17.5, 9.0),
+        (1, 128, 8, 1, 512, 18.2, 9.6), (1, 128, 8, 1, 32768, 43.0, 36.1), (8, 128, 8, 1, 8192, 24.8, 18.6),
+        (32, 128, 8, 1, 32768, 39.9, 35.0), (128, 128, 8, 1, 131072, 69.2, 95.8), (1, 128, 4, 2, 512, 18.9, 15.5),
+        (8, 128, 4, 2, 8192, 28.8, 26.4), (128, 128, 4, 2, 131072, 106.2, 64.5), (4, 128, 4, 2, 32768, 44.8, 37.1),
+        (4, 128, 4, 1, 32768, 36.7, 25.6), (1, 32, 8, 1, 8192, 25.3, 13.8), (8, 32, 8, 1, 8192, 20.0, 13.2),
+        (64, 32, 8, 1, 524288, 113.6, 329.9), (1, 16, 1, 2, 8192, 25.4, 14.1), (8, 16, 1, 1, 65536, 30.9, 15.5),
+        (64, 16, 1, 2, 524288, 113.3, 59.1), (128, 16, 1, 1, 131072, 39.9, 19.8), (1, 16, 1, 1, 512, 17.9, 9.0),
     ]
     for Bn, h_q, g, s_q, tokens, t_a, t_g in measured:
         ch = B.gqla_select_path(B.make_shape(Bn, h_q, g, 128, 512, 64, s_q, B.GQLA_BF16), tokens)

@@ -293,7 +293,10 @@ __global__ void __launch_bounds__(kThreads) combine_project_f32_kernel(CombineAr
 // the four waves share out r_kv and join their sums through LDS, whence results leave as 16-byte vectors.
 // kTail: only the last a.tail positions of every sequence, from the same sums (the two calls give the same bits).
 // (Each element by itself, two loads a product and one workgroup a page: 14 us where this takes 4.9, over 64 tokens, r_kv = 32.)
-template <bool kTail>
+// kLoop: the grid may be smaller than the row, a workgroup takes every gridDim.x-th eight.  An instance of its own, since the
+// loop holds its state across the barriers: over those 64 tokens 5.1 us with it, 5.0 without, and 0.4 us of
+// the 24.6 that both decode paths and the switch take at that size.
+template <bool kTail, bool kLoop>
 __global__ void __launch_bounds__(kThreads) expand_f32_kernel(ExpandArgs a) {
   constexpr int kTok = 8, kRow = 72;  // kRow: 64 column vectors; padded so that the writes below spread over the banks
   __shared__ f32x4 c_s[512 * kTok / 4];             // [r][token]
@@ -304,7 +307,10 @@ __global__ void __launch_bounds__(kThreads) expand_f32_kernel(ExpandArgs a) {
     const int tok0 = (int)at;
     const int32_t pg_in = page_of(a.latent, b, tok0 / P);
     const int32_t pg_out = page_of(a.expanded, b, tok0 / P);
-    if (pg_in < 0 || pg_out < 0) continue;  // whole workgroup
+    if (pg_in < 0 || pg_out < 0) {  // whole workgroup
+      if (kLoop) continue;
+      return;
+    }
     const int slot0 = tok0 % P, first = max(from - tok0, 0), valid = min(kTok, L - tok0);  // tokens first .. valid - 1 are written
     const int W = a.r_kv + a.d_r, gc = a.group_count;
     const float* in = (const float*)a.latent.pool + ((int64_t)pg_in * P + slot0) * W;
@@ -327,7 +333,7 @@ __global__ void __launch_bounds__(kThreads) expand_f32_kernel(ExpandArgs a) {
       const int per = (is_v ? a.d_v : a.d_h) / 4, x = is_v ? cv - nk : cv;
       const f32x4* w = (const f32x4*)(is_v ? a.w_uv : a.w_uk) + (int64_t)(a.group_begin + x / per) * a.r_kv * per + x % per;
       f32x4 lo[4] = {}, hi[4] = {};  // [column]: tokens 0..3, 4..7
-  #pragma unroll 4
+#pragma unroll 4
       for (int r = wave; r < a.r_kv; r += kThreads / 64) {
         const f32x4 wv = w[(int64_t)r * per], c0 = c_s[r * 2], c1 = c_s[r * 2 + 1];
         for (int k = 0; k < 4; ++k)
@@ -363,6 +369,7 @@ __global__ void __launch_bounds__(kThreads) expand_f32_kernel(ExpandArgs a) {
         *(f32x4*)(out + ((int64_t)(jj * (a.d_h / 8) + d / 8) * P + slot0 + tok) * 8 + d % 8) = sum;
       }
     }
+    if (!kLoop) return;
   }
 }
 
@@ -419,7 +426,7 @@ hipError_t launch_compress_f32(const CompressArgs& a, hipStream_t s) {
 }
 hipError_t launch_expand_tail_f32(const ExpandArgs& a, hipStream_t s) {
   const int col_blocks = (a.group_count * (a.d_h + a.d_v) + 255) / 256;
-  expand_f32_kernel<true><<<dim3((a.tail + 6) / 8 + 1, a.B, col_blocks), kThreads, 0, s>>>(a);
+  expand_f32_kernel<true, false><<<dim3((a.tail + 6) / 8 + 1, a.B, col_blocks), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 hipError_t launch_append_latent(const AppendArgs& a, hipStream_t s) {
@@ -465,7 +472,8 @@ hipError_t launch_expand_f32(const ExpandArgs& a, hipStream_t s) {
   // What a row of the page table could hold bounds the tokens; beyond 8192 of them a workgroup takes every 1024th eight.  (With a
   // workgroup for each, rows of 131 072 tokens made 16 sequences x 4000 tokens, four column blocks take 231 us instead of 190.)
   const int eights = a.max_tokens / 8;
-  expand_f32_kernel<false><<<dim3(eights < 1024 ? eights : 1024, a.B, col_blocks), kThreads, 0, s>>>(a);
+  if (eights <= 1024) expand_f32_kernel<false, false><<<dim3(eights, a.B, col_blocks), kThreads, 0, s>>>(a);
+  else expand_f32_kernel<false, true><<<dim3(1024, a.B, col_blocks), kThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 

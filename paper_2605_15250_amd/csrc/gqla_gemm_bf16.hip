@@ -612,8 +612,8 @@ __global__ void __launch_bounds__(64 * WAVES) expand_tail_bf16_kernel(ExpandArgs
 // The results leave through LDS as whole rows (c_kv | k_R, 64 of them contiguous in the latent page).
 // Measured, 122 680 tokens in 32 ragged sequences, g d_h = 1024 (129 GFLOP, 409 MB): 246 us with registers -> LDS staging two
 // stages of 32 k ahead; 183 us with LDS-DMA and a ring of four such stages; 171 us with rotated starts; 138 us in this form
-// (whole lines, private rings, dense numbering of the tiles): 0.93 PFLOP/s, 3.0 TB/s.  MFMAs are in flight half of the time
-// a CU is busy; the rest is waiting for A^+ and keys (37 % of the wave cycles) and the start and end of a tile.
+// (whole lines, private rings, dense numbering of the tiles): 0.93 PFLOP/s, 3.0 TB/s.  The MFMA pipes are busy 46 % of the time;
+// the rest is waiting for A^+ and keys (20 % of the wave cycles), the start and end of a tile, and a clock below the nominal.
 constexpr int kCompressK = 64;                        // contraction elements per stage
 constexpr int kCompressTok = 128;                     // tokens per workgroup
 constexpr int kCompressUnits = 7;                     // ring of A^+ units per wave
@@ -914,9 +914,9 @@ static hipError_t launch_expand_one_shot(const ExpandArgs& a, void* ws, hipStrea
       hipFuncSetAttribute((const void*)expand_bf16_kernel<DH, DV, 512, 64, FP8>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
   // The lengths live on the device, so the kernel decides how the last round is shared out; whole rounds of 256, so that
-  // those shares find workgroups as well.  Measured: one sequence of 8192 tokens, 8 groups 81 us in 32 workgroups, 28 us in
-  // 256; 20 ragged sequences of 3000 to 6000 tokens into the 8-bit cache (355 blocks) 207 -> 183 us; 122 680 ragged tokens in
-  // 32 sequences 285 -> 240 us (holes in a grid over sequences gave some dies a third round of blocks).
+  // those shares find workgroups as well.  Measured against a grid over (blocks of the longest sequence, sequences), whose holes
+  // gave some dies a third round of blocks: one sequence of 8192 tokens, 8 groups 80 -> 31 us; 20 ragged sequences of 3000 to 6000
+  // tokens into the 8-bit cache 216 -> 190 us; 122 680 ragged tokens in 32 sequences 286 -> 240 us.
   const int64_t blocks = ((int64_t)a.max_tokens + 255) / 256 * a.B;
   const unsigned grid = (unsigned)std::min<int64_t>((blocks + 255) & ~(int64_t)255, kMaxWorkgroups);
   pack_weights_bf16_kernel<DH, DV, 512><<<dim3(a.group_count * NSUB, 512 / 64), 256, 0, s>>>(a, (__bf16*)ws);

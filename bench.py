@@ -13,8 +13,8 @@ cache switch gqla_expand_cache (Sec. 3.1: done once at deployment) is timed in t
 the library records around that kernel inside the timed steps, see gqla_time_next_decode_kernel); `rooflines` has both
 decode kernels and the expansion; the per-call times and the GQA kernel's come from passes of the same steps right
 behind the timed one (each event is a packet in the stream and would be charged to `value`).  Also in
-the line: the other workload shapes (configs[1] with rotating cache buffers so that it is not served from the
-last-level cache, configs[4] ragged and paged), both paths at the operating points of the paper's Sec. 4.2.3 table,
+the line: the other workload shapes (32 heads x 32 sequences with rotating cache buffers so that it is not served from the
+last-level cache, 128 ragged sequences, paged), both paths at the operating points of the paper's Sec. 4.2.3 table,
 the oracle's CPU rate on a bounded sample, and timings of the calls
 around the path (measured ceilings of the chip, the single-group slice, the 8-bit caches, the reverse cache switch, the
 rotary step and W^O, each path's whole decode step as one HIP graph, the absorb step with a value dim of its own)."""
@@ -54,7 +54,7 @@ def parse_args():
     ap.add_argument("--crossover", action="store_true",
                     help="also time both decode paths over B = 1 .. 128 (canonical shape, L = 8192, s_q = 1 and 2): where the faster path changes")
     ap.add_argument("--no-other-configs", action="store_true",
-                    help="skip the rows of the other workload shapes (configs[1] with rotating cache buffers, configs[4] ragged and "
+                    help="skip the rows of the other workload shapes (32 heads x 32 sequences with rotating cache buffers, 128 sequences, ragged and "
                          "paged; both decode paths and the expansion, five timed calls each, device-generated N(0,1) latents: "
                          "their parity is covered by tests/)")
     return ap.parse_args()
@@ -238,7 +238,7 @@ def main():
         measured = {"hbm_stream_read_GBs": nbytes / t_rd / 1e9, "mfma_bf16_TFLOPs": B.gqla_probe_mfma_flops(iters, num_cus) / t_mf / 1e12,
                     "how": "gqla_probe_stream_read over %.2f GB (16-byte loads, %d workgroups); gqla_probe_mfma_bf16: register-resident "
                            "32x32x16 bf16 MFMAs with random operand bits, %.0f ms sustained" % (nbytes / 1e9, 8 * num_cus, t_mf * 1e3)}
-        # single-group slice of the GQA leg (configs[3]): 16 heads, one group, 320 cached elements per token
+        # single-group slice of the GQA leg: 16 heads, one group, 320 cached elements per token
         G = cg.h_q // cg.g
         j0 = 3
         sl = Decoder(cg, Gq["lens"], Gq["table"], Gq["dec"].num_pages, groups=1, group_begin=j0, use_page_table=False)
@@ -257,7 +257,7 @@ def main():
                     "tokens_per_s": cg.B * cg.s_q / t_dec, "expand_cache_ms": t_ex * 1e3}
         sl.latent_pool = None
         sl.close()
-        # the per-step cache updates of the GQA leg (configs[3]): append the step's s_q rows of every sequence and
+        # the per-step cache updates of the GQA leg: append the step's s_q rows of every sequence and
         # expand just those positions -- what a serving step pays once the context has been expanded in one shot.
         # The rows written are the ones the cache already holds at those positions, so its content does not change.
         gd = Gq["dec"]
@@ -286,7 +286,7 @@ def main():
                   "rel_l2_vs_16bit_cache": float(torch.linalg.norm(out8.float() - d16) / torch.linalg.norm(d16))}
         gd.expanded_fp8_pool = None
         del out8
-        # the absorb leg (configs[1]) over an 8-bit latent cache (c_kv as E4M3 codes with one scale, k_R in 16 bits):
+        # the absorb leg (128 heads) over an 8-bit latent cache (c_kv as E4M3 codes with one scale, k_R in 16 bits):
         # 640 instead of 1152 bytes per token.  The scale 2^-6 keeps the standard-normal latent of this workload inside
         # the format's range.  Decode kernel timed by the library's events, as for the 16-bit cache.
         ad = A["dec"]
@@ -426,8 +426,8 @@ def main():
         dk.close()
         del dk, o_k, l_k, qh_k
 
-    # ---- the other workload shapes: configs[1] (LLaMA-3-8B-converted, h_q = 32) and configs[4] (ragged, paged, s_q = 2) ----
-    # Five timed calls each after a short steady warm-up.  configs[1]'s latent cache (151 MB) would fit the chip's 256 MB
+    # ---- the other workload shapes: LLaMA-3-8B-converted (h_q = 32) and 128 sequences (ragged, paged, s_q = 2) ----
+    # Five timed calls each after a short steady warm-up.  The first one's latent cache (151 MB) would fit the chip's 256 MB
     # last-level cache if the same buffer were decoded again and again, so four copies of it are decoded in rotation
     # (604 MB between two uses of a line); the other caches are larger than that cache to begin with.
     other = None

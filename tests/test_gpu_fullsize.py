@@ -142,7 +142,7 @@ def test_c1_llama3_shape_both_paths():
 
 
 def test_c2_c3_canonical_both_paths_with_mtp():
-    """configs[2] and configs[3] share shape and weights; the s_q = 2 configuration exercises both paths (row 1 of the
+    """The canonical absorb and GQA decodes share shape and weights; the s_q = 2 configuration exercises both paths (row 1 of the
     step is a plain s_q = 1 decode at length L, row 0 one at length L - 1)."""
     case = FullCase(S.CONFIGS["C3"])
     try:
@@ -152,7 +152,7 @@ def test_c2_c3_canonical_both_paths_with_mtp():
 
 
 def test_c3_step_updates_and_fp8_cache_at_full_size():
-    """configs[3] at full size: the per-step cache updates (append + tail expansion on top of a one-shot expansion of
+    """The canonical GQA decode at full size: the per-step cache updates (append + tail expansion on top of a one-shot expansion of
     the prefix) must reproduce the one-shot expansion of everything bit for bit, and the decode over the 8-bit cache
     (expand -> quantise on the GPU) is checked on sampled (sequence, group) slices against the oracle's chain."""
     from oracle import fp8_cache as F8
@@ -247,7 +247,7 @@ def test_c2_size_with_the_value_dim_of_the_mla_checkpoints():
 
 
 def test_c2_fp8_latent_at_full_size():
-    """configs[2] over the 8-bit latent cache (Sec. 2 / Sec. 5.1 (i): quantised caches; format of this build): the
+    """The canonical absorb decode over the 8-bit latent cache (Sec. 2 / Sec. 5.1 (i): quantised caches; format of this build): the
     quantising cache switch on the GPU holds the oracle's codes bit for bit on sampled sequences, and the decode is
     checked on sampled (sequence, group) slices against the oracle's MQA-absorb decode (Sec. 3.1) on the dequantised
     latent, consuming the q_hat bits the GPU consumes."""
@@ -327,7 +327,7 @@ def test_c4_ragged_paged_both_paths():
 
 
 def test_c3_compress_rope_and_output_projection_at_full_size():
-    """configs[3] at full size, the shapes bench.py times: the reverse cache switch over all 524288 tokens (sampled
+    """The canonical GQA decode at full size, the shapes bench.py times: the reverse cache switch over all 524288 tokens (sampled
     sequences against the oracle's compression of the oracle's expansion; every recovered latent finite and close to
     the original), the rotary step on all 64 x 2 x 129 vectors (sampled tokens), and W^O with d_model = 7168 on the
     128 rows (four whole rows and 2000 sampled elements against the oracle)."""

@@ -57,7 +57,7 @@ def test_rope_step_matches_the_oracle(key, lens, s_q, base):
     ("C1", 5, 2, 256, 32),      # 10 rows: one ragged row tile, 16 k-ranges
     ("C1", 70, 2, 128, 32),     # 140 rows: two row blocks, the second ragged
     ("C3", 3, 1, 384, 128),     # K = 16384
-    ("C1", 64, 1, 4096, 32),    # the bench shape of configs[1]
+    ("C1", 64, 1, 4096, 32),    # 32 heads x 32 sequences, as the bench times it
     ("C1", 40, 2, 384, 24),     # K = 3072: 36 workgroups, not a multiple of the eight dies they are dealt over
     ("C1", 150, 2, 256, 32),    # 300 rows: three row blocks, the last ragged
     ("C1", 20, 2, 4096, 40),    # K = 5120: seven k-ranges, the last one shorter

@@ -784,7 +784,10 @@ __device__ __forceinline__ void acc_scale_rb(int rb, float alpha) {
 //                  one workgroup barrier, then the first key fragments of tile i+1 are requested
 // The barrier is the only one of the tile: each wave waits for its share of tile i+1's staging before it arrives, so
 // passing it means "tile i+1 has landed for everyone", "the probabilities of tile i are visible" and "everyone is done
-// with tile i-1", whose buffer the staging of tile i+3 (issued in the next iteration's gaps) overwrites.
+// with tile i-1", whose buffer the staging of tile i+3 (issued in the next iteration's gaps) overwrites.  What must not stand
+// between the barrier and the next tile's first MFMA is pinned in front of it (the sum of the probabilities, 16 dependent
+// additions, and the addresses of the next staging: the compiler had moved both behind the barrier; kernel 134 -> 130 us at
+// 64 sequences x 8192 tokens x 128 rows).
 // The softmax state (reference maximum, denominator) of a row lives in the wave that owns its row block.  A move of the
 // reference maximum of rows that already have output (rare: the maximum must grow by more than 2^8) has to rescale
 // accumulators in all four waves: the owning wave announces it in the sign bit of its first probability (probabilities
@@ -914,9 +917,12 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
   // rows of a tile past the chunk end (or a whole tile behind an out-of-pool page id) hold whatever the page holds:
   // zeroed in LDS by the whole workgroup before anyone reads them, so that 0 * v stays 0
   auto zero_rows = [&](int slot, int valid) {
-    for (int idx = threadIdx.x; idx < (kTile - valid) * (W / 8); idx += 256) {
+    int tid = threadIdx.x, zero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zero), "+v"(tid));  // formed here: nothing of this rare path is kept in registers across the loop
+    const u32x4 zeros = {(uint32_t)zero, (uint32_t)zero, (uint32_t)zero, (uint32_t)zero};
+    for (int idx = tid; idx < (kTile - valid) * (W / 8); idx += 256) {
       const int r = valid + idx / (W / 8), c = idx % (W / 8);
-      *(u32x4*)(smem + slot * TILE_BYTES + (c >> 3) * PANEL + r * 128 + (c & 7) * 16) = u32x4{0u, 0u, 0u, 0u};
+      *(u32x4*)(smem + slot * TILE_BYTES + (c >> 3) * PANEL + r * 128 + (c & 7) * 16) = zeros;
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
     __syncthreads();
@@ -983,6 +989,8 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
         lk_slot = 0;
         ++lk_p;
       }
+      // (pinned here: the compiler would move all of it behind the tile's barrier, in front of the next tile's first MFMA)
+      asm volatile("" : "+s"(next_g), "+s"(st_slot), "+s"(lk_slot), "+s"(lk_p));
     };
 
     // ---------------- phase 1: S^T(it), staging of tile it+2, first operands of phase 2 ----------------
@@ -1019,6 +1027,8 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
         // the factors travel through the idle half of the exchange (no probabilities of tile it are written before the
         // second barrier below)
         float* al = (float*)exw;
+        int n = lane;  // (formed here, as in zero_rows)
+        asm volatile("v_and_b32 %0, 31, %0" : "+v"(n));
         if (announce_prev) al[wave * 32 + n] = alpha_prev;  // both half-waves hold the row's factor and write the same value
         __builtin_amdgcn_s_waitcnt(0xc07f);
         __syncthreads();
@@ -1090,6 +1100,7 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
         w1[q] = pack_bf16(s[8 + 2 * q], s[8 + 2 * q + 1]);
       } else if (g == 27) {
         l_run += psum;
+        asm volatile("" : "+v"(l_run));  // (added up here, not behind the barrier)
         if (announce) w0[0] |= 0x8000u;  // sign bit of the first probability
         *(u32x4*)(exw + (wave * 2 + 0) * 1024 + lane * 16) = w0;
       } else if (g == 28) {

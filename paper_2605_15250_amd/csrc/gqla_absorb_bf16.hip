@@ -1,4 +1,4 @@
-// MQA-absorb split-L decode over the latent cache, bf16 MFMA (paper Sec. 3.1, MQA-absorb equation, lines 2-5).
+// MQA-absorb split-L decode over the 16-bit or 8-bit latent cache, bf16 MFMA (paper Sec. 3.1, MQA-absorb equation, lines 2-5).
 //
 // One workgroup of 4 waves per (chunk, block of 128 query rows); wave w owns rows 32w..32w+31 of the block.
 // A 32-token latent tile [32][r_kv + d_r] is staged once into LDS (global_load_lds into a ring of four tile
@@ -747,6 +747,15 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
     a.part_lse[(int64_t)chunk * a.M + row] = l_tot > 0.f ? (m_o + fast_log2(l_tot)) * kLn2 : GQLA_NEG_INF;
 }
 
+// eight E4M3 codes as bf16 (exact)
+__device__ __forceinline__ bf16x8 widen_e4m3x8(uint32_t w0, uint32_t w1) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2v;
+  const bf16x2v p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false), p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true);
+  const bf16x2v p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false), p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true);
+  const u32x4 r = {__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1), __builtin_bit_cast(uint32_t, p2), __builtin_bit_cast(uint32_t, p3)};
+  return __builtin_bit_cast(bf16x8, r);
+}
+
 // every accumulator of row block rb (tiles 4*dtl + rb, dtl = 0..3) of this lane times alpha
 __device__ __forceinline__ void acc_scale_rb(int rb, float alpha) {
   float t0, t1;
@@ -793,24 +802,36 @@ __device__ __forceinline__ void acc_scale_rb(int rb, float alpha) {
 // accumulators in all four waves: the owning wave announces it in the sign bit of its first probability (probabilities
 // are never negative), all waves see the same bits, and together they take a slow path that passes the factors through
 // the idle half of the exchange.
-// Requires whole blocks of 128 rows (h_q s_q a multiple of 128; the launcher sends other row counts to the kernel above):
-// there is no branch per row block, and the register budget is exact -- the compiler must never run out of ordinary
+// FP8: the cache holds E4M3 codes of c_kv (one scale) and k_R in 16 bits (page format in the next section).  The same MFMAs on
+// the same bf16 operands: codes and k_R are staged as they are (20 KB a tile instead of 36) and widened in registers
+// (v_cvt_scalef32_pk_bf16_fp8, exact) -- the keys by every wave for itself, 128 conversions a tile, in the gaps of S^T; the
+// values once, by the wave that owns their dims, out of transposed 8-bit reads.  The scale enters the content part of the
+// logits (the RoPE part has accumulators of its own and is added in the softmax) and the chunk's output.  8-bit MFMAs on the
+// codes, with queries and probabilities split in two, would save the widening and take as long; they add 64 products in
+// about 15 bits below the largest (measured: 1.6e-5 of the logits' norm, 2.6e-8 with these), so they are not used.
+// Against one wave per 32 rows that widened a quarter of each tile on its way into a bf16 buffer (two buffers, softmax in the
+// open): 64 ragged sequences of 3000 to 12000 tokens x 128 rows 172 -> 146 us; 64 x 4096 x 64 rows 89 -> 84 us a step.
+// 16 bits: whole blocks of 128 rows (the launcher sends other row counts to the kernel above).  8 bits: any row count above
+// 32; rows beyond the last read that one's queries, see no token and store nothing.  There is no branch per row block, and
+// the register budget is exact -- the compiler must never run out of ordinary
 // registers here, or it would park values in accumulation registers, which hold O^T behind its back (the MFMA
 // statements name their accumulators as clobbered, and the build checks the generated code for both).
-template <int RKV, int DR>
-__global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeArgs a, int row_blocks) {
+template <int RKV, int DR, bool FP8>
+__global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeArgs a, int row_blocks, float c_scale) {
   constexpr int W = RKV + DR;
-  constexpr int ROWB = W * 2;
-  constexpr int NP = W / 64;
+  constexpr int CB = FP8 ? 1 : 2;              // bytes per element of c_kv
+  constexpr int NPC = RKV * CB / 128;          // panels of c_kv; k_R is one more
+  constexpr int NP = NPC + 1;
   constexpr int PANEL = kTile * 128;
   constexpr int KS = W / 16;
+  constexpr int KS_R = DR / 16;                // k-steps over the RoPE key
   constexpr int DT = RKV / 32;
-  constexpr int TILE_BYTES = kTile * ROWB;
+  constexpr int TILE_BYTES = NP * PANEL;
   constexpr int EX = kSlots * TILE_BYTES;  // exchange: [2 buffers][4 row blocks][2 k-steps][64 lanes][16 bytes]
   constexpr int KR = 4;                    // key fragments in flight (more do not fit the 256 ordinary registers)
   static_assert(DT == 16, "O^T fills the 256 accumulation registers exactly: 4 dim tiles x 4 row blocks per wave");
-  static_assert(W % 64 == 0 && RKV % 128 == 0, "latent row must be a whole number of 128-byte panels, two per wave");
-  static_assert(KS == 36 && NP == 9, "the gap schedule below is written for 36 key k-steps and 9 staging instructions");
+  static_assert(DR == 64 && RKV % 128 == 0, "latent row must be a whole number of 128-byte panels, one or two per wave and one of k_R");
+  static_assert(KS == 36 && NP <= 9, "the gap schedule below is written for 36 key k-steps and up to 9 staging instructions");
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   int chunk, rbk;
@@ -832,16 +853,24 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
   const ChunkEntry ce = a.chunks[chunk];
 
   const int row0 = rbk * kRowsPerBlock;
-  const int rho = row0 + wave * 32 + n;  // row = t * h_q + i (always a real row here)
+  const int rho = row0 + wave * 32 + n;  // row = t * h_q + i
+  const bool row_ok = !FP8 || rho < a.M;  // (16 bits: always a real row)
   const int t = rho / a.h_q;
-  const int vis_end = min(ce.tok_end, ce.L - a.s_q + t + 1);
+  const int vis_end = row_ok ? min(ce.tok_end, ce.L - a.s_q + t + 1) : 0;
   const int unmasked_end = min(ce.tok_end, ce.L - a.s_q + 1);
 
   const int P = a.cache.page_size;
   const char* pool = (const char*)a.cache.pool;
   const int32_t* table_row = a.cache.page_table ? a.cache.page_table + (int64_t)ce.b * a.cache.max_pages : nullptr;
   auto checked = [&](int32_t pg) -> int32_t { return ((uint32_t)pg < (uint32_t)a.cache.num_pages) ? pg : -1; };
-  auto tile_src = [&](int32_t pg, int slot) -> const char* { return pool + ((int64_t)(pg >= 0 ? pg : 0) * P + slot) * ROWB; };
+  // first row of a tile, and (8 bits, where k_R has a plane of its own behind the codes of the page) its first k_R row; an
+  // id outside the pool falls back to page 0
+  constexpr int ROWB = FP8 ? RKV : 2 * W;
+  const int64_t page_bytes = (int64_t)P * (RKV * CB + DR * 2);
+  auto tile_src = [&](int32_t pg, int slot) -> const char* { return pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + (int64_t)slot * ROWB; };
+  auto kr_src = [&](int32_t pg, int slot) -> const char* {
+    return FP8 ? pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + (int64_t)P * RKV + (int64_t)slot * (DR * 2) : nullptr;
+  };
 
   // per-lane LDS offsets inside a tile (panel layout of gqla_lds.h): key fragment of k-step ks = 4*a4 + b at
   // kbase[b] + a4*PANEL; transposed value reads at vbase + compile-time offsets (this wave's dims: panels 2w, 2w+1)
@@ -850,10 +879,29 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
 #pragma unroll
     for (int b = 0; b < 4; ++b) kbase[b] = n * 128 + (((2 * b + h) ^ lds_swz(n)) << 4);
     const int i16 = lane & 15, e = i16 >> 2, q = i16 & 3, g1 = (lane >> 4) & 1;
-    vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8;
-    vbase += wave * 2 * PANEL;
+    if constexpr (FP8) {
+      // Transposed 8-bit reads: 16 lanes address 8 tokens x 16 dims (lane 2 k + p: 8 bytes of token k) and each receives
+      // the 8 tokens of one dim.  Token k of k-step u is row 16 u + 8 (k / 4) + 4 h + k % 4, the order in which a lane of
+      // S^T holds them.  The second group of 16 lanes takes the dims two chunks further on (not one), so that a half-wave
+      // meets every bank once; dim tile d of this wave is chunks vchunk(d), vchunk(d) + 2 of panel `wave`.
+      const int k = i16 >> 1, row = 8 * (k >> 2) + 4 * h + (k & 3);
+      vbase = row * 128 + (((2 * g1) ^ lds_swz(row)) << 4) + (i16 & 1) * 8 + wave * PANEL;
+    } else {
+      vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8;
+      vbase += wave * 2 * PANEL;
+    }
   }
   const uint32_t stage_off = stage_lane_offset<kTile, NP, 4, ROWB>(wave, lane);
+  const uint32_t kr_off = FP8 ? stage_lane_offset<kTile, 1, 4, DR * 2>(wave, lane) : 0;
+  // request u (0 .. NP - 1) of this wave's share of a tile
+  auto stage_step = [&](char* dst, const char* src, const char* kr, int u) __attribute__((always_inline)) {
+    if (FP8 && u == NPC) stage_panels_step<kTile, 1, 4, DR * 2, true>(dst + NPC * PANEL, kr, wave, kr_off, 0);
+    else stage_panels_step<kTile, NP, 4, ROWB, true>(dst, src, wave, stage_off, u);
+  };
+  auto stage_tile = [&](int slot, int32_t pg, int row) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < NP; ++u) stage_step(smem + slot * TILE_BYTES, tile_src(pg, row), kr_src(pg, row), u);
+  };
 
   GQLA_STAMP(4);
   float m_ref = GQLA_NEG_INF, l_run = 0.f;
@@ -862,11 +910,15 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
   // workgroup waits for before its first MFMA; the page ids (a dependent scalar load) arrive in their shadow
   bf16x8 qf[KS];
   {
-    const int64_t qrow = (int64_t)ce.b * a.M + rho;
-    const __bf16* ph = (const __bf16*)a.q_a + qrow * RKV + h * 8;
+    const int64_t qrow = (int64_t)ce.b * a.M + (FP8 ? min(rho, a.M - 1) : rho);
+    const __bf16* ph = (const __bf16*)a.q_a + qrow * RKV + h * 8 * (FP8 ? 2 : 1);
     const __bf16* pr = (const __bf16*)a.q_r + qrow * DR + h * 8;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(ks < RKV / 16 ? ph + ks * 16 : pr + (ks - RKV / 16) * 16);
+    for (int ks = 0; ks < KS; ++ks) {
+      // 8 bits: a 16-byte vector of codes is a lane's share of two k-steps, dims 32 (ks / 2) + 16 h + 8 (ks % 2) + 0..7
+      const int dim = FP8 ? 32 * (ks >> 1) + 8 * (ks & 1) : 16 * ks;
+      qf[ks] = *(const bf16x8*)(ks < RKV / 16 ? ph + dim : pr + (ks - RKV / 16) * 16);
+    }
   }
 
   const int n_tiles = (ce.tok_end - ce.tok_begin + kTile - 1) / kTile;
@@ -894,7 +946,7 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
   }
   GQLA_STAMP(5);
   int32_t pg_raw = 0;
-  const char* next_g = pool;  // first row of the tile the next iteration stages (set when the window moves)
+  const char *next_g = pool, *next_kr = pool;  // first rows of the tile the next iteration stages (set when the window moves)
   const int p_first = ce.tok_begin / P;
   int st_slot = (3 * kTile) % P;                                     // slot of tile it+3 in its page
   int lk_slot = (4 * kTile) % P, lk_p = p_first + (4 * kTile) / P;   // tile it+4
@@ -905,23 +957,22 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
   // as fragments or staged through LDS in whole lines, and the same with the chunks of a sequence on one die -- it is
   // neither the shape of the loads nor their volume.  The queries go first (above), then tile 0; tiles 1 and 2 are
   // requested once those have landed, while tile 0 is being multiplied.
-  stage_panels_full<kTile, NP, 4, ROWB, true>(smem, tile_src(pg0, 0), wave, lane);
+  stage_tile(0, pg0, 0);
   acc_zero();  // 256 register writes, in the shadow of the requests above
   // The query loads complete here, before the loop (the compiler's wait for them also covers the request for tile 0
   // above); inside the loop only hand-counted waits remain.
 #pragma unroll
-  for (int k = 0; k < KS; k += 9)
-    asm volatile("" : "+v"(qf[k]), "+v"(qf[k + 1]), "+v"(qf[k + 2]), "+v"(qf[k + 3]), "+v"(qf[k + 4]), "+v"(qf[k + 5]),
-                      "+v"(qf[k + 6]), "+v"(qf[k + 7]), "+v"(qf[k + 8]));
+  for (int k = 0; k < KS; k += 4) asm volatile("" : "+v"(qf[k]), "+v"(qf[k + 1]), "+v"(qf[k + 2]), "+v"(qf[k + 3]));
 
   // rows of a tile past the chunk end (or a whole tile behind an out-of-pool page id) hold whatever the page holds:
   // zeroed in LDS by the whole workgroup before anyone reads them, so that 0 * v stays 0
   auto zero_rows = [&](int slot, int valid) {
+    constexpr int kChunks = NP * 8;
     int tid = threadIdx.x, zero;
     asm volatile("v_mov_b32 %0, 0" : "=v"(zero), "+v"(tid));  // formed here: nothing of this rare path is kept in registers across the loop
     const u32x4 zeros = {(uint32_t)zero, (uint32_t)zero, (uint32_t)zero, (uint32_t)zero};
-    for (int idx = tid; idx < (kTile - valid) * (W / 8); idx += 256) {
-      const int r = valid + idx / (W / 8), c = idx % (W / 8);
+    for (int idx = tid; idx < (kTile - valid) * kChunks; idx += 256) {
+      const int r = valid + idx / kChunks, c = idx % kChunks;
       *(u32x4*)(smem + slot * TILE_BYTES + (c >> 3) * PANEL + r * 128 + (c & 7) * 16) = zeros;
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
@@ -931,33 +982,61 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();  // the first tiles have landed for every wave
   GQLA_STAMP(7);
-  if (n_tiles > 1) stage_panels_full<kTile, NP, 4, ROWB, true>(smem + TILE_BYTES, tile_src(pg1, kTile % P), wave, lane);
-  if (n_tiles > 2) stage_panels_full<kTile, NP, 4, ROWB, true>(smem + 2 * TILE_BYTES, tile_src(pg2, (2 * kTile) % P), wave, lane);
+  if (n_tiles > 1) stage_tile(1, pg1, kTile % P);
+  if (n_tiles > 2) stage_tile(2, pg2, (2 * kTile) % P);
   {
     const int valid0 = pg0 >= 0 ? min(kTile, ce.tok_end - ce.tok_begin) : 0;
     if (valid0 < kTile) zero_rows(0, valid0);
   }
 
   // operands that live across the phases of the pipeline
-  bf16x8 kf[KR];        // key fragments, requested KR MFMAs ahead of their use
+  bf16x8 kf[KR];        // key fragments, requested KR MFMAs ahead of their use (8 bits: of k_R)
+  [[maybe_unused]] u32x4 kraw[3];        // 8 bits: codes of the keys, two k-steps each, and ...
+  [[maybe_unused]] bf16x8 kw[3];         // ... widened fragments, ready two MFMAs ahead (first k_R as it is, with kf[0])
   bf16x8 pfr[4][2];     // probabilities of the tile whose O^T update is running: [row block][k-step]
   i16x4 vr[2][4][2];    // its value fragments [k-step][dim tile][read]
+  [[maybe_unused]] u32x2 vraw[2][4];     // 8 bits: codes of its values, and ...
+  [[maybe_unused]] u32x4 vw[2];          // ... widened fragments of this dim tile and the next
   f32x16 s;             // raw logits of the tile whose softmax is running
+  [[maybe_unused]] f32x16 s_r;           // 8 bits: their RoPE part (the cache's scale enters s alone)
   float alpha_prev = 1.f;   // factor of this wave's rows announced with the probabilities of the previous tile
   bool announce_prev = false;
 
   auto load_k = [&](const char* tb, int ks) __attribute__((always_inline)) {  // key fragment of k-step ks of the tile at tb
-    kf[ks % KR] = *(const bf16x8*)(tb + kbase[ks & 3] + (ks >> 2) * PANEL);
+    kf[ks % KR] = *(const bf16x8*)(tb + kbase[ks & 3] + (FP8 ? NPC : ks >> 2) * PANEL);
   };
+  auto load_codes = [&](const char* tb, int i) __attribute__((always_inline)) {  // of k-steps 2 i, 2 i + 1
+    kraw[i % 3] = *(const u32x4*)(tb + kbase[i & 3] + (i >> 2) * PANEL);
+  };
+  auto load_kr = [&](const char* tb, int ks) __attribute__((always_inline)) { (ks < 3 ? kw[ks] : kf[0]) = *(const bf16x8*)(tb + kbase[ks] + NPC * PANEL); };
+  auto first_keys = [&](const char* tb) __attribute__((always_inline)) {
+    if constexpr (FP8) {  // the first two; the rest follow at the start of the tile
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) load_kr(tb, ks);
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KR; ++ks) load_k(tb, ks);
+    }
+  };
+  auto widen_half = [&](u32x4& w, const u32x2& c, int half) __attribute__((always_inline)) {  // codes 4 half .. 4 half + 3
+    w[2 * half] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[half], 1.0f, false));
+    w[2 * half + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(c[half], 1.0f, true));
+  };
+  constexpr auto vchunk = [](int d) constexpr { return (d & 1) + 4 * (d >> 1); };
   auto load_v = [&](const char* tb, int u, int d) __attribute__((always_inline)) {
+    if constexpr (FP8) {
+      typedef __attribute__((ext_vector_type(2))) int i32x2;
+      const char* p = tb + (vbase ^ (vchunk(d) << 4)) + 16 * u * 128;
+      vraw[u][d] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i32x2*)p));
+      return;
+    }
     const int off = (d >> 1) * PANEL + (16 * u) * 128;
     vr[u][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tb + vbase + (off + 64 * (d & 1))));
     vr[u][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tb + vbase + (off + 8 * 128 + 64 * (1 - (d & 1)))));
   };
   auto load_p = [&](const char* exr, int rb, int u) __attribute__((always_inline)) { pfr[rb][u] = *(const bf16x8*)(exr + (rb * 2 + u) * 1024); };
 
-#pragma unroll
-  for (int ks = 0; ks < KR; ++ks) load_k(smem, ks);
+  first_keys(smem);
 
   // Iterations 0 .. n_tiles: iteration it computes S^T of tile it (HAS_S: it < n_tiles) and updates O^T with tile it-1
   // (HAS_PV: it > 0); STAGE: tile it+2 exists and is staged in this iteration (tiles 0..2 were staged up front).  The
@@ -983,25 +1062,66 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
       pg1 = pg2;
       pg2 = pg3;  // pg3 (tile it+4) is the same page unless a new one was looked up; set behind the barrier
       next_g = tile_src(pg2, st_slot);
+      if (FP8) next_kr = kr_src(pg2, st_slot);
       st_slot = lk_slot;
       lk_slot += kTile;
       if (lk_slot == P) {
         lk_slot = 0;
         ++lk_p;
       }
-      // (pinned here: the compiler would move all of it behind the tile's barrier, in front of the next tile's first MFMA)
+      // (here and not behind the tile's barrier, where the compiler would move it all, in front of the next tile's first MFMA)
       asm volatile("" : "+s"(next_g), "+s"(st_slot), "+s"(lk_slot), "+s"(lk_p));
+      if (FP8) asm volatile("" : "+s"(next_kr));
     };
 
     // ---------------- phase 1: S^T(it), staging of tile it+2, first operands of phase 2 ----------------
     if constexpr (HAS_S) {
+      if constexpr (FP8) {  // (not ahead of the end of the last iteration: more would be kept across it than there are registers)
+        load_codes(buf, 0);
+        load_kr(buf, 2);
+        load_kr(buf, 3);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (FP8)
+      static_for<KS>([&](auto GI) __attribute__((always_inline)) {
+        constexpr int g = decltype(GI)::value, ks = g - KS_R;  // the RoPE k-steps first: the first codes are widened behind them
+        if (g == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s_r) : "v"(kw[0]), "v"(qf[KS - KS_R]));
+        else if (g < 3) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s_r) : "v"(kw[g % 3]), "v"(qf[KS - KS_R + g % 3]));
+        else if (g == 3) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s_r) : "v"(kf[0]), "v"(qf[KS - 1]));
+        else if (ks == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(kw[0]), "v"(qf[0]));
+        else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(kw[ks < 0 ? 0 : ks % 3]), "v"(qf[ks < 0 ? 0 : ks]));
+        __builtin_amdgcn_sched_barrier(0);
+        if (g < 2) load_codes(buf, g + 1);
+        // Widened two MFMAs ahead of their use (the matrix pipeline does not wait for a vector-ALU result by itself), 3, 3 and 6
+        // conversions in turn: up to three cost nothing behind an MFMA, four to six cost the same six cycles.
+        constexpr int c0 = g < 2 ? 0 : 4 * (g - 2) + (g % 3 == 0 ? 2 : g % 3 == 1 ? 1 : 0), c1 = g < 2 ? 0 : 4 * (g - 1) + (g % 3 == 2 ? 2 : g % 3 == 0 ? 1 : 0);
+        static_for<6>([&](auto CI) __attribute__((always_inline)) {
+          constexpr int c = c0 + decltype(CI)::value;  // conversion: codes 2 (c % 4), .. + 1 of k-step c / 4
+          if constexpr (c < c1 && c < RKV / 4) {
+            const uint32_t w = kraw[(c >> 3) % 3][(c >> 1) & 3];
+            const uint32_t r = __builtin_bit_cast(uint32_t, (c & 1) ? __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true)
+                                                                    : __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false));
+            u32x4 x = __builtin_bit_cast(u32x4, kw[(c >> 2) % 3]);
+            x[c & 3] = r;
+            kw[(c >> 2) % 3] = __builtin_bit_cast(bf16x8, x);
+            if constexpr (c % 8 == 7 && (c >> 3) + 3 < RKV / 32) load_codes(buf, (c >> 3) + 3);
+          }
+        });
+        if (STAGE && g % 6 == 4 && g / 6 < NP) stage_step(next_buf, next_g, next_kr, g / 6);
+        if (HAS_PV) {  // operands of the first k-step of the O^T update, in the last gaps
+          if (g >= 26 && g < 30) load_v(pbuf, 0, g - 26);
+          if (g >= 30 && g < 34) load_p(exr, g - 30, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      else
       static_for<KS>([&](auto KSI) __attribute__((always_inline)) {
         constexpr int ks = decltype(KSI)::value;
         if (ks == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(kf[0]), "v"(qf[0]));
         else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(kf[ks % KR]), "v"(qf[ks]));
         __builtin_amdgcn_sched_barrier(0);
         if (ks + KR < KS) load_k(buf, ks + KR);
-        if (STAGE && ks % 3 == 1 && ks / 3 < 9) stage_panels_step<kTile, NP, 4, ROWB, true>(next_buf, next_g, wave, stage_off, ks / 3);
+        if (STAGE && ks % 3 == 1 && ks / 3 < NP) stage_step(next_buf, next_g, next_kr, ks / 3);
         if (HAS_PV) {  // operands of the first k-step of the O^T update, in the last gaps
           if (ks >= 28 && ks < 32) load_p(exr, ks - 28, 0);
           if (ks >= 32) load_v(pbuf, 0, ks - 32);
@@ -1047,11 +1167,20 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
     }
     // softmax state of this iteration (pieces run in the gaps below)
     constexpr bool sm = HAS_S;
-    const bool need_mask = (tok + kTile > unmasked_end) || !tile_ok;
+    const bool need_mask = (tok + kTile > unmasked_end) || !tile_ok || !row_ok;
     const int lim = tile_ok ? vis_end : 0;
     float tmax = 0.f, m_use = 0.f, psum = 0.f, alpha = 1.f;
     bool announce = false;
     u32x4 w0 = {0u, 0u, 0u, 0u}, w1 = {0u, 0u, 0u, 0u};
+    float whole[16];
+    auto add_rope = [&](int q) __attribute__((always_inline)) {  // logits 4 q .. 4 q + 3 complete
+#pragma unroll
+      for (int i = 4 * q; i < 4 * q + 4; ++i) whole[i] = __builtin_fmaf(s[i], c_scale, s_r[i]);
+    };
+    auto& x = [&]() -> auto& {  // the logits, and later the probabilities
+      if constexpr (FP8) return whole;
+      else return s;
+    }();
     auto softmax_piece = [&](auto GI) __attribute__((always_inline)) {  // g = 0..31: position in the phase
       constexpr int g = decltype(GI)::value;
       if (g == 2) {
@@ -1064,21 +1193,30 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
           asm volatile("" : "+v"(dist));
 #pragma unroll
           for (int i = 0; i < 16; ++i)
-            if (need_mask && 8 * (i >> 2) + (i & 3) >= dist) s[i] = GQLA_NEG_INF;
+            if (FP8) {
+              s[i] = 8 * (i >> 2) + (i & 3) >= dist ? GQLA_NEG_INF : s[i];
+              s_r[i] = 8 * (i >> 2) + (i & 3) >= dist ? 0.f : s_r[i];
+            } else if (need_mask && 8 * (i >> 2) + (i & 3) >= dist) {
+              s[i] = GQLA_NEG_INF;
+            }
         }
+        if (FP8) add_rope(0);
         // the row maximum of the tile: eight three-way maxima (written as instructions: the logits come out of inline
         // assembly, and the compiler would first canonicalise every one of them)
-        tmax = max3(s[0], s[1], s[2]);
-        tmax = max3(tmax, s[3], s[4]);
+        tmax = max3(x[0], x[1], x[2]);
+        tmax = max3(tmax, x[3], FP8 ? x[3] : x[4]);
       } else if (g == 3) {
-        tmax = max3(tmax, s[5], s[6]);
-        tmax = max3(tmax, s[7], s[8]);
+        if (FP8) add_rope(1);
+        tmax = FP8 ? max3(tmax, x[4], x[5]) : max3(tmax, x[5], x[6]);
+        tmax = FP8 ? max3(tmax, x[6], x[7]) : max3(tmax, x[7], x[8]);
       } else if (g == 4) {
-        tmax = max3(tmax, s[9], s[10]);
-        tmax = max3(tmax, s[11], s[12]);
+        if (FP8) add_rope(2);
+        tmax = FP8 ? max3(tmax, x[8], x[9]) : max3(tmax, x[9], x[10]);
+        tmax = FP8 ? max3(tmax, x[10], x[11]) : max3(tmax, x[11], x[12]);
       } else if (g == 5) {
-        tmax = max3(tmax, s[13], s[14]);
-        tmax = max3(tmax, s[15], s[15]);
+        if (FP8) add_rope(3);
+        tmax = FP8 ? max3(tmax, x[12], x[13]) : max3(tmax, x[13], x[14]);
+        tmax = FP8 ? max3(tmax, x[14], x[15]) : max3(tmax, x[15], x[15]);
       } else if (g == 6) {
         tmax = pair_max(tmax) * a.scale_log2e;
         if (__builtin_amdgcn_ballot_w64(tmax > m_ref + kRescaleThreshold) != 0) {
@@ -1092,12 +1230,12 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
         m_use = (m_ref == GQLA_NEG_INF) ? 0.f : m_ref;
       } else if (g >= 7 && g < 23) {
         constexpr int e = g >= 7 && g < 23 ? g - 7 : 0;
-        s[e] = fast_exp2(__builtin_fmaf(s[e], a.scale_log2e, -m_use));  // the probability replaces the logit
-        psum += s[e];
+        x[e] = fast_exp2(__builtin_fmaf(x[e], a.scale_log2e, -m_use));  // the probability replaces the logit
+        psum += x[e];
       } else if (g >= 23 && g < 27) {
         constexpr int q = g >= 23 && g < 27 ? g - 23 : 0;
-        w0[q] = pack_bf16(s[2 * q], s[2 * q + 1]);
-        w1[q] = pack_bf16(s[8 + 2 * q], s[8 + 2 * q + 1]);
+        w0[q] = pack_bf16(x[2 * q], x[2 * q + 1]);
+        w1[q] = pack_bf16(x[8 + 2 * q], x[8 + 2 * q + 1]);
       } else if (g == 27) {
         l_run += psum;
         asm volatile("" : "+v"(l_run));  // (added up here, not behind the barrier)
@@ -1108,10 +1246,17 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
       }
     };
     if (HAS_PV) {
+      if constexpr (FP8) {
+        widen_half(vw[0], vraw[0][0], 0);
+        widen_half(vw[0], vraw[0][0], 1);
+        asm volatile("s_nop 1" : "+v"(vw[0]));  // two wait states between a vector-ALU write and an MFMA that reads it
+      }
       static_for<32>([&](auto GI) __attribute__((always_inline)) {
         constexpr int g = decltype(GI)::value;
         constexpr int u = g >> 4, d = (g >> 2) & 3, rb = g & 3;
-        {
+        if constexpr (FP8) {
+          acc_mfma(4 * d + rb, __builtin_bit_cast(bf16x8, vw[d & 1]), pfr[rb][u]);
+        } else {
           const i16x4 lo = vr[u][d][0], hi = vr[u][d][1];
           const i16x8 fr = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
           acc_mfma(4 * d + rb, __builtin_bit_cast(bf16x8, fr), pfr[rb][u]);
@@ -1119,7 +1264,12 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
         __builtin_amdgcn_sched_barrier(0);
         if (g == 0 && HAS_S) move_window();
         if (g >= 8 && g < 12) load_p(exr, g - 8, 1);  // second k-step's operands, as the first k-step's registers free up
-        if (g >= 12 && g < 16) load_v(pbuf, 1, g - 12);
+        if constexpr (FP8) {
+          if (g >= 4 && g < 8) load_v(pbuf, 1, g - 4);
+          if constexpr (rb < 2 && g < 28) widen_half(vw[(d + 1) & 1], vraw[(g + 4) >> 4][(d + 1) & 3], rb);  // two MFMAs and more ahead of its use
+        } else {
+          if (g >= 12 && g < 16) load_v(pbuf, 1, g - 12);
+        }
         if (sm) softmax_piece(GI);
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -1134,7 +1284,7 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
 
     // ---------------- the tile's barrier ----------------
     if (HAS_S) {
-      if (it + 2 < n_tiles) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");  // this wave's share of tile it+1 has landed
+      if (FP8 ? STAGE || it + 2 < n_tiles : it + 2 < n_tiles) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(NP) : "memory");  // this wave's share of tile it+1 has landed
       else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the probabilities are written
       __syncthreads();
@@ -1142,9 +1292,7 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
       if (it + 1 < n_tiles) {
         const int valid1 = pg0 >= 0 ? min(kTile, ce.tok_end - (tok + kTile)) : 0;  // (the window has moved: pg0 is tile it+1)
         if (valid1 < kTile) zero_rows((it + 1) & (kSlots - 1), valid1);  // only the chunk's last tile can have invalid rows
-        const char* nbuf = smem + ((it + 1) & (kSlots - 1)) * TILE_BYTES;
-#pragma unroll
-        for (int ks = 0; ks < KR; ++ks) load_k(nbuf, ks);
+        first_keys(smem + ((it + 1) & (kSlots - 1)) * TILE_BYTES);
       }
       // the page of tile it+4 joins the window (the scalar load was requested at the top of the iteration; no LDS
       // operation is outstanding here, so its wait costs nothing extra)
@@ -1159,12 +1307,20 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
   iteration(0, T_{}, F_{}, F_{});
   {
     int it = 1;
+    if constexpr (FP8) {
+      // one loop: behind the last tile the staging goes on, from page 0 into buffers that nobody reads any more (a second
+      // loop without it did not fit the registers)
 #pragma unroll 1
-    for (; it + 2 < n_tiles; ++it) iteration(it, T_{}, T_{}, T_{});
+      for (; it < n_tiles; ++it) iteration(it, T_{}, T_{}, T_{});
+    } else {
 #pragma unroll 1
-    for (; it < n_tiles; ++it) iteration(it, T_{}, T_{}, F_{});
+      for (; it + 2 < n_tiles; ++it) iteration(it, T_{}, T_{}, T_{});
+#pragma unroll 1
+      for (; it < n_tiles; ++it) iteration(it, T_{}, T_{}, F_{});
+    }
   }
   iteration(n_tiles, F_{}, T_{}, F_{});
+  if (FP8) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no request may outlive the workgroup's LDS
 
 #ifdef GQLA_PHASE_TIMING
   if (threadIdx.x == 0) {
@@ -1178,16 +1334,18 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
   const float l_tot = pair_sum(l_run);
   __syncthreads();  // every wave is done with the exchange
   float* inv_l = (float*)(smem + EX);
-  if (h == 0) inv_l[wave * 32 + n] = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  if (h == 0) inv_l[wave * 32 + n] = (l_tot > 0.f ? 1.f / l_tot : 0.f) * (FP8 ? c_scale : 1.f);
   __builtin_amdgcn_s_waitcnt(0xc07f);
   __syncthreads();
-  if (h == 0)
+  if (h == 0 && row_ok)
     a.part_lse[(int64_t)chunk * a.M + rho] = l_tot > 0.f ? (m_ref + fast_log2(l_tot)) * kLn2 : GQLA_NEG_INF;
 #pragma unroll
   for (int rb = 0; rb < 4; ++rb) {
     const int row = row0 + rb * 32 + n;
+    if (FP8 && row >= a.M) continue;
     const float inv = inv_l[rb * 32 + n];
-    // dims 4 h .. 4 h + 3 of vector 16 wave + 4 d + q of the lane's row: 512 contiguous bytes per store instruction
+    // dims 4 h .. 4 h + 3 of vector 16 wave + 4 d + q (8 bits: of the chunks of dim tile d) of the lane's row: 512 contiguous
+    // bytes per store instruction
     __bf16* po = (__bf16*)a.part_o + part_vec_index(chunk, row, a.M, RKV / 8, 16 * wave) * 8 + 4 * h;
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
@@ -1196,7 +1354,7 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         u32x2 v = {pack_bf16(x[4 * q] * inv, x[4 * q + 1] * inv), pack_bf16(x[4 * q + 2] * inv, x[4 * q + 3] * inv)};
-        *(u32x2*)(po + (4 * d + q) * (32 * 8)) = v;
+        *(u32x2*)(po + (FP8 ? 2 * (vchunk(d) + 2 * (q >> 1)) + (q & 1) : 4 * d + q) * (32 * 8)) = v;
       }
     }
   }
@@ -1205,9 +1363,9 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
 // ---- MQA-absorb decode over an 8-bit latent cache (c_kv as E4M3 codes with one scale, k_R in 16 bits) ----
 // The paper names quantised caches as complementary and fixes no format (Sec. 2; Sec. 5.1, item (i)); the page format is
 // this library's (gqla.h): code rows [P][r_kv] back to back, then k_R [P][d_r] in 16 bits -- r_kv + 2 d_r bytes per token.
-// The decode is the MQA-absorb equation on c' = value(code) * scale.  One wave per 32 rows as in
-// decode_absorb_bf16_kernel above, or (SPLIT = 4) four waves sharing 32 rows: each contracts a quarter of the key dimension,
-// they sum their S^T through LDS and own a quarter of O^T each.  Same MFMAs: the codes are widened to bf16 ONCE per tile on their way into LDS, by the wave that fetched them, so that every row block reads
+// The decode is the MQA-absorb equation on c' = value(code) * scale.  This kernel: at most 32 rows per workgroup, four waves
+// share them: each contracts a quarter of the key dimension,
+// they sum their S^T through LDS and own a quarter of O^T each (more rows: the kernel above).  Same MFMAs: the codes are widened to bf16 ONCE per tile on their way into LDS, by the wave that fetched them, so that every row block reads
 // ready-made bf16 fragments:
 //   tile it+2:  four 16-byte loads of codes per lane (whole 128-byte lines: 8 rows x 128 code bytes per wave
 //               instruction) and one of k_R, in flight in 20 registers for one whole iteration
@@ -1219,15 +1377,7 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
 // kernel is counted by hand.
 // The scale enters twice, both times outside the MFMAs: on the content part of the logits (between the latent k-steps
 // and the RoPE k-steps of S^T) and on the normalised output.
-__device__ __forceinline__ bf16x8 widen_e4m3x8(uint32_t w0, uint32_t w1) {
-  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2v;
-  const bf16x2v p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false), p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true);
-  const bf16x2v p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false), p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true);
-  const u32x4 r = {__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1), __builtin_bit_cast(uint32_t, p2), __builtin_bit_cast(uint32_t, p3)};
-  return __builtin_bit_cast(bf16x8, r);
-}
-
-template <int RKV, int DR, int SPLIT>
+template <int RKV, int DR>
 __global__ void __launch_bounds__(256) decode_absorb_fp8_kernel(DecodeArgs a, int row_blocks, float c_scale) {
   constexpr int W = RKV + DR;        // elements per latent row (in LDS: all bf16)
   constexpr int NP = W / 64;         // 128-byte panels per latent row in LDS
@@ -1236,10 +1386,10 @@ __global__ void __launch_bounds__(256) decode_absorb_fp8_kernel(DecodeArgs a, in
   constexpr int KS_C = RKV / 16;     // ... of which over the latent (the rest over the RoPE key)
   constexpr int DT = RKV / 32;       // 32-wide tiles of the latent output
   constexpr int TILE_BYTES = kTile * W * 2;
+  constexpr int SPLIT = 4;           // waves that share the 32 rows
   constexpr int RPB = kRowsPerBlock / SPLIT;
   constexpr int KB = 4 / SPLIT;
   constexpr int DTW = DT / SPLIT;
-  static_assert(SPLIT == 1 || SPLIT == 4, "one wave or the whole workgroup per 32 rows");
   static_assert(RKV == 512 && DR == 64, "the staging below is written for 8 code panels of 64 bytes per row and one k_R panel");
   static_assert(DT == 16, "O^T fills the 256 accumulation registers exactly");
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -1730,14 +1880,15 @@ static hipError_t launch_decode_absorb_rows32(const DecodeArgs& a, hipStream_t s
   return hipGetLastError();
 }
 
-static hipError_t launch_decode_absorb_shared(const DecodeArgs& a, hipStream_t s) {
-  constexpr int kLds = kSlots * kTile * (512 + 64) * 2 + 2 * 8192;  // tile ring + the double-buffered exchange: all 160 KB
+template <bool FP8>
+static hipError_t launch_decode_absorb_shared(const DecodeArgs& a, float c_scale, hipStream_t s) {
+  constexpr int kLds = kSlots * kTile * (512 * (FP8 ? 1 : 2) + 64 * 2) + 2 * 8192;  // tile ring + the double-buffered exchange (16 bits: all 160 KB)
   static const hipError_t attr =
-      hipFuncSetAttribute((const void*)decode_absorb_shared_bf16_kernel<512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+      hipFuncSetAttribute((const void*)decode_absorb_shared_bf16_kernel<512, 64, FP8>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
-  const int row_blocks = a.M / kRowsPerBlock;
+  const int row_blocks = (a.M + kRowsPerBlock - 1) / kRowsPerBlock;
   const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
-  decode_absorb_shared_bf16_kernel<512, 64><<<chunks_padded * row_blocks, 256, kLds, s>>>(a, row_blocks);
+  decode_absorb_shared_bf16_kernel<512, 64, FP8><<<chunks_padded * row_blocks, 256, kLds, s>>>(a, row_blocks, c_scale);
   return hipGetLastError();
 }
 
@@ -1750,26 +1901,20 @@ hipError_t launch_decode_absorb_bf16(const DecodeArgs& a, hipStream_t s) {
   if (a.M <= 32 || chunks_padded * ((a.M + 31) / 32) <= a.num_cus) return launch_decode_absorb_rows32(a, s);
   // whole blocks of 128 rows (h_q s_q a multiple of 128): the pipelined kernel with shared probabilities; other row
   // counts above 32: one wave per 32 rows, each with its own probabilities
-  return a.M % kRowsPerBlock == 0 ? launch_decode_absorb_shared(a, s) : launch_decode_absorb_general(a, s);
-}
-
-template <int SPLIT>
-static hipError_t launch_decode_absorb_fp8_split(const DecodeArgs& a, float c_scale, hipStream_t s) {
-  constexpr int kLds = 2 * kTile * (512 + 64) * 2 + (SPLIT > 1 ? 4 * 4096 : 0);  // two bf16 tile buffers (+ the team exchange)
-  static const hipError_t attr =
-      hipFuncSetAttribute((const void*)decode_absorb_fp8_kernel<512, 64, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-  if (attr != hipSuccess) return attr;
-  const int row_blocks = (a.M + kRowsPerBlock / SPLIT - 1) / (kRowsPerBlock / SPLIT);
-  const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
-  decode_absorb_fp8_kernel<512, 64, SPLIT><<<chunks_padded * row_blocks, 256, kLds, s>>>(a, row_blocks, c_scale);
-  return hipGetLastError();
+  return a.M % kRowsPerBlock == 0 ? launch_decode_absorb_shared<false>(a, 1.f, s) : launch_decode_absorb_general(a, s);
 }
 
 hipError_t launch_decode_absorb_fp8(const DecodeArgs& a, float c_scale, hipStream_t s) {
-  // the same choice of row mapping as for the 16-bit cache
-  const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
-  if (a.M <= 32 || chunks_padded * ((a.M + 31) / 32) <= a.num_cus) return launch_decode_absorb_fp8_split<4>(a, c_scale, s);
-  return launch_decode_absorb_fp8_split<1>(a, c_scale, s);
+  // the same choice of row mapping as for the 16-bit cache; more rows: blocks of 128, the last one padded (64 rows: see the
+  // kernel)
+  const int chunks_padded = (a.n_chunks + 7) / 8 * 8, row_blocks = (a.M + 31) / 32;
+  if (a.M > 32 && chunks_padded * row_blocks > a.num_cus) return launch_decode_absorb_shared<true>(a, c_scale, s);
+  constexpr int kLds = 2 * kTile * (512 + 64) * 2 + 4 * 4096;  // two bf16 tile buffers, the team exchange
+  static const hipError_t attr =
+      hipFuncSetAttribute((const void*)decode_absorb_fp8_kernel<512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  if (attr != hipSuccess) return attr;
+  decode_absorb_fp8_kernel<512, 64><<<chunks_padded * row_blocks, 256, kLds, s>>>(a, row_blocks, c_scale);
+  return hipGetLastError();
 }
 
 template <int DV>

@@ -50,7 +50,7 @@ def _compile(src: str, extra) -> str:
 # stale data).  The compiler touches accumulation registers itself (v_accvgpr_write / _read / _mov outside the assembly
 # blocks) only when it runs out of ordinary registers: the build checks the generated assembly and refuses such a
 # kernel instead of shipping silent corruption.
-NAMED_AGPR_SOURCES = {"gqla_absorb_bf16.hip": ["decode_absorb_bf16_kernel", "decode_absorb_shared_bf16_kernel", "decode_absorb_fp8_kernel"],
+NAMED_AGPR_SOURCES = {"gqla_absorb_bf16.hip": ["decode_absorb_bf16_kernel", "decode_absorb_shared_bf16_kernel"],
                       "gqla_gemm_bf16.hip": ["expand_bf16_kernel"]}
 
 

@@ -442,6 +442,15 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
   if (h == 0) a.part_lse[prow] = l_tot > 0.f ? (m_ref + fast_log2(l_tot)) * kLn2 : GQLA_NEG_INF;
 }
 
+// eight E4M3 codes as bf16 (exact)
+__device__ __forceinline__ bf16x8 widen_e4m3x8(uint32_t w0, uint32_t w1) {
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2v;
+  const bf16x2v p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false), p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true);
+  const bf16x2v p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false), p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true);
+  const u32x4 r = {__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1), __builtin_bit_cast(uint32_t, p2), __builtin_bit_cast(uint32_t, p3)};
+  return __builtin_bit_cast(bf16x8, r);
+}
+
 // At most 32 query rows per workgroup (at most 32 rows per sequence, or so few chunks that one workgroup per 32 rows still
 // fits the chip in one round).  With so few rows a tile is little work and what costs is the chain of a tile -- S^T, softmax,
 // probabilities to everyone, O^T -- on which one wave per SIMD issues at best an instruction every four cycles.  So eight
@@ -460,20 +469,33 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
 // the key dimension and traded fp32 partial sums (2.9 k cycles a tile; the same four waves with O^T one tile late: 22.0 us);
 // one of 32768 tokens x 16 rows 81 -> 46 us for the whole step; 32 ragged sequences of 4096 tokens x 32 rows (151 MB, all
 // compute units) 34.9 -> 29.5 us, 5.1 TB/s: there the loop runs at the memory's rate and the rest is its start.
-template <int RKV, int DR>
-__global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeArgs a, int row_blocks) {
+// FP8: the cache holds E4M3 codes of c_kv (one scale) and k_R in 16 bits (page format: see the next kernel).  Codes are staged
+// as they are -- a pair takes 40 KB, so three pairs fit and two are under way -- and widened in registers (exact): the keys
+// by each wave for its 16 tokens, 64 conversions a pair, the values out of transposed 8-bit reads, 32.  Against four waves
+// that split the key dimension, widened each tile through registers into a bf16 buffer and traded fp32 partial sums with two
+// barriers a tile (step without W^O): one sequence of 8192 tokens x 128 rows 42.2 -> 31.0 us, 64 x 8192 x 16 rows
+// 144 -> 76 us, 128 ragged sequences x 20 rows 80 -> 56 us.
+template <int RKV, int DR, bool FP8>
+__global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeArgs a, int row_blocks, float c_scale) {
   constexpr int W = RKV + DR;
-  constexpr int ROWB = W * 2;
-  constexpr int NP = W / 64;
+  constexpr int CB = FP8 ? 1 : 2;             // bytes per element of c_kv
+  constexpr int ROWB = FP8 ? RKV : 2 * W;     // bytes from one row of a page to the next
+  constexpr int NPC = RKV * CB / 128;         // panels of c_kv; k_R is one more
+  constexpr int NP = NPC + 1;
+  constexpr int QP = W / 64;                  // panels of the queries
   constexpr int PANEL = kTile * 128;
   constexpr int KS = W / 32;                  // k-steps of 32
-  constexpr int TILE_BYTES = kTile * ROWB;
-  constexpr int kQPanels = (NP + 1) / 2;      // panels of the queries that waves 0..3 request; the others take the rest
-  static_assert(RKV == 512 && DR == 64 && kSlots == 4, "eight waves of 64 latent dims; two pairs of tiles");
+  constexpr int KS_C = RKV / 32;
+  constexpr int TILE_BYTES = NP * PANEL;
+  constexpr int PAIRS = FP8 ? 3 : 2;          // ring: pairs of tiles
+  constexpr int QBUF = FP8 ? 4 : 3;           // tile buffer where the queries start out
+  constexpr int kQPanels = (QP + 1) / 2;      // panels of the queries that waves 0..3 request; the others take the rest
+  static_assert(RKV == 512 && DR == 64, "eight waves of 64 latent dims");
+  static_assert(QBUF * TILE_BYTES + QP * PANEL <= 2 * PAIRS * TILE_BYTES, "the queries lie in the ring");
   extern __shared__ __attribute__((aligned(16))) char smem[];
   // Probabilities, [parity of the pair][16 tokens][lane] 16 bytes: with one barrier per pair a wave may publish those of pair
   // j while another still reads those of j - 1.
-  char* const pex = smem + kSlots * TILE_BYTES;
+  char* const pex = smem + 2 * PAIRS * TILE_BYTES;
   float* const mex = (float*)(pex + 2 * 4096);   // row maxima, and at the end the denominators: [16 tokens][row]
 
   int chunk, rbk;
@@ -501,25 +523,26 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
   auto checked = [&](int32_t pg) -> int32_t { return ((uint32_t)pg < (uint32_t)a.cache.num_pages) ? pg : -1; };
   // tiles are always staged whole: rows past the chunk end come from the page, an out-of-pool page id falls back to page 0;
   // such rows are zeroed in LDS before use
-  auto tile_src = [&](int32_t pg, int slot) -> const char* { return pool + ((int64_t)(pg >= 0 ? pg : 0) * P + slot) * ROWB; };
+  const int64_t page_bytes = (int64_t)P * (RKV * CB + DR * 2);
+  auto tile_src = [&](int32_t pg, int slot) -> const char* { return pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + (int64_t)slot * ROWB; };
 
-  {  // queries into buffer 3; rows beyond the last read that one instead (their results are not stored)
+  {  // queries into buffer QBUF; rows beyond the last read that one instead (their results are not stored)
     const int srow = 8 * tb + (lane >> 3), c = (lane & 7) ^ ((4 * tb + (lane >> 4)) & 7);
     const int64_t qrow = (int64_t)ce.b * a.M + min(rho0 + srow, a.M - 1);
     const char* gh = (const char*)a.q_a + qrow * (RKV * 2) + c * 16;
     const char* gr = (const char*)a.q_r + qrow * (DR * 2) + c * 16;
 #pragma unroll
-    for (int u = 0; u < NP; ++u) {
+    for (int u = 0; u < QP; ++u) {
       if ((u < kQPanels) != (rh == 0)) continue;
-      const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr_t)(smem + 3 * TILE_BYTES + u * PANEL + tb * 1024);
+      const uint32_t dst = (uint32_t)(uintptr_t)(lds_ptr_t)(smem + QBUF * TILE_BYTES + u * PANEL + tb * 1024);
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(dst), "v"(u < RKV / 64 ? gh + u * 128 : gr + (u - RKV / 64) * 128) : "memory");
     }
   }
   const int n_tiles = (ce.tok_end - ce.tok_begin + kTile - 1) / kTile;
   const int n_pairs = (n_tiles + 1) / 2;
-  // A pair of tiles lies in one page (pages hold a multiple of 64 tokens, chunks start on one).  Pages of pairs j (cur) and
-  // j + 1 (nxt, first token in slot nxt_slot); the table entry of pair j + 2 is looked up during iteration j through the
-  // scalar cache.  (lk_p, lk_slot): page index and slot of the next pair to look up.
+  // A pair of tiles lies in one page (pages hold a multiple of 64 tokens, chunks start on one).  Pages of pairs j (pg[0]) to
+  // j + PAIRS - 1, whose first tokens are in slots slot[..]; the table entry of pair j + PAIRS is looked up during iteration j
+  // through the scalar cache.  (lk_p, lk_slot): page index and slot of the next pair to look up.
   constexpr int kPair = 2 * kTile;
   int lk_p = ce.tok_begin / P, lk_slot = 0;
   auto advance = [&]() {
@@ -529,47 +552,64 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
       ++lk_p;
     }
   };
-  int32_t cur, nxt, raw = 0;
-  int nxt_slot;
+  int32_t pg[PAIRS], raw = 0;
+  int slot[PAIRS];
   {
-    const int p0 = __builtin_amdgcn_readfirstlane(lk_p);
-    advance();
-    const int p1 = __builtin_amdgcn_readfirstlane(n_pairs > 1 ? lk_p : p0);
-    nxt_slot = lk_slot;
-    advance();
-    int32_t r0, r1;
-    if (table_row) {  // both scalar loads in flight together, one wait
-      asm volatile("s_load_dword %0, %1, 0x0" : "=s"(r0) : "s"(table_row + p0) : "memory");
-      asm volatile("s_load_dword %0, %1, 0x0" : "=s"(r1) : "s"(table_row + p1) : "memory");
-      asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r0), "+s"(r1) : : "memory");
-    } else {
-      r0 = ce.b * a.cache.max_pages + p0;
-      r1 = ce.b * a.cache.max_pages + p1;
+    int p[PAIRS];
+    int32_t r[PAIRS];
+#pragma unroll
+    for (int u = 0; u < PAIRS; ++u) {
+      p[u] = __builtin_amdgcn_readfirstlane(u < n_pairs ? lk_p : p[0]);
+      slot[u] = lk_slot;
+      advance();
     }
-    cur = checked(r0);
-    nxt = checked(r1);
+    if (table_row) {  // the scalar loads in flight together, one wait
+#pragma unroll
+      for (int u = 0; u < PAIRS; ++u) asm volatile("s_load_dword %0, %1, 0x0" : "=s"(r[u]) : "s"(table_row + p[u]) : "memory");
+      if constexpr (PAIRS == 3) asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r[0]), "+s"(r[1]), "+s"(r[PAIRS - 1]) : : "memory");
+      else asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(r[0]), "+s"(r[1]) : : "memory");
+    } else {
+#pragma unroll
+      for (int u = 0; u < PAIRS; ++u) r[u] = ce.b * a.cache.max_pages + p[u];
+    }
+#pragma unroll
+    for (int u = 0; u < PAIRS; ++u) pg[u] = checked(r[u]);
   }
-  auto stage_tile = [&](int buffer, int32_t pg, int slot) { stage_panels_full<kTile, NP, 4, ROWB, true>(smem + buffer * TILE_BYTES, tile_src(pg, slot), tb, lane); };
-  // tiles 0 and 1, and 2 behind them; tile 3 waits until the queries have left its buffer
-  if (rh == 0) {
-    stage_tile(0, cur, 0);
-    if (n_tiles > 2) stage_tile(2, nxt, nxt_slot);
-  } else if (n_tiles > 1) {
-    stage_tile(1, cur, kTile);
-  }
+  auto stage_tile = [&](int buffer, int32_t page, int row) {
+    char* dst = smem + buffer * TILE_BYTES;
+    if constexpr (FP8) {  // codes, and k_R out of its plane behind the codes of the page
+      stage_panels_full<kTile, NPC, 4, RKV, true>(dst, tile_src(page, row), tb, lane);
+      stage_panels_full<kTile, 1, 4, DR * 2, true>(dst + NPC * PANEL, tile_src(page, 0) + (int64_t)P * RKV + (int64_t)row * (DR * 2), tb, lane);
+    } else {
+      stage_panels_full<kTile, NP, 4, ROWB, true>(dst, tile_src(page, row), tb, lane);
+    }
+  };
+  // Tiles 0 and 1, and behind them what lies clear of the queries: tile 2 (16 bits), tiles 2 and 3 (8 bits).  Wave group rh
+  // requests tile rh of a pair.
+  const bool ahead = 2 + rh < n_tiles && (FP8 || rh == 0);  // this wave has requests of pair 1 out
+  if (rh < n_tiles) stage_tile(rh, pg[0], rh * kTile);
+  if (ahead) stage_tile(2 + rh, pg[1], slot[1] + rh * kTile);
 
-  // per-lane LDS offsets.  Operand fragments of S^T, k-step ks: panel ks / 2, in-panel chunk 4 (ks & 1) + g4.
-  uint32_t kbase[2], qbase[2], vbase;
+  // per-lane LDS offsets.  Operand fragments of S^T, k-step ks: panel ks / 2, in-panel chunk 4 (ks & 1) + g4.  8 bits: a
+  // 16-byte vector of codes is a lane's share of two k-steps, dims 64 (ks / 2) + 16 g4 + 8 (ks % 2) + 0..7 (qcode: the queries
+  // of those dims).
+  uint32_t kbase[2], qbase[2], qcode[2], vbase;
   {
     const int krow = 16 * (tb & 1) + n16, qrow = 16 * rh + n16;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       kbase[b] = (tb >> 1) * TILE_BYTES + krow * 128 + (((4 * b + g4) ^ lds_swz(krow)) << 4);
-      qbase[b] = 3 * TILE_BYTES + qrow * 128 + (((4 * b + g4) ^ lds_swz(qrow)) << 4);
+      qbase[b] = QBUF * TILE_BYTES + qrow * 128 + (((4 * b + g4) ^ lds_swz(qrow)) << 4);
+      qcode[b] = QBUF * TILE_BYTES + qrow * 128 + (((2 * g4 + b) ^ lds_swz(qrow)) << 4);
     }
     // value fragments (transposed reads): as in the kernel above, panel `wave`
     const int i16 = lane & 15, e = i16 >> 2, q = i16 & 3, g1 = (lane >> 4) & 1;
-    vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8 + wave * PANEL;
+    if constexpr (FP8) {  // 8-bit transposed reads: see the next kernel; dim tile d is chunks d, d + 2 of half a panel
+      const int t = i16 >> 1, row = 8 * (t >> 2) + 4 * h + (t & 3);
+      vbase = row * 128 + (((4 * (wave & 1) + 2 * g1) ^ lds_swz(row)) << 4) + (i16 & 1) * 8 + (wave >> 1) * PANEL;
+    } else {
+      vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8 + wave * PANEL;
+    }
   }
   f32x16 o[2];
 #pragma unroll
@@ -578,16 +618,17 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
     for (int i = 0; i < 16; ++i) o[d][i] = 0.f;
   float m_s = GQLA_NEG_INF, m_o = GQLA_NEG_INF, l_run = 0.f;  // reference of this lane's row in S^T, in O^T
 
-  // queries and tiles 0, 1 (tile 2, if there, is what waves 0..3 have requested last)
-  if (rh == 0 && n_tiles > 2) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
+  // queries and tiles 0, 1 (pair 1, where this wave has a part in it, was requested last)
+  if (ahead) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(NP) : "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   bf16x8 qf[KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(smem + qbase[ks & 1] + (ks >> 1) * PANEL);
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(smem + (FP8 && ks < KS_C ? qcode : qbase)[ks & 1] + (ks >> 1) * PANEL);
 
   float z[4], z_max = GQLA_NEG_INF, psum_last = 0.f;  // of the last pair: raw logits, scaled maximum, sum of probabilities
-  i16x4 r[4][2][2] = {};                              // value fragments of the last pair
+  typedef typename std::conditional<FP8, u32x2, i16x4>::type value_t;
+  value_t r[4][2][FP8 ? 1 : 2] = {};                  // value fragments of the last pair (8 bits: codes)
   char* const p_dst = pex + tb * 1024 + ((g4 & 1) * 32 + 16 * rh + n16) * 16 + (g4 >> 1) * 8;
   auto publish = [&](int pair, float m_use, bool flag) {
     float p[4], sum = 0.f;
@@ -600,12 +641,13 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
     return sum;
   };
 
+  int ring = 0;  // j % PAIRS
 #pragma unroll 1
   for (int j = 0;; ++j) {
     const int tok = ce.tok_begin + j * kPair;
-    char* const buf = smem + (j & 1) * 2 * TILE_BYTES;
+    char* const buf = smem + ring * 2 * TILE_BYTES;
     const bool more = j < n_pairs;
-    const bool lookup = j + 2 < n_pairs;
+    const bool lookup = j + PAIRS < n_pairs;
     const int look_slot = lk_slot;
     if (lookup) {
       const int p = __builtin_amdgcn_readfirstlane(lk_p);
@@ -613,15 +655,19 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
       else raw = ce.b * a.cache.max_pages + p;
       advance();
     }
-    if (j > 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (j > 0) {  // pair j has landed; 8 bits: pair j + 1 may be under way
+      if (FP8 && 2 * j + 2 + rh < n_tiles) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(NP) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
     __syncthreads();
-    if (2 * j + 2 + rh < n_tiles && !(j == 0 && rh == 0)) stage_tile((2 * (j + 1) & 2) + rh, nxt, nxt_slot + rh * kTile);
-    const bool whole = cur >= 0 && tok + kPair <= ce.tok_end;
+    const int last = ring == 0 ? PAIRS - 1 : ring - 1;  // buffers of pair j - 1, for pair j + PAIRS - 1
+    if (2 * (j + PAIRS - 1) + rh < n_tiles && !(j == 0 && ahead && !FP8)) stage_tile(2 * last + rh, pg[PAIRS - 1], slot[PAIRS - 1] + rh * kTile);
+    const bool whole = pg[0] >= 0 && tok + kPair <= ce.tok_end;
     if (more && !whole) {
       // rows past the chunk end hold whatever the page holds (NaN bits included): zero them so that 0 * v stays 0
-      const int valid = cur >= 0 ? max(ce.tok_end - tok, 0) : 0;
-      for (int idx = threadIdx.x; idx < (kPair - valid) * (W / 8); idx += 512) {
-        const int rr = valid + idx / (W / 8), c = idx % (W / 8);
+      const int valid = pg[0] >= 0 ? max(ce.tok_end - tok, 0) : 0;
+      for (int idx = threadIdx.x; idx < (kPair - valid) * (NP * 8); idx += 512) {
+        const int rr = valid + idx / (NP * 8), c = idx % (NP * 8);
         *(u32x4*)(buf + rr / kTile * TILE_BYTES + (c >> 3) * PANEL + rr % kTile * 128 + (c & 7) * 16) = u32x4{0u, 0u, 0u, 0u};
       }
       __syncthreads();
@@ -640,8 +686,13 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
       for (int u = 0; u < 4; ++u) pw[u] = u32x4{0u, 0u, 0u, 0u};
     }
     auto key_frag = [&](int ks) { return *(const bf16x8*)(buf + kbase[ks & 1] + (ks >> 1) * PANEL); };
-    bf16x8 f[NP];
-    static_for<NP>([&](auto k) { f[decltype(k)::value] = key_frag(decltype(k)::value); });
+    constexpr int KF = FP8 ? KS_C / 2 + KS - KS_C : KS / 2;  // fragments requested ahead (8 bits: all, codes of two k-steps each, then k_R)
+    bf16x8 f[KF];
+    static_for<KF>([&](auto k) {
+      constexpr int u = decltype(k)::value;
+      // (codes: in-panel chunk 4 (u & 1) + g4, k_R: k-steps KS_C, KS_C + 1 of the last panel)
+      f[u] = FP8 && u >= KS_C / 2 ? *(const bf16x8*)(buf + kbase[u & 1] + NPC * PANEL) : key_frag(u);
+    });
     if (j > 0) {
       const uint32_t flags = pw[0][0] | pw[0][2] | pw[1][0] | pw[1][2] | pw[2][0] | pw[2][2] | pw[3][0] | pw[3][2];
       if (__builtin_amdgcn_ballot_w64((flags & 0x8000u) != 0) != 0) {  // the same bits in every wave: all come here or none
@@ -672,16 +723,30 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
       constexpr int u = decltype(uc)::value;
 #pragma unroll
       for (int d = 0; d < 2; ++d) {
-        const i16x4 lo = r[u][d][0], hi = r[u][d][1];
-        const i16x8 fr = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        o[d] = mfma32(__builtin_bit_cast(bf16x8, fr), __builtin_bit_cast(bf16x8, pw[u]), o[d]);
+        bf16x8 fr;
+        if constexpr (FP8) {
+          fr = widen_e4m3x8(r[u][d][0][0], r[u][d][0][1]);
+        } else {
+          const i16x4 lo = r[u][d][0], hi = r[u][d][1];
+          const i16x8 x = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+          fr = __builtin_bit_cast(bf16x8, x);
+        }
+        o[d] = mfma32(fr, __builtin_bit_cast(bf16x8, pw[u]), o[d]);
       }
     };
     f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    [[maybe_unused]] f32x4 s_r = {0.f, 0.f, 0.f, 0.f};  // 8 bits: the RoPE part (the cache's scale enters the rest alone)
     static_for<KS>([&](auto kc) {
       constexpr int ks = decltype(kc)::value;
-      s[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[ks % NP], qf[ks], s[ks & 1], 0, 0, 0);
-      if constexpr (ks + NP < KS) f[ks] = key_frag(ks + NP);
+      if constexpr (!FP8) {
+        s[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[ks % KF], qf[ks], s[ks & 1], 0, 0, 0);
+        if constexpr (ks + KF < KS) f[ks] = key_frag(ks + KF);
+      } else if constexpr (ks < KS_C) {
+        const u32x4 c = __builtin_bit_cast(u32x4, f[ks / 2]);
+        s[ks & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16((ks & 1) ? widen_e4m3x8(c[2], c[3]) : widen_e4m3x8(c[0], c[1]), qf[ks], s[ks & 1], 0, 0, 0);
+      } else {
+        s_r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[KS_C / 2 + ks - KS_C], qf[ks], s_r, 0, 0, 0);
+      }
       if constexpr (ks % 4 == 3) output_step(std::integral_constant<int, ks / 4>{});
     });
     if (!more) break;
@@ -691,14 +756,20 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
 #pragma unroll
       for (int d = 0; d < 2; ++d) {
         const int off = (u >> 1) * TILE_BYTES + 16 * (u & 1) * 128;
+        if constexpr (FP8) {
+          typedef __attribute__((ext_vector_type(2))) int i32x2;
+          r[u][d][0] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i32x2*)(buf + (vbase ^ (d << 4)) + off)));
+          continue;
+        } else {
         r[u][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 64 * d)));
         r[u][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 8 * 128 + 64 * (1 - d))));
+        }
       }
     // ---- softmax of this wave's 16 tokens x 16 rows ----
 #pragma unroll
-    for (int i = 0; i < 4; ++i) z[i] = s[0][i] + s[1][i];
+    for (int i = 0; i < 4; ++i) z[i] = FP8 ? __builtin_fmaf(s[0][i] + s[1][i], c_scale, s_r[i]) : s[0][i] + s[1][i];
     if (!whole || tok + kPair > unmasked_end) {
-      const int lim = cur >= 0 ? vis_end : 0;
+      const int lim = pg[0] >= 0 ? vis_end : 0;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (tok + 16 * tb + 4 * g4 + i >= lim) z[i] = GQLA_NEG_INF;
@@ -712,12 +783,17 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
     const bool move = __builtin_amdgcn_ballot_w64(z_max > m_s + kRescaleThreshold) != 0;
     psum_last = publish(j, (m_s == GQLA_NEG_INF) ? 0.f : m_s, move);
 
-    cur = nxt;
-    nxt = -1;
-    nxt_slot = look_slot;
+    ring = ring + 1 == PAIRS ? 0 : ring + 1;
+#pragma unroll
+    for (int u = 0; u + 1 < PAIRS; ++u) {
+      pg[u] = pg[u + 1];
+      slot[u] = slot[u + 1];
+    }
+    pg[PAIRS - 1] = -1;
+    slot[PAIRS - 1] = look_slot;
     if (lookup) {
       if (table_row) asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(raw) : : "memory");
-      nxt = checked(raw);
+      pg[PAIRS - 1] = checked(raw);
     }
   }
 
@@ -734,26 +810,17 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
   const float l_tot = mex[n] + mex[32 + n] + mex[64 + n] + mex[96 + n];
   const int row = rho0 + n;
   if (row >= a.M) return;
-  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  const float inv = (l_tot > 0.f ? 1.f / l_tot : 0.f) * (FP8 ? c_scale : 1.f);
   // dims 4 h .. 4 h + 3 of vector 4 (2 wave + d) + q of the row: consecutive rows in consecutive lanes
   __bf16* po = (__bf16*)a.part_o + part_vec_index(chunk, row, a.M, RKV / 8, 0) * 8 + 4 * h;
 #pragma unroll
   for (int d = 0; d < 2; ++d)
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      *(u32x2*)(po + ((wave * 2 + d) * 4 + q) * (32 * 8)) =
+      *(u32x2*)(po + (FP8 ? 8 * wave + 2 * (d + 2 * (q >> 1)) + (q & 1) : (wave * 2 + d) * 4 + q) * (32 * 8)) =
           u32x2{pack_bf16(o[d][4 * q] * inv, o[d][4 * q + 1] * inv), pack_bf16(o[d][4 * q + 2] * inv, o[d][4 * q + 3] * inv)};
   if (h == 0 && wave == 0)
     a.part_lse[(int64_t)chunk * a.M + row] = l_tot > 0.f ? (m_o + fast_log2(l_tot)) * kLn2 : GQLA_NEG_INF;
-}
-
-// eight E4M3 codes as bf16 (exact)
-__device__ __forceinline__ bf16x8 widen_e4m3x8(uint32_t w0, uint32_t w1) {
-  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2v;
-  const bf16x2v p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false), p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true);
-  const bf16x2v p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false), p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true);
-  const u32x4 r = {__builtin_bit_cast(uint32_t, p0), __builtin_bit_cast(uint32_t, p1), __builtin_bit_cast(uint32_t, p2), __builtin_bit_cast(uint32_t, p3)};
-  return __builtin_bit_cast(bf16x8, r);
 }
 
 // every accumulator of row block rb (tiles 4*dtl + rb, dtl = 0..3) of this lane times alpha
@@ -802,7 +869,9 @@ __device__ __forceinline__ void acc_scale_rb(int rb, float alpha) {
 // accumulators in all four waves: the owning wave announces it in the sign bit of its first probability (probabilities
 // are never negative), all waves see the same bits, and together they take a slow path that passes the factors through
 // the idle half of the exchange.
-// FP8: the cache holds E4M3 codes of c_kv (one scale) and k_R in 16 bits (page format in the next section).  The same MFMAs on
+// FP8: the cache holds E4M3 codes of c_kv with one scale, and k_R in 16 bits.  The paper names quantised caches as complementary
+// and fixes no format (Sec. 2; Sec. 5.1, item (i)); the page format is this library's (gqla.h): code rows [P][r_kv] back to
+// back, then k_R [P][d_r] -- r_kv + 2 d_r bytes per token; the decode is the MQA-absorb equation on value(code) * scale.  The same MFMAs on
 // the same bf16 operands: codes and k_R are staged as they are (20 KB a tile instead of 36) and widened in registers
 // (v_cvt_scalef32_pk_bf16_fp8, exact) -- the keys by every wave for itself, 128 conversions a tile, in the gaps of S^T; the
 // values once, by the wave that owns their dims, out of transposed 8-bit reads.  The scale enters the content part of the
@@ -1360,325 +1429,6 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
   }
 }
 
-// ---- MQA-absorb decode over an 8-bit latent cache (c_kv as E4M3 codes with one scale, k_R in 16 bits) ----
-// The paper names quantised caches as complementary and fixes no format (Sec. 2; Sec. 5.1, item (i)); the page format is
-// this library's (gqla.h): code rows [P][r_kv] back to back, then k_R [P][d_r] in 16 bits -- r_kv + 2 d_r bytes per token.
-// The decode is the MQA-absorb equation on c' = value(code) * scale.  This kernel: at most 32 rows per workgroup, four waves
-// share them: each contracts a quarter of the key dimension,
-// they sum their S^T through LDS and own a quarter of O^T each (more rows: the kernel above).  Same MFMAs: the codes are widened to bf16 ONCE per tile on their way into LDS, by the wave that fetched them, so that every row block reads
-// ready-made bf16 fragments:
-//   tile it+2:  four 16-byte loads of codes per lane (whole 128-byte lines: 8 rows x 128 code bytes per wave
-//               instruction) and one of k_R, in flight in 20 registers for one whole iteration
-//   tile it+1:  its codes (requested one iteration ago) are widened (v_cvt_scalef32_pk_bf16_fp8, exact) and written to
-//               the idle one of two LDS tile buffers in the panel layout of gqla_lds.h -- the lanes of a 16-lane group
-//               cover 4 rows x 4 chunk pairs, which the layout's XOR spreads over all 64 banks; its k_R rows (already
-//               16-bit) are written as they came
-// Everything in flight is an ordinary load into registers: the compiler places every wait itself, and no wait of this
-// kernel is counted by hand.
-// The scale enters twice, both times outside the MFMAs: on the content part of the logits (between the latent k-steps
-// and the RoPE k-steps of S^T) and on the normalised output.
-template <int RKV, int DR>
-__global__ void __launch_bounds__(256) decode_absorb_fp8_kernel(DecodeArgs a, int row_blocks, float c_scale) {
-  constexpr int W = RKV + DR;        // elements per latent row (in LDS: all bf16)
-  constexpr int NP = W / 64;         // 128-byte panels per latent row in LDS
-  constexpr int PANEL = kTile * 128; // bytes per panel
-  constexpr int KS = W / 16;         // k-steps of the key contraction
-  constexpr int KS_C = RKV / 16;     // ... of which over the latent (the rest over the RoPE key)
-  constexpr int DT = RKV / 32;       // 32-wide tiles of the latent output
-  constexpr int TILE_BYTES = kTile * W * 2;
-  constexpr int SPLIT = 4;           // waves that share the 32 rows
-  constexpr int RPB = kRowsPerBlock / SPLIT;
-  constexpr int KB = 4 / SPLIT;
-  constexpr int DTW = DT / SPLIT;
-  static_assert(RKV == 512 && DR == 64, "the staging below is written for 8 code panels of 64 bytes per row and one k_R panel");
-  static_assert(DT == 16, "O^T fills the 256 accumulation registers exactly");
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-
-  int chunk, rbk;
-  {
-    const int id = blockIdx.x;
-    const int grp = id / (8 * row_blocks), rem = id % (8 * row_blocks);
-    rbk = rem / 8;
-    chunk = grp * 8 + rem % 8;
-  }
-  if (chunk >= a.n_chunks) return;  // whole workgroup leaves together
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int n = lane & 31, h = lane >> 5;
-  const ChunkEntry ce = a.chunks[chunk];
-
-  const int part = wave & (SPLIT - 1), team = wave / SPLIT;
-  const int rho = rbk * RPB + team * 32 + n;  // row = t * h_q + i
-  const bool row_ok = rho < a.M;
-  const int t = row_ok ? rho / a.h_q : 0;
-  const int vis_end = row_ok ? min(ce.tok_end, ce.L - a.s_q + t + 1) : 0;
-  const int unmasked_end = min(ce.tok_end, ce.L - a.s_q + 1);
-  const bool wave_active = SPLIT > 1 || rbk * RPB + team * 32 < a.M;
-
-  const int P = a.cache.page_size;
-  const char* pool = (const char*)a.cache.pool;
-  const int64_t page_bytes = (int64_t)P * (RKV + 2 * DR);
-  const int32_t* table_row = a.cache.page_table ? a.cache.page_table + (int64_t)ce.b * a.cache.max_pages : nullptr;
-  auto checked = [&](int32_t pg) -> int32_t { return ((uint32_t)pg < (uint32_t)a.cache.num_pages) ? pg : -1; };
-  // first code row / first k_R row of a tile: page pg (page 0 for an id outside the pool; such a tile is zeroed), slot `slot`
-  auto code_src = [&](int32_t pg, int slot) -> const char* { return pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + (int64_t)slot * RKV; };
-  auto kr_src = [&](int32_t pg, int slot) -> const char* {
-    return pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + (int64_t)P * RKV + (int64_t)slot * (DR * 2);
-  };
-
-  uint32_t kbase[KB], vbase;
-  {
-#pragma unroll
-    for (int b = 0; b < KB; ++b) kbase[b] = n * 128 + (((2 * (part * KB + b) + h) ^ lds_swz(n)) << 4);
-    const int i16 = lane & 15, e = i16 >> 2, q = i16 & 3, g1 = (lane >> 4) & 1;
-    vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8;
-    vbase += part * (DTW / 2) * PANEL;
-  }
-  // staging: load i (0..3) of this lane fetches the 16 codes of row R, dims 16*k .. 16*k+15, k = 4*(2i + hp) + kq, and
-  // writes them as chunks 2k, 2k+1 of row R: panel 2i + hp, in-panel slots (2kq) ^ swz, (2kq+1) ^ swz
-  const int st_R = 8 * wave + 4 * ((lane >> 4) & 1) + ((lane >> 2) & 3), st_kq = lane & 3, st_hp = lane >> 5;
-  const uint32_t st_goff = st_R * RKV + (4 * st_hp + st_kq) * 16;
-  const uint32_t st_w0 = st_R * 128 + (((2 * st_kq) ^ lds_swz(st_R)) << 4) + st_hp * PANEL;
-  const uint32_t st_w1 = st_R * 128 + (((2 * st_kq + 1) ^ lds_swz(st_R)) << 4) + st_hp * PANEL;
-  // ... and one 16-byte piece of k_R: row kr_R, chunk lane % 8 (eight lanes per 128-byte row)
-  const int kr_R = 8 * wave + (lane >> 3);
-  const uint32_t kr_goff = kr_R * (DR * 2) + (lane & 7) * 16;
-  const uint32_t kr_w = (RKV / 64) * PANEL + kr_R * 128 + (((lane & 7) ^ lds_swz(kr_R)) << 4);
-
-  acc_zero();
-  float m_ref = GQLA_NEG_INF, l_run = 0.f;
-  const int n_tiles = (ce.tok_end - ce.tok_begin + kTile - 1) / kTile;
-
-  u32x4 codes[4], kr16;  // in flight: 4 x 16 codes and 8 elements of k_R per lane
-  auto load_tile = [&](int32_t pg, int slot) __attribute__((always_inline)) {
-    const char* src = code_src(pg, slot);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) codes[i] = __builtin_nontemporal_load((const u32x4*)(src + st_goff + i * 128));
-    kr16 = __builtin_nontemporal_load((const u32x4*)(kr_src(pg, slot) + kr_goff));
-  };
-  // widen the codes in flight and write them as rows of the bf16 tile at `slot`; rows >= valid are written as zeros
-  // (slots past the chunk end hold whatever the page holds, and 0 * v must stay 0)
-  auto write_tile = [&](char* slot, int valid) __attribute__((always_inline)) {
-    const bool keep = st_R < valid;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      u32x4 lo = __builtin_bit_cast(u32x4, widen_e4m3x8(codes[i][0], codes[i][1]));
-      u32x4 hi = __builtin_bit_cast(u32x4, widen_e4m3x8(codes[i][2], codes[i][3]));
-      if (!keep) lo = hi = u32x4{0u, 0u, 0u, 0u};
-      *(u32x4*)(slot + st_w0 + i * 2 * PANEL) = lo;
-      *(u32x4*)(slot + st_w1 + i * 2 * PANEL) = hi;
-    }
-    *(u32x4*)(slot + kr_w) = kr_R < valid ? kr16 : u32x4{0u, 0u, 0u, 0u};
-  };
-  auto page_now = [&](int tile) -> int32_t {  // synchronous lookup (start-up only)
-    const int p = (ce.tok_begin + tile * kTile) / P;
-    return checked(table_row ? table_row[p] : ce.b * a.cache.max_pages + p);
-  };
-
-  // queries of this lane's row, as B fragments (requested first: their latency overlaps the first tile's)
-  bf16x8 qf[KS / SPLIT];
-  {
-    const int64_t qrow = (int64_t)ce.b * a.M + min(rho, a.M - 1);
-    const __bf16* ph = (const __bf16*)a.q_a + qrow * RKV + h * 8 + part * KB * 16;
-    const __bf16* pr = (const __bf16*)a.q_r + qrow * DR + h * 8 + part * KB * 16;
-#pragma unroll
-    for (int a4 = 0; a4 < KS / 4; ++a4)
-#pragma unroll
-      for (int b = 0; b < KB; ++b)
-        qf[a4 * KB + b] = *(const bf16x8*)((a4 < RKV / 64 ? ph + a4 * 64 : pr + (a4 - RKV / 64) * 64) + b * 16);
-  }
-  // start-up: tile 0 into buffer 0, codes of tile 1 in flight
-  int32_t pg_cur = page_now(0);
-  int32_t pg_n1 = n_tiles > 1 ? page_now(1) : -1;  // page of tile it+1
-  load_tile(pg_cur, 0);
-  // the query loads complete here
-#pragma unroll
-  for (int k = 0; k < KS / SPLIT; k += 9)
-    asm volatile("" : "+v"(qf[k]), "+v"(qf[k + 1]), "+v"(qf[k + 2]), "+v"(qf[k + 3]), "+v"(qf[k + 4]), "+v"(qf[k + 5]),
-                      "+v"(qf[k + 6]), "+v"(qf[k + 7]), "+v"(qf[k + 8]));
-  static_assert((KS / SPLIT) % 9 == 0, "query fragments are touched nine at a time");
-  write_tile(smem, pg_cur >= 0 ? min(kTile, ce.tok_end - ce.tok_begin) : 0);
-  if (n_tiles > 1) load_tile(pg_n1, kTile % P);
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the tile is written
-  __syncthreads();
-  int32_t pg_lane = 0;
-  int lane_zero;
-  asm volatile("v_mov_b32 %0, 0" : "=v"(lane_zero));
-
-#pragma unroll 1
-  for (int it = 0; it < n_tiles; ++it) {
-    const int tok = ce.tok_begin + it * kTile;
-    const char* buf = smem + (it & 1) * TILE_BYTES;
-    char* nbuf = smem + ((it + 1) & 1) * TILE_BYTES;
-    // page of tile it+2: looked up when that tile starts a page, consumed behind the S phase.  An ordinary load into a
-    // vector register (every lane reads the same entry; the lane-dependent zero keeps the compiler from turning it into
-    // a load-and-wait on the spot), so that the compiler itself waits for it where the value is first read.  (A scalar
-    // load issued and awaited by hand is not safe here: this loop's control flow makes the compiler copy the value
-    // between registers, and a copy ahead of the hand-placed wait reads the register while the load is pending.)
-    const int tok2 = tok + 2 * kTile;
-    const bool has2 = it + 2 < n_tiles;
-    const bool new_page = has2 && (tok2 % P) == 0;
-    if (new_page && table_row) pg_lane = table_row[tok2 / P + lane_zero];
-    const bool tile_ok = pg_cur >= 0;
-
-    // tile it+1 into the idle buffer (every wave passed the last barrier: nobody reads tile it-1 any more), the codes of
-    // tile it+2 into flight.  No LDS read of this wave is outstanding where this is called.
-    auto stage_step = [&]() __attribute__((always_inline)) {
-      const int32_t pg_n2 = !has2 ? -1 : (new_page ? checked(table_row ? __builtin_amdgcn_readfirstlane(pg_lane)
-                                                                           : ce.b * a.cache.max_pages + tok2 / P) : pg_n1);
-      if (it + 1 < n_tiles) {
-        write_tile(nbuf, pg_n1 >= 0 ? min(kTile, ce.tok_end - (tok + kTile)) : 0);
-      }
-      if (has2) load_tile(pg_n2, tok2 % P);
-      pg_cur = pg_n1;  // (used again only in the next iteration)
-      pg_n1 = pg_n2;
-    };
-    auto end_of_tile = [&]() __attribute__((always_inline)) {
-      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's rows of tile it+1 are written
-      __syncthreads();
-    };
-    const bool need_mask = (tok + kTile > unmasked_end) || !row_ok || !tile_ok;
-    const int lim = tile_ok ? vis_end : 0;
-
-    // ---- S^T[token][row] = Kt * Qhat^T: latent k-steps, the scale, RoPE k-steps ----
-    // (waves without query rows only stage: ONE call site of stage_step for both kinds, so that the codes in flight
-    // live in the same registers on every path and nothing has to wait for them before the staging itself)
-    f32x16 s;
-    if (wave_active) {
-      bf16x8 f[2][KB];  // fragment batches: loads run one batch (one panel) ahead of their use
-#pragma unroll
-      for (int b = 0; b < KB; ++b) f[0][b] = *(const bf16x8*)(buf + kbase[b]);
-#pragma unroll
-      for (int a4 = 0; a4 < KS / 4; ++a4) {
-        if (a4 + 1 < KS / 4) {
-#pragma unroll
-          for (int b = 0; b < KB; ++b) f[(a4 + 1) & 1][b] = *(const bf16x8*)(buf + kbase[b] + ((a4 + 1) * PANEL));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (a4 == KS_C / 4) {  // the latent part is complete: the cache's scale, before the RoPE part is added
-          asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s));
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s[i] *= c_scale;
-          asm volatile("s_nop 1" : "+v"(s));
-        }
-#pragma unroll
-        for (int b = 0; b < KB; ++b) {
-          if (a4 == 0 && b == 0) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(s) : "v"(f[0][0]), "v"(qf[0]));
-          else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(s) : "v"(f[a4 & 1][b]), "v"(qf[a4 * KB + b]));
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    stage_step();
-    if (wave_active) {
-    // first batch of value fragments: issued now, consumed after the softmax
-    i16x4 r[2][4][2];
-    auto load_v = [&](int slot, int u, int p4) __attribute__((always_inline)) {
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const int dt = 4 * p4 + d;
-        const int off = (dt >> 1) * PANEL + (16 * u) * 128;
-        r[slot][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 64 * (dt & 1))));
-        r[slot][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 8 * 128 + 64 * (1 - (dt & 1)))));
-      }
-    };
-    constexpr int NBT = 2 * (DTW / 4);
-    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s));  // the matrix pipeline's result is not interlocked against vector-ALU reads
-    if constexpr (SPLIT > 1) {
-      // team sum of the partial S^T: [wave][quarter][lane] 16-byte slots behind the two tile buffers.  (The scale was
-      // applied to every wave's latent part; the RoPE part is spread over the waves like the latent part.)
-      char* ex = smem + 2 * TILE_BYTES;
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *(f32x4*)(ex + wave * 4096 + q * 1024 + lane * 16) = f32x4{s[4 * q], s[4 * q + 1], s[4 * q + 2], s[4 * q + 3]};
-      __builtin_amdgcn_s_waitcnt(0xc07f);
-      __syncthreads();  // the next write to these slots comes after the end-of-tile barrier, which follows these reads
-#pragma unroll
-      for (int w = 0; w < SPLIT; ++w)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 x = *(const f32x4*)(ex + (team * SPLIT + w) * 4096 + q * 1024 + lane * 16);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) s[4 * q + e] = (w == 0) ? x[e] : s[4 * q + e] + x[e];
-        }
-    }
-    load_v(0, 0, 0);
-
-    // ---- online softmax (base 2); register i is token tok + 8*(i/4) + 4*h + i%4 ----
-    if (__builtin_amdgcn_ballot_w64(need_mask) != 0) {
-      int dist = lim - tok - 4 * h;
-      asm volatile("" : "+v"(dist));
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (need_mask && 8 * (i >> 2) + (i & 3) >= dist) s[i] = GQLA_NEG_INF;
-    }
-    float tmax = s[0];
-#pragma unroll
-    for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
-    tmax = pair_max(tmax) * a.scale_log2e;
-    if (__builtin_amdgcn_ballot_w64(tmax > m_ref + kRescaleThreshold) != 0) {
-      const float m_new = fmaxf(m_ref, tmax);
-      const float alpha = fast_exp2(m_ref - ((m_new == GQLA_NEG_INF) ? 0.f : m_new));
-      m_ref = m_new;
-      l_run *= alpha;
-      if (it > 0) acc_scale(alpha);
-    }
-    const float m_use = (m_ref == GQLA_NEG_INF) ? 0.f : m_ref;
-    bf16x8 pf[2];
-    {
-      float p[16], psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        p[e] = fast_exp2(__builtin_fmaf(s[e], a.scale_log2e, -m_use));
-        psum += p[e];
-      }
-      l_run += psum;
-      const u32x4 w0 = {pack_bf16(p[0], p[1]), pack_bf16(p[2], p[3]), pack_bf16(p[4], p[5]), pack_bf16(p[6], p[7])};
-      const u32x4 w1 = {pack_bf16(p[8], p[9]), pack_bf16(p[10], p[11]), pack_bf16(p[12], p[13]), pack_bf16(p[14], p[15])};
-      pf[0] = __builtin_bit_cast(bf16x8, w0);
-      pf[1] = __builtin_bit_cast(bf16x8, w1);
-    }
-    asm volatile("s_nop 1" : "+v"(pf[0]), "+v"(pf[1]));  // two wait states between a vector-ALU write and an MFMA that reads it
-    __builtin_amdgcn_sched_barrier(0);
-
-    // ---- O^T[r][row] += C^T * P^T, value fragments one batch of four tiles ahead ----
-#pragma unroll
-    for (int bt = 0; bt < NBT; ++bt) {
-      const int u = bt / (DTW / 4), p4 = bt % (DTW / 4);
-      if (bt + 1 < NBT) load_v((bt + 1) & 1, (bt + 1) / (DTW / 4), (bt + 1) % (DTW / 4));
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const i16x4 lo = r[bt & 1][d][0], hi = r[bt & 1][d][1];
-        const i16x8 fr = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        acc_mfma(4 * p4 + d, __builtin_bit_cast(bf16x8, fr), pf[u]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    }
-    end_of_tile();
-  }
-
-  const float l_tot = pair_sum(l_run);
-  if (!row_ok) return;
-  const float inv = (l_tot > 0.f ? 1.f / l_tot : 0.f) * c_scale;  // o_hat = scale * sum_s p_s value(code_s)
-  const int64_t prow = (int64_t)chunk * a.M + rho;
-  // this lane holds dims 4 h .. 4 h + 3 of vector 4 (part DTW + dt) + q of its row: with consecutive rows in consecutive
-  // lanes a store instruction writes 512 contiguous bytes
-  __bf16* po = (__bf16*)a.part_o + part_vec_index(chunk, rho, a.M, RKV / 8, 0) * 8 + 4 * h;
-#pragma unroll
-  for (int dt = 0; dt < DTW; ++dt) {
-    float x[16];
-    acc_read(dt, dt == 0, x);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      u32x2 v = {pack_bf16(x[4 * q] * inv, x[4 * q + 1] * inv), pack_bf16(x[4 * q + 2] * inv, x[4 * q + 3] * inv)};
-      *(u32x2*)(po + ((part * DTW + dt) * 4 + q) * (32 * 8)) = v;
-    }
-  }
-  if (h == 0 && part == 0) a.part_lse[prow] = l_tot > 0.f ? (m_ref + fast_log2(l_tot)) * kLn2 : GQLA_NEG_INF;
-}
-
 // ---- combine + latent-output projection: out = W_UV[j]^T (sum_k w_k o_hat_k)   (MQA-absorb equation, line 6) ----
 // A workgroup of 8 waves takes blocks of query rows of one group j.  W_UV[j] ([r_kv][128 of the value dims], 128 KB) is
 // staged in LDS once and stays there for all of them.  Per block:
@@ -1869,14 +1619,15 @@ static hipError_t launch_decode_absorb_general(const DecodeArgs& a, hipStream_t 
   return hipGetLastError();
 }
 
-static hipError_t launch_decode_absorb_rows32(const DecodeArgs& a, hipStream_t s) {
-  constexpr int kLds = kSlots * kTile * (512 + 64) * 2 + 2 * 4096 + 512;  // tile ring, probabilities, row maxima
+template <bool FP8>
+static hipError_t launch_decode_absorb_rows32(const DecodeArgs& a, float c_scale, hipStream_t s) {
+  constexpr int kLds = (FP8 ? 6 * kTile * (512 + 64 * 2) : 4 * kTile * (512 + 64) * 2) + 2 * 4096 + 512;  // tile ring, probabilities, row maxima
   static const hipError_t attr =
-      hipFuncSetAttribute((const void*)decode_absorb_rows32_bf16_kernel<512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+      hipFuncSetAttribute((const void*)decode_absorb_rows32_bf16_kernel<512, 64, FP8>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
   const int row_blocks = (a.M + 31) / 32;
   const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
-  decode_absorb_rows32_bf16_kernel<512, 64><<<chunks_padded * row_blocks, 512, kLds, s>>>(a, row_blocks);
+  decode_absorb_rows32_bf16_kernel<512, 64, FP8><<<chunks_padded * row_blocks, 512, kLds, s>>>(a, row_blocks, c_scale);
   return hipGetLastError();
 }
 
@@ -1898,7 +1649,7 @@ hipError_t launch_decode_absorb_bf16(const DecodeArgs& a, hipStream_t s) {
   // chunks the chip is nowhere near its memory rate).  Beyond one round the re-reads cost more than they give: 64 sequences
   // x 4096 tokens x 64 rows take 104 us a step that way and 92 us with the general kernel, 96 rows 139 and 97 us.
   const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
-  if (a.M <= 32 || chunks_padded * ((a.M + 31) / 32) <= a.num_cus) return launch_decode_absorb_rows32(a, s);
+  if (a.M <= 32 || chunks_padded * ((a.M + 31) / 32) <= a.num_cus) return launch_decode_absorb_rows32<false>(a, 1.f, s);
   // whole blocks of 128 rows (h_q s_q a multiple of 128): the pipelined kernel with shared probabilities; other row
   // counts above 32: one wave per 32 rows, each with its own probabilities
   return a.M % kRowsPerBlock == 0 ? launch_decode_absorb_shared<false>(a, 1.f, s) : launch_decode_absorb_general(a, s);
@@ -1907,14 +1658,9 @@ hipError_t launch_decode_absorb_bf16(const DecodeArgs& a, hipStream_t s) {
 hipError_t launch_decode_absorb_fp8(const DecodeArgs& a, float c_scale, hipStream_t s) {
   // the same choice of row mapping as for the 16-bit cache; more rows: blocks of 128, the last one padded (64 rows: see the
   // kernel)
-  const int chunks_padded = (a.n_chunks + 7) / 8 * 8, row_blocks = (a.M + 31) / 32;
-  if (a.M > 32 && chunks_padded * row_blocks > a.num_cus) return launch_decode_absorb_shared<true>(a, c_scale, s);
-  constexpr int kLds = 2 * kTile * (512 + 64) * 2 + 4 * 4096;  // two bf16 tile buffers, the team exchange
-  static const hipError_t attr =
-      hipFuncSetAttribute((const void*)decode_absorb_fp8_kernel<512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
-  if (attr != hipSuccess) return attr;
-  decode_absorb_fp8_kernel<512, 64><<<chunks_padded * row_blocks, 256, kLds, s>>>(a, row_blocks, c_scale);
-  return hipGetLastError();
+  const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
+  if (a.M <= 32 || chunks_padded * ((a.M + 31) / 32) <= a.num_cus) return launch_decode_absorb_rows32<true>(a, c_scale, s);
+  return launch_decode_absorb_shared<true>(a, c_scale, s);
 }
 
 template <int DV>

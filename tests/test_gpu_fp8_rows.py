@@ -1,8 +1,8 @@
-"""The decode over the 8-bit latent cache for more than 32 query rows, at the edges of its row blocks, tiles and chunks: row
-counts that end inside a block of 128 and inside a wave's 32 rows, chunks of one tile to many (the ring of four buffers fills,
-wraps and drains), a last tile with one token, pages of several tiles, and logits that make a row's maximum move in every tile
-(all four waves then rescale together).  num_cus = 1 keeps small batches on this kernel.  Same codes on both sides, so the
-plain 16-bit bar: 2e-2 absolute, 1e-2 relative."""
+"""The two decode kernels over the 8-bit latent cache at the edges of their row blocks, tiles and chunks: row counts that end
+inside a block (128 rows; with 32 and fewer, or few chunks, 32) and inside a wave's rows, chunks of one tile to many (the rings
+of four tiles and of three pairs fill, wrap and drain), a last tile with one token, pages of several tiles, and logits that
+make a row's maximum move in every tile (all waves then rescale together).  num_cus = 1 sends more than 32 rows to the kernel
+for blocks of 128.  Same codes on both sides, so the plain 16-bit bar: 2e-2 absolute, 1e-2 relative."""
 import numpy as np
 import pytest
 import torch
@@ -16,22 +16,27 @@ from test_gpu_parity import Case, check, host
 pytestmark = pytest.mark.gpu
 
 
-def _case(h_q, g, s_q, lens, cp, **kw):
+def _case(h_q, g, s_q, lens, cp, num_cus=1, **kw):
     cfg = S.CONFIGS["C2"].with_(B=len(lens), h_q=h_q, g=g, s_q=s_q, L=0, paged=True, seed=97, **kw)
-    print("fp8 rows", h_q, g, s_q, lens, cp, flush=True)
-    return Case(cfg, lens=lens, chunk_pages=(cp, cp), num_cus=1)
+    print("fp8 rows", h_q, g, s_q, lens, cp, num_cus, flush=True)
+    return Case(cfg, lens=lens, chunk_pages=(cp, cp), num_cus=num_cus)
 
 
-@pytest.mark.parametrize("h_q,g,s_q,lens,cp,c_scale", [
-    (33, 1, 1, [161, 1], 2, 0.5),                       # one row in the second wave
-    (20, 5, 2, [65, 700, 2], 2, 0.37),                  # 40 rows, two step tokens
-    (64, 8, 1, [33, 65, 97, 129, 257], 1, 1.0),         # 64 rows: the last two waves without rows; chunks of one and two tiles
-    (128, 8, 1, [1, 31, 32, 96, 97, 1000], 16, 0.75),   # one to 32 tiles in a chunk
-    (80, 8, 2, [300, 70], 3, 0.02),                     # 160 rows: a second block of 32; part of the latent saturates
-    (132, 4, 1, [130, 64], 1, 2.5),                     # four rows in the second block
+@pytest.mark.parametrize("h_q,g,s_q,lens,cp,c_scale,num_cus", [
+    (33, 1, 1, [161, 1], 2, 0.5, 1),                       # one row in the second wave
+    (20, 5, 2, [65, 700, 2], 2, 0.37, 1),                  # 40 rows, two step tokens
+    (64, 8, 1, [33, 65, 97, 129, 257], 1, 1.0, 1),         # 64 rows: the last two waves without rows; chunks of one and two tiles
+    (128, 8, 1, [1, 31, 32, 96, 97, 1000], 16, 0.75, 1),   # one to 32 tiles in a chunk
+    (80, 8, 2, [300, 70], 3, 0.02, 1),                     # 160 rows: a second block of 32; part of the latent saturates
+    (132, 4, 1, [130, 64], 1, 2.5, 1),                     # four rows in the second block
+    (1, 1, 1, [1, 33, 64], 1, 0.5, 256),                     # one row
+    (16, 1, 2, [2, 31, 32, 33, 65, 97, 129, 161, 193, 225, 417], 8, 0.37, 256),   # 32 rows; one to 14 tiles in a chunk
+    (20, 4, 1, [700, 1], 3, 1.0, 256),                       # 20 rows of 32
+    (80, 8, 1, [300, 70], 2, 0.02, 256),                     # the third block ends after 16 rows
+    (128, 8, 1, [1000], 4, 2.5, 256),                        # four workgroups of 32 rows a chunk
 ])
-def test_rows_tiles_and_chunks(h_q, g, s_q, lens, cp, c_scale):
-    case = _case(h_q, g, s_q, lens, cp)
+def test_rows_tiles_and_chunks(h_q, g, s_q, lens, cp, c_scale, num_cus):
+    case = _case(h_q, g, s_q, lens, cp, num_cus)
     try:
         codes, pool = _oracle_pool(case, c_scale, fill=0xFF)      # slots no token owns: NaN codes
         case.dec.latent_fp8_pool = torch.from_numpy(pool).cuda()
@@ -40,8 +45,9 @@ def test_rows_tiles_and_chunks(h_q, g, s_q, lens, cp, c_scale):
         case.close()
 
 
-def test_pages_of_several_tiles():
-    case = _case(128, 8, 1, [256, 193, 500, 40], 1, page_size=256)
+@pytest.mark.parametrize("h_q,num_cus", [(128, 1), (16, 256)])
+def test_pages_of_several_tiles(h_q, num_cus):
+    case = _case(h_q, 8, 1, [256, 193, 500, 40], 1, num_cus, page_size=256)
     try:
         codes, pool = _oracle_pool(case, 0.5)
         case.dec.latent_fp8_pool = torch.from_numpy(pool).cuda()
@@ -50,11 +56,11 @@ def test_pages_of_several_tiles():
         case.close()
 
 
-@pytest.mark.parametrize("h_q", [64, 128])
-def test_maximum_moves_in_every_tile(h_q):
+@pytest.mark.parametrize("h_q,num_cus", [(64, 1), (128, 1), (16, 256)])
+def test_maximum_moves_in_every_tile(h_q, num_cus):
     """k_R of tile i grows along a fixed direction that all queries share: each tile's logits exceed the last ones by 12 or
     more in base 2, past the threshold of 8."""
-    case = _case(h_q, 8, 1, [32 * 6, 32 * 5 + 9], 64)
+    case = _case(h_q, 8, 1, [32 * 6, 32 * 5 + 9], 64, num_cus)
     try:
         cfg, dec = case.cfg, case.dec
         dq = np.zeros_like(case.q_r)

@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
 #pragma unroll
     for (int b = 0; b < 4; ++b) kbase[b] = n * 128 + (((2 * b + h) ^ lds_swz(n)) << 4);
     const int i16 = lane & 15, e = i16 >> 2, q = i16 & 3, g1 = (lane >> 4) & 1;
-    vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8;
+    vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ lds_swz(4 * h + e)) << 4) + (q & 1) * 8;
   }
 
   static_assert(DT == 16, "O^T fills the 256 accumulation registers exactly");
@@ -341,8 +341,8 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
         for (int d = 0; d < 4; ++d) {
           const int dt = 4 * p4 + d;
           const int off = (dt >> 1) * PANEL + (16 * u) * 128;
-          r[slot][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 64 * (dt & 1))));
-          r[slot][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 8 * 128 + 64 * (1 - (dt & 1)))));
+          r[slot][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + (vbase ^ (64 * (dt & 1))) + off));
+          r[slot][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + (vbase ^ (64 * (dt & 1) + 16)) + (off + 8 * 128)));
         }
       };
       constexpr int NBT = 2 * (DT / 4);  // batches of four value fragments: k-step bt / (DT/4), tiles 4*(bt % (DT/4)) ..
@@ -527,7 +527,7 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
   auto tile_src = [&](int32_t pg, int slot) -> const char* { return pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + (int64_t)slot * ROWB; };
 
   {  // queries into buffer QBUF; rows beyond the last read that one instead (their results are not stored)
-    const int srow = 8 * tb + (lane >> 3), c = (lane & 7) ^ ((4 * tb + (lane >> 4)) & 7);
+    const int srow = 8 * tb + (lane >> 3), c = (lane & 7) ^ lds_swz(srow);
     const int64_t qrow = (int64_t)ce.b * a.M + min(rho0 + srow, a.M - 1);
     const char* gh = (const char*)a.q_a + qrow * (RKV * 2) + c * 16;
     const char* gr = (const char*)a.q_r + qrow * (DR * 2) + c * 16;
@@ -590,25 +590,29 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
   if (rh < n_tiles) stage_tile(rh, pg[0], rh * kTile);
   if (ahead) stage_tile(2 + rh, pg[1], slot[1] + rh * kTile);
 
-  // per-lane LDS offsets.  Operand fragments of S^T, k-step ks: panel ks / 2, in-panel chunk 4 (ks & 1) + g4.  8 bits: a
-  // 16-byte vector of codes is a lane's share of two k-steps, dims 64 (ks / 2) + 16 g4 + 8 (ks % 2) + 0..7 (qcode: the queries
-  // of those dims).
-  uint32_t kbase[2], qbase[2], qcode[2], vbase;
+  // per-lane LDS offsets.  Operand fragments of S^T, k-step ks: panel ks / 2, in-panel chunk 2 (ks & 1) + place(g4) with
+  // place = 0, 4, 1, 5: lanes 16 apart then read chunks 4 apart, which keeps the 16 lanes that the LDS serves together (16
+  // rows, half of them on each of the two chunks) on different banks.  8 bits: a 16-byte vector of codes is a lane's share of
+  // two k-steps, dims 128 (ks / 4) + 16 (2 (ks / 2 % 2) + place(g4)) + 8 (ks % 2) + 0..7 (qcode[ks % 4]: the queries of those
+  // dims).
+  uint32_t kbase[2], qbase[2], qcode[4], vbase;
   {
-    const int krow = 16 * (tb & 1) + n16, qrow = 16 * rh + n16;
+    const int krow = 16 * (tb & 1) + n16, qrow = 16 * rh + n16, place = 4 * (g4 & 1) + (g4 >> 1);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      kbase[b] = (tb >> 1) * TILE_BYTES + krow * 128 + (((4 * b + g4) ^ lds_swz(krow)) << 4);
-      qbase[b] = QBUF * TILE_BYTES + qrow * 128 + (((4 * b + g4) ^ lds_swz(qrow)) << 4);
-      qcode[b] = QBUF * TILE_BYTES + qrow * 128 + (((2 * g4 + b) ^ lds_swz(qrow)) << 4);
+      kbase[b] = (tb >> 1) * TILE_BYTES + krow * 128 + (((2 * b + place) ^ lds_swz(krow)) << 4);
+      qbase[b] = QBUF * TILE_BYTES + qrow * 128 + (((2 * b + place) ^ lds_swz(qrow)) << 4);
     }
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      qcode[b] = QBUF * TILE_BYTES + (g4 & 1) * PANEL + qrow * 128 + (((2 * ((g4 >> 1) + 2 * (b >> 1)) + (b & 1)) ^ lds_swz(qrow)) << 4);
     // value fragments (transposed reads): as in the kernel above, panel `wave`
     const int i16 = lane & 15, e = i16 >> 2, q = i16 & 3, g1 = (lane >> 4) & 1;
     if constexpr (FP8) {  // 8-bit transposed reads: see the next kernel; dim tile d is chunks d, d + 2 of half a panel
       const int t = i16 >> 1, row = 8 * (t >> 2) + 4 * h + (t & 3);
       vbase = row * 128 + (((4 * (wave & 1) + 2 * g1) ^ lds_swz(row)) << 4) + (i16 & 1) * 8 + (wave >> 1) * PANEL;
     } else {
-      vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8 + wave * PANEL;
+      vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ lds_swz(4 * h + e)) << 4) + (q & 1) * 8 + wave * PANEL;
     }
   }
   f32x16 o[2];
@@ -624,7 +628,7 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
   __syncthreads();
   bf16x8 qf[KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(smem + (FP8 && ks < KS_C ? qcode : qbase)[ks & 1] + (ks >> 1) * PANEL);
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(FP8 && ks < KS_C ? smem + qcode[ks & 3] + 2 * (ks >> 2) * PANEL : smem + qbase[ks & 1] + (ks >> 1) * PANEL);
 
   float z[4], z_max = GQLA_NEG_INF, psum_last = 0.f;  // of the last pair: raw logits, scaled maximum, sum of probabilities
   typedef typename std::conditional<FP8, u32x2, i16x4>::type value_t;
@@ -690,7 +694,7 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
     bf16x8 f[KF];
     static_for<KF>([&](auto k) {
       constexpr int u = decltype(k)::value;
-      // (codes: in-panel chunk 4 (u & 1) + g4, k_R: k-steps KS_C, KS_C + 1 of the last panel)
+      // (8 bits: vectors 0 .. KS_C / 2 - 1 of codes, then k-steps KS_C, KS_C + 1 of the last panel, k_R)
       f[u] = FP8 && u >= KS_C / 2 ? *(const bf16x8*)(buf + kbase[u & 1] + NPC * PANEL) : key_frag(u);
     });
     if (j > 0) {
@@ -761,8 +765,8 @@ __global__ void __launch_bounds__(512) decode_absorb_rows32_bf16_kernel(DecodeAr
           r[u][d][0] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i32x2*)(buf + (vbase ^ (d << 4)) + off)));
           continue;
         } else {
-        r[u][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 64 * d)));
-        r[u][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + vbase + (off + 8 * 128 + 64 * (1 - d))));
+        r[u][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + (vbase ^ (64 * d)) + off));
+        r[u][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(buf + (vbase ^ (64 * d + 16)) + (off + 8 * 128)));
         }
       }
     // ---- softmax of this wave's 16 tokens x 16 rows ----
@@ -956,7 +960,7 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
       const int k = i16 >> 1, row = 8 * (k >> 2) + 4 * h + (k & 3);
       vbase = row * 128 + (((2 * g1) ^ lds_swz(row)) << 4) + (i16 & 1) * 8 + wave * PANEL;
     } else {
-      vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ (2 * h + (e >> 1))) << 4) + (q & 1) * 8;
+      vbase = (4 * h + e) * 128 + (((2 * g1 + (q >> 1)) ^ lds_swz(4 * h + e)) << 4) + (q & 1) * 8;
       vbase += wave * 2 * PANEL;
     }
   }
@@ -1100,8 +1104,8 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
       return;
     }
     const int off = (d >> 1) * PANEL + (16 * u) * 128;
-    vr[u][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tb + vbase + (off + 64 * (d & 1))));
-    vr[u][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tb + vbase + (off + 8 * 128 + 64 * (1 - (d & 1)))));
+    vr[u][d][0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tb + (vbase ^ (64 * (d & 1))) + off));
+    vr[u][d][1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(tb + (vbase ^ (64 * (d & 1) + 16)) + (off + 8 * 128)));
   };
   auto load_p = [&](const char* exr, int rb, int u) __attribute__((always_inline)) { pfr[rb][u] = *(const bf16x8*)(exr + (rb * 2 + u) * 1024); };
 

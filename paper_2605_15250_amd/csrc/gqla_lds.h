@@ -1,8 +1,11 @@
 // LDS staging of row-major bf16 matrices for MFMA operands on gfx950.
 //
 // Panel layout.  A staged matrix of R rows and 8*NP 16-byte chunks per row is kept as NP panels of [R][128 bytes]:
-// chunk c of row r lives in panel c / 8 at byte  r*128 + (((c & 7) ^ swz(r)) << 4),  swz(r) = (r >> 1) & 7.
-// The XOR spreads both access patterns below over the LDS banks:
+// chunk c of row r lives in panel c / 8 at byte  r*128 + (((c & 7) ^ swz(r)) << 4),  swz(r) = bits 1, 2, 3 of r, bit 1 on top.
+// The XOR spreads both access patterns below over the 64 LDS banks (two rows).  Row fragments: 16 consecutive rows' chunks c
+// have 16 places, whatever the order of the three bits.  Transposed fragments: 16 lanes read four rows' pairs of chunks at a
+// time (8 bytes a lane), and rows r, r + 2, which begin at the same bank, must differ in a bit above the pair's, hence bit 1 of
+// the row on top (with (r >> 1) & 7 both met in the same two places: every transposed read took twice its time).
 //   row fragment         lane (m = l % 32, h = l / 32) reads 8 consecutive elements of row m (an MFMA operand whose
 //                        contraction index runs along the row)                                  -> ds_read_b128
 //   transposed fragment  the contraction index runs DOWN the rows: each lane needs 2 x 4 consecutive rows of one
@@ -20,14 +23,14 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __attribute__((address_space(1))) const void* gbl_ptr_t;
 typedef __attribute__((ext_vector_type(8))) short i16x8;
 
-__device__ __forceinline__ int lds_swz(int row) { return (row >> 1) & 7; }
+__device__ __forceinline__ int lds_swz(int row) { return ((row << 1) & 4) | ((row >> 1) & 2) | ((row >> 3) & 1); }
 
 // Staging of a whole matrix with ROWS rows of NP*128 bytes (row stride GSTRIDE bytes) by the NWAVES waves of a
 // workgroup (NWAVES even and dividing ROWS/8).  Completion: s_waitcnt vmcnt(..) by each wave, then a workgroup barrier.
 template <int ROWS, int NP, int NWAVES, int GSTRIDE>
 __device__ __forceinline__ uint32_t stage_lane_offset(int wave, int lane) {
   const int row0 = 8 * wave + (lane >> 3);
-  const int c = (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7);
+  const int c = (lane & 7) ^ lds_swz(row0);
   return row0 * GSTRIDE + c * 16;
 }
 // g and wave must be wave-uniform; lane_off = stage_lane_offset(wave, lane) is the only per-lane part of the address.
@@ -73,27 +76,9 @@ __device__ __forceinline__ bf16x8 row_frag(const char* lds, int row, int chunk) 
   return *(const bf16x8*)(lds + (chunk >> 3) * (ROWS * 128) + row * 128 + (((chunk & 7) ^ lds_swz(row)) << 4));
 }
 
-// Transposed fragment: lane l receives column (col0 + l % 32) of rows row_a + 0..3 (elements 0..3) and row_b + 0..3
-// (elements 4..7); row_a, row_b are per-lane-half values supplied by the caller (multiples of 4), col0 a multiple of 32.
-template <int ROWS>
-__device__ __forceinline__ bf16x8 tr_frag(const char* lds, int row_a, int row_b, int col0, int lane) {
-  const int i16 = lane & 15;
-  const int e = i16 >> 2, q = i16 & 3;  // this lane ADDRESSES row (+e), columns 4q..4q+3 of its 16-column block
-  const int col = col0 + ((lane >> 4) & 1) * 16 + 4 * q;
-  const int chunk = col >> 3, sub = (col & 7) * 2;
-  const int ra = row_a + e, rb = row_b + e;
-  const char* panel = lds + (chunk >> 3) * (ROWS * 128) + sub;
-  const char* pa = panel + ra * 128 + (((chunk & 7) ^ lds_swz(ra)) << 4);
-  const char* pb = panel + rb * 128 + (((chunk & 7) ^ lds_swz(rb)) << 4);
-  const i16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)pa);
-  const i16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)pb);
-  const i16x8 r = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return __builtin_bit_cast(bf16x8, r);
-}
-
 // Transposed fragments in natural contraction order out of a staged [ROWS][NP*64] matrix: fragment (ks, mt) holds,
 // for column 32*mt + l % 32, rows 16*ks + 8*(l / 32) + 0..7.  The per-lane part of the two read addresses depends only
-// on the parity of mt (the swizzle flips the 64-byte half with the lane half), so four lane offsets cover the
+// on the parity of mt, so four lane offsets cover the
 // whole matrix and everything else is a compile-time offset:  base[read][mt & 1] + (mt >> 1)*ROWS*128 + ks*2048.
 struct TrNatural {
   uint32_t base[2][2];
@@ -105,10 +90,10 @@ __device__ __forceinline__ TrNatural make_tr_natural(int lane) {
   TrNatural t;
 #pragma unroll
   for (int rd = 0; rd < 2; ++rd) {
-    const int x = 2 * rd + (e >> 1);  // low swizzle bits of row 16*ks + 8*h + e + 4*rd; bit 2 of the swizzle is h
+    const int row = 8 * h + e + 4 * rd;
 #pragma unroll
     for (int par = 0; par < 2; ++par)
-      t.base[rd][par] = (8 * h + e + 4 * rd) * 128 + ((4 * (par ^ h) + (cl ^ x)) << 4) + sub;
+      t.base[rd][par] = row * 128 + (((4 * par + cl) ^ lds_swz(row)) << 4) + sub;
   }
   return t;
 }

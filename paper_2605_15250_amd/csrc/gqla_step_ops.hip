@@ -134,7 +134,7 @@ __global__ void __launch_bounds__(256) out_proj_bf16_kernel(OutProjArgs a) {
   // staging role of this lane inside a block of 8 rows: row (lane >> 3) of the block, and the 16-byte chunk of the row
   // that the panel layout wants at LDS position lane & 7 (blocks of one wave are 4 apart, so the swizzle term is fixed)
   const int srow = lane >> 3;
-  const int schunk = (lane & 7) ^ ((4 * wave + (lane >> 4)) & 7);
+  const int schunk = (lane & 7) ^ lds_swz(8 * wave + srow);
   const uint32_t w_off = (uint32_t)(srow * stride + schunk * 16);
   const char* wsrc = (const char*)a.w_o + (int64_t)col0 * stride + (int64_t)kbeg * 2;
   const char* osrc = (const char*)a.o + (int64_t)m0 * stride + (int64_t)kbeg * 2;

@@ -1434,11 +1434,11 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
 }
 
 // ---- combine + latent-output projection: out = W_UV[j]^T (sum_k w_k o_hat_k)   (MQA-absorb equation, line 6) ----
-// A workgroup of 8 waves takes blocks of query rows of one group j.  W_UV[j] ([r_kv][128 of the value dims], 128 KB) is
-// staged in LDS once and stays there for all of them.  Per block:
+// A workgroup of 8 waves takes blocks of query rows of one group j.  W_UV[j] ([r_kv][PD = 128 or 64 of the value dims], 128 or
+// 64 KB) is staged in LDS once and stays there for all of them.  Per block:
 //   merge     wave w merges the chunk partials of latent dims [64 w, 64 w + 64) by their log-sum-exps (online, kNB chunks in
 //             flight) and writes the merged latent as four MFMA operand fragments (bf16) into a 32 KB exchange
-//   project   O^T[d][row] = W^T[d][r] * Ohat^T[r][row]: wave w < 4 owns value dims [32 w, 32 w + 32) over all r; the first
+//   project   O^T[d][row] = W^T[d][r] * Ohat^T[r][row]: wave w < PD / 32 owns value dims [32 w, 32 w + 32) over all r; the first
 //             partials of everyone's next block are already requested
 // A block has 32 columns: 32 rows, or rows_per_block = 8 or 4 rows times 4 or 8 slices of the chunks (column = row +
 // rows_per_block * slice), so that a single sequence's long chain of partials (20 to 130 chunks) is merged by all lanes at
@@ -1449,21 +1449,21 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
 // Measured (kernel): one sequence, 22 chunks, 128 rows: 18.2 -> 7.9 us; 64 sequences, 4 chunks each: 13.1 -> 12.0 us; 128
 // ragged sequences of 256 rows, 201 MB of partials: 50.7 -> 35.5 us.  (Before: a block per workgroup, W_UV staged by each and
 // ahead of the partials, the K range split over the waves and 64 KB of fp32 results summed through LDS.)
-// DV: value dims per head (columns of W_UV[j], elements of an output row); a workgroup projects onto 128 of them, blockIdx.z
-// selects which (the merge is repeated per slice of 128).
-template <int RKV, int DV>
+// DV: value dims per head (columns of W_UV[j], elements of an output row); a workgroup projects onto PD of them, blockIdx.z
+// selects which (the merge is repeated per slice).  PD = 64 where that still is one workgroup per unit: a unit stages half of
+// W_UV (4 sequences x 8192 tokens x 128 rows 8.8 -> 8.2 us, 32 ragged x 32 rows 7.8 -> 7.2, 16 rows of a group 8.6 -> 7.8).
+template <int RKV, int DV, int PD>
 __global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a, int rows_per_group, int log2_rows, int n_blocks) {
-  constexpr int DH = 128;
   constexpr int KSW = RKV / 16 / 8;  // k-steps of the contraction that one wave merges
   constexpr int kNB = 4;             // chunks in flight
   static_assert(KSW == 4, "eight waves x 4 k-steps");
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  char* const exch = smem + RKV * DH * 2;  // [k-step][lane][16 bytes]
+  char* const exch = smem + RKV * PD * 2;  // [k-step][lane][16 bytes]
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
   const int j = blockIdx.y;
-  const int col0 = blockIdx.z * DH;  // first value dim of this workgroup
+  const int col0 = blockIdx.z * PD;  // first value dim of this workgroup
   const int rows = 1 << log2_rows, slice = n >> log2_rows, slices = 32 >> log2_rows;
   const int64_t chunk_stride = (int64_t)((a.M + 31) / 32) * 32 * RKV;  // elements from one chunk's partials to the next
 
@@ -1499,10 +1499,10 @@ __global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a
     // (the builtin, not the assembly of gqla_lds.h: the compiler then counts these requests and waits for the partials
     // without them)
     __builtin_amdgcn_sched_barrier(0);
-    const uint32_t off = stage_lane_offset<RKV, DH / 64, 8, DV * 2>(wave, lane);
+    const uint32_t off = stage_lane_offset<RKV, PD / 64, 8, DV * 2>(wave, lane);
     const char* w = (const char*)a.w_uv + ((int64_t)j * RKV * DV + col0) * 2;
 #pragma unroll
-    for (int u = 0; u < 16; ++u)  // panel u / 8, rows 64 (u % 8) + 8 wave + 0..7
+    for (int u = 0; u < PD / 8; ++u)  // panel u / 8, rows 64 (u % 8) + 8 wave + 0..7
       __builtin_amdgcn_global_load_lds((gbl_ptr_t)(w + off + (64 * (u & 7)) * (DV * 2) + (u >> 3) * 128),
                                        (lds_ptr_t)(smem + (u >> 3) * (RKV * 128) + (wave + 8 * (u & 7)) * 1024), 16, 0, 0);
   }
@@ -1587,7 +1587,7 @@ __global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);            // lgkmcnt(0)
     __syncthreads();                               // the exchange (and, the first time, W_UV[j]) is complete
-    if (wave < 4) {
+    if (wave < PD / 32) {
       f32x16 o;
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[i] = 0.f;
@@ -1667,21 +1667,28 @@ hipError_t launch_decode_absorb_fp8(const DecodeArgs& a, float c_scale, hipStrea
   return launch_decode_absorb_shared<true>(a, c_scale, s);
 }
 
-template <int DV>
-static hipError_t launch_combine_project_dv(const CombineArgs& a, hipStream_t s) {
-  constexpr int kLds = 512 * 128 * 2 + 32 * 1024;  // W_UV[j] and the exchange: all 160 KB
+template <int DV, int PD>
+static hipError_t launch_combine_project_dims(const CombineArgs& a, int log2_rows, int n_blocks, hipStream_t s) {
+  constexpr int kLds = 512 * PD * 2 + 32 * 1024;  // W_UV[j] and the exchange (128 dims: all 160 KB)
   // once per process (function-local statics are initialised under a lock); an error is reported by every call
   static const hipError_t attr =
-      hipFuncSetAttribute((const void*)combine_project_bf16_kernel<512, DV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+      hipFuncSetAttribute((const void*)combine_project_bf16_kernel<512, DV, PD>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
+  const int per_group = 256 / (a.g * (DV / PD));  // workgroups per group: one per compute unit, each with its share of the blocks
+  combine_project_bf16_kernel<512, DV, PD><<<dim3(n_blocks < per_group || per_group < 1 ? n_blocks : per_group, a.g, DV / PD), 512, kLds, s>>>(
+      a, a.B * a.s_q * a.G, log2_rows, n_blocks);
+  return hipGetLastError();
+}
+
+template <int DV>
+static hipError_t launch_combine_project_dv(const CombineArgs& a, hipStream_t s) {
   const int rows_per_group = a.B * a.s_q * a.G;
   // 32 rows per block fill the MFMA tile; with fewer than half a chip's worth of such blocks, 8 or 4 rows each
   const int log2_rows = ((rows_per_group + 31) / 32) * a.g >= 128 ? 5 : (((rows_per_group + 7) / 8) * a.g >= 128 ? 3 : 2);
   const int n_blocks = (rows_per_group + (1 << log2_rows) - 1) >> log2_rows;
-  const int per_group = 256 / (a.g * (DV / 128));  // workgroups per group: one per compute unit, each with its share of the blocks
-  combine_project_bf16_kernel<512, DV><<<dim3(n_blocks < per_group || per_group < 1 ? n_blocks : per_group, a.g, DV / 128), 512, kLds, s>>>(
-      a, rows_per_group, log2_rows, n_blocks);
-  return hipGetLastError();
+  // half of the value dims per workgroup where twice as many workgroups still run at once
+  if (n_blocks * a.g * (DV / 64) <= 256) return launch_combine_project_dims<DV, 64>(a, log2_rows, n_blocks, s);
+  return launch_combine_project_dims<DV, 128>(a, log2_rows, n_blocks, s);
 }
 
 hipError_t launch_combine_project_bf16(const CombineArgs& a, hipStream_t s) {

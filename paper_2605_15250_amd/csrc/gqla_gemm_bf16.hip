@@ -622,6 +622,37 @@ constexpr int kCompressUnit = 32 * kCompressK * 2;    // bytes of a unit: 32 row
 constexpr int kCompressKeys = kCompressTok * kCompressK * 2;
 constexpr int kCompressLds = 4 * kCompressUnits * kCompressUnit + kCompressKeySlots * kCompressKeys;  // all 160 KB
 
+// The two 64-token halves of a tile: page and slot (P is a multiple of 64, so a half lies in one page).  A half
+// without tokens or behind a page id outside the pool reads page 0 instead: a token is one MFMA column, and the
+// columns of such a half are never stored.
+// The four table entries (two halves, two caches) come with one load, a lane each.
+struct CompressHalves {
+  const char* src[2];
+  int32_t pg_out[2];
+};
+template <int DH, int DV, int DR>
+__device__ __forceinline__ CompressHalves compress_halves(const CompressArgs& a, int b, int tok0, int L) {
+  const int lane = threadIdx.x & 63, P = a.expanded.page_size;
+  const int64_t in_page_bytes = (int64_t)P * (a.g * (DH + DV) + DR) * 2;
+  const int my_tok = tok0 + 64 * (lane & 1);
+  // (selected field by field: through a reference to either view a lane would load the fields from memory first)
+  const bool out = lane & 2;
+  const int p = my_tok / P, max_pages = out ? a.latent.max_pages : a.expanded.max_pages, num_pages = out ? a.latent.num_pages : a.expanded.num_pages;
+  const int32_t* const table = out ? a.latent.page_table : a.expanded.page_table;
+  int32_t pg = -1;
+  if (my_tok < L && p < max_pages) pg = table ? table[(int64_t)b * max_pages + p] : b * max_pages + p;
+  if ((uint32_t)pg >= (uint32_t)num_pages) pg = -1;
+  CompressHalves r;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int tk = tok0 + 64 * e;
+    const int32_t pin = __builtin_amdgcn_readlane(pg, e);
+    r.pg_out[e] = pin >= 0 ? __builtin_amdgcn_readlane(pg, 2 + e) : -1;
+    r.src[e] = (const char*)a.expanded.pool + (pin >= 0 ? pin : 0) * in_page_bytes + (pin >= 0 ? tk % P : 0) * 16;
+  }
+  return r;
+}
+
 // Tile `id` of the numbering: 128-token tile `blk` of sequence b, which has L tokens.
 template <int DH, int DV, int RKV, int DR>
 __device__ __forceinline__ void compress_tile(const CompressArgs& a, char* smem, int id, int b, int blk, int L) {
@@ -636,26 +667,9 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, char* smem,
   const int P = a.expanded.page_size;
   const int tok0 = blk * kCompressTok;
   const int K = a.g * DH;
-  const int64_t in_page_bytes = (int64_t)P * (a.g * (DH + DV) + DR) * 2;
 
-  // the two 64-token halves of the tile: page and slot (P is a multiple of 64, so a half lies in one page).  A half
-  // without tokens or behind a page id outside the pool reads page 0 instead: a token is one MFMA column, and the
-  // columns of such a half are never stored.
-  // The four table entries (two halves, two caches) come with one load, a lane each.
-  const char* half_src[2];
-  int32_t pg_out[2];
-  {
-    const int my_tok = tok0 + 64 * (lane & 1);
-    const CacheView& view = lane & 2 ? a.latent : a.expanded;
-    const int32_t pg = my_tok < L ? page_of(view, b, my_tok / P) : -1;
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int tk = tok0 + 64 * e;
-      const int32_t pin = __builtin_amdgcn_readlane(pg, e);
-      pg_out[e] = pin >= 0 ? __builtin_amdgcn_readlane(pg, 2 + e) : -1;
-      half_src[e] = (const char*)a.expanded.pool + (pin >= 0 ? pin : 0) * in_page_bytes + (pin >= 0 ? tk % P : 0) * 16;
-    }
-  }
+  const CompressHalves hv = compress_halves<DH, DV, DR>(a, b, tok0, L);
+  const char* const* half_src = hv.src;
   // k_R of the tile, kept for the end: vector plane (tid >> 7) + 2 i of token tid % 128
   u32x4 kr[DR / 16];
   {
@@ -801,11 +815,11 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, char* smem,
   __syncthreads();
 #pragma unroll
   for (int e = 0; e < 2; ++e) {
-    if (pg_out[e] < 0) continue;
+    if (hv.pg_out[e] < 0) continue;
     const int tk = tok0 + 64 * e;
     constexpr int VPR = W / 8;                        // 16-byte vectors per row
     const int total = min(64, L - tk) * VPR;
-    u32x4* dst = (u32x4*)((char*)a.latent.pool + ((int64_t)pg_out[e] * P + tk % P) * (W * 2));
+    u32x4* dst = (u32x4*)((char*)a.latent.pool + ((int64_t)hv.pg_out[e] * P + tk % P) * (W * 2));
     for (int v = tid; v < total; v += 256) {
       const int r = v / VPR, c = v % VPR;
       __builtin_nontemporal_store(*(const u32x4*)(smem + (64 * e + r) * PITCH + c * 16), dst + v);
@@ -813,18 +827,139 @@ __device__ __forceinline__ void compress_tile(const CompressArgs& a, char* smem,
   }
 }
 
-// Grid as in the expansion: bounded, a workgroup takes tile blockIdx.x, then the one a grid further, and so on.
+// A share of the latent dims of a tile (a quarter or a half: 128 RT dims from 128 RT part on), for calls with few tiles: a tile
+// alone is 1024 MFMAs per wave and 1 MB of A^+ through one unit, 14 us, while most of the chip idles.  Wave w owns 32 RT latent
+// dims of all 128 tokens.  Stages of 64 k hold 128 RT rows of A^+ (panel layout of gqla_lds.h) and the keys of the tile (as
+// above), 16 RT and 16 KB, in a ring of five or three; one barrier per stage: stage p is awaited (counted: requests complete in
+// order), and the buffer that stage p - 1 has just left takes the requests of stage p + NS - 1.  What bounds it is the unit's
+// memory path (64 bytes a clock) and the start and end of a tile.  Whole tiles -> shares, g d_h = 1024: one sequence of 2400
+// tokens 24.1 -> 15.0 us, 76 tiles of four 24.8 -> 22.2.
+constexpr int kCompressQuarterTiles = 64, kCompressHalfTiles = 96;   // at most: see the kernel below
+template <int DH, int DV, int RKV, int DR, int RT>
+__device__ __forceinline__ void compress_part(const CompressArgs& a, char* smem, int id, int b, int blk, int L, int part) {
+  constexpr int W = RKV + DR, DIMS = 128 * RT, NS = RT == 1 ? 5 : 3;
+  constexpr int ABYTES = DIMS * kCompressK * 2, STAGE = ABYTES + kCompressKeys;
+  constexpr int PITCH = DIMS * 2 + 16;                 // bytes per token of the output tile in LDS
+  static_assert(NS * STAGE <= kCompressLds && kCompressTok * PITCH <= kCompressLds, "the rings, and the output tile over them");
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, h = lane >> 5;
+  const int P = a.expanded.page_size;
+  const int tok0 = blk * kCompressTok;
+  const int K = a.g * DH;
+  const CompressHalves hv = compress_halves<DH, DV, DR>(a, b, tok0, L);
+  const int64_t plane = (int64_t)P * 16;              // bytes of one vector plane of the page
+  // k_R of the tile (first share only), kept for the end: vector plane (tid >> 7) + 2 i of token tid % 128
+  u32x4 kr[DR / 16];
+  if (part == 0) {
+    const int tk = tid & (kCompressTok - 1);
+    const char* src = (tk & 64 ? hv.src[1] : hv.src[0]) + (int64_t)a.g * P * (DH + DV) * 2 + (tk & 63) * 16;
+#pragma unroll
+    for (int i = 0; i < DR / 16; ++i) kr[i] = *(const u32x4*)(src + (int64_t)((tid >> 7) + 2 * i) * P * 16);
+  }
+  const int stages = K / kCompressK;
+  int at = (id >> 3) % stages;                        // rotated walk, as above
+  int fill = 0;
+  const uint32_t a_off = (uint32_t)((lane >> 3) * K * 2 + (((lane & 7) ^ lds_swz(8 * wave + (lane >> 3))) << 4));  // rows 8 (wave + 4 j) ..
+  const char* const a_rows = (const char*)a.w_inv + (int64_t)(DIMS * part) * K * 2;
+  auto request = [&]() __attribute__((always_inline)) {  // this wave's share of the next stage
+    char* const buf = smem + fill * STAGE;
+    fill = fill + 1 == NS ? 0 : fill + 1;
+    auto dma = [&](char* dst, uint32_t off, const char* src) __attribute__((always_inline)) {
+      const uint32_t d = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)dst);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(d), "v"(off), "s"(src) : "memory");
+    };
+#pragma unroll
+    for (int j = 0; j < 4 * RT; ++j) dma(buf + (wave + 4 * j) * 1024, a_off, a_rows + (int64_t)(8 * (wave + 4 * j)) * K * 2 + at * (kCompressK * 2));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)                       // planes 2 wave, 2 wave + 1 of both token halves
+      dma(buf + ABYTES + (2 * wave + (i >> 1)) * (kCompressTok * 16) + (i & 1) * 1024, lane * 16, hv.src[i & 1] + (int64_t)(8 * at + 2 * wave + (i >> 1)) * plane);
+    at = at + 1 == stages ? 0 : at + 1;
+  };
+  f32x16 acc[RT][4];                                  // [latent tile][token tile]
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[rt][tt][i] = 0.f;
+#pragma unroll
+  for (int p = 0; p < NS - 1; ++p)
+    if (p < stages) request();
+  int slot = 0;
+  for (int st = 0; st < stages; ++st) {
+    const int behind = min(stages - 1 - st, NS - 2);  // stages requested behind this one
+    static_for<NS - 1>([&](auto q) {
+      if (behind == decltype(q)::value) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(decltype(q)::value * (4 * RT + 4)) : "memory");
+    });
+    __syncthreads();
+    if (st + NS - 1 < stages) request();
+    const char* const buf = smem + slot * STAGE;
+    slot = slot + 1 == NS ? 0 : slot + 1;
+    bf16x8 af[4][RT], kf[4][4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) af[ks][rt] = row_frag<DIMS>(buf, 32 * (RT * wave + rt) + n, 2 * ks + h);
+#pragma unroll
+      for (int tt = 0; tt < 4; ++tt) kf[ks][tt] = *(const bf16x8*)(buf + ABYTES + (2 * ks + h) * (kCompressTok * 16) + (32 * tt + n) * 16);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int tt = 0; tt < 4; ++tt) acc[rt][tt] = mfma32(af[ks][rt], kf[ks][tt], acc[rt][tt]);
+  }
+  __syncthreads();                                    // every wave has read the last stage
+#pragma unroll
+  for (int tt = 0; tt < 4; ++tt)
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *(u32x2*)(smem + (32 * tt + n) * PITCH + (32 * (RT * wave + rt) + 8 * q + 4 * h) * 2) =
+            u32x2{pack_bf16(acc[rt][tt][4 * q], acc[rt][tt][4 * q + 1]), pack_bf16(acc[rt][tt][4 * q + 2], acc[rt][tt][4 * q + 3])};
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    if (hv.pg_out[e] < 0) continue;
+    const int tk = tok0 + 64 * e, rows = min(64, L - tk);
+    char* const dst = (char*)a.latent.pool + ((int64_t)hv.pg_out[e] * P + tk % P) * (W * 2);
+    constexpr int VPR = DIMS / 8;                     // 16-byte vectors of a row's share
+    for (int v = tid; v < rows * VPR; v += 256)
+      __builtin_nontemporal_store(*(const u32x4*)(smem + (64 * e + v / VPR) * PITCH + v % VPR * 16), (u32x4*)(dst + (int64_t)(v / VPR) * (W * 2) + part * (DIMS * 2) + v % VPR * 16));
+    if (part == 0 && (tid & 64) == 64 * e && (tid & 63) < rows) {
+#pragma unroll
+      for (int i = 0; i < DR / 16; ++i) __builtin_nontemporal_store(kr[i], (u32x4*)(dst + (int64_t)(tid & 63) * (W * 2) + RKV * 2 + ((tid >> 7) + 2 * i) * 16));
+    }
+  }
+}
+
+// Grid as in the expansion: bounded, a workgroup takes tile blockIdx.x, then the one a grid further, and so on.  With few tiles
+// (the lengths live on the device: counted here) a workgroup takes a quarter or half of a tile's latent dims, as long as all
+// of them run at once (quarters in two rounds: 76 tiles 24.9 -> 29.4 us) and do not crowd the L2 that serves A^+ and the keys,
+// which each share reads again (halves: 76 tiles 24.8 -> 22.2 us, but 126 tiles 25.7 -> 26.7).
 template <int DH, int DV, int RKV, int DR>
 __global__ void __launch_bounds__(256) compress_bf16_kernel(CompressArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   BlockScan<kCompressTok> blocks;
   const int total = blocks.count(a.seq_lens, a.B, a.max_tokens);
-  for (int id = blockIdx.x; id < total; id += gridDim.x) {
-    int b, blk, L;
-    if (!blocks.find(id, b, blk, L)) return;  // whole workgroup
-    compress_tile<DH, DV, RKV, DR>(a, smem, id, b, blk, L);
-    __syncthreads();  // the next tile's requests go where this one's rows leave from
+  if (__builtin_expect(total > kCompressHalfTiles, 1)) {
+    for (int id = blockIdx.x; id < total; id += gridDim.x) {
+      int b, blk, L;
+      if (!blocks.find(id, b, blk, L)) return;  // whole workgroup
+      compress_tile<DH, DV, RKV, DR>(a, smem, id, b, blk, L);
+      __syncthreads();  // the next tile's requests go where this one's rows leave from
+    }
+    return;
   }
+  const int shares = total <= kCompressQuarterTiles ? 4 : 2, id = blockIdx.x;
+  int b, blk, L;
+  if (id >= shares * total || !blocks.find(id / shares, b, blk, L)) return;  // whole workgroup (the grid holds every share)
+  if (shares == 4) compress_part<DH, DV, RKV, DR, 1>(a, smem, id, b, blk, L, id & 3);
+  else compress_part<DH, DV, RKV, DR, 2>(a, smem, id, b, blk, L, id & 1);
 }
 
 // Workgroups of a launch over blocks of ragged sequences: eight rounds of 256.  Up to that number (half a million tokens of
@@ -841,8 +976,10 @@ static hipError_t launch_compress_dims(const CompressArgs& a, hipStream_t s) {
   static const hipError_t attr =
       hipFuncSetAttribute((const void*)compress_bf16_kernel<DH, DV, 512, 64>, hipFuncAttributeMaxDynamicSharedMemorySize, kCompressLds);
   if (attr != hipSuccess) return attr;
+  // as many workgroups as tiles that the rows of the page table could hold, and enough for the shares of a few
   const int64_t blocks = ((int64_t)a.max_tokens + kCompressTok - 1) / kCompressTok * a.B;
-  compress_bf16_kernel<DH, DV, 512, 64><<<(unsigned)std::min<int64_t>(blocks, kMaxWorkgroups), 256, kCompressLds, s>>>(a);
+  const int64_t grid = std::max(std::min<int64_t>(blocks, kMaxWorkgroups), std::min<int64_t>(4 * blocks, 256));
+  compress_bf16_kernel<DH, DV, 512, 64><<<(unsigned)grid, 256, kCompressLds, s>>>(a);
   return hipGetLastError();
 }
 

@@ -197,7 +197,9 @@ __device__ __forceinline__ int expand_parts(int rest, int groups) {  // shares o
 }
 
 // One block of 256 tokens (block `blk` of sequence b, which has L) and groups jj_begin .. jj_begin + jj_count - 1 of the slice.
-template <int DH, int DV, int RKV, int DR, bool FP8>
+// DIRECT: the weights come as the caller holds them, without step 1 (a launch of 5 us, as much as a short call's second): a stage
+// is staged as a panel of [512 latent dims][128 bytes] (gqla_lds.h) and its fragments are read transposed, two reads each.
+template <int DH, int DV, int RKV, int DR, bool FP8, bool DIRECT>
 __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* packed, char* smem, int b, int blk, int L, int jj_begin, int jj_count) {
   constexpr int W = RKV + DR;
   constexpr int KS = RKV / 16;
@@ -239,15 +241,28 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
       asm volatile("global_load_dwordx4 %0, %1, off" : "=a"(xf[nt][ks]) : "v"(in_row + ks * 16 + h * 8));
   }
 
-  // LDS-DMA of one stage: 64 instructions of 1 KB, 16 per wave, linear (the packed layout is already fragment order)
-  auto stage_in_step = [&](int stage, char* buf, int u) {  // u = 0..15
-    const char* src = (const char*)packed + (int64_t)stage * STAGE_BYTES + wave * (16 * 1024);
-    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)(buf + wave * (16 * 1024)));
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(lane * 16), "s"(src + u * 1024), "n"(u * 1024) : "memory", "scc");  // the add writes SCC
-  };
-  auto stage_in = [&](int stage, char* buf) {
+  // LDS-DMA of one stage: 64 instructions of 1 KB, 16 per wave, linear (the packed layout is already fragment order).  DIRECT: 8
+  // rows x 128 bytes of column block `mtp` of a weight matrix; the swizzle of a lane's row alternates with u.
+  uint32_t w_off[2][2];  // [kind][u & 1]
 #pragma unroll
-    for (int u = 0; u < 16; ++u) stage_in_step(stage, buf, u);
+  for (int i = 0; i < 4; ++i) w_off[i >> 1][i & 1] = (lane >> 3) * ((i >> 1 ? DV : DH) * 2) + (((lane & 7) ^ lds_swz(8 * (i & 1) + (lane >> 3))) << 4);
+  const TrNatural tr = make_tr_natural(lane);
+  auto stage_in_step = [&](int stage, auto SUBT, char* buf, int u) {  // u = 0..15; SUBT: stage % NSUB
+    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)(buf + wave * (16 * 1024)));
+    if constexpr (DIRECT) {
+      constexpr int sub = decltype(SUBT)::value, kind = sub >= NSK, mtp = kind ? sub - NSK : sub, dim = kind ? DV : DH;
+      const int jj = stage / NSUB;
+      const char* src = (const char*)(kind ? a.w_uv : a.w_uk) + (((int64_t)(a.group_begin + jj_begin + jj) * RKV + 8 * (16 * wave + u)) * dim + 64 * mtp) * 2;
+      const uint32_t off = w_off[kind][u & 1];
+      asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(off), "s"(src), "n"(u * 1024) : "memory", "scc");
+    } else {
+      const char* src = (const char*)packed + (int64_t)stage * STAGE_BYTES + wave * (16 * 1024) + u * 1024;
+      const uint32_t off = lane * 16;
+      asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(off), "s"(src), "n"(u * 1024) : "memory", "scc");  // the add writes SCC
+    }
+  };
+  auto stage_in = [&](int stage, auto SUBT, char* buf) {
+    static_for<16>([&](auto U) { stage_in_step(stage, SUBT, buf, decltype(U)::value); });
   };
   // results of the previous stage ([token tile][32-column half]), kept until the next stage's arithmetic is under way
   f32x16 accs[2][2][2];  // [stage parity][token tile][32-column half]: one set accumulates while the other is stored
@@ -258,7 +273,7 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
   // stores address the page through one uniform base and 32-bit offsets (a page is at most a few MB)
   const uint32_t plane_k = (uint32_t)DH * P, plane_v = (uint32_t)DV * P;          // elements of one group's K and V plane
   // from here on groups are counted from the share's first: its offset is in these and in `packed`
-  packed += (int64_t)jj_begin * NSUB * (STAGE_BYTES / 2);
+  if (!DIRECT) packed += (int64_t)jj_begin * NSUB * (STAGE_BYTES / 2);
   const uint32_t k_lane = (uint32_t)jj_begin * plane_k + (uint32_t)(slot0 + n) * 8 + (uint32_t)h * P * 8;   // K plane: token slot0 + n, 8-dim block + h
   const uint32_t v_lane = (uint32_t)jj_begin * plane_v + (uint32_t)((slot0 >> 3) + h) * DV * 8 + n * 8;     // V plane: dim n, 8-token block slot0/8 + h
   const bool wave_full = tokw + 64 <= L;                                          // no token of this wave lies beyond L_b
@@ -345,8 +360,7 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
     emit_prev(pack_prev(par, nt, e, qp), kind, mtp, jj, nt, e, qp);
   };
 
-  const int n_stages = jj_count * NSUB;
-  stage_in(0, smem);
+  stage_in(0, std::integral_constant<int, 0>{}, smem);
   wait_all_memory();
   __syncthreads();
   for (int jj = 0; jj < jj_count; ++jj) {
@@ -354,7 +368,15 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
       constexpr int sub = decltype(SUB)::value;
       const int stage = jj * NSUB + sub;
       const int odd = stage & 1;                       // LDS buffer of this stage
-      const char* buf = smem + odd * STAGE_BYTES + lane * 16;
+      const char* buf = smem + odd * STAGE_BYTES + (DIRECT ? 0 : lane * 16);
+      auto weight = [&](int ks, int e) __attribute__((always_inline)) -> bf16x8 {
+        if constexpr (DIRECT) return tr_natural_frag<RKV>(buf, tr, ks, e);
+        else return *(const bf16x8*)(buf + (2 * ks + e) * 1024);
+      };
+      // the stage after this one (behind the last: that one again, into the buffer nobody reads any more: no branch)
+      const bool last_group = jj + 1 == jj_count;
+      using Next = std::integral_constant<int, (sub + 1) % NSUB>;
+      const int next = sub + 1 < NSUB ? stage + 1 : (last_group ? jj * NSUB : stage + 1);
       f32x16 (&acc)[2][2] = accs[sub & 1];
       // the stage before this one, whose results leave in this stage's shadow (none at the start of a group when the
       // group's last stage has stored its own)
@@ -366,8 +388,8 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
         bf16x8 w[DEPTH + 1][2];
 #pragma unroll
         for (int ks = 0; ks < DEPTH; ++ks) {
-          w[ks][0] = *(const bf16x8*)(buf + (2 * ks) * 1024);
-          w[ks][1] = *(const bf16x8*)(buf + (2 * ks + 1) * 1024);
+          w[ks][0] = weight(ks, 0);
+          w[ks][1] = weight(ks, 1);
         }
         // A wave issues in order and is alone on its SIMD: whatever stands between two matrix instructions delays the
         // second one unless it fits into the 32 cycles the first one occupies the pipe.  The other work of a k-step is
@@ -390,14 +412,13 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
         for (int ks = 0; ks < KS; ++ks) {
           __builtin_amdgcn_sched_barrier(0);
           mm(ks, 0, 0);
-          if (ks + DEPTH < KS) w[(ks + DEPTH) % (DEPTH + 1)][0] = *(const bf16x8*)(buf + (2 * (ks + DEPTH)) * 1024);
+          if (ks + DEPTH < KS) w[(ks + DEPTH) % (DEPTH + 1)][0] = weight(ks + DEPTH, 0);
           __builtin_amdgcn_sched_barrier(0);
           mm(ks, 0, 1);
-          if (ks + DEPTH < KS) w[(ks + DEPTH) % (DEPTH + 1)][1] = *(const bf16x8*)(buf + (2 * (ks + DEPTH) + 1) * 1024);
+          if (ks + DEPTH < KS) w[(ks + DEPTH) % (DEPTH + 1)][1] = weight(ks + DEPTH, 1);
           __builtin_amdgcn_sched_barrier(0);
           mm(ks, 1, 0);
-          // (after the last stage this stages that stage once more, into the buffer nobody reads any more: no branch)
-          if (ks < 16) stage_in_step(min(stage + 1, n_stages - 1), smem + (odd ^ 1) * STAGE_BYTES, ks);
+          if (ks < 16) stage_in_step(next, Next{}, smem + (odd ^ 1) * STAGE_BYTES, ks);
           __builtin_amdgcn_sched_barrier(0);
           mm(ks, 1, 1);
           // the previous stage's results leave in the shadow of this stage's MFMAs
@@ -421,7 +442,7 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
           }
         }
       } else {
-        stage_in(min(stage + 1, n_stages - 1), smem + (odd ^ 1) * STAGE_BYTES);  // a wave without tokens still stages its share
+        stage_in(next, Next{}, smem + (odd ^ 1) * STAGE_BYTES);  // a wave without tokens still stages its share
       }
       wait_all_memory();
       __syncthreads();  // next stage has landed; everyone is done with this stage's buffer
@@ -460,7 +481,7 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
 // workgroups, as far as one round takes it (each reads the latent rows again).
 // The lengths live on the device and the host knows only what a page-table row could hold, so the grid is bounded and a
 // workgroup takes block blockIdx.x, then the one a grid further, and so on.
-template <int DH, int DV, int RKV, int DR, bool FP8>
+template <int DH, int DV, int RKV, int DR, bool FP8, bool DIRECT>
 __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __bf16* packed) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int gc = a.group_count;
@@ -479,7 +500,7 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
     int b, blk, L;
     if (!blocks.find(id, b, blk, L)) return;  // whole workgroup
     // (the last stage's barrier has freed both LDS buffers for the next block)
-    expand_block<DH, DV, RKV, DR, FP8>(a, packed, smem, b, blk, L, jj_begin, jj_end - jj_begin);
+    expand_block<DH, DV, RKV, DR, FP8, DIRECT>(a, packed, smem, b, blk, L, jj_begin, jj_end - jj_begin);
   }
 }
 
@@ -496,13 +517,16 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
 // FP8 = true: `expanded` is an 8-bit cache (E4M3 code planes, see the header); every result is first rounded to bf16,
 // the value the 16-bit cache would hold, and then quantised, so that the codes equal those of expanding into a 16-bit
 // cache and converting it.
-template <int DH, int DV, int RKV, int DR, bool FP8, int WAVES>
+// DIRECT (WAVES = 1): the weights come as the caller holds them, without a launch that repacks them: the wave's 32 columns of all
+// RKV rows go to LDS by LDS-DMA (64 bytes a row, back to back: 16 lanes of a transposed read meet every bank once) and are
+// read as the same fragments, transposed.
+template <int DH, int DV, int RKV, int DR, bool FP8, int WAVES, bool DIRECT>
 __global__ void __launch_bounds__(64 * WAVES) expand_tail_bf16_kernel(ExpandArgs a, const __bf16* packed) {
   constexpr int W = RKV + DR;
   constexpr int KS = RKV / 16;
   constexpr int NSK = DH / 64, NSUB = (DH + DV) / 64;
   static_assert(!FP8 || (DH == 128 && DV == 128), "the 8-bit page format is written for equal dims of 128");
-  static_assert(WAVES == 1 || WAVES == 2, "one half of a stage, or both halves");
+  static_assert(WAVES == 1 || (WAVES == 2 && !DIRECT), "one half of a stage, or both halves");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
@@ -510,6 +534,16 @@ __global__ void __launch_bounds__(64 * WAVES) expand_tail_bf16_kernel(ExpandArgs
   const int jj = stage / NSUB, sub = stage % NSUB;
   const int kind = sub >= NSK, mtp = kind ? sub - NSK : sub;
   const int e = WAVES == 1 ? blockIdx.x & 1 : wave & 1;
+  __shared__ __attribute__((aligned(16))) char w_lds[DIRECT ? RKV * 64 : 16];
+  if constexpr (DIRECT) {  // (ahead of the chain length -> page -> latent row)
+    const int dim = kind ? DV : DH;
+    const char* w = (const char*)(kind ? a.w_uv : a.w_uk) + ((int64_t)(a.group_begin + jj) * RKV * dim + 64 * mtp + 32 * e) * 2;
+    const uint32_t off = (lane >> 2) * (dim * 2) + (lane & 3) * 16;  // 16 rows an instruction
+    const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)w_lds);
+#pragma unroll
+    for (int u = 0; u < RKV / 16; ++u)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst + u * 1024), "v"(off), "s"(w + (int64_t)(16 * u) * (dim * 2)) : "memory");
+  }
   const int idx = blockIdx.y * 32 + n;  // this lane's token in the list
   const int P = a.latent.page_size;
   const int gc = a.group_count;
@@ -537,9 +571,22 @@ __global__ void __launch_bounds__(64 * WAVES) expand_tail_bf16_kernel(ExpandArgs
   bf16x8 xf[KS], wv[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) asm volatile("global_load_dwordx4 %0, %1, off" : "=a"(xf[ks]) : "v"(row + ks * 16 + h * 8));
+  if constexpr (!DIRECT) {
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) wv[ks] = *(const bf16x8*)(wf + (int64_t)ks * 1024);
+    for (int ks = 0; ks < KS; ++ks) wv[ks] = *(const bf16x8*)(wf + (int64_t)ks * 1024);
+  }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if constexpr (DIRECT) {
+    const int i16 = lane & 15;  // addresses row 8 h + i16 / 4 (+ 4) of the k-step, columns 16 ((lane / 16) % 2) + 4 (i16 % 4) ..
+    const char* base = w_lds + (8 * h + (i16 >> 2)) * 64 + ((lane >> 4) & 1) * 32 + (i16 & 3) * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const i16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(base + ks * 1024));
+      const i16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4*)(base + ks * 1024 + 256));
+      const i16x8 r = {x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+      wv[ks] = __builtin_bit_cast(bf16x8, r);
+    }
+  }
   f32x16 acc;
   mfma_va_first(acc, wv[0], xf[0]);
 #pragma unroll
@@ -1017,6 +1064,13 @@ template <int DH, int DV, bool FP8>
 static hipError_t launch_expand_tail_dims(const ExpandArgs& a, void* ws, hipStream_t s) {
   constexpr int NSUB = (DH + DV) / 64;
   const int tokens = a.B * a.tail;
+  const int stages = a.group_count * NSUB, tiles = (tokens + 31) / 32;
+  // Weights that are not repacked yet and few tokens: taken as they are (4 tokens, 8 groups, 8-bit step 27.8 -> 23.0 us, 64 tokens
+  // 201.3 -> 198.6: a launch of 5 us less, 2 us more for the transposed reads).
+  if (a.weights == 0 && tiles <= 8) {
+    expand_tail_bf16_kernel<DH, DV, 512, 64, FP8, 1, true><<<dim3(stages * 2, tiles), 64, 0, s>>>(a, nullptr);
+    return hipGetLastError();
+  }
   if (a.weights != 2) {
     pack_weights_bf16_kernel<DH, DV, 512><<<dim3(a.group_count * NSUB, 512 / 64), 256, 0, s>>>(a, (__bf16*)ws);
     const hipError_t e = hipGetLastError();
@@ -1028,11 +1082,10 @@ static hipError_t launch_expand_tail_dims(const ExpandArgs& a, void* ws, hipStre
   // rows by itself, and from a few hundred waves on that costs more than the spread gives.  Two waves on the same rows then:
   // one group, 1024 waves 9.6 -> 8.8 us, 4096 waves 33.8 -> 29.5 us; 512 waves 5.9 us either way, 256 waves 4.9 against 5.5.
   // (8 groups, 8192 tokens: 104 us in pairs, 92 us as single waves; 4 groups the same to 3 %.)
-  const int stages = a.group_count * NSUB, tiles = (tokens + 31) / 32;
   if (stages <= 4 && (int64_t)tiles * stages * 2 >= 512)
-    expand_tail_bf16_kernel<DH, DV, 512, 64, FP8, 2><<<dim3(stages, tiles), 128, 0, s>>>(a, (const __bf16*)ws);
+    expand_tail_bf16_kernel<DH, DV, 512, 64, FP8, 2, false><<<dim3(stages, tiles), 128, 0, s>>>(a, (const __bf16*)ws);
   else
-    expand_tail_bf16_kernel<DH, DV, 512, 64, FP8, 1><<<dim3(stages * 2, tiles), 64, 0, s>>>(a, (const __bf16*)ws);
+    expand_tail_bf16_kernel<DH, DV, 512, 64, FP8, 1, false><<<dim3(stages * 2, tiles), 64, 0, s>>>(a, (const __bf16*)ws);
   return hipGetLastError();
 }
 
@@ -1042,25 +1095,33 @@ hipError_t launch_expand_tail_bf16(const ExpandArgs& a, void* ws, hipStream_t s)
 
 hipError_t launch_expand_tail_fp8(const ExpandArgs& a, void* ws, hipStream_t s) { return launch_expand_tail_dims<128, 128, true>(a, ws, s); }
 
-template <int DH, int DV, bool FP8>
-static hipError_t launch_expand_one_shot(const ExpandArgs& a, void* ws, hipStream_t s) {
+template <int DH, int DV, bool FP8, bool DIRECT>
+static hipError_t launch_expand_kernel(const ExpandArgs& a, const void* ws, unsigned grid, hipStream_t s) {
   constexpr int kLds = 2 * (512 / 16) * 2 * 1024;
-  constexpr int NSUB = (DH + DV) / 64;
   // once per process (function-local statics are initialised under a lock); an error is reported by every call
   static const hipError_t attr =
-      hipFuncSetAttribute((const void*)expand_bf16_kernel<DH, DV, 512, 64, FP8>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+      hipFuncSetAttribute((const void*)expand_bf16_kernel<DH, DV, 512, 64, FP8, DIRECT>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
+  expand_bf16_kernel<DH, DV, 512, 64, FP8, DIRECT><<<grid, 256, kLds, s>>>(a, (const __bf16*)ws);
+  return hipGetLastError();
+}
+template <int DH, int DV, bool FP8>
+static hipError_t launch_expand_one_shot(const ExpandArgs& a, void* ws, hipStream_t s) {
+  constexpr int NSUB = (DH + DV) / 64;
   // The lengths live on the device, so the kernel decides how the last round is shared out; whole rounds of 256, so that
   // those shares find workgroups as well.  Measured against a grid over (blocks of the longest sequence, sequences), whose holes
   // gave some dies a third round of blocks: one sequence of 8192 tokens, 8 groups 80 -> 31 us; 20 ragged sequences of 3000 to 6000
   // tokens into the 8-bit cache 216 -> 190 us; 122 680 ragged tokens in 32 sequences 286 -> 240 us.
   const int64_t blocks = ((int64_t)a.max_tokens + 255) / 256 * a.B;
   const unsigned grid = (unsigned)std::min<int64_t>((blocks + 255) & ~(int64_t)255, kMaxWorkgroups);
+  // Few blocks (what the rows of the page table could hold): the weights as they are, without the launch that repacks them.  The
+  // transposed reads cost a block 3 %: 10 blocks, 8 groups 24.6 -> 21.8 us, 66 blocks, 4 groups of (192, 256) 31.2 -> 30.6, 80
+  // blocks the same either way, 128 blocks 64.1 -> 66.0.
+  if (blocks <= 72) return launch_expand_kernel<DH, DV, FP8, true>(a, nullptr, grid, s);
   pack_weights_bf16_kernel<DH, DV, 512><<<dim3(a.group_count * NSUB, 512 / 64), 256, 0, s>>>(a, (__bf16*)ws);
-  hipError_t e = hipGetLastError();
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  expand_bf16_kernel<DH, DV, 512, 64, FP8><<<grid, 256, kLds, s>>>(a, (const __bf16*)ws);
-  return hipGetLastError();
+  return launch_expand_kernel<DH, DV, FP8, false>(a, ws, grid, s);
 }
 hipError_t launch_expand_bf16(const ExpandArgs& a, void* ws, hipStream_t s) {
   return a.d_h == 192 ? launch_expand_one_shot<192, 256, false>(a, ws, s) : launch_expand_one_shot<128, 128, false>(a, ws, s);

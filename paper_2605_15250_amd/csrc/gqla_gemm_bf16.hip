@@ -478,7 +478,10 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
 
 // Workgroup -> (256-token block, share of the groups).  A compute unit holds one workgroup: blocks run in rounds of 256.
 // Blocks of whole rounds keep all groups; if the last round has at most 128, its blocks share their groups out over `parts`
-// workgroups, as far as one round takes it (each reads the latent rows again).
+// workgroups, as far as one round takes it (each reads the latent rows again).  With more blocks in it than 128, but at least two
+// groups' time to win, its (block, group) pairs are dealt out evenly in order, and a workgroup may go from one block into the
+// next (8 groups, 146 ragged blocks into the 8-bit cache 102.1 -> 83.4 us, 144 blocks 88.7 -> 81.0, 400 216 -> 198, 184 the same to
+// 1.5 %; one block a workgroup leaves the other units idle).
 // The lengths live on the device and the host knows only what a page-table row could hold, so the grid is bounded and a
 // workgroup takes block blockIdx.x, then the one a grid further, and so on.
 template <int DH, int DV, int RKV, int DR, bool FP8, bool DIRECT>
@@ -489,18 +492,29 @@ __global__ void __launch_bounds__(256) expand_bf16_kernel(ExpandArgs a, const __
   const int total = blocks.count(a.seq_lens, a.B, a.max_tokens);
   const int whole = total & ~255, rest = total & 255;
   const int parts = rest > 0 && rest <= 128 && gc > 1 ? expand_parts(rest, gc) : 1;
-  for (int wg = blockIdx.x; wg < whole + rest * parts; wg += gridDim.x) {
-    int id = wg, jj_begin = 0, jj_end = gc;
-    if (wg >= whole && parts > 1) {
+  const bool even = rest > 128 && rest * gc <= 256 * (gc - 2);
+  for (int wg = blockIdx.x; wg < whole + (even ? 256 : rest * parts); wg += gridDim.x) {
+    int id = wg, jj = 0, left = gc;  // `left` groups from group jj of block id on, over the end of the block into the next
+    if (wg >= whole && even) {
+      const int u0 = (wg - whole) * (rest * gc) / 256, u1 = (wg - whole + 1) * (rest * gc) / 256;
+      id = whole + u0 / gc;
+      jj = u0 % gc;
+      left = u1 - u0;
+    } else if (wg >= whole && parts > 1) {
       const int part = (wg - whole) % parts;
       id = whole + (wg - whole) / parts;
-      jj_begin = gc * part / parts;
-      jj_end = gc * (part + 1) / parts;
+      jj = gc * part / parts;
+      left = gc * (part + 1) / parts - jj;
     }
-    int b, blk, L;
-    if (!blocks.find(id, b, blk, L)) return;  // whole workgroup
-    // (the last stage's barrier has freed both LDS buffers for the next block)
-    expand_block<DH, DV, RKV, DR, FP8, DIRECT>(a, packed, smem, b, blk, L, jj_begin, jj_end - jj_begin);
+    for (; left > 0; ++id) {
+      int b, blk, L;
+      if (!blocks.find(id, b, blk, L)) return;  // whole workgroup
+      const int n = min(gc - jj, left);
+      // (the last stage's barrier has freed both LDS buffers for the next block)
+      expand_block<DH, DV, RKV, DR, FP8, DIRECT>(a, packed, smem, b, blk, L, jj, n);
+      left -= n;
+      jj = 0;
+    }
   }
 }
 

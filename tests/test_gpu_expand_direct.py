@@ -1,5 +1,7 @@
-"""Expansion and tail expansion that take the weights as the caller holds them (few blocks, few tokens) against the paths that
-repack them first: the same bits, at the edges between the two -- 72 blocks that the page-table rows could hold, 256 tail tokens -- and on ragged, padded and empty rows, slices of the groups and both pairs of dims."""
+"""The ways the expansion shares its work out, each against another of them, bit for bit: weights as the caller holds them (few
+blocks, few tail tokens) against repacked ones, at the edges between the two -- 72 blocks that the page-table rows could hold,
+256 tail tokens -- and on ragged, padded and empty rows, slices of the groups and both pairs of dims; a last round whose
+(block, group) pairs are dealt out evenly."""
 import numpy as np
 import pytest
 import torch
@@ -95,3 +97,38 @@ def test_tail(g, d_h, d_v, nb, tail, fp8):
         wrote = outs[0] != 0x5A
         assert torch.equal(outs[0][wrote], outs[1][wrote])
         assert int(wrote.sum()) >= sum(min(n, tail) for n in lens) * elems * 0.9     # (a code may equal the fill)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("g,d_h,d_v,blocks", [
+    (8, 128, 128, 129),                                  # the fewest whose (block, group) pairs are dealt out evenly
+    (8, 128, 128, 192),                                  # the most: six groups a workgroup
+    (8, 128, 128, 193),                                  # one block a workgroup
+    (8, 128, 128, 256 + 150),                            # behind a whole round
+    (3, 128, 128, 82),                                   # shares of one and two groups, as before
+    (5, 192, 256, 150),
+])
+def test_last_round_dealt_out_evenly(g, d_h, d_v, blocks, fp8):
+    """One call over all sequences against calls over 40 of them at a time: the same bits."""
+    if fp8 and d_h != 128:
+        pytest.skip("the 8-bit expanded cache has key and value dims of 128")
+    lens = [1 + (29 * i) % 90 for i in range(blocks - 2)] + [300]
+    B, s = _setup(g, d_h, d_v, lens, 292)                # rows that could hold 73 blocks: repacked weights in every call
+    ws = torch.empty(g * s["r_kv"] * (d_h + d_v) * 2, dtype=torch.uint8, device="cuda")
+    elems = B.gqla_expanded_fp8_bytes_per_token(g, d_h, s["d_r"]) if fp8 else 2 * (g * (d_h + d_v) + s["d_r"])
+    outs = []
+    for step in (len(lens), 40):
+        out = torch.full((s["num_pages"] * 64 * elems,), 0x5A, dtype=torch.uint8, device="cuda")
+        for b0 in range(0, len(lens), step):
+            lens_d, table = s["lens"][b0:b0 + step].clone(), s["table"][b0:b0 + step].contiguous()
+            shape = B.make_shape(len(lens_d), 4 * g, g, d_h, s["r_kv"], s["d_r"], 1, B.GQLA_BF16, 0.0, d_v)
+            lat = B.make_cache(s["pool"], lens_d, table, 64, 292, s["num_pages"])
+            exp = B.make_cache(out, lens_d, table, 64, 292, s["num_pages"], g)
+            print("expand even", g, d_h, blocks, fp8, step, b0, flush=True)
+            if fp8:
+                B.gqla_expand_cache_fp8(shape, lat, s["w_uk"], s["w_uv"], 0, g, exp, 0.02, 0.03, ws)
+            else:
+                B.gqla_expand_cache(shape, lat, s["w_uk"], s["w_uv"], 0, g, exp, ws)
+            torch.cuda.synchronize()
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])

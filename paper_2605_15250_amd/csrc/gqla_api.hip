@@ -644,7 +644,7 @@ size_t gqla_output_projection_workspace_bytes(const gqla_shape* shape, int32_t d
   const int64_t M = (int64_t)shape->batch * shape->s_q, K = (int64_t)shape->h_q * value_dim(shape);
   if (M == 0 || d_model % 128 || K % 256 || K > (1 << 24)) return 0;
   int krange = 0;
-  const int ksplit = out_proj_split((int)M, (int)K, d_model, &krange);
+  const int ksplit = out_proj_split((int)M, (int)K, d_model, out_proj_rows((int)M, (int)K, d_model), &krange);
   return ksplit > 1 ? (size_t)ksplit * M * d_model * sizeof(float) : 0;
 }
 
@@ -668,10 +668,16 @@ gqla_status gqla_output_projection(const gqla_shape* shape, int32_t d_model, con
   a.D = d_model;
   a.ksplit = 1;
   a.krange = (int32_t)K;
+  a.rows = 0;
   hipStream_t s = static_cast<hipStream_t>(stream);
   if (shape->dtype != GQLA_BF16) return launch_out_proj_f32(a, s) == hipSuccess ? GQLA_OK : GQLA_ERR_DEVICE;
   if (d_model % 128 || K % 256 || K > (1 << 24)) return GQLA_ERR_SHAPE;   // the kernel's row offsets inside a tile are 32-bit
-  a.ksplit = out_proj_split(a.M, a.K, a.D, &a.krange);
+  a.rows = out_proj_rows(a.M, a.K, a.D);
+  a.ksplit = out_proj_split(a.M, a.K, a.D, a.rows, &a.krange);
+  if (a.rows == 256 && ws_bytes < (size_t)a.ksplit * M * d_model * sizeof(float)) {   // scratch for half as many ranges: 128 rows
+    a.rows = 128;
+    a.ksplit = out_proj_split(a.M, a.K, a.D, a.rows, &a.krange);
+  }
   if (a.ksplit > 1) {
     if (!ws) return GQLA_ERR_NULL;
     if (ws_bytes < (size_t)a.ksplit * M * d_model * sizeof(float)) return GQLA_ERR_WORKSPACE;

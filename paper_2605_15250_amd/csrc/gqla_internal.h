@@ -101,6 +101,7 @@ struct OutProjArgs {
   void* y;          // [M][D]
   float* partial;   // [ksplit][M][D] when ksplit > 1
   int32_t M, K, D, ksplit, krange;
+  int32_t rows;     // per workgroup: 64, 128 or 256
 };
 
 struct AbsorbQueryArgs {
@@ -142,7 +143,8 @@ hipError_t launch_compress_bf16(const CompressArgs&, hipStream_t);
 hipError_t launch_rope_step(const RopeArgs&, bool bf16, hipStream_t);
 hipError_t launch_out_proj_f32(const OutProjArgs&, hipStream_t);
 hipError_t launch_out_proj_bf16(const OutProjArgs&, hipStream_t);
-int out_proj_split(int M, int K, int D, int* krange);  // k-ranges of the bf16 kernel (needs D % 128 == 0, K % 256 == 0)
+int out_proj_rows(int M, int K, int D);
+int out_proj_split(int M, int K, int D, int rows, int* krange);  // k-ranges of the bf16 kernel (needs D % 128 == 0, K % 256 == 0)
 hipError_t launch_decode_gqa_fp8(const DecodeArgs&, float k_scale, float v_scale, hipStream_t);
 
 hipError_t launch_probe_stream_read(const void* src, size_t bytes, uint32_t* sink, int blocks, hipStream_t);

@@ -1,5 +1,6 @@
 // The steps either side of the decode path: the decoupled rotary embedding of the step's q^R and k^R (Sec. 3.1,
 // "Architecture") and the output projection y = W^O [o_1; ...; o_hq] (last line of both path equations).
+#include <algorithm>
 #include <type_traits>
 
 #include "gqla_device.h"
@@ -86,7 +87,7 @@ __global__ void __launch_bounds__(64) out_proj_f32_kernel(OutProjArgs a) {
 
 // ---- output projection, bf16 ------------------------------------------------------------------------------------------
 // Y^T[n][m] = W^O[n][k] o^T[k][m]: few rows (M = B s_q), a weight matrix that is read once from HBM.  A workgroup of 4
-// waves owns 128 output columns x up to 128 rows x a range of k.  W^O reaches the matrix cores through LDS: whole
+// waves owns 128 output columns x up to 128 rows x a range of k (of 8 waves: up to 256 rows).  W^O reaches the matrix cores through LDS: whole
 // 128-byte pieces of its rows are requested with LDS-DMA (8 rows x 128 bytes per wave instruction, each lane 16 bytes of
 // a row; every byte of every line is fetched exactly once and never passes through registers) into the panel layout of
 // gqla_lds.h, in stages of 64 k, and read back as conflict-free 16-byte A fragments.  The rows of o for the stage travel
@@ -99,17 +100,20 @@ __global__ void __launch_bounds__(64) out_proj_f32_kernel(OutProjArgs a) {
 constexpr int kOpN = 128;                    // output columns per workgroup
 constexpr int kOpK = 256;                    // granule of the k-ranges
 constexpr int kOsK = 64;                     // k per stage: one 128-byte panel per row
-constexpr int kOsStages = 4;                 // ring depth (measured: five and six stages, which would still fit, change nothing)
 constexpr int kOsWBytes = kOpN * 128;        // W^O part of a stage: 128 rows (output columns) x 128 bytes
 template <int MT>
-constexpr int out_proj_lds() { return kOsStages * (kOsWBytes + 32 * MT * 128); }
+constexpr int out_proj_stages() { return MT > 4 ? 3 : 4; }   // ring depth (64, 128 rows: five and six stages, which would still fit, change nothing)
+template <int MT>
+constexpr int out_proj_waves() { return MT > 4 ? 8 : 4; }
+template <int MT>
+constexpr int out_proj_lds() { return out_proj_stages<MT>() * (kOsWBytes + 32 * MT * 128); }
 
 template <int MT>
-__global__ void __launch_bounds__(256) out_proj_bf16_kernel(OutProjArgs a) {
+__global__ void __launch_bounds__(64 * out_proj_waves<MT>()) out_proj_bf16_kernel(OutProjArgs a) {
   constexpr int OB = 32 * MT * 128;          // o part of a stage: 32 MT rows x 128 bytes
   constexpr int STAGE = kOsWBytes + OB;
-  constexpr int NS = kOsStages;
-  constexpr int PER = 4 + MT;                // LDS-DMA requests per wave and stage: 16 + 4 MT blocks of 8 rows over 4 waves
+  constexpr int NS = out_proj_stages<MT>(), NW = out_proj_waves<MT>();
+  constexpr int WPER = 16 / NW, OPER = 4 * MT / NW, PER = WPER + OPER;   // LDS-DMA requests per wave and stage: 16 + 4 MT blocks of 8 rows
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -132,16 +136,16 @@ __global__ void __launch_bounds__(256) out_proj_bf16_kernel(OutProjArgs a) {
   const int64_t stride = (int64_t)a.K * 2;   // bytes from one row of W^O (or of o) to the next
 
   // staging role of this lane inside a block of 8 rows: row (lane >> 3) of the block, and the 16-byte chunk of the row
-  // that the panel layout wants at LDS position lane & 7 (blocks of one wave are 4 apart, so the swizzle term is fixed)
+  // that the panel layout wants at LDS position lane & 7 (blocks of one wave are NW apart, so the swizzle term is fixed)
   const int srow = lane >> 3;
   const int schunk = (lane & 7) ^ lds_swz(8 * wave + srow);
   const uint32_t w_off = (uint32_t)(srow * stride + schunk * 16);
   const char* wsrc = (const char*)a.w_o + (int64_t)col0 * stride + (int64_t)kbeg * 2;
   const char* osrc = (const char*)a.o + (int64_t)m0 * stride + (int64_t)kbeg * 2;
   // rows of o beyond the call's last row read that last row instead (their results are never stored)
-  uint32_t o_off[MT];
+  uint32_t o_off[OPER];
 #pragma unroll
-  for (int j = 0; j < MT; ++j) o_off[j] = (uint32_t)(min(8 * (wave + 4 * j) + srow, rows - 1) * stride + schunk * 16);
+  for (int j = 0; j < OPER; ++j) o_off[j] = (uint32_t)(min(8 * (wave + NW * j) + srow, rows - 1) * stride + schunk * 16);
 
   // The stages of a k-range are taken in rotated order, from a start that differs from one column tile to the next:
   // rows of W^O lie a multiple of 512 bytes apart, so workgroups that walk their k-ranges in step would ask the same
@@ -155,22 +159,23 @@ __global__ void __launch_bounds__(256) out_proj_bf16_kernel(OutProjArgs a) {
     const char* ok = osrc + (int64_t)kpos * (kOsK * 2);
     kpos = kpos + 1 == nst ? 0 : kpos + 1;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int blk = wave + 4 * j;
+    for (int j = 0; j < WPER; ++j) {
+      const int blk = wave + NW * j;
       const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)(buf + blk * 1024));
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(dst), "v"(w_off), "s"(wk + (int64_t)blk * 8 * stride) : "memory");
     }
 #pragma unroll
-    for (int j = 0; j < MT; ++j) {
-      const int blk = wave + 4 * j;
+    for (int j = 0; j < OPER; ++j) {
+      const int blk = wave + NW * j;
       const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_ptr_t)(buf + kOsWBytes + blk * 1024));
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(o_off[j]), "s"(ok) : "memory");
     }
   };
 
   // Output tile of a wave: CW x RW blocks of 32 columns x 32 rows (64 rows: the four waves side by side, 1 x 2 each;
-  // 128 rows: two by two waves, 2 x 2 each, so that a fragment read from LDS serves two matrix instructions).
-  constexpr int CW = MT / 2, RW = 2, NWC = kOpN / (32 * CW);
+  // 128 rows: two by two waves, 2 x 2 each, 256 rows: two by four, so that a fragment read from LDS serves two matrix
+  // instructions).
+  constexpr int CW = MT > 2 ? 2 : 1, RW = 2, NWC = kOpN / (32 * CW);
   const int wc = wave % NWC, wr = wave / NWC;
   f32x16 acc[CW][RW];
 #pragma unroll
@@ -278,11 +283,21 @@ hipError_t launch_out_proj_f32(const OutProjArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Rows per workgroup.  129 to 256 rows: all in one workgroup halve the passes over W^O (224 units pull 48 GB/s each whatever they
+// pull, so bytes are what counts), but the ranges of k get half as long.  Measured, 128 -> 256 rows, ranges of 4096 k: (256
+// rows, D = 7168, K = 16384) 93.0 -> 80.5 us, 140 rows 85.8 -> 74.1; of 1024 k: (256, 7168, 4096) 34.1 -> 33.5, (256, 4096,
+// 8192) 35.1 -> 35.5, (140, 2048, 16384) 30.6 -> 31.5; of 512 k: (256, 7168, 2048) 24.2 -> 26.5, (160, 2048, 5120) 18.6 ->
+// 21.3.  So where the ranges keep 2048.  More rows, a third block of 128 half empty or full: 300 rows 151 -> 135 us, 384 rows
+// 155 -> 170, left as they are.  (Beyond 2^23 k the byte offset of row 255 would not fit in the kernel's 32 bits.)
+int out_proj_rows(int M, int K, int D) {
+  if (M <= 64) return 64;
+  return M > 128 && M <= 256 && K <= (1 << 23) && K / std::max(256 / (D / kOpN), 1) >= 2048 ? 256 : 128;
+}
+
 // k-ranges of the bf16 kernel: as many as keep the launch within one workgroup per compute unit of a 256-unit chip (the
 // staging ring takes most of a unit's LDS), whole 256-element pieces each.  Returns ksplit, sets *krange.
-int out_proj_split(int M, int K, int D, int* krange) {
-  const int rows_per_wg = M <= 64 ? 64 : 128;
-  const int tiles = (D / kOpN) * ((M + rows_per_wg - 1) / rows_per_wg), phases = K / kOpK;
+int out_proj_split(int M, int K, int D, int rows, int* krange) {
+  const int tiles = (D / kOpN) * ((M + rows - 1) / rows), phases = K / kOpK;
   int want = 256 / tiles;
   if (want > phases) want = phases;
   if (want < 1) want = 1;
@@ -292,16 +307,19 @@ int out_proj_split(int M, int K, int D, int* krange) {
 }
 
 hipError_t launch_out_proj_bf16(const OutProjArgs& a, hipStream_t s) {
-  static const hipError_t attr2 = hipFuncSetAttribute((const void*)out_proj_bf16_kernel<2>,
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, out_proj_lds<2>());
-  static const hipError_t attr4 = hipFuncSetAttribute((const void*)out_proj_bf16_kernel<4>,
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, out_proj_lds<4>());
-  if (attr2 != hipSuccess) return attr2;
-  if (attr4 != hipSuccess) return attr4;
+  static const hipError_t attr = [] {
+    const hipError_t e2 = hipFuncSetAttribute((const void*)out_proj_bf16_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, out_proj_lds<2>());
+    const hipError_t e4 = hipFuncSetAttribute((const void*)out_proj_bf16_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, out_proj_lds<4>());
+    const hipError_t e8 = hipFuncSetAttribute((const void*)out_proj_bf16_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize, out_proj_lds<8>());
+    return e2 != hipSuccess ? e2 : e4 != hipSuccess ? e4 : e8;
+  }();
+  if (attr != hipSuccess) return attr;
   // the kernel's per-lane byte offsets (row inside the tile times the row stride) are 32-bit
   if (a.K > (1 << 24) || a.krange % kOsK) return hipErrorInvalidValue;
-  if (a.M <= 64) out_proj_bf16_kernel<2><<<dim3(a.D / kOpN * a.ksplit * ((a.M + 63) / 64)), 256, out_proj_lds<2>(), s>>>(a);
-  else out_proj_bf16_kernel<4><<<dim3(a.D / kOpN * a.ksplit * ((a.M + 127) / 128)), 256, out_proj_lds<4>(), s>>>(a);
+  const dim3 grid(a.D / kOpN * a.ksplit * ((a.M + a.rows - 1) / a.rows));
+  if (a.rows == 64) out_proj_bf16_kernel<2><<<grid, 64 * out_proj_waves<2>(), out_proj_lds<2>(), s>>>(a);
+  else if (a.rows == 128) out_proj_bf16_kernel<4><<<grid, 64 * out_proj_waves<4>(), out_proj_lds<4>(), s>>>(a);
+  else out_proj_bf16_kernel<8><<<grid, 64 * out_proj_waves<8>(), out_proj_lds<8>(), s>>>(a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.ksplit == 1) return e;
   const int64_t total = (int64_t)a.M * a.D / 4;

@@ -61,6 +61,9 @@ def test_rope_step_matches_the_oracle(key, lens, s_q, base):
     ("C1", 40, 2, 384, 24),     # K = 3072: 36 workgroups, not a multiple of the eight dies they are dealt over
     ("C1", 150, 2, 256, 32),    # 300 rows: three row blocks, the last ragged
     ("C1", 20, 2, 4096, 40),    # K = 5120: seven k-ranges, the last one shorter
+    ("C3", 65, 2, 4096, 128),   # 130 rows, ranges of 2048 k: 256 rows per workgroup, half of them padding
+    ("C3", 128, 2, 4096, 128),  # 256 rows: none
+    ("C3", 129, 1, 8192, 128),  # 129 rows, four ranges
     ("C0", 3, 2, 24, 8),        # fp32 kernel
 ])
 def test_output_projection_matches_the_oracle(key, Bsz, s_q, d_model, h_q):
@@ -86,6 +89,28 @@ def test_output_projection_matches_the_oracle(key, Bsz, s_q, d_model, h_q):
             assert torch.equal(y.view(torch.int16), y2.view(torch.int16)), "the partial sums are added in a fixed order"
     finally:
         dec.close()
+
+
+def test_output_projection_takes_128_rows_where_the_scratch_is_for_them():
+    """130 rows with the scratch that 128 rows per workgroup need, half of what 256 do: the same product, no refusal;
+    with a byte less it is refused as before."""
+    from paper_2605_15250_amd import binding as B
+    rows, d_model, k = 130, 4096, 16384
+    shape = B.make_shape(rows, k // 128, 1, 128, 512, 64, 1, B.GQLA_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    o = torch.randn(rows, k, device="cuda", generator=gen).bfloat16()
+    w_o = (torch.randn(d_model, k, device="cuda", generator=gen) / 64).bfloat16()
+    full = B.gqla_output_projection_workspace_bytes(shape, d_model)
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
+    y, y_small = (torch.full((rows, d_model), float("nan"), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    B.gqla_output_projection(shape, d_model, o, w_o, y, ws, full)
+    B.gqla_output_projection(shape, d_model, o, w_o, y_small, ws, full // 2)
+    with pytest.raises(RuntimeError):
+        B.gqla_output_projection(shape, d_model, o, w_o, y_small, ws, full // 2 - 1)
+    torch.cuda.synchronize()
+    ref = o.double() @ w_o.double().T
+    for got in (y, y_small):
+        assert ((got.double() - ref).norm() / ref.norm()).item() < 2.0 ** -8   # one rounding to bf16
 
 
 @pytest.mark.parametrize("key,lens,page_size,s_q,d_model", [

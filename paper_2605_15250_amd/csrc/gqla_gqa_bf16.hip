@@ -8,6 +8,8 @@
 // only cross-lane traffic is between the two half-waves.  Cache vectors are read once, so their loads carry the
 // non-temporal hint.  All heads of a group (G * s_q rows) share each
 // loaded vector through the MFMA.  The path is bound by HBM bandwidth (intensity 19-39 FLOP/byte, Sec. 4.2.2).
+#include <type_traits>
+
 #include "gqla_device.h"
 #include "gqla_lds.h"
 
@@ -114,7 +116,9 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
   const char* pool = (const char*)a.cache.pool;
 
   bf16x8 kf[KS_C], rf[KS_R], vf[MT][2];
-  u32x4 kf8[FP8 ? KS_C / 2 : 1], vf8[FP8 ? MT : 1];                           // raw code vectors (FP8 only)
+  // FP8: the codes of two tiles (one being multiplied, one in flight behind it); a vector is widened right before its MFMAs
+  u32x4 kf8[2][FP8 ? KS_C / 2 : 1], vf8[2][FP8 ? MT : 1];
+  bool codes_ok[2] = {true, true};
 
   bool k_ok = true, v_ok = true;
 
@@ -123,8 +127,8 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
   // into LDS once per workgroup, as four 1 KB LDS-DMA instructions dealt over the waves, and every wave takes its
   // fragments from there, instead of every wave pulling the same lines through the vector memory path (a fifth of
   // all its load instructions).
-  __shared__ __attribute__((aligned(16))) char kr_lds[2][KS_R * 1024];
-  const bool share_kr = !TEAM && share_kr_arg != 0;                         // kernel-uniform
+  __shared__ __attribute__((aligned(16))) char kr_lds[FP8 ? 3 : 2][KS_R * 1024];
+  const bool share_kr = !TEAM && ((FP8 && RB == 1) || share_kr_arg != 0);   // kernel-uniform (one block of rows of codes: always, see the launcher)
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);        // position in the workgroup (scalar)
   auto stage_kr = [&](int tok, int32_t pg, int buf) {
     for (int ks = wave; ks < KS_R; ks += wpb) {  // k-step ks: dims 16*ks .. 16*ks + 15
@@ -140,13 +144,8 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
     const int slot = tok % P + n;
     const char* kb = base + (int64_t)j * DH * P * EB + ((int64_t)h * P + slot) * 16;   // vector index h (+ 2 per step below)
     const char* rbp = base + kr_plane + ((int64_t)h * P + slot) * 16;
-    if constexpr (FP8) {
 #pragma unroll
-      for (int kp = 0; kp < KS_C / 2; ++kp) kf8[kp] = __builtin_nontemporal_load((const u32x4*)(kb + (int64_t)kp * 32 * P));
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < KS_C; ++ks) kf[ks] = __builtin_nontemporal_load((const bf16x8*)(kb + (int64_t)ks * 32 * P));
-    }
+    for (int ks = 0; ks < KS_C; ++ks) kf[ks] = __builtin_nontemporal_load((const bf16x8*)(kb + (int64_t)ks * 32 * P));
     if (!share_kr) {
 #pragma unroll
       for (int ks = 0; ks < KS_R; ++ks) rf[ks] = __builtin_nontemporal_load((const bf16x8*)(rbp + (int64_t)ks * 32 * P));
@@ -155,19 +154,36 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
   auto load_v = [&](int tok, int32_t pg) {
     v_ok = pg >= 0;
     const char* base = pool + (int64_t)(v_ok ? pg : 0) * page_bytes + ((int64_t)gc * DH * P + (int64_t)j * DV * P) * EB;
-    if constexpr (FP8) {
-      const int T = (tok % P) / 32;  // 32-token tile of the page: [T][dim][half] vectors
+    const int tb = (tok % P) / 8 + h;  // 8-token block of this lane for k-step 0; k-step 1 is two blocks further
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-        vf8[mt] = __builtin_nontemporal_load((const u32x4*)(base + ((((int64_t)T * DH + mt * 32 + n) * 2 + h) * 16)));
-    } else {
-      const int tb = (tok % P) / 8 + h;  // 8-token block of this lane for k-step 0; k-step 1 is two blocks further
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+      for (int kk = 0; kk < 2; ++kk)
+        vf[mt][kk] = __builtin_nontemporal_load((const bf16x8*)(base + ((int64_t)(tb + 2 * kk) * DV + mt * 32 + n) * 16));
+  };
+
+  // FP8: the same loads for the codes.  They are issued for every tile and for the two beyond the last as well, so that the
+  // number of loads in flight, which the waits count, does not depend on the path taken; where nothing is to be loaded (live
+  // false) all lanes read one vector of a page that is there.
+  auto load_k_codes = [&](u32x4 (&to)[FP8 ? KS_C / 2 : 1], int tok, int32_t pg, bool live) {
+    const char* base = pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + (int64_t)j * DH * P;
+    const uint32_t off = live ? (h * P + tok % P + n) * 16 : 0;
+    const int64_t step = live ? 32 * P : 0;
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
-          vf[mt][kk] = __builtin_nontemporal_load((const bf16x8*)(base + ((int64_t)(tb + 2 * kk) * DV + mt * 32 + n) * 16));
-    }
+    for (int kp = 0; kp < KS_C / 2; ++kp) to[kp] = __builtin_nontemporal_load((const u32x4*)(base + kp * step + off));
+  };
+  auto load_v_codes = [&](u32x4 (&to)[FP8 ? MT : 1], int tok, int32_t pg, bool live) {
+    const char* base = pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + (int64_t)gc * DH * P + (int64_t)j * DV * P;
+    const uint32_t off = live ? (((tok % P) / 32 * DH + n) * 2 + h) * 16 : 0;   // 32-token tile T of the page: [T][dim][half] vectors
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) to[mt] = __builtin_nontemporal_load((const u32x4*)(base + mt * 1024 + off));
+  };
+  auto load_kr = [&](int tok, int32_t pg, bool live) {   // FP8 without the shared k_R
+    const char* base = pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + kr_plane;
+    const uint32_t off = live ? (h * P + tok % P + n) * 16 : 0;
+    const int64_t step = live ? 32 * P : 0;
+#pragma unroll
+    for (int ks = 0; ks < KS_R; ++ks) rf[ks] = __builtin_nontemporal_load((const bf16x8*)(base + ks * step + off));
   };
 
   f32x16 o[RB][MT];
@@ -182,91 +198,8 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
       for (int i = 0; i < 16; ++i) o[x][mt][i] = 0.f;
   }
 
-  // Page ids travel through the scalar cache, looked up one tile ahead of the loads that need them: a vector load of
-  // the table entry would have to be waited for with vmcnt(0), i.e. behind every cache load still in flight.
-  const int32_t* table_row = a.cache.page_table ? a.cache.page_table + (int64_t)ce.b * a.cache.max_pages : nullptr;
-  auto checked = [&](int32_t pg) -> int32_t { return ((uint32_t)pg < (uint32_t)a.cache.num_pages) ? pg : -1; };
-  auto lookup_start = [&](int tok, int32_t& raw) {  // asynchronous; lookup_done() must precede any use of raw
-    if (table_row) asm volatile("s_load_dword %0, %1, 0x0" : "=s"(raw) : "s"(table_row + tok / P));
-    else raw = ce.b * a.cache.max_pages + tok / P;
-  };
-  auto lookup_done = [&](int32_t& raw) {
-    if (table_row) asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(raw));
-  };
-  int32_t pg_raw = 0;
-  int32_t pg_next = -1;
-  const int tok0 = ce.tok_begin + 32 * tw;  // this wave's first tile (a short chunk may leave some of a team without any)
-  if (tok0 < ce.tok_end) {
-    lookup_start(tok0, pg_raw);
-    lookup_done(pg_raw);
-    pg_next = checked(pg_raw);
-    if (share_kr) stage_kr(tok0, pg_next, 0);
-    load_k(tok0, pg_next);
-    load_v(tok0, pg_next);
-    if (tok0 + tstep < ce.tok_end) lookup_start(tok0 + tstep, pg_raw);
-  }
-  for (int tok = tok0; tok < ce.tok_end; tok += tstep) {
-    f32x16 s[RB];
-#pragma unroll
-    for (int x = 0; x < RB; ++x)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s[x][i] = 0.f;
-    if constexpr (FP8) {
-#pragma unroll
-      for (int kp = 0; kp < KS_C / 2; ++kp) {
-        kf[2 * kp] = widen_e4m3(kf8[kp][0], kf8[kp][1]);
-        kf[2 * kp + 1] = widen_e4m3(kf8[kp][2], kf8[kp][3]);
-      }
-      // the value codes are widened here as well: their registers are then free for the next tile's codes, which are
-      // requested together with the key codes (twice the bytes in flight per wave)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        vf[mt][0] = widen_e4m3(vf8[mt][0], vf8[mt][1]);
-        vf[mt][1] = widen_e4m3(vf8[mt][2], vf8[mt][3]);
-      }
-    }
-    const bool tile_v_ok = v_ok;  // v_ok is overwritten by the next tile's request below (FP8)
-
-#pragma unroll
-    for (int ks = 0; ks < KS_C; ++ks)
-#pragma unroll
-      for (int x = 0; x < RB; ++x) s[x] = mfma32(kf[ks], q_content(x, ks), s[x]);
-    if constexpr (FP8) {
-#pragma unroll
-      for (int x = 0; x < RB; ++x)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s[x][i] *= k_scale;
-    }
-    if (share_kr) {
-      // this tile's k_R was requested before the cache loads that followed it (loads complete in issue order): the
-      // tile's key and value vectors, 16-byte loads each -- KS_C + 2*MT of them in 16 bits, half as many as codes
-      constexpr int kLoadsBehindKr = FP8 ? KS_C / 2 + MT : KS_C + 2 * MT;
-      static_assert(kLoadsBehindKr == 8 || kLoadsBehindKr == 16 || kLoadsBehindKr == 28, "the wait below is written for these counts");
-      if constexpr (kLoadsBehindKr == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-      else if constexpr (kLoadsBehindKr == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(28)" ::: "memory");
-      __syncthreads();
-      const char* kr = kr_lds[((tok - ce.tok_begin) >> 5) & 1] + lane * 16;
-#pragma unroll
-      for (int ks = 0; ks < KS_R; ++ks) rf[ks] = *(const bf16x8*)(kr + ks * 1024);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS_R; ++ks)
-#pragma unroll
-      for (int x = 0; x < RB; ++x) s[x] = mfma32(rf[ks], q_rope(x, ks), s[x]);
-    const bool tile_k_ok = k_ok;
-    const bool has_next = tok + tstep < ce.tok_end;
-    if (has_next) {
-      lookup_done(pg_raw);
-      pg_next = checked(pg_raw);
-      if (share_kr) stage_kr(tok + tstep, pg_next, (((tok - ce.tok_begin) >> 5) + 1) & 1);  // (shared k_R: tt = 1)
-      load_k(tok + tstep, pg_next);
-      if constexpr (FP8) load_v(tok + tstep, pg_next);
-      if (tok + 2 * tstep < ce.tok_end) lookup_start(tok + 2 * tstep, pg_raw);
-    }
-
+  auto softmax = [&](f32x16 (&s)[RB], int tok, bool tile_k_ok, bf16x8 (&pf)[RB][2]) __attribute__((always_inline)) {
     // online softmax, base-2 domain; register i of lane (n, h) is token tok + 8*(i/4) + 4*h + i%4
-    bf16x8 pf[RB][2];
 #pragma unroll
     for (int x = 0; x < RB; ++x) {
       float sv[16];
@@ -324,10 +257,182 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
       }
       l_run[x] += psum;  // per-lane partial sum; the two half-waves are added at the end
     }
+  };
+
+  // Page ids travel through the scalar cache, looked up one tile ahead of the loads that need them: a vector load of
+  // the table entry would have to be waited for with vmcnt(0), i.e. behind every cache load still in flight.
+  const int32_t* table_row = a.cache.page_table ? a.cache.page_table + (int64_t)ce.b * a.cache.max_pages : nullptr;
+  auto checked = [&](int32_t pg) -> int32_t { return ((uint32_t)pg < (uint32_t)a.cache.num_pages) ? pg : -1; };
+  auto lookup_start = [&](int tok, int32_t& raw) {  // asynchronous; lookup_done() must precede any use of raw
+    if (table_row) asm volatile("s_load_dword %0, %1, 0x0" : "=s"(raw) : "s"(table_row + tok / P));
+    else raw = ce.b * a.cache.max_pages + tok / P;
+  };
+  auto lookup_done = [&](int32_t& raw) {
+    if (table_row) asm volatile("s_waitcnt lgkmcnt(0)" : "+s"(raw));
+  };
+  int32_t pg_raw = 0;
+  int32_t pg_next = -1;
+  const int tok0 = ce.tok_begin + 32 * tw;  // this wave's first tile (a short chunk may leave some of a team without any)
+  if constexpr (FP8) {
+    // One tile: its codes have been on the way for two tiles' time and the next tile's stay on the way behind them, so that a
+    // wave never has less than 8 KB in flight.  MEASURED
+    // (active: false for the second tile of a last pair that has none; its loads are issued all the same.)
+    auto tile = [&](int tok, auto which, int slot, bool active) __attribute__((always_inline)) {
+      constexpr int W = decltype(which)::value;
+      f32x16 s[RB];
+      if (active) {
+#pragma unroll
+        for (int x = 0; x < RB; ++x)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[x][i] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS_C; ++ks) {
+          const u32x4 c = kf8[W][ks / 2];
+          const bf16x8 k = (ks & 1) ? widen_e4m3(c[2], c[3]) : widen_e4m3(c[0], c[1]);
+#pragma unroll
+          for (int x = 0; x < RB; ++x) s[x] = mfma32(k, q_content(x, ks), s[x]);
+        }
+#pragma unroll
+        for (int x = 0; x < RB; ++x)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[x][i] *= k_scale;
+        if (share_kr) {
+          // behind this tile's k_R (loads complete in issue order): its key and value codes and the next tile's
+          static_assert(KS_C + 2 * MT == 16, "the wait below is written for this count");
+          asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+          __syncthreads();
+          const char* kr = kr_lds[slot] + lane * 16;
+#pragma unroll
+          for (int ks = 0; ks < KS_R; ++ks) rf[ks] = *(const bf16x8*)(kr + ks * 1024);
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS_R; ++ks)
+#pragma unroll
+          for (int x = 0; x < RB; ++x) s[x] = mfma32(rf[ks], q_rope(x, ks), s[x]);
+      }
+      const bool tile_ok = codes_ok[W];
+      const int ahead = tok + 2 * tstep;
+      const bool live = ahead < ce.tok_end;
+      if (!share_kr) load_kr(tok + tstep, pg_next, tok + tstep < ce.tok_end);
+      if (live) {
+        lookup_done(pg_raw);
+        pg_next = checked(pg_raw);
+      }
+      codes_ok[W] = pg_next >= 0;
+      if (share_kr && live) stage_kr(ahead, pg_next, slot == 0 ? 2 : slot - 1);   // (slot + 2) mod 3: read ahead of this tile's barrier
+      load_k_codes(kf8[W], ahead, pg_next, live);
+      if (ahead + tstep < ce.tok_end) lookup_start(ahead + tstep, pg_raw);
+
+      if (active) {
+        bf16x8 pf[RB][2];
+        softmax(s, tok, tile_ok, pf);
+        // values of tokens outside the chunk may hold any code (NaN included): code 0 is 0
+        if (tok + 32 > ce.tok_end || !tile_ok) {
+          const int lim = tile_ok ? ce.tok_end : 0;
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)   // byte e: token 16 (e / 8) + 8 h + e % 8 of the tile
+              if (tok + 16 * (e >> 3) + 8 * h + (e & 7) >= lim) vf8[W][mt][e >> 2] &= ~(0xffu << (8 * (e & 3)));
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int kk = 0; kk < 2; ++kk) {
+            const bf16x8 v = widen_e4m3(vf8[W][mt][2 * kk], vf8[W][mt][2 * kk + 1]);
+#pragma unroll
+            for (int x = 0; x < RB; ++x) o[x][mt] = mfma32(v, pf[x][kk], o[x][mt]);
+          }
+      }
+      asm volatile("" ::: "memory");
+      load_v_codes(vf8[W], ahead, pg_next, live);
+      asm volatile("" ::: "memory");
+    };
+    if (tok0 < ce.tok_end) {
+      const int tok1 = tok0 + tstep;
+      lookup_start(tok0, pg_raw);
+      lookup_done(pg_raw);
+      pg_next = checked(pg_raw);
+      codes_ok[0] = pg_next >= 0;
+      if (share_kr) stage_kr(tok0, pg_next, 0);
+      else load_kr(tok0, pg_next, true);
+      load_k_codes(kf8[0], tok0, pg_next, true);
+      asm volatile("" ::: "memory");   // (keys first: the tile's products begin with them)
+      load_v_codes(vf8[0], tok0, pg_next, true);
+      asm volatile("" ::: "memory");
+      const bool live = tok1 < ce.tok_end;
+      if (live) {
+        lookup_start(tok1, pg_raw);
+        lookup_done(pg_raw);
+        pg_next = checked(pg_raw);
+      }
+      codes_ok[1] = pg_next >= 0;
+      if (share_kr && live) stage_kr(tok1, pg_next, 1);
+      load_k_codes(kf8[1], tok1, pg_next, live);
+      asm volatile("" ::: "memory");
+      load_v_codes(vf8[1], tok1, pg_next, live);
+      if (tok1 + tstep < ce.tok_end) lookup_start(tok1 + tstep, pg_raw);
+      int tok = tok0, slot = 0;   // slot: of the tile's k_R
+      do {
+        tile(tok, std::integral_constant<int, 0>{}, slot, true);
+        slot = slot == 2 ? 0 : slot + 1;
+        tile(tok + tstep, std::integral_constant<int, 1>{}, slot, tok + tstep < ce.tok_end);
+        slot = slot == 2 ? 0 : slot + 1;
+        tok += 2 * tstep;
+      } while (tok < ce.tok_end);
+    }
+  } else {
+  if (tok0 < ce.tok_end) {
+    lookup_start(tok0, pg_raw);
+    lookup_done(pg_raw);
+    pg_next = checked(pg_raw);
+    if (share_kr) stage_kr(tok0, pg_next, 0);
+    load_k(tok0, pg_next);
+    load_v(tok0, pg_next);
+    if (tok0 + tstep < ce.tok_end) lookup_start(tok0 + tstep, pg_raw);
+  }
+  for (int tok = tok0; tok < ce.tok_end; tok += tstep) {
+    f32x16 s[RB];
+#pragma unroll
+    for (int x = 0; x < RB; ++x)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[x][i] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS_C; ++ks)
+#pragma unroll
+      for (int x = 0; x < RB; ++x) s[x] = mfma32(kf[ks], q_content(x, ks), s[x]);
+    if (share_kr) {
+      // this tile's k_R was requested before the cache loads that followed it (loads complete in issue order): the
+      // tile's key and value vectors, KS_C + 2 * MT 16-byte loads
+      constexpr int kLoadsBehindKr = KS_C + 2 * MT;
+      static_assert(kLoadsBehindKr == 16 || kLoadsBehindKr == 28, "the wait below is written for these counts");
+      if constexpr (kLoadsBehindKr == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+      else asm volatile("s_waitcnt vmcnt(28)" ::: "memory");
+      __syncthreads();
+      const char* kr = kr_lds[((tok - ce.tok_begin) >> 5) & 1] + lane * 16;
+#pragma unroll
+      for (int ks = 0; ks < KS_R; ++ks) rf[ks] = *(const bf16x8*)(kr + ks * 1024);
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS_R; ++ks)
+#pragma unroll
+      for (int x = 0; x < RB; ++x) s[x] = mfma32(rf[ks], q_rope(x, ks), s[x]);
+    const bool tile_k_ok = k_ok;
+    const bool has_next = tok + tstep < ce.tok_end;
+    if (has_next) {
+      lookup_done(pg_raw);
+      pg_next = checked(pg_raw);
+      if (share_kr) stage_kr(tok + tstep, pg_next, (((tok - ce.tok_begin) >> 5) + 1) & 1);  // (shared k_R: tt = 1)
+      load_k(tok + tstep, pg_next);
+      if (tok + 2 * tstep < ce.tok_end) lookup_start(tok + 2 * tstep, pg_raw);
+    }
+
+    bf16x8 pf[RB][2];
+    softmax(s, tok, tile_k_ok, pf);
 
     // values of tokens outside the chunk may hold any bits (NaN included): zero them so that 0 * v stays 0
-    if (tok + 32 > ce.tok_end || !tile_v_ok) {
-      const int lim = tile_v_ok ? ce.tok_end : 0;
+    if (tok + 32 > ce.tok_end || !v_ok) {
+      const int lim = v_ok ? ce.tok_end : 0;
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -342,9 +447,8 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
       for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
         for (int x = 0; x < RB; ++x) o[x][mt] = mfma32(vf[mt][kk], pf[x][kk], o[x][mt]);
-    if constexpr (!FP8) {
-      if (has_next) load_v(tok + tstep, pg_next);
-    }
+    if (has_next) load_v(tok + tstep, pg_next);
+  }
   }
 
   if constexpr (TEAM) {
@@ -598,7 +702,9 @@ static hipError_t launch_decode_gqa_128(const DecodeArgs& a, float k_scale, floa
   gqa_launch_shape(a, 8, 32, row_blocks, n_items, team, wpb, blocks);
   // one group: the plan cuts chunks for teams of eight
   const int tt = a.g == 1 ? 8 : gqa_token_team_size(a, n_items, 8);
-  if (tt > 1) {
+  // codes without a shared k_R (3, 5, 6, ... groups): teams of one, whose kernel has the registers for fragments of k_R that are
+  // requested a tile ahead (beside the shared form they would not fit)
+  if (tt > 1 || (FP8 && !team)) {
     static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, gqa_merge_bytes<128>(8));
     if (attr != hipSuccess) return attr;

@@ -405,17 +405,24 @@ __global__ void compress_f32_kernel(CompressArgs a) {
 }
 
 // The step's latent rows into their cache slots (any element type: rows are copied as 16-byte vectors).
-// One workgroup per (step token, sequence).
+// One workgroup per (step token, sequence).  A chain of memory latencies, length -> page id -> slot; the row itself depends on
+// neither and is requested first (with the rotary step, a step of one sequence x 128 heads 34.0 -> 32.3 us, of 32 x 32 heads
+// 56.6 -> 55.8).
 __global__ void append_latent_kernel(AppendArgs a) {
   const int t = blockIdx.x, b = blockIdx.y;
+  const int vecs = a.row_bytes / 16;
+  const u32x4* src = (const u32x4*)((const char*)a.rows + ((int64_t)b * a.s_q + t) * a.row_bytes);
+  u32x4 v = {0, 0, 0, 0};
+  if ((int)threadIdx.x < vecs) v = src[threadIdx.x];
+  asm volatile("" ::: "memory");   // (the request stays ahead of the branches below)
   const int pos = a.seq_lens[b] - a.s_q + t;
   if (pos < 0) return;
   const int P = a.latent.page_size;
   const int32_t pg = page_of(a.latent, b, pos / P);
   if (pg < 0) return;
-  const u32x4* src = (const u32x4*)((const char*)a.rows + ((int64_t)b * a.s_q + t) * a.row_bytes);
   u32x4* dst = (u32x4*)((char*)a.latent.pool + ((int64_t)pg * P + pos % P) * a.row_bytes);
-  for (int i = threadIdx.x; i < a.row_bytes / 16; i += blockDim.x) dst[i] = src[i];
+  if ((int)threadIdx.x < vecs) dst[threadIdx.x] = v;
+  for (int i = threadIdx.x + blockDim.x; i < vecs; i += blockDim.x) dst[i] = src[i];
 }
 
 }  // namespace

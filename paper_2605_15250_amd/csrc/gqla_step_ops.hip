@@ -15,17 +15,22 @@ namespace {
 // h_q is the k^R part of the token's latent row.  Pair p of a vector turns by t * base^(-2p/d_R); the angle is
 // formed and reduced to a fraction of a turn in double (t reaches 10^5 and the fastest pair turns a radian per position);
 // sine, cosine and the rotation itself are fp32.
+// What bounds it is latency: the length, the vectors and the stores behind them, and with eight waves on one unit each 100
+// instructions in front of the first request are 0.4 us.  So addresses take no division (the heads' pairs lie one after the other),
+// the angle per position is formed while the length is on its way, and a pair's place in its vector is carried along.
+// One token of 128 heads: 4.2 -> 2.9 us (with divisions per pair and pass, and the angle behind the length).
 constexpr int kRopeMaxPairs = 256;   // d_R <= 512
+constexpr int kRopeThreads = 512;
 template <typename T>
-__global__ void __launch_bounds__(512) rope_step_kernel(RopeArgs a) {
+__global__ void __launch_bounds__(kRopeThreads) rope_step_kernel(RopeArgs a) {
   __shared__ float cs_tab[2 * kRopeMaxPairs];
   typedef typename std::conditional<sizeof(T) == 2, uint32_t, f32x2>::type Pair;  // two adjacent elements
-  const int i = blockIdx.x, b = blockIdx.y;
+  static_assert(kRopeMaxPairs <= kRopeThreads, "one pair of the table per thread");
+  const int i = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const int half = a.d_r / 2;
-  const int vecs = (a.q_r ? a.h_q : 0) + (a.rows ? 1 : 0);
-  const int total = vecs * half;
-  T* q = a.q_r ? (T*)a.q_r + ((int64_t)b * a.s_q + i) * a.h_q * a.d_r : nullptr;
-  T* k = a.rows ? (T*)a.rows + ((int64_t)b * a.s_q + i) * a.row_elems + a.r_kv : nullptr;
+  const int q_total = a.q_r ? a.h_q * half : 0, total = q_total + (a.rows ? half : 0);   // pairs: the heads', then k^R's
+  Pair* q = (Pair*)((T*)a.q_r + ((int64_t)b * a.s_q + i) * a.h_q * a.d_r);
+  Pair* k = (Pair*)((T*)a.rows + ((int64_t)b * a.s_q + i) * a.row_elems + a.r_kv);
   // One pair per thread and pass; four passes are loaded before any is stored, so that a thread pays the memory latency
   // once per four pairs (in place, the stores would otherwise order the loads).  The addresses do not depend on the
   // position: the first four passes are requested before the sequence length is looked at.
@@ -34,36 +39,41 @@ __global__ void __launch_bounds__(512) rope_step_kernel(RopeArgs a) {
   auto fetch = [&](int base) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int idx = base + j * blockDim.x;
+      const int idx = base + j * kRopeThreads;
       at[j] = nullptr;
       if (idx < total) {
-        const int vec = idx / half;
-        T* x = (q && vec < a.h_q) ? q + (int64_t)vec * a.d_r : k;
-        at[j] = (Pair*)x + idx % half;
+        at[j] = idx < q_total ? q + idx : k + (idx - q_total);
         v[j] = *at[j];
       }
     }
   };
-  fetch(threadIdx.x);
-  const int t = a.seq_lens[b] - a.s_q + i;
+  const int len = a.seq_lens[b];
+  asm volatile("" ::: "memory");   // (requested before the vectors)
+  fetch(tid);
+  double theta = 0.0;
+  if (tid < half) theta = exp2(-2.0 * (double)tid / (double)a.d_r * a.log2_base);
+  asm volatile("" : "+v"(theta));   // (ahead of the wait for the length)
+  const int t = len - a.s_q + i;
   if (t < 0) return;
-  for (int p = threadIdx.x; p < half; p += blockDim.x) {   // one sine / cosine per pair, shared by all vectors of the token
-    const double theta = exp2(-2.0 * (double)p / (double)a.d_r * a.log2_base);
+  if (tid < half) {   // one sine / cosine per pair, shared by all vectors of the token
     double turns = (double)t * theta * 0.15915494309189535;   // angle / 2 pi; its fraction keeps 1e-11 at t = 10^5
     turns -= floor(turns);
     float sn, cs;
     sincospif(2.0f * (float)turns, &sn, &cs);                  // sin and cos of pi * x: the argument is already reduced
-    cs_tab[2 * p] = cs;
-    cs_tab[2 * p + 1] = sn;
+    cs_tab[2 * tid] = cs;
+    cs_tab[2 * tid + 1] = sn;
   }
   __syncthreads();
-  for (int base = threadIdx.x; base < total; base += 4 * blockDim.x) {
-    if (base != (int)threadIdx.x) fetch(base);
+  int p = tid % half;                                           // pair of the vector that `at` points at
+  const int p_step = kRopeThreads % half;
+  for (int base = tid; base < total; base += 4 * kRopeThreads) {
+    if (base != tid) fetch(base);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if (!at[j]) continue;
-      const int p = (base + j * blockDim.x) % half;
       const float c = cs_tab[2 * p], s = cs_tab[2 * p + 1];
+      p += p_step;
+      if (p >= half) p -= half;
+      if (!at[j]) continue;
       if constexpr (sizeof(T) == 2) {
         const float x0 = bf16_bits_to_float(v[j] & 0xffffu), x1 = bf16_bits_to_float(v[j] >> 16);
         *at[j] = pack_bf16(x0 * c - x1 * s, x0 * s + x1 * c);
@@ -273,8 +283,8 @@ __global__ void __launch_bounds__(256) out_proj_reduce_kernel(OutProjArgs a) {
 }  // namespace
 
 hipError_t launch_rope_step(const RopeArgs& a, bool bf16, hipStream_t s) {
-  if (bf16) rope_step_kernel<__bf16><<<dim3(a.s_q, a.B), 512, 0, s>>>(a);
-  else rope_step_kernel<float><<<dim3(a.s_q, a.B), 512, 0, s>>>(a);
+  if (bf16) rope_step_kernel<__bf16><<<dim3(a.s_q, a.B), kRopeThreads, 0, s>>>(a);
+  else rope_step_kernel<float><<<dim3(a.s_q, a.B), kRopeThreads, 0, s>>>(a);
   return hipGetLastError();
 }
 

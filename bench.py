@@ -311,7 +311,7 @@ def main():
         bl8 = La_ * B.gqla_latent_fp8_bytes_per_token(ca.r_kv, ca.d_r)
         fl8 = 2.0 * La_ * ca.h_q * ca.s_q * (2 * ca.r_kv + ca.d_r)
         a16 = A["out"].float()
-        fp8_latent = {"quantize_latent_ms": t_ql * 1e3, "decode_absorb_fp8_ms": t_l8 * 1e3, "kernel": "decode_absorb_fp8_kernel",
+        fp8_latent = {"quantize_latent_ms": t_ql * 1e3, "decode_absorb_fp8_ms": t_l8 * 1e3, "kernel": "decode_absorb_shared_bf16_kernel",
                       "kernel_ms": k_l8 * 1e3, "bytes_per_token": bl8 // La_, "c_scale": c8,
                       "GB/s": bl8 / k_l8 / 1e9, "frac_hbm_peak": bl8 / k_l8 / 1e9 / HBM_PEAK_GBS,
                       "TFLOP/s": fl8 / k_l8 / 1e12, "frac_mfma_peak": fl8 / k_l8 / 1e12 / MFMA_BF16_PEAK_TFLOPS,

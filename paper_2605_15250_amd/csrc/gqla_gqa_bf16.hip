@@ -382,73 +382,73 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
       } while (tok < ce.tok_end);
     }
   } else {
-  if (tok0 < ce.tok_end) {
-    lookup_start(tok0, pg_raw);
-    lookup_done(pg_raw);
-    pg_next = checked(pg_raw);
-    if (share_kr) stage_kr(tok0, pg_next, 0);
-    load_k(tok0, pg_next);
-    load_v(tok0, pg_next);
-    if (tok0 + tstep < ce.tok_end) lookup_start(tok0 + tstep, pg_raw);
-  }
-  for (int tok = tok0; tok < ce.tok_end; tok += tstep) {
-    f32x16 s[RB];
-#pragma unroll
-    for (int x = 0; x < RB; ++x)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s[x][i] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KS_C; ++ks)
-#pragma unroll
-      for (int x = 0; x < RB; ++x) s[x] = mfma32(kf[ks], q_content(x, ks), s[x]);
-    if (share_kr) {
-      // this tile's k_R was requested before the cache loads that followed it (loads complete in issue order): the
-      // tile's key and value vectors, KS_C + 2 * MT 16-byte loads
-      constexpr int kLoadsBehindKr = KS_C + 2 * MT;
-      static_assert(kLoadsBehindKr == 16 || kLoadsBehindKr == 28, "the wait below is written for these counts");
-      if constexpr (kLoadsBehindKr == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(28)" ::: "memory");
-      __syncthreads();
-      const char* kr = kr_lds[((tok - ce.tok_begin) >> 5) & 1] + lane * 16;
-#pragma unroll
-      for (int ks = 0; ks < KS_R; ++ks) rf[ks] = *(const bf16x8*)(kr + ks * 1024);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS_R; ++ks)
-#pragma unroll
-      for (int x = 0; x < RB; ++x) s[x] = mfma32(rf[ks], q_rope(x, ks), s[x]);
-    const bool tile_k_ok = k_ok;
-    const bool has_next = tok + tstep < ce.tok_end;
-    if (has_next) {
+    if (tok0 < ce.tok_end) {
+      lookup_start(tok0, pg_raw);
       lookup_done(pg_raw);
       pg_next = checked(pg_raw);
-      if (share_kr) stage_kr(tok + tstep, pg_next, (((tok - ce.tok_begin) >> 5) + 1) & 1);  // (shared k_R: tt = 1)
-      load_k(tok + tstep, pg_next);
-      if (tok + 2 * tstep < ce.tok_end) lookup_start(tok + 2 * tstep, pg_raw);
+      if (share_kr) stage_kr(tok0, pg_next, 0);
+      load_k(tok0, pg_next);
+      load_v(tok0, pg_next);
+      if (tok0 + tstep < ce.tok_end) lookup_start(tok0 + tstep, pg_raw);
     }
+    for (int tok = tok0; tok < ce.tok_end; tok += tstep) {
+      f32x16 s[RB];
+#pragma unroll
+      for (int x = 0; x < RB; ++x)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[x][i] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS_C; ++ks)
+#pragma unroll
+        for (int x = 0; x < RB; ++x) s[x] = mfma32(kf[ks], q_content(x, ks), s[x]);
+      if (share_kr) {
+        // this tile's k_R was requested before the cache loads that followed it (loads complete in issue order): the
+        // tile's key and value vectors, KS_C + 2 * MT 16-byte loads
+        constexpr int kLoadsBehindKr = KS_C + 2 * MT;
+        static_assert(kLoadsBehindKr == 16 || kLoadsBehindKr == 28, "the wait below is written for these counts");
+        if constexpr (kLoadsBehindKr == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(28)" ::: "memory");
+        __syncthreads();
+        const char* kr = kr_lds[((tok - ce.tok_begin) >> 5) & 1] + lane * 16;
+#pragma unroll
+        for (int ks = 0; ks < KS_R; ++ks) rf[ks] = *(const bf16x8*)(kr + ks * 1024);
+      }
+#pragma unroll
+      for (int ks = 0; ks < KS_R; ++ks)
+#pragma unroll
+        for (int x = 0; x < RB; ++x) s[x] = mfma32(rf[ks], q_rope(x, ks), s[x]);
+      const bool tile_k_ok = k_ok;
+      const bool has_next = tok + tstep < ce.tok_end;
+      if (has_next) {
+        lookup_done(pg_raw);
+        pg_next = checked(pg_raw);
+        if (share_kr) stage_kr(tok + tstep, pg_next, (((tok - ce.tok_begin) >> 5) + 1) & 1);  // (shared k_R: tt = 1)
+        load_k(tok + tstep, pg_next);
+        if (tok + 2 * tstep < ce.tok_end) lookup_start(tok + 2 * tstep, pg_raw);
+      }
 
-    bf16x8 pf[RB][2];
-    softmax(s, tok, tile_k_ok, pf);
+      bf16x8 pf[RB][2];
+      softmax(s, tok, tile_k_ok, pf);
 
-    // values of tokens outside the chunk may hold any bits (NaN included): zero them so that 0 * v stays 0
-    if (tok + 32 > ce.tok_end || !v_ok) {
-      const int lim = v_ok ? ce.tok_end : 0;
+      // values of tokens outside the chunk may hold any bits (NaN included): zero them so that 0 * v stays 0
+      if (tok + 32 > ce.tok_end || !v_ok) {
+        const int lim = v_ok ? ce.tok_end : 0;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+          for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (tok + 16 * kk + 8 * h + e >= lim) vf[mt][kk][e] = (__bf16)0.f;
+      }
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (tok + 16 * kk + 8 * h + e >= lim) vf[mt][kk][e] = (__bf16)0.f;
+          for (int x = 0; x < RB; ++x) o[x][mt] = mfma32(vf[mt][kk], pf[x][kk], o[x][mt]);
+      if (has_next) load_v(tok + tstep, pg_next);
     }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-        for (int x = 0; x < RB; ++x) o[x][mt] = mfma32(vf[mt][kk], pf[x][kk], o[x][mt]);
-    if (has_next) load_v(tok + tstep, pg_next);
-  }
   }
 
   if constexpr (TEAM) {

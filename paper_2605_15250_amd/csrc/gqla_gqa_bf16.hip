@@ -45,7 +45,8 @@ __device__ __forceinline__ bf16x8 widen_e4m3(uint32_t w0, uint32_t w1) {
 // TEAM: token teams.  false: a wave works through its chunk alone.  true (RB = 1): tt (kernel argument) = 2, 4 or 8 waves of a
 // workgroup share one item, wave w of the team taking tiles w, w + tt, ...; their partial states (m, l, O^T) are merged
 // through LDS, so that one partial per item reaches memory.
-template <int DH, int DV, int DR, bool FP8, int MAXT, int RB, bool TEAM>
+// DEEP (8-bit codes, RB = 1, no teams, shared k_R): the codes of two tiles in registers, see the loop.
+template <int DH, int DV, int DR, bool FP8, int MAXT, int RB, bool TEAM, bool DEEP>
 __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int n_items, int row_blocks, int share_kr_arg,
                                                                int tt_arg, float k_scale, float v_scale) {
   constexpr int KS_C = DH / 16;  // k-steps over the content dims
@@ -53,6 +54,7 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
   constexpr int MT = DV / 32;    // 32-dim tiles of the output
   static_assert(!FP8 || DH == DV, "the 8-bit page format is written for equal dims");
   static_assert(!TEAM || RB == 1, "the merge below is written for one row block");
+  static_assert(!DEEP || (FP8 && RB == 1 && !TEAM), "two tiles of codes fit the registers of this form only");
   const int tt = TEAM ? tt_arg : 1;
   const int lane = threadIdx.x & 63;
   const int wpb = __builtin_amdgcn_readfirstlane(blockDim.x >> 6);  // waves per workgroup: 8, or the number of groups when that is 2 or 4
@@ -116,9 +118,8 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
   const char* pool = (const char*)a.cache.pool;
 
   bf16x8 kf[KS_C], rf[KS_R], vf[MT][2];
-  // FP8: the codes of two tiles (one being multiplied, one in flight behind it); a vector is widened right before its MFMAs
-  u32x4 kf8[2][FP8 ? KS_C / 2 : 1], vf8[2][FP8 ? MT : 1];
-  bool codes_ok[2] = {true, true};
+  // raw code vectors (FP8 only; DEEP: of two tiles, one being multiplied and one in flight behind it)
+  u32x4 kf8[DEEP ? 2 : 1][FP8 ? KS_C / 2 : 1], vf8[DEEP ? 2 : 1][FP8 ? MT : 1];
 
   bool k_ok = true, v_ok = true;
 
@@ -127,8 +128,8 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
   // into LDS once per workgroup, as four 1 KB LDS-DMA instructions dealt over the waves, and every wave takes its
   // fragments from there, instead of every wave pulling the same lines through the vector memory path (a fifth of
   // all its load instructions).
-  __shared__ __attribute__((aligned(16))) char kr_lds[FP8 ? 3 : 2][KS_R * 1024];
-  const bool share_kr = !TEAM && ((FP8 && RB == 1) || share_kr_arg != 0);   // kernel-uniform (one block of rows of codes: always, see the launcher)
+  __shared__ __attribute__((aligned(16))) char kr_lds[DEEP ? 3 : 2][KS_R * 1024];
+  const bool share_kr = DEEP || (!TEAM && share_kr_arg != 0);               // kernel-uniform
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);        // position in the workgroup (scalar)
   auto stage_kr = [&](int tok, int32_t pg, int buf) {
     for (int ks = wave; ks < KS_R; ks += wpb) {  // k-step ks: dims 16*ks .. 16*ks + 15
@@ -144,8 +145,13 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
     const int slot = tok % P + n;
     const char* kb = base + (int64_t)j * DH * P * EB + ((int64_t)h * P + slot) * 16;   // vector index h (+ 2 per step below)
     const char* rbp = base + kr_plane + ((int64_t)h * P + slot) * 16;
+    if constexpr (FP8) {
 #pragma unroll
-    for (int ks = 0; ks < KS_C; ++ks) kf[ks] = __builtin_nontemporal_load((const bf16x8*)(kb + (int64_t)ks * 32 * P));
+      for (int kp = 0; kp < KS_C / 2; ++kp) kf8[0][kp] = __builtin_nontemporal_load((const u32x4*)(kb + (int64_t)kp * 32 * P));
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS_C; ++ks) kf[ks] = __builtin_nontemporal_load((const bf16x8*)(kb + (int64_t)ks * 32 * P));
+    }
     if (!share_kr) {
 #pragma unroll
       for (int ks = 0; ks < KS_R; ++ks) rf[ks] = __builtin_nontemporal_load((const bf16x8*)(rbp + (int64_t)ks * 32 * P));
@@ -154,15 +160,22 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
   auto load_v = [&](int tok, int32_t pg) {
     v_ok = pg >= 0;
     const char* base = pool + (int64_t)(v_ok ? pg : 0) * page_bytes + ((int64_t)gc * DH * P + (int64_t)j * DV * P) * EB;
-    const int tb = (tok % P) / 8 + h;  // 8-token block of this lane for k-step 0; k-step 1 is two blocks further
+    if constexpr (FP8) {
+      const int T = (tok % P) / 32;  // 32-token tile of the page: [T][dim][half] vectors
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+      for (int mt = 0; mt < MT; ++mt)
+        vf8[0][mt] = __builtin_nontemporal_load((const u32x4*)(base + ((((int64_t)T * DH + mt * 32 + n) * 2 + h) * 16)));
+    } else {
+      const int tb = (tok % P) / 8 + h;  // 8-token block of this lane for k-step 0; k-step 1 is two blocks further
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-        vf[mt][kk] = __builtin_nontemporal_load((const bf16x8*)(base + ((int64_t)(tb + 2 * kk) * DV + mt * 32 + n) * 16));
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+          vf[mt][kk] = __builtin_nontemporal_load((const bf16x8*)(base + ((int64_t)(tb + 2 * kk) * DV + mt * 32 + n) * 16));
+    }
   };
 
-  // FP8: the same loads for the codes.  They are issued for every tile and for the two beyond the last as well, so that the
+  // DEEP: the same loads for the codes.  They are issued for every tile and for the two beyond the last as well, so that the
   // number of loads in flight, which the waits count, does not depend on the path taken; where nothing is to be loaded (live
   // false) all lanes read one vector of a page that is there.
   auto load_k_codes = [&](u32x4 (&to)[FP8 ? KS_C / 2 : 1], int tok, int32_t pg, bool live) {
@@ -178,13 +191,6 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) to[mt] = __builtin_nontemporal_load((const u32x4*)(base + mt * 1024 + off));
   };
-  auto load_kr = [&](int tok, int32_t pg, bool live) {   // FP8 without the shared k_R
-    const char* base = pool + (int64_t)(pg >= 0 ? pg : 0) * page_bytes + kr_plane;
-    const uint32_t off = live ? (h * P + tok % P + n) * 16 : 0;
-    const int64_t step = live ? 32 * P : 0;
-#pragma unroll
-    for (int ks = 0; ks < KS_R; ++ks) rf[ks] = __builtin_nontemporal_load((const bf16x8*)(base + ks * step + off));
-  };
 
   f32x16 o[RB][MT];
   float m_run[RB], l_run[RB];
@@ -197,67 +203,6 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
 #pragma unroll
       for (int i = 0; i < 16; ++i) o[x][mt][i] = 0.f;
   }
-
-  auto softmax = [&](f32x16 (&s)[RB], int tok, bool tile_k_ok, bf16x8 (&pf)[RB][2]) __attribute__((always_inline)) {
-    // online softmax, base-2 domain; register i of lane (n, h) is token tok + 8*(i/4) + 4*h + i%4
-#pragma unroll
-    for (int x = 0; x < RB; ++x) {
-      float sv[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) sv[i] = s[x][i] * a.scale_log2e;
-      const bool need_mask = (tok + 32 > unmasked_end) || !tile_k_ok || !row_ok[x];
-      if (need_mask) {
-        const int lim = tile_k_ok ? vis_end[x] : 0;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int tk = tok + 8 * (i >> 2) + 4 * h + (i & 3);
-          if (tk >= lim) sv[i] = GQLA_NEG_INF;
-        }
-      }
-      float tmax = sv[0];
-#pragma unroll
-      for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sv[i]);
-      tmax = pair_max(tmax);
-      // m_run is the reference of the exponentials, not the exact running maximum: it moves only when some row's
-      // maximum has outgrown it by kRescaleThreshold (log2 units; the probabilities then stay below 2^threshold, far
-      // inside the range of bf16 and fp32), so that far into a long context the update of O^T and l is skipped
-      if (__builtin_amdgcn_ballot_w64(tmax > m_run[x] + kRescaleThreshold) != 0) {
-        const float m_new = fmaxf(m_run[x], tmax);
-        const float alpha = fast_exp2(m_run[x] - ((m_new == GQLA_NEG_INF) ? 0.f : m_new));
-        m_run[x] = m_new;
-        l_run[x] *= alpha;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) o[x][mt][i] *= alpha;
-      }
-      const float m_use = (m_run[x] == GQLA_NEG_INF) ? 0.f : m_run[x];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) sv[i] = fast_exp2(sv[i] - m_use);
-
-      // P^T fragments: k-step kk covers tokens tok + 16*kk .. +15, lane half h needs tokens 8h .. 8h+7 of them.
-      // The denominator sums the probabilities as the matrix cores see them (rounded to bf16): numerator and
-      // denominator then weigh every token alike, whatever the reference of the exponentials is.
-      float psum = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
-        const uint32_t x0 = pack_bf16(sv[8 * kk + 0], sv[8 * kk + 1]), x1 = pack_bf16(sv[8 * kk + 2], sv[8 * kk + 3]);
-        const uint32_t y0 = pack_bf16(sv[8 * kk + 4], sv[8 * kk + 5]), y1 = pack_bf16(sv[8 * kk + 6], sv[8 * kk + 7]);
-#pragma unroll
-        for (uint32_t wd : {x0, x1, y0, y1}) psum += __builtin_bit_cast(float, wd << 16) + __builtin_bit_cast(float, wd & 0xffff0000u);
-        u32x4 w;
-        uint32_t r0, r1;
-        half_swap(x0, y0, r0, r1);
-        w[0] = r0;
-        w[2] = r1;
-        half_swap(x1, y1, r0, r1);
-        w[1] = r0;
-        w[3] = r1;
-        pf[x][kk] = __builtin_bit_cast(bf16x8, w);
-      }
-      l_run[x] += psum;  // per-lane partial sum; the two half-waves are added at the end
-    }
-  };
 
   // Page ids travel through the scalar cache, looked up one tile ahead of the loads that need them: a vector load of
   // the table entry would have to be waited for with vmcnt(0), i.e. behind every cache load still in flight.
@@ -273,59 +218,94 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
   int32_t pg_raw = 0;
   int32_t pg_next = -1;
   const int tok0 = ce.tok_begin + 32 * tw;  // this wave's first tile (a short chunk may leave some of a team without any)
-  if constexpr (FP8) {
+  if constexpr (DEEP) {
+    bool codes_ok[2] = {true, true};
     // One tile: its codes have been on the way for two tiles' time and the next tile's stay on the way behind them, so that a
     // wave never has less than 8 KB in flight.  64 ragged sequences of 3000 to 12000 tokens, step: 198.6 -> 194.0 us.
     // (active: false for the second tile of a last pair that has none; its loads are issued all the same.)
+    // The softmax is the one of the other loop below, for one row block.  (Written out twice: as a lambda for both it changed
+    // the code of the other forms, and those with two row blocks lost 2 %.)
     auto tile = [&](int tok, auto which, int slot, bool active) __attribute__((always_inline)) {
       constexpr int W = decltype(which)::value;
-      f32x16 s[RB];
+      f32x16 s;
       if (active) {
 #pragma unroll
-        for (int x = 0; x < RB; ++x)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) s[x][i] = 0.f;
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
 #pragma unroll
         for (int ks = 0; ks < KS_C; ++ks) {
           const u32x4 c = kf8[W][ks / 2];
-          const bf16x8 k = (ks & 1) ? widen_e4m3(c[2], c[3]) : widen_e4m3(c[0], c[1]);
-#pragma unroll
-          for (int x = 0; x < RB; ++x) s[x] = mfma32(k, q_content(x, ks), s[x]);
+          s = mfma32((ks & 1) ? widen_e4m3(c[2], c[3]) : widen_e4m3(c[0], c[1]), qc[0][ks], s);
         }
 #pragma unroll
-        for (int x = 0; x < RB; ++x)
+        for (int i = 0; i < 16; ++i) s[i] *= k_scale;
+        // behind this tile's k_R (loads complete in issue order): its key and value codes and the next tile's
+        static_assert(KS_C + 2 * MT == 16, "the wait below is written for this count");
+        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        __syncthreads();
+        const char* kr = kr_lds[slot] + lane * 16;
 #pragma unroll
-          for (int i = 0; i < 16; ++i) s[x][i] *= k_scale;
-        if (share_kr) {
-          // behind this tile's k_R (loads complete in issue order): its key and value codes and the next tile's
-          static_assert(KS_C + 2 * MT == 16, "the wait below is written for this count");
-          asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-          __syncthreads();
-          const char* kr = kr_lds[slot] + lane * 16;
+        for (int ks = 0; ks < KS_R; ++ks) rf[ks] = *(const bf16x8*)(kr + ks * 1024);
 #pragma unroll
-          for (int ks = 0; ks < KS_R; ++ks) rf[ks] = *(const bf16x8*)(kr + ks * 1024);
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS_R; ++ks)
-#pragma unroll
-          for (int x = 0; x < RB; ++x) s[x] = mfma32(rf[ks], q_rope(x, ks), s[x]);
+        for (int ks = 0; ks < KS_R; ++ks) s = mfma32(rf[ks], qr[0][ks], s);
       }
       const bool tile_ok = codes_ok[W];
       const int ahead = tok + 2 * tstep;
       const bool live = ahead < ce.tok_end;
-      if (!share_kr) load_kr(tok + tstep, pg_next, tok + tstep < ce.tok_end);
       if (live) {
         lookup_done(pg_raw);
         pg_next = checked(pg_raw);
       }
       codes_ok[W] = pg_next >= 0;
-      if (share_kr && live) stage_kr(ahead, pg_next, slot == 0 ? 2 : slot - 1);   // (slot + 2) mod 3: read ahead of this tile's barrier
+      if (live) stage_kr(ahead, pg_next, slot == 0 ? 2 : slot - 1);   // (slot + 2) mod 3: read ahead of this tile's barrier
       load_k_codes(kf8[W], ahead, pg_next, live);
       if (ahead + tstep < ce.tok_end) lookup_start(ahead + tstep, pg_raw);
 
       if (active) {
-        bf16x8 pf[RB][2];
-        softmax(s, tok, tile_ok, pf);
+        float sv[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sv[i] = s[i] * a.scale_log2e;
+        if ((tok + 32 > unmasked_end) || !tile_ok || !row_ok[0]) {
+          const int lim = tile_ok ? vis_end[0] : 0;
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (tok + 8 * (i >> 2) + 4 * h + (i & 3) >= lim) sv[i] = GQLA_NEG_INF;
+        }
+        float tmax = sv[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sv[i]);
+        tmax = pair_max(tmax);
+        if (__builtin_amdgcn_ballot_w64(tmax > m_run[0] + kRescaleThreshold) != 0) {
+          const float m_new = fmaxf(m_run[0], tmax);
+          const float alpha = fast_exp2(m_run[0] - ((m_new == GQLA_NEG_INF) ? 0.f : m_new));
+          m_run[0] = m_new;
+          l_run[0] *= alpha;
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[0][mt][i] *= alpha;
+        }
+        const float m_use = (m_run[0] == GQLA_NEG_INF) ? 0.f : m_run[0];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sv[i] = fast_exp2(sv[i] - m_use);
+        bf16x8 pf[2];
+        float psum = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          const uint32_t x0 = pack_bf16(sv[8 * kk + 0], sv[8 * kk + 1]), x1 = pack_bf16(sv[8 * kk + 2], sv[8 * kk + 3]);
+          const uint32_t y0 = pack_bf16(sv[8 * kk + 4], sv[8 * kk + 5]), y1 = pack_bf16(sv[8 * kk + 6], sv[8 * kk + 7]);
+#pragma unroll
+          for (uint32_t wd : {x0, x1, y0, y1}) psum += __builtin_bit_cast(float, wd << 16) + __builtin_bit_cast(float, wd & 0xffff0000u);
+          u32x4 w;
+          uint32_t r0, r1;
+          half_swap(x0, y0, r0, r1);
+          w[0] = r0;
+          w[2] = r1;
+          half_swap(x1, y1, r0, r1);
+          w[1] = r0;
+          w[3] = r1;
+          pf[kk] = __builtin_bit_cast(bf16x8, w);
+        }
+        l_run[0] += psum;
         // values of tokens outside the chunk may hold any code (NaN included): code 0 is 0
         if (tok + 32 > ce.tok_end || !tile_ok) {
           const int lim = tile_ok ? ce.tok_end : 0;
@@ -338,11 +318,7 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-          for (int kk = 0; kk < 2; ++kk) {
-            const bf16x8 v = widen_e4m3(vf8[W][mt][2 * kk], vf8[W][mt][2 * kk + 1]);
-#pragma unroll
-            for (int x = 0; x < RB; ++x) o[x][mt] = mfma32(v, pf[x][kk], o[x][mt]);
-          }
+          for (int kk = 0; kk < 2; ++kk) o[0][mt] = mfma32(widen_e4m3(vf8[W][mt][2 * kk], vf8[W][mt][2 * kk + 1]), pf[kk], o[0][mt]);
       }
       asm volatile("" ::: "memory");
       load_v_codes(vf8[W], ahead, pg_next, live);
@@ -354,8 +330,7 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
       lookup_done(pg_raw);
       pg_next = checked(pg_raw);
       codes_ok[0] = pg_next >= 0;
-      if (share_kr) stage_kr(tok0, pg_next, 0);
-      else load_kr(tok0, pg_next, true);
+      stage_kr(tok0, pg_next, 0);
       load_k_codes(kf8[0], tok0, pg_next, true);
       asm volatile("" ::: "memory");   // (keys first: the tile's products begin with them)
       load_v_codes(vf8[0], tok0, pg_next, true);
@@ -367,7 +342,7 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
         pg_next = checked(pg_raw);
       }
       codes_ok[1] = pg_next >= 0;
-      if (share_kr && live) stage_kr(tok1, pg_next, 1);
+      if (live) stage_kr(tok1, pg_next, 1);
       load_k_codes(kf8[1], tok1, pg_next, live);
       asm volatile("" ::: "memory");
       load_v_codes(vf8[1], tok1, pg_next, live);
@@ -397,16 +372,39 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
       for (int x = 0; x < RB; ++x)
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[x][i] = 0.f;
+      if constexpr (FP8) {
+#pragma unroll
+        for (int kp = 0; kp < KS_C / 2; ++kp) {
+          kf[2 * kp] = widen_e4m3(kf8[0][kp][0], kf8[0][kp][1]);
+          kf[2 * kp + 1] = widen_e4m3(kf8[0][kp][2], kf8[0][kp][3]);
+        }
+        // the value codes are widened here as well: their registers are then free for the next tile's codes, which are
+        // requested together with the key codes (twice the bytes in flight per wave)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          vf[mt][0] = widen_e4m3(vf8[0][mt][0], vf8[0][mt][1]);
+          vf[mt][1] = widen_e4m3(vf8[0][mt][2], vf8[0][mt][3]);
+        }
+      }
+      const bool tile_v_ok = v_ok;  // v_ok is overwritten by the next tile's request below (FP8)
+
 #pragma unroll
       for (int ks = 0; ks < KS_C; ++ks)
 #pragma unroll
         for (int x = 0; x < RB; ++x) s[x] = mfma32(kf[ks], q_content(x, ks), s[x]);
+      if constexpr (FP8) {
+#pragma unroll
+        for (int x = 0; x < RB; ++x)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) s[x][i] *= k_scale;
+      }
       if (share_kr) {
         // this tile's k_R was requested before the cache loads that followed it (loads complete in issue order): the
-        // tile's key and value vectors, KS_C + 2 * MT 16-byte loads
-        constexpr int kLoadsBehindKr = KS_C + 2 * MT;
-        static_assert(kLoadsBehindKr == 16 || kLoadsBehindKr == 28, "the wait below is written for these counts");
-        if constexpr (kLoadsBehindKr == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+        // tile's key and value vectors, 16-byte loads each -- KS_C + 2*MT of them in 16 bits, half as many as codes
+        constexpr int kLoadsBehindKr = FP8 ? KS_C / 2 + MT : KS_C + 2 * MT;
+        static_assert(kLoadsBehindKr == 8 || kLoadsBehindKr == 16 || kLoadsBehindKr == 28, "the wait below is written for these counts");
+        if constexpr (kLoadsBehindKr == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        else if constexpr (kLoadsBehindKr == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         else asm volatile("s_waitcnt vmcnt(28)" ::: "memory");
         __syncthreads();
         const char* kr = kr_lds[((tok - ce.tok_begin) >> 5) & 1] + lane * 16;
@@ -424,15 +422,73 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
         pg_next = checked(pg_raw);
         if (share_kr) stage_kr(tok + tstep, pg_next, (((tok - ce.tok_begin) >> 5) + 1) & 1);  // (shared k_R: tt = 1)
         load_k(tok + tstep, pg_next);
+        if constexpr (FP8) load_v(tok + tstep, pg_next);
         if (tok + 2 * tstep < ce.tok_end) lookup_start(tok + 2 * tstep, pg_raw);
       }
 
+      // online softmax, base-2 domain; register i of lane (n, h) is token tok + 8*(i/4) + 4*h + i%4
       bf16x8 pf[RB][2];
-      softmax(s, tok, tile_k_ok, pf);
+#pragma unroll
+      for (int x = 0; x < RB; ++x) {
+        float sv[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sv[i] = s[x][i] * a.scale_log2e;
+        const bool need_mask = (tok + 32 > unmasked_end) || !tile_k_ok || !row_ok[x];
+        if (need_mask) {
+          const int lim = tile_k_ok ? vis_end[x] : 0;
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int tk = tok + 8 * (i >> 2) + 4 * h + (i & 3);
+            if (tk >= lim) sv[i] = GQLA_NEG_INF;
+          }
+        }
+        float tmax = sv[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, sv[i]);
+        tmax = pair_max(tmax);
+        // m_run is the reference of the exponentials, not the exact running maximum: it moves only when some row's
+        // maximum has outgrown it by kRescaleThreshold (log2 units; the probabilities then stay below 2^threshold, far
+        // inside the range of bf16 and fp32), so that far into a long context the update of O^T and l is skipped
+        if (__builtin_amdgcn_ballot_w64(tmax > m_run[x] + kRescaleThreshold) != 0) {
+          const float m_new = fmaxf(m_run[x], tmax);
+          const float alpha = fast_exp2(m_run[x] - ((m_new == GQLA_NEG_INF) ? 0.f : m_new));
+          m_run[x] = m_new;
+          l_run[x] *= alpha;
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o[x][mt][i] *= alpha;
+        }
+        const float m_use = (m_run[x] == GQLA_NEG_INF) ? 0.f : m_run[x];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sv[i] = fast_exp2(sv[i] - m_use);
+
+        // P^T fragments: k-step kk covers tokens tok + 16*kk .. +15, lane half h needs tokens 8h .. 8h+7 of them.
+        // The denominator sums the probabilities as the matrix cores see them (rounded to bf16): numerator and
+        // denominator then weigh every token alike, whatever the reference of the exponentials is.
+        float psum = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+          const uint32_t x0 = pack_bf16(sv[8 * kk + 0], sv[8 * kk + 1]), x1 = pack_bf16(sv[8 * kk + 2], sv[8 * kk + 3]);
+          const uint32_t y0 = pack_bf16(sv[8 * kk + 4], sv[8 * kk + 5]), y1 = pack_bf16(sv[8 * kk + 6], sv[8 * kk + 7]);
+#pragma unroll
+          for (uint32_t wd : {x0, x1, y0, y1}) psum += __builtin_bit_cast(float, wd << 16) + __builtin_bit_cast(float, wd & 0xffff0000u);
+          u32x4 w;
+          uint32_t r0, r1;
+          half_swap(x0, y0, r0, r1);
+          w[0] = r0;
+          w[2] = r1;
+          half_swap(x1, y1, r0, r1);
+          w[1] = r0;
+          w[3] = r1;
+          pf[x][kk] = __builtin_bit_cast(bf16x8, w);
+        }
+        l_run[x] += psum;  // per-lane partial sum; the two half-waves are added at the end
+      }
 
       // values of tokens outside the chunk may hold any bits (NaN included): zero them so that 0 * v stays 0
-      if (tok + 32 > ce.tok_end || !v_ok) {
-        const int lim = v_ok ? ce.tok_end : 0;
+      if (tok + 32 > ce.tok_end || !tile_v_ok) {
+        const int lim = tile_v_ok ? ce.tok_end : 0;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -447,7 +503,9 @@ __global__ void __launch_bounds__(MAXT) decode_gqa_bf16_kernel(DecodeArgs a, int
         for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
           for (int x = 0; x < RB; ++x) o[x][mt] = mfma32(vf[mt][kk], pf[x][kk], o[x][mt]);
-      if (has_next) load_v(tok + tstep, pg_next);
+      if constexpr (!FP8) {
+        if (has_next) load_v(tok + tstep, pg_next);
+      }
     }
   }
 
@@ -685,6 +743,16 @@ static int gqa_team_waves(const DecodeArgs& a, int n_items, int tt, int waves) {
 template <int DV>
 constexpr int gqa_merge_bytes(int waves) { return waves * (DV / 32 * 4 * 64 * 16 + 2 * 32 * 4); }  // O^T, then m and l per (wave, row)
 
+// 8-bit codes, eight waves that share k_R: two tiles of codes in flight where a chunk is long enough for the second tile's loads
+// at its start and the two empty tiles at its end; the more query rows, the later.  One tile over two (time of the call), 8 groups,
+// one round of 2048 waves, ragged sequences of several chunks (sequences of one chunk each): 4 rows a group, chunks of 2 tiles 0.95
+// (0.95), 4 1.04 (1.02), 8 1.06 (1.05); 8 rows, 4 tiles (1.03); 16 rows, 4 tiles 1.00 (0.93), 6 0.98 to 1.06 (0.95), 8 1.04 (1.00),
+// 12 1.03 (1.01); 32 rows, 8 tiles 1.03 (0.94), 12 1.02 (0.98), 16 1.08 (1.00), 48 (1.04).  16 and 32 groups the same to 2 %.  (Drawn
+// where neither kind loses.)
+// Forms that the second tile made slower in all sizes keep one: teams (one sequence of 8192 tokens, 8 groups 13.7 us against 14.8),
+// two or four groups (64 ragged sequences of 3000 to 12000 tokens, 4 groups 101 us against 106), k_R not shared (32 x 4096, 3 groups
+// 29.7 against 32.8), two row blocks a wave (64 ragged, 48 rows of 8 groups 340 against 364).
+static bool gqa_codes_deep(const DecodeArgs& a) { return a.g % 8 == 0 && a.chunk_tiles >= 4 && 2 * a.chunk_tiles > a.G * a.s_q; }
 template <bool FP8>
 static hipError_t launch_decode_gqa_128(const DecodeArgs& a, float k_scale, float v_scale, hipStream_t s) {
   int row_blocks, n_items, wpb, blocks;
@@ -692,28 +760,32 @@ static hipError_t launch_decode_gqa_128(const DecodeArgs& a, float k_scale, floa
   if (a.G * a.s_q > 32) {  // more than one row block per group: two per wave, four waves per workgroup
     gqa_launch_shape(a, 4, 64, row_blocks, n_items, team, wpb, blocks);
     constexpr int kQBytesPerWave = 2 * (128 / 16 + 64 / 16) * 1024;  // both row blocks' query fragments
-    static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 256, 2, false>,
+    static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 256, 2, false, false>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 4 * kQBytesPerWave);
     if (attr != hipSuccess) return attr;
-    decode_gqa_bf16_kernel<128, 128, 64, FP8, 256, 2, false><<<blocks, 64 * wpb, wpb * kQBytesPerWave, s>>>(a, n_items, row_blocks, team ? 1 : 0,
+    decode_gqa_bf16_kernel<128, 128, 64, FP8, 256, 2, false, false><<<blocks, 64 * wpb, wpb * kQBytesPerWave, s>>>(a, n_items, row_blocks, team ? 1 : 0,
                                                                                                     1, k_scale, v_scale);
     return hipGetLastError();
   }
   gqa_launch_shape(a, 8, 32, row_blocks, n_items, team, wpb, blocks);
   // one group: the plan cuts chunks for teams of eight
   const int tt = a.g == 1 ? 8 : gqa_token_team_size(a, n_items, 8);
-  // codes without a shared k_R (3, 5, 6, ... groups): teams of one, whose kernel has the registers for fragments of k_R that are
-  // requested a tile ahead (beside the shared form they would not fit)
-  if (tt > 1 || (FP8 && !team)) {
-    static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true>,
+  if (tt > 1) {
+    static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true, false>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, gqa_merge_bytes<128>(8));
     if (attr != hipSuccess) return attr;
     const int w = gqa_team_waves(a, n_items, tt, 8);
-    decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true><<<(n_items * tt + w - 1) / w, 64 * w, gqa_merge_bytes<128>(w), s>>>(a, n_items, row_blocks, 0, tt,
+    decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, true, false><<<(n_items * tt + w - 1) / w, 64 * w, gqa_merge_bytes<128>(w), s>>>(a, n_items, row_blocks, 0, tt,
                                                                                                                          k_scale, v_scale);
     return hipGetLastError();
   }
-  decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, false><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, k_scale, v_scale);
+  if constexpr (FP8) {
+    if (gqa_codes_deep(a)) {
+      decode_gqa_bf16_kernel<128, 128, 64, true, 512, 1, false, true><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, 1, 1, k_scale, v_scale);
+      return hipGetLastError();
+    }
+  }
+  decode_gqa_bf16_kernel<128, 128, 64, FP8, 512, 1, false, false><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, k_scale, v_scale);
   return hipGetLastError();
 }
 
@@ -724,14 +796,14 @@ hipError_t launch_decode_gqa_bf16(const DecodeArgs& a, hipStream_t s) {
     gqa_launch_shape(a, 4, 32, row_blocks, n_items, team, wpb, blocks);
     const int tt = gqa_token_team_size(a, n_items, 4);
     if (tt > 1) {
-      static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, true>,
+      static const hipError_t attr = hipFuncSetAttribute((const void*)decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, true, false>,
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, gqa_merge_bytes<256>(4));
       if (attr != hipSuccess) return attr;
       const int w = gqa_team_waves(a, n_items, tt, 4);
-      decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, true><<<(n_items * tt + w - 1) / w, 64 * w, gqa_merge_bytes<256>(w), s>>>(a, n_items, row_blocks, 0, tt, 1.f, 1.f);
+      decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, true, false><<<(n_items * tt + w - 1) / w, 64 * w, gqa_merge_bytes<256>(w), s>>>(a, n_items, row_blocks, 0, tt, 1.f, 1.f);
       return hipGetLastError();
     }
-    decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, false><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, 1.f, 1.f);
+    decode_gqa_bf16_kernel<192, 256, 64, false, 256, 1, false, false><<<blocks, 64 * wpb, 0, s>>>(a, n_items, row_blocks, team ? 1 : 0, 1, 1.f, 1.f);
     return hipGetLastError();
   }
   return launch_decode_gqa_128<false>(a, 1.f, 1.f, s);

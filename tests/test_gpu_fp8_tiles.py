@@ -1,7 +1,8 @@
-"""The GQA decode over the 8-bit cache works through its tiles in pairs, two requested ahead: chunks of one to seven tiles (last
-pairs with and without a second tile) in each form of the kernel -- k_R shared by all waves of a workgroup, by those of a row
-block, not at all (three, five groups), token teams, two row blocks a wave -- with NaN codes in every byte that no token owns, and
-with a page id out of range (its tokens count as absent).  Bars as everywhere."""
+"""The GQA decode over the 8-bit cache, chunks of one to seven tiles in each form of the kernel -- k_R shared by all waves of a
+workgroup, by those of a row block, not at all (three, five groups), token teams, two row blocks a wave -- and the form that keeps
+two tiles of codes in flight (groups a multiple of eight, chunks of at least four tiles and more than half as many as a group has rows:
+either side of those lines, and sequences of one tile to the whole chunk, last pairs with and without a second tile) -- with NaN codes in
+every byte that no token owns, and with a page id out of range (its tokens count as absent).  Bars as everywhere."""
 import numpy as np
 import pytest
 import torch
@@ -26,6 +27,13 @@ pytestmark = pytest.mark.gpu
     (16, 1, 2, [33, 300, 900], 8, 256, None),                          # one group: teams of eight, waves with no, one, two tiles
     (128, 4, 2, [33, 65, 97, 200], 4, 1, None),                        # two row blocks a wave
     (120, 3, 1, [33, 65, 97, 200], 4, 1, 1),                           # the same, k_R not shared
+    (56, 8, 1, [1, 32, 33, 64, 65, 97, 128, 300], 2, 1, None),         # 7 rows, four tiles: two in flight
+    (64, 8, 1, [1, 33, 64, 130, 300], 2, 1, None),                     # 8 rows: one
+    (128, 8, 1, [1, 33, 64, 130, 225, 320, 600], 5, 1, None),          # 16 rows, ten tiles: two
+    (128, 8, 1, [33, 161, 256, 400], 4, 1, None),                      # eight: one
+    (128, 8, 2, [2, 33, 64, 290, 545, 576, 700], 9, 1, None),          # 32 rows, eighteen tiles: two
+    (128, 8, 2, [33, 417, 512, 700], 8, 1, None),                      # sixteen: one
+    (48, 16, 1, [33, 200, 129], 4, 1, 1),                              # 16 groups, two in flight, the second page of each sequence lost
 ])
 def test_fp8_tiles(h_q, g, s_q, lens, cp, num_cus, lost):
     print("fp8 tiles", h_q, g, s_q, lens, cp, num_cus, lost, flush=True)

@@ -1449,11 +1449,15 @@ __global__ void __launch_bounds__(256) decode_absorb_shared_bf16_kernel(DecodeAr
 // Measured (kernel): one sequence, 22 chunks, 128 rows: 18.2 -> 7.9 us; 64 sequences, 4 chunks each: 13.1 -> 12.0 us; 128
 // ragged sequences of 256 rows, 201 MB of partials: 50.7 -> 35.5 us.  (Before: a block per workgroup, W_UV staged by each and
 // ahead of the partials, the K range split over the waves and 64 KB of fp32 results summed through LDS.)
-// DV: value dims per head (columns of W_UV[j], elements of an output row); a workgroup projects onto PD of them, blockIdx.z
-// selects which (the merge is repeated per slice).  PD = 64 where that still is one workgroup per unit: a unit stages half of
+// DV: value dims per head (columns of W_UV[j], elements of an output row); a workgroup projects onto PD of them (the merge is
+// repeated per slice).  PD = 64 where that still is one workgroup per unit: a unit stages half of
 // W_UV (4 sequences x 8192 tokens x 128 rows 8.8 -> 8.2 us, 32 ragged x 32 rows 7.8 -> 7.2, 16 rows of a group 8.6 -> 7.8).
+// The slices of a block go to ids that are equal modulo 8, i.e. to one die: read through two L2s, a block's partials also cost the
+// next call's decode, which writes those lines again (4 sequences of 2000 to 4000 tokens, 3 groups x 36 rows: 27.7 -> 25.0 us a call;
+// with all 128 dims in one workgroup 25.7).
+// wgs: workgroups per group and slice.
 template <int RKV, int DV, int PD>
-__global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a, int rows_per_group, int log2_rows, int n_blocks) {
+__global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a, int rows_per_group, int log2_rows, int n_blocks, int wgs) {
   constexpr int KSW = RKV / 16 / 8;  // k-steps of the contraction that one wave merges
   constexpr int kNB = 4;             // chunks in flight
   static_assert(KSW == 4, "eight waves x 4 k-steps");
@@ -1462,8 +1466,11 @@ __global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 31, h = lane >> 5;
-  const int j = blockIdx.y;
-  const int col0 = blockIdx.z * PD;  // first value dim of this workgroup
+  constexpr int kSlices = DV / PD;
+  const int wg = kSlices == 1 ? blockIdx.x : blockIdx.x / (8 * kSlices) * 8 + blockIdx.x % 8;
+  if (wg >= wgs * a.g) return;  // whole workgroup (the grid is filled up to eights)
+  const int j = wg / wgs, first = wg % wgs;
+  const int col0 = kSlices == 1 ? 0 : blockIdx.x / 8 % kSlices * PD;  // first value dim of this workgroup
   const int rows = 1 << log2_rows, slice = n >> log2_rows, slices = 32 >> log2_rows;
   const int64_t chunk_stride = (int64_t)((a.M + 31) / 32) * 32 * RKV;  // elements from one chunk's partials to the next
 
@@ -1492,7 +1499,7 @@ __global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a
     for (int ks = 0; ks < KSW; ++ks) v[k][ks] = *(const u32x4*)(po + ks * (2 * 32 * 8));
   };
 
-  Row row = row_of(blockIdx.x);
+  Row row = row_of(first);
 #pragma unroll
   for (int k = 0; k < kNB; ++k) fetch(row, k, row.s0 + slice + k * slices);
   {
@@ -1518,9 +1525,9 @@ __global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a
   };
   bool staged = false;
 
-  for (int blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {
+  for (int blk = first; blk < n_blocks; blk += wgs) {
     Row next = row;
-    if (blk + (int)gridDim.x < n_blocks) next = row_of(blk + gridDim.x);  // (its chunk range arrives behind the merge)
+    if (blk + wgs < n_blocks) next = row_of(blk + wgs);  // (its chunk range arrives behind the merge)
     float m = GQLA_NEG_INF, den = 0.f;
     float acc[KSW][8];  // merged latent of this lane's column, dims 16 * (KSW * wave + ks) + 8 * h + 0..7
 #pragma unroll
@@ -1571,7 +1578,7 @@ __global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a
     float den_row = den * scale_own;
     for (int o = rows; o < 32; o <<= 1) den_row += __shfl_xor(den_row, o);
     const float norm = (row.ok && den_row > 0.f) ? scale_own / den_row : 0.f;
-    if (blk != (int)blockIdx.x) __syncthreads();  // every wave has read the previous block's exchange
+    if (blk != first) __syncthreads();  // every wave has read the previous block's exchange
 #pragma unroll
     for (int ks = 0; ks < KSW; ++ks)
       *(u32x4*)(exch + (KSW * wave + ks) * 1024 + lane * 16) =
@@ -1581,7 +1588,7 @@ __global__ void __launch_bounds__(512) combine_project_bf16_kernel(CombineArgs a
       wait_all_memory();                           // W_UV[j]: this wave's share
       staged = true;
     }
-    if (blk + (int)gridDim.x < n_blocks) {
+    if (blk + wgs < n_blocks) {
 #pragma unroll
       for (int k = 0; k < kNB; ++k) fetch(next, k, next.s0 + slice + k * slices);
     }
@@ -1675,8 +1682,9 @@ static hipError_t launch_combine_project_dims(const CombineArgs& a, int log2_row
       hipFuncSetAttribute((const void*)combine_project_bf16_kernel<512, DV, PD>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return attr;
   const int per_group = 256 / (a.g * (DV / PD));  // workgroups per group: one per compute unit, each with its share of the blocks
-  combine_project_bf16_kernel<512, DV, PD><<<dim3(n_blocks < per_group || per_group < 1 ? n_blocks : per_group, a.g, DV / PD), 512, kLds, s>>>(
-      a, a.B * a.s_q * a.G, log2_rows, n_blocks);
+  const int wgs = n_blocks < per_group || per_group < 1 ? n_blocks : per_group;
+  const int grid = DV == PD ? wgs * a.g : (wgs * a.g + 7) / 8 * 8 * (DV / PD);
+  combine_project_bf16_kernel<512, DV, PD><<<grid, 512, kLds, s>>>(a, a.B * a.s_q * a.G, log2_rows, n_blocks, wgs);
   return hipGetLastError();
 }
 

@@ -16,6 +16,12 @@ pytestmark = pytest.mark.gpu
     (64, 8, 2, 128, 0, [100] * 8),                   # 16 blocks of 8 rows, 256 workgroups: the last with halves
     (64, 8, 2, 128, 0, [100] * 9),                   # 18 blocks: 128 dims together
     (20, 4, 2, 192, 256, [90, 200]),                 # four halves of 256 value dims
+    # the halves of a block go to ids equal modulo 8: workgroups per half not a multiple of 8, the grid filled up
+    (54, 3, 2, 128, 0, [300, 70, 2, 130]),           # 108 and 4 empty ones
+    (18, 1, 2, 128, 0, [500]),                       # 9 and 7
+    (20, 5, 1, 192, 256, [130, 64, 3]),              # four quarters, 15 and 1
+    (30, 15, 1, 192, 256, [200] * 9),                # both 128s, 75 and 5
+    (20, 5, 2, 192, 256, [40] * 60),                 # 60 blocks a group in 25 workgroups, 125 and 3
 ])
 def test_halves(h_q, g, s_q, d_h, d_v, lens):
     cfg = S.CONFIGS["C3"].with_(B=len(lens), h_q=h_q, g=g, s_q=s_q, L=0, paged=True, seed=98, d_h=d_h, d_v=d_v)

@@ -1080,8 +1080,14 @@ static hipError_t launch_expand_tail_dims(const ExpandArgs& a, void* ws, hipStre
   const int tokens = a.B * a.tail;
   const int stages = a.group_count * NSUB, tiles = (tokens + 31) / 32;
   // Weights that are not repacked yet and few tokens: taken as they are (4 tokens, 8 groups, 8-bit step 27.8 -> 23.0 us, 64 tokens
-  // 201.3 -> 198.6: a launch of 5 us less, 2 us more for the transposed reads).
-  if (a.weights == 0 && tiles <= 8) {
+  // 201.3 -> 198.6: a launch of 5 us less, 2 us more for the transposed reads).  Each tile of 32 tokens reads all weights that way,
+  // 64 KB a stage and slower than repacked ones once they are far beyond the L2s, so the more stages, the fewer tiles.  Call,
+  // repacked over direct, 16-bit / 8-bit cache of (128, 128): 192 stages (48 groups), 8 tiles 1.25 / 1.09; 256 stages, 6 tiles 1.15 /
+  // 1.02, 8 1.07 / 0.96; 320 stages, 3 tiles 1.07 / 1.01, 4 1.08 / 0.97, 5 0.94 / 0.89; 384 stages, 2 tiles 1.17 / 1.12, 3 1.02 / 0.92;
+  // 448 stages, 2 tiles 1.04 / 0.98; 512 stages, 1 tile 1.47 / 1.43, 2 1.02 / 0.96, 8 0.75 / 0.69; of (192, 256): 224 stages (32
+  // groups), 6 tiles 1.05, 8 0.98; 448 stages, 1 tile 1.53, 2 1.11, 4 0.85.
+  const int most = stages <= 192 ? 8 : stages <= 256 ? 6 : stages <= 320 ? 3 : stages <= 384 ? 2 : 1;
+  if (a.weights == 0 && tiles <= most) {
     expand_tail_bf16_kernel<DH, DV, 512, 64, FP8, 1, true><<<dim3(stages * 2, tiles), 64, 0, s>>>(a, nullptr);
     return hipGetLastError();
   }

@@ -100,6 +100,45 @@ def test_tail(g, d_h, d_v, nb, tail, fp8):
 
 
 @pytest.mark.parametrize("fp8", [False, True])
+@pytest.mark.parametrize("g,d_h,d_v,tokens,repacked", [
+    (48, 128, 128, 256, False),                          # 192 stages, eight tiles
+    (64, 128, 128, 192, False),                          # 256, six
+    (64, 128, 128, 193, True),                           # seven
+    (80, 128, 128, 96, False),                           # 320, three
+    (65, 128, 128, 97, True),                            # 260, four
+    (96, 128, 128, 65, True),                            # 384, three
+    (128, 128, 128, 32, False),                          # 512, one
+    (128, 128, 128, 33, True),                           # two
+    (64, 192, 256, 32, False),                           # 448, one
+    (64, 192, 256, 64, True),                            # two
+])
+def test_tail_of_many_groups(g, d_h, d_v, tokens, repacked, fp8):
+    """Weights far beyond the caches are repacked from fewer tokens on (each tile of 32 tokens reads them all); the scratch shows
+    which form ran.  Against the whole expansion: the same bits."""
+    if fp8 and d_h != 128:
+        pytest.skip("the 8-bit expanded cache has key and value dims of 128")
+    lens = [1 + (37 * i) % 90 for i in range(tokens)]
+    B, s = _setup(g, d_h, d_v, lens, max(-(-n // 64) for n in lens))
+    shape = B.make_shape(tokens, g, g, d_h, s["r_kv"], s["d_r"], 1, B.GQLA_BF16, 0.0, d_v)
+    elems = B.gqla_expanded_fp8_bytes_per_token(g, d_h, s["d_r"]) if fp8 else 2 * (g * (d_h + d_v) + s["d_r"])
+    lat, t1 = _cache(B, s, s["pool"], s["max_pages"])
+    outs = [torch.full((s["num_pages"] * 64 * elems,), 0x5A, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    scales = (0.02, 0.03) if fp8 else ()
+    print("tail many groups", g, d_h, tokens, fp8, flush=True)
+    ws = torch.full((B.gqla_expand_workspace_bytes(shape, g),), 0x5A, dtype=torch.uint8, device="cuda")
+    exp, t2 = _cache(B, s, outs[0], s["max_pages"], g)
+    (B.gqla_expand_cache_tail_fp8 if fp8 else B.gqla_expand_cache_tail)(shape, lat, s["w_uk"], s["w_uv"], 0, g, exp, 1, *scales, ws)
+    torch.cuda.synchronize()
+    assert bool((ws != 0x5A).any()) == repacked
+    exp, t2 = _cache(B, s, outs[1], s["max_pages"], g)
+    (B.gqla_expand_cache_fp8 if fp8 else B.gqla_expand_cache)(shape, lat, s["w_uk"], s["w_uv"], 0, g, exp, *scales, ws)
+    torch.cuda.synchronize()
+    wrote = outs[0] != 0x5A
+    assert torch.equal(outs[0][wrote], outs[1][wrote])
+    assert int(wrote.sum()) >= tokens * elems * 0.9      # (a byte may equal the fill)
+
+
+@pytest.mark.parametrize("fp8", [False, True])
 @pytest.mark.parametrize("g,d_h,d_v,blocks", [
     (8, 128, 128, 129),                                  # the fewest whose (block, group) pairs are dealt out evenly
     (8, 128, 128, 192),                                  # the most: six groups a workgroup

@@ -189,7 +189,7 @@ __global__ void __launch_bounds__(256) pack_weights_bf16_kernel(ExpandArgs a, __
 // that the end-of-stage wait (which also covers stores on this hardware) finds them long gone.
 // With an odd number of stages per group (DH = 192, DV = 256: seven) the two result sets would meet at the group
 // boundary, so there the group's last stage stores its results at once instead of in the next stage's shadow.
-__device__ __forceinline__ int expand_parts(int rest, int groups) {  // shares of the groups for `rest` blocks of a round
+__host__ __device__ __forceinline__ int expand_parts(int rest, int groups) {  // shares of the groups for `rest` blocks of a round
   int p = 256 / rest;
   if (p > groups) p = groups;
   const int per = (groups + p - 1) / p;
@@ -1134,10 +1134,19 @@ static hipError_t launch_expand_one_shot(const ExpandArgs& a, void* ws, hipStrea
   // tokens into the 8-bit cache 216 -> 190 us; 122 680 ragged tokens in 32 sequences 286 -> 240 us.
   const int64_t blocks = ((int64_t)a.max_tokens + 255) / 256 * a.B;
   const unsigned grid = (unsigned)std::min<int64_t>((blocks + 255) & ~(int64_t)255, kMaxWorkgroups);
-  // Few blocks (what the rows of the page table could hold): the weights as they are, without the launch that repacks them.  The
-  // transposed reads cost a block 3 %: 10 blocks, 8 groups 24.6 -> 21.8 us, 66 blocks, 4 groups of (192, 256) 31.2 -> 30.6, 80
-  // blocks the same either way, 128 blocks 64.1 -> 66.0.
-  if (blocks <= 72) return launch_expand_kernel<DH, DV, FP8, true>(a, nullptr, grid, s);
+  // Few blocks (what the rows of the page table could hold) and few groups a workgroup: the weights as they are, without the launch
+  // that repacks them.  The transposed reads cost a block 3 % (10 blocks, 8 groups 24.6 -> 21.8 us, 80 blocks the same either way,
+  // 128 blocks 64.1 -> 66.0), and a wave whose 64 tokens are not all there about 1 us a group, which stores at half the speed for
+  // want of scalar registers (sequences of 20 to 250 tokens: 20 blocks, 32 groups, 3 a workgroup 1.05 times as fast; 44 blocks, 7 a
+  // workgroup 1.00; 60 blocks, 48 groups, 12 a workgroup 0.96; 72 blocks, 64 groups, 22 a workgroup 0.91).  With seven stages a group,
+  // (192, 256), that outweighs the launch at once (200 tokens, 1 group 30.4 us repacked, 32.5 direct; 64 ragged sequences, 8 groups
+  // 51.7 and 56.0; full waves 2 to 10 % faster): always repacked.
+  if constexpr (NSUB % 2 == 0) {
+    if (blocks <= 72) {
+      const int parts = expand_parts((int)blocks, a.group_count);
+      if ((a.group_count + parts - 1) / parts <= 6) return launch_expand_kernel<DH, DV, FP8, true>(a, nullptr, grid, s);
+    }
+  }
   pack_weights_bf16_kernel<DH, DV, 512><<<dim3(a.group_count * NSUB, 512 / 64), 256, 0, s>>>(a, (__bf16*)ws);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

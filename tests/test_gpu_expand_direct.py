@@ -36,6 +36,8 @@ def _cache(B, s, pool, width, groups=0):
     (4, 1, 2, 128, 128, [700, 0, 31]),                   # a slice of two groups
     (5, 0, 5, 192, 256, [513, 90]),                      # seven stages a group
     (1, 0, 1, 128, 128, [256 * 9 + 5]),                  # one group: nothing to share out
+    (32, 1, 24, 128, 128, [70] * 64),                    # 24 groups in four shares: six a workgroup
+    (32, 1, 25, 128, 128, [70] * 64),                    # seven: repacked
 ])
 def test_one_shot(g, first, count, d_h, d_v, lens, fp8):
     if fp8 and d_h != 128:
@@ -52,12 +54,15 @@ def test_one_shot(g, first, count, d_h, d_v, lens, fp8):
         lat, t1 = _cache(B, s, s["pool"], width)
         exp, t2 = _cache(B, s, out, width, count)
         print("expand direct", g, first, count, d_h, fp8, width, flush=True)
+        ws.fill_(0x5A)
         if fp8:
             B.gqla_expand_cache_fp8(shape, lat, s["w_uk"], s["w_uv"], first, count, exp, 0.02, 0.03, ws)
         else:
             B.gqla_expand_cache(shape, lat, s["w_uk"], s["w_uv"], first, count, exp, ws)
         torch.cuda.synchronize()
         got.append(out)
+        # the scratch shows which form ran: few blocks of (128, 128) and few groups as they are, the rest repacked
+        assert bool((ws != 0x5A).any()) == (width == wide or d_h == 192 or count == 25)
     assert torch.equal(got[0], got[1])
 
 

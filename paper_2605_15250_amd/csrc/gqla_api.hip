@@ -674,7 +674,8 @@ gqla_status gqla_output_projection(const gqla_shape* shape, int32_t d_model, con
   if (d_model % 128 || K % 256 || K > (1 << 24)) return GQLA_ERR_SHAPE;   // the kernel's row offsets inside a tile are 32-bit
   a.rows = out_proj_rows(a.M, a.K, a.D);
   a.ksplit = out_proj_split(a.M, a.K, a.D, a.rows, &a.krange);
-  if (a.rows == 256 && ws_bytes < (size_t)a.ksplit * M * d_model * sizeof(float)) {   // scratch for half as many ranges: 128 rows
+  // no scratch, or enough for half as many ranges only: 128 rows
+  if (a.rows == 256 && a.ksplit > 1 && (!ws || ws_bytes < (size_t)a.ksplit * M * d_model * sizeof(float))) {
     a.rows = 128;
     a.ksplit = out_proj_split(a.M, a.K, a.D, a.rows, &a.krange);
   }

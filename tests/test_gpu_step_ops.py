@@ -113,6 +113,48 @@ def test_output_projection_takes_128_rows_where_the_scratch_is_for_them():
         assert ((got.double() - ref).norm() / ref.norm()).item() < 2.0 ** -8   # one rounding to bf16
 
 
+@pytest.mark.parametrize("rows,d_model,k", [
+    (129, 16512, 2048),         # one range, stored without a reduction: no scratch asked for, none passed
+    (256, 16512, 2304),
+    (130, 4096, 16640),         # 65 pieces of 256 k in eight ranges: the last has two, the others nine
+    (200, 8320, 6144),          # three ranges
+])
+def test_output_projection_256_rows(rows, d_model, k):
+    from paper_2605_15250_amd import binding as B
+    shape = B.make_shape(rows, k // 128, 1, 128, 512, 64, 1, B.GQLA_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    o = torch.randn(rows, k, device="cuda", generator=gen).bfloat16()
+    w_o = (torch.randn(d_model, k, device="cuda", generator=gen) / 64).bfloat16()
+    n = B.gqla_output_projection_workspace_bytes(shape, d_model)
+    assert (n == 0) == (d_model > 16384)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda") if n else None
+    y = torch.full((rows, d_model), float("nan"), dtype=torch.bfloat16, device="cuda")
+    print("256 rows", rows, d_model, k, n, flush=True)
+    B.gqla_output_projection(shape, d_model, o, w_o, y, ws)
+    torch.cuda.synchronize()
+    ref = o.double() @ w_o.double().T
+    assert ((y.double() - ref).norm() / ref.norm()).item() < 2.0 ** -8   # one rounding to bf16
+
+
+def test_output_projection_without_scratch_where_128_rows_need_none():
+    """256 rows per workgroup would take two ranges and scratch; without any (whatever size is claimed for it) 128 rows do it in
+    one range, as they did before there was a choice."""
+    from paper_2605_15250_amd import binding as B
+    rows, d_model, k = 130, 16384, 6144
+    shape = B.make_shape(rows, k // 128, 1, 128, 512, 64, 1, B.GQLA_BF16)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    o = torch.randn(rows, k, device="cuda", generator=gen).bfloat16()
+    w_o = (torch.randn(d_model, k, device="cuda", generator=gen) / 64).bfloat16()
+    full = B.gqla_output_projection_workspace_bytes(shape, d_model)
+    assert full == 2 * rows * d_model * 4
+    ref = o.double() @ w_o.double().T
+    for ws_bytes in (0, full):
+        y = torch.full((rows, d_model), float("nan"), dtype=torch.bfloat16, device="cuda")
+        B.gqla_output_projection(shape, d_model, o, w_o, y, None, ws_bytes)
+        torch.cuda.synchronize()
+        assert ((y.double() - ref).norm() / ref.norm()).item() < 2.0 ** -8   # one rounding to bf16
+
+
 @pytest.mark.parametrize("key,lens,page_size,s_q,d_model", [
     ("C3", [300, 2, 64, 129, 1000], 64, 2, 256),
     ("C1", [65, 64, 1, 4000], 64, 1, 384),

@@ -297,11 +297,16 @@ hipError_t launch_out_proj_f32(const OutProjArgs& a, hipStream_t s) {
 // pull, so bytes are what counts), but the ranges of k get half as long.  Measured, 128 -> 256 rows, ranges of 4096 k: (256
 // rows, D = 7168, K = 16384) 93.0 -> 80.5 us, 140 rows 85.8 -> 74.1; of 1024 k: (256, 7168, 4096) 34.1 -> 33.5, (256, 4096,
 // 8192) 35.1 -> 35.5, (140, 2048, 16384) 30.6 -> 31.5; of 512 k: (256, 7168, 2048) 24.2 -> 26.5, (160, 2048, 5120) 18.6 ->
-// 21.3.  So where the ranges keep 2048.  More rows, a third block of 128 half empty or full: 300 rows 151 -> 135 us, 384 rows
-// 155 -> 170, left as they are.  (Beyond 2^23 k the byte offset of row 255 would not fit in the kernel's 32 bits.)
+// 21.3; of 2048 k: (129, 8192, 8192) 49.7 -> 44.2, (256, 8192, 8192) 53.6 -> 52.6, (256, 4096, 16384) 54.6 -> 48.5.  So where the
+// ranges keep 2048.  Two ranges (d_model over 10880, up to 16384) cost a reduction that 128 rows do without, so there 3072: K = 4096,
+// D = 16384, 129 rows 44.1 -> 44.5, 192 rows 45.0 -> 47.8, 256 rows 47.2 -> 52.9, D = 12288 44.1 -> 39.0, 42.2 -> 41.6, 43.5 ->
+// 44.2; K = 6144, D = 16384 69.6 -> 56.7, 70.2 -> 60.7, 70.4 -> 69.5.  One range (d_model over 16384): (256, 18432, 2048) 47.4 -> 33.0.
+// More rows, a third block of 128 half empty or full: 300 rows 151 -> 135 us, 384 rows 155 -> 170: 256 at most.  (Beyond 2^23 k
+// the byte offset of row 255 would not fit in the kernel's 32 bits.)
 int out_proj_rows(int M, int K, int D) {
   if (M <= 64) return 64;
-  return M > 128 && M <= 256 && K <= (1 << 23) && K / std::max(256 / (D / kOpN), 1) >= 2048 ? 256 : 128;
+  const int ranges = std::max(256 / (D / kOpN), 1);
+  return M > 128 && M <= 256 && K <= (1 << 23) && K / ranges >= (ranges == 2 ? 3072 : 2048) ? 256 : 128;
 }
 
 // k-ranges of the bf16 kernel: as many as keep the launch within one workgroup per compute unit of a 256-unit chip (the

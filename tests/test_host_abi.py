@@ -351,6 +351,11 @@ def test_step_ops_validate_on_the_host():
     # 7168 columns (56 tiles), K = 16384 (64 pieces): 256 // 56 = 4 ranges of 16 pieces
     big = B.make_shape(64, 128, 8, 128, 512, 64, 1, B.GQLA_BF16)
     assert B.gqla_output_projection_workspace_bytes(big, 7168) == 4 * 64 * 7168 * 4
+    # 129 to 256 rows with two ranges, where 128 rows per workgroup need none and no reduction: only from 3072 k a range on
+    rows = lambda k: B.make_shape(200, k // 128, 1, 128, 512, 64, 1, B.GQLA_BF16)
+    assert B.gqla_output_projection_workspace_bytes(rows(4096), 16384) == 0
+    assert B.gqla_output_projection_workspace_bytes(rows(5888), 12288) == 0
+    assert B.gqla_output_projection_workspace_bytes(rows(6144), 16384) == 2 * 200 * 16384 * 4
     # compress: needs all groups, matching geometry, g d_h >= r_kv
     full = B.make_cache(A, A, None, 64, 4, 8, 8)
     lat = B.make_cache(A, A, None, 64, 4, 8, 0)

@@ -53,6 +53,44 @@ def test_rope_step_matches_the_oracle(key, lens, s_q, base):
     assert torch.equal(d_q2, d_q) and torch.equal(d_rows2, d_rows)
 
 
+@pytest.mark.parametrize("d_r,h_q,s_q", [
+    (24, 1, 1),        # 12 pairs: thread 500 starts in the middle of a vector, 512 pairs on is pair 8 further
+    (24, 300, 2),      # 3600 pairs: more than the four slots of one pass
+    (40, 130, 1),      # 20 pairs a vector
+    (96, 50, 2),       # 48
+    (232, 40, 1),      # 116
+    (512, 9, 1),       # 256, the most
+])
+def test_rope_step_pairs_carried_along(d_r, h_q, s_q):
+    """Rotary dims whose half does not divide the 512 threads: a pair's place in its vector moves from slot to slot and from pass to
+    pass.  All pairs together, the queries alone and the rows alone."""
+    from paper_2605_15250_amd import binding as B
+    lens, base, r_kv = [1000, 1, 70001], 10000.0, 16
+    shape = B.make_shape(len(lens), h_q, 1, 16, r_kv, d_r, s_q, B.GQLA_F32)
+    d_lens = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    r = S.rng(1619, d_r)
+    q = r.standard_normal((len(lens), s_q, h_q, d_r), dtype=np.float32)
+    rows = r.standard_normal((len(lens), s_q, r_kv + d_r), dtype=np.float32)
+    for with_q, with_rows in ((True, True), (True, False), (False, True)):
+        d_q, d_rows = torch.from_numpy(q).cuda(), torch.from_numpy(rows).cuda()
+        print("rope pairs", d_r, h_q, s_q, with_q, with_rows, flush=True)
+        B.gqla_rope_step(shape, d_lens, base, d_q if with_q else None, d_rows if with_rows else None)
+        torch.cuda.synchronize()
+        got_q, got_rows = host(d_q), host(d_rows)
+        assert np.array_equal(got_rows[..., :r_kv], rows[..., :r_kv])
+        for b, L in enumerate(lens):
+            for i in range(s_q):
+                t = L - s_q + i
+                if t < 0 or not with_q:
+                    assert np.array_equal(got_q[b, i], q[b, i])
+                else:
+                    check("rope q_R d_r %d seq %d tok %d" % (d_r, b, i), got_q[b, i], O.rope(q[b, i], t, base), "f32")
+                if t < 0 or not with_rows:
+                    assert np.array_equal(got_rows[b, i], rows[b, i])
+                else:
+                    check("rope k_R d_r %d seq %d tok %d" % (d_r, b, i), got_rows[b, i, r_kv:], O.rope(rows[b, i, r_kv:], t, base), "f32")
+
+
 @pytest.mark.parametrize("key,Bsz,s_q,d_model,h_q", [
     ("C1", 5, 2, 256, 32),      # 10 rows: one ragged row tile, 16 k-ranges
     ("C1", 70, 2, 128, 32),     # 140 rows: two row blocks, the second ragged

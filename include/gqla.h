@@ -171,8 +171,9 @@ gqla_status gqla_decode_absorb(const gqla_shape* shape, const gqla_plan* plan, c
  * expanded->groups == group_count groups and which must use the same page_size, max_pages and page ids
  * (page_table content) as `latent`.  A slice with group_count < g is one rank's share of head-axis
  * tensor parallelism.  `ws` is device scratch of at least gqla_expand_workspace_bytes(shape, group_count) bytes
- * (16-byte aligned; it receives the slice's weights reordered for the matrix cores and may be reused or freed
- * once the call's kernels have run); with dtype GQLA_F32 no scratch is needed and ws may be NULL.
+ * (16-byte aligned; it may be reused or freed once the call's kernels have run, and what it holds then is unspecified:
+ * calls with few tokens leave it as it was, others reorder the slice's weights in it); with dtype GQLA_F32 no scratch is
+ * needed and ws may be NULL.
  * Errors: GQLA_ERR_SHAPE for a group range outside [0, g) or expanded->groups != group_count, GQLA_ERR_PAGE when
  * the two caches disagree on geometry, GQLA_ERR_WORKSPACE when ws is NULL or too small. */
 gqla_status gqla_expand_cache(const gqla_shape* shape, const gqla_cache* latent, const void* w_uk,
@@ -201,13 +202,14 @@ gqla_status gqla_expand_cache_tail(const gqla_shape* shape, const gqla_cache* la
                                    const gqla_cache* expanded, int32_t tail_tokens, void* ws, size_t ws_bytes,
                                    void* stream);
 
-/* The step's expansion with the weights repacked ahead of time.  gqla_expand_cache and gqla_expand_cache_tail first
- * reorder the slice's W_UK, W_UV into the operand order of the matrix instructions, in the caller's scratch; a serving
- * loop, whose weights do not change, does that once: gqla_pack_expand_weights writes the reordered copy of groups
+/* The step's expansion with the weights repacked ahead of time.  gqla_expand_cache and gqla_expand_cache_tail reorder the
+ * slice's W_UK, W_UV into the operand order of the matrix instructions, in the caller's scratch, unless there are so few tokens
+ * that reading the weights as they are is faster; a serving loop, whose weights do not change, reorders them once:
+ * gqla_pack_expand_weights (and nothing else: see `ws` above) writes the reordered copy of groups
  * group_begin .. group_begin + group_count - 1 into `packed` (device memory, 16-byte aligned, at least
  * gqla_expand_workspace_bytes(shape, group_count) bytes; the layout is the library's own and holds for this build and
  * this shape only), and gqla_expand_cache_tail_packed is gqla_expand_cache_tail reading that copy -- same results bit
- * for bit, one kernel less per step.  GQLA_BF16 only (GQLA_ERR_DTYPE otherwise: the fp32 kernels read the weights as they
+ * for bit, never a reordering kernel.  GQLA_BF16 only (GQLA_ERR_DTYPE otherwise: the fp32 kernels read the weights as they
  * are); `packed` must stay untouched between the two calls; other arguments, geometry rules and errors as for
  * gqla_expand_cache_tail (GQLA_ERR_WORKSPACE when packed_bytes is too small).  Both calls only enqueue work on `stream`. */
 gqla_status gqla_pack_expand_weights(const gqla_shape* shape, const void* w_uk, const void* w_uv, int32_t group_begin,
@@ -326,7 +328,7 @@ int64_t gqla_expanded_fp8_bytes_per_token(int32_t groups, int32_t d_h, int32_t d
  * device) into an 8-bit one with the same page geometry and page ids (each cache may have its own page table); bytes
  * of slots no token owns are left as they are.  gqla_decode_absorb_fp8 is gqla_decode_absorb over such a cache (same
  * plan, workspace and outputs): the MQA-absorb equation (Sec. 3.1) with keys [c'; k_R] and values c', c' = value(code)
- * * c_scale; the codes are widened to bf16 (exactly) on their way into LDS, the scale is applied to the content part
+ * * c_scale; the codes are widened to bf16 (exactly) in registers, the scale is applied to the content part
  * of the logits and to the output.  GQLA_BF16 shapes only (GQLA_ERR_DTYPE otherwise); a scale that is not positive and
  * finite: GQLA_ERR_SHAPE; other errors as for gqla_decode_absorb. */
 gqla_status gqla_quantize_latent(const gqla_shape* shape, const gqla_cache* latent, const gqla_cache* latent_fp8,

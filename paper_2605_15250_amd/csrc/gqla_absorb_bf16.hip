@@ -171,8 +171,9 @@ __global__ void __launch_bounds__(256) decode_absorb_bf16_kernel(DecodeArgs a, i
   //                    -> four bases (b = 0..3), plus a4*PANEL.
   //  value fragments   (transposed reads) this lane addresses row R0 + 4*h + e (and 8 rows further for the second read),
   //                    4 columns at 32*dt + 16*g1 + 4*q: panel dt/2, in-panel chunk 4*(dt & 1) + cl, cl = 2*g1 + q/2.
-  //                    With R0 a multiple of 16, swz = 2*h + e/2 for the first read and 4 + that for the second, so the
-  //                    chunk lands at 4*(dt & 1) + (cl ^ swz) resp. 4*(1 - (dt & 1)) + (cl ^ swz): one base per lane.
+  //                    With R0 a multiple of 16 the chunk lands at (4*(dt & 1) + cl) ^ lds_swz(4*h + e); 8 rows further the
+  //                    swizzle differs in bit 0, so dt & 1 flips bit 2 of the chunk (64 bytes) and the second read bit 0 (16 bytes): one
+  //                    base per lane.
   uint32_t kbase[4], vbase;
   {
 #pragma unroll

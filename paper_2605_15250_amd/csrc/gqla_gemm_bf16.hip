@@ -373,7 +373,7 @@ __device__ __forceinline__ void expand_block(const ExpandArgs& a, const __bf16* 
         if constexpr (DIRECT) return tr_natural_frag<RKV>(buf, tr, ks, e);
         else return *(const bf16x8*)(buf + (2 * ks + e) * 1024);
       };
-      // the stage after this one (behind the last: that one again, into the buffer nobody reads any more: no branch)
+      // the stage after this one (behind the last: the last group's first, into the buffer nobody reads any more: no branch)
       const bool last_group = jj + 1 == jj_count;
       using Next = std::integral_constant<int, (sub + 1) % NSUB>;
       const int next = sub + 1 < NSUB ? stage + 1 : (last_group ? jj * NSUB : stage + 1);

@@ -1669,7 +1669,8 @@ hipError_t launch_decode_absorb_bf16(const DecodeArgs& a, hipStream_t s) {
 
 hipError_t launch_decode_absorb_fp8(const DecodeArgs& a, float c_scale, hipStream_t s) {
   // the same choice of row mapping as for the 16-bit cache; more rows: blocks of 128, the last one padded (64 rows: see the
-  // kernel)
+  // kernel; padding most of a second block still wins over one wave per 32 rows: 64 ragged sequences of 3000 to 12000 tokens x 130
+  // rows 343 -> 289 us, x 160 rows 342 -> 290, 128 of 300 to 900 x 144 rows 85 -> 69)
   const int chunks_padded = (a.n_chunks + 7) / 8 * 8;
   if (a.M <= 32 || chunks_padded * ((a.M + 31) / 32) <= a.num_cus) return launch_decode_absorb_rows32<true>(a, c_scale, s);
   return launch_decode_absorb_shared<true>(a, c_scale, s);

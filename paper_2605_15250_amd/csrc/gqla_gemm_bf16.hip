@@ -1001,7 +1001,8 @@ __device__ __forceinline__ void compress_part(const CompressArgs& a, char* smem,
 // Grid as in the expansion: bounded, a workgroup takes tile blockIdx.x, then the one a grid further, and so on.  With few tiles
 // (the lengths live on the device: counted here) a workgroup takes a quarter or half of a tile's latent dims, as long as all
 // of them run at once (quarters in two rounds: 76 tiles 24.9 -> 29.4 us) and do not crowd the L2 that serves A^+ and the keys,
-// which each share reads again (halves: 76 tiles 24.8 -> 22.2 us, but 126 tiles 25.7 -> 26.7).
+// which each share reads again (halves: 65 tiles 24.2 -> 21.5 us, 96 tiles 24.6 -> 22.9, but 126 tiles 25.7 -> 26.7; the same with
+// g d_h = 768 to 4096: 96 tiles 7 to 13 % faster).
 template <int DH, int DV, int RKV, int DR>
 __global__ void __launch_bounds__(256) compress_bf16_kernel(CompressArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];

@@ -54,16 +54,38 @@ def test_one_shot(g, first, count, d_h, d_v, lens, fp8):
         lat, t1 = _cache(B, s, s["pool"], width)
         exp, t2 = _cache(B, s, out, width, count)
         print("expand direct", g, first, count, d_h, fp8, width, flush=True)
-        ws.fill_(0x5A)
         if fp8:
             B.gqla_expand_cache_fp8(shape, lat, s["w_uk"], s["w_uv"], first, count, exp, 0.02, 0.03, ws)
         else:
             B.gqla_expand_cache(shape, lat, s["w_uk"], s["w_uv"], first, count, exp, ws)
         torch.cuda.synchronize()
         got.append(out)
-        # the scratch shows which form ran: few blocks of (128, 128) and few groups as they are, the rest repacked
-        assert bool((ws != 0x5A).any()) == (width == wide or d_h == 192 or count == 25)
     assert torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("g,count,d_h,d_v,lens,wide,repacked", [
+    (8, 8, 128, 128, [300, 70], False, False),
+    (8, 8, 128, 128, [300, 70], True, True),             # the page-table rows could hold more than 72 blocks
+    (32, 24, 128, 128, [70] * 64, False, False),         # 24 groups in four shares: six a workgroup
+    (32, 25, 128, 128, [70] * 64, False, True),          # seven
+    (1, 1, 192, 256, [200], False, True),                # (192, 256)
+    (8, 8, 192, 256, [20, 250], False, True),
+])
+def test_one_shot_form(g, count, d_h, d_v, lens, wide, repacked):
+    """Which calls repack the weights: those whose last waves, of fewer than 64 tokens, would lose more than the launch costs.  The
+    scratch shows it."""
+    need = max(-(-n // 64) for n in lens)
+    width = 4 * 73 if wide else need
+    B, s = _setup(g, d_h, d_v, lens, width)
+    shape = B.make_shape(s["nb"], g, g, d_h, s["r_kv"], s["d_r"], 1, B.GQLA_BF16, 0.0, d_v)
+    ws = torch.full((B.gqla_expand_workspace_bytes(shape, count),), 0x5A, dtype=torch.uint8, device="cuda")
+    out = torch.zeros(s["num_pages"] * 64 * (count * (d_h + d_v) + s["d_r"]), dtype=torch.bfloat16, device="cuda")
+    lat, t1 = _cache(B, s, s["pool"], width)
+    exp, t2 = _cache(B, s, out, width, count)
+    print("expand form", g, count, d_h, wide, flush=True)
+    B.gqla_expand_cache(shape, lat, s["w_uk"], s["w_uv"], 0, count, exp, ws)
+    torch.cuda.synchronize()
+    assert bool((ws != 0x5A).any()) == repacked
 
 
 @pytest.mark.parametrize("fp8", [False, True])
